@@ -181,6 +181,29 @@ typedef struct swaa_fwd_args {
 int swaa_attn_fwd_ex(const swaa_fwd_args *args);
 
 /*
+ * swaa_attn_fwd_ex with scratch memory.  Few query rows on many keys -- a chunk of a long
+ * prompt, single generated tokens in a packed batch (paper App. D) -- are too few workgroups
+ * for the chip; with a workspace the keys of such rows are split over several workgroups
+ * and a second kernel merges their partial results.  Which calls gain is decided from the
+ * sizes in args (and, for packed batches, from the sequences' lengths on the device).
+ *
+ *   workspace        device scratch memory owned by the caller, 16-byte aligned, of at least
+ *                    swaa_attn_fwd_ex_workspace_bytes(args) bytes; contents before and after
+ *                    the call are meaningless, and calls that may overlap on the device need
+ *                    separate workspaces.  NULL: the call is swaa_attn_fwd_ex.
+ *
+ * Returns SWAA_OK or a negative swaa_status (SWAA_ERR_WORKSPACE: misaligned or too small).
+ */
+int swaa_attn_fwd_ex_ws(const swaa_fwd_args *args, void *workspace, long long workspace_bytes);
+
+/*
+ * Bytes of workspace swaa_attn_fwd_ex_ws needs for this argument block (0 if its keys are not
+ * split; below 72 MiB), or a negative swaa_status if the arguments are invalid.  Host-only
+ * arithmetic: no device memory is read, and the tensors' contents do not matter.
+ */
+long long swaa_attn_fwd_ex_workspace_bytes(const swaa_fwd_args *args);
+
+/*
  * Number of visible (query, key) pairs per head under the mask of swaa_attn_fwd, i.e.
  * sum over i in [0, N) of |Vis(i)|; the benchmark counts 4*D floating-point
  * operations per pair (paper App. A: the cost of sliding window attention is

@@ -25,7 +25,8 @@ SWAA_BF16 = 0
 SWAA_F16 = 1
 
 # every symbol include/swaa.h declares
-EXPORTS = ("swaa_attn_fwd", "swaa_attn_fwd_fa_decode", "swaa_attn_fwd_ex", "swaa_visible_pairs",
+EXPORTS = ("swaa_attn_fwd", "swaa_attn_fwd_fa_decode", "swaa_attn_fwd_ex", "swaa_attn_fwd_ex_ws",
+           "swaa_attn_fwd_ex_workspace_bytes", "swaa_visible_pairs",
            "swaa_visible_pairs_fa_decode",
            "swaa_attn_decode", "swaa_attn_decode_ex", "swaa_attn_decode_workspace_bytes", "swaa_attn_decode_ex_workspace_bytes", "swaa_attn_decode_static", "swaa_attn_bwd", "swaa_attn_bwd_workspace_bytes",
            "swaa_status_string", "swaa_version")
@@ -91,6 +92,10 @@ def load_library() -> ctypes.CDLL:
         ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_float, ctypes.c_void_p]
     lib.swaa_attn_fwd_ex.restype = ctypes.c_int
     lib.swaa_attn_fwd_ex.argtypes = [ctypes.POINTER(SwaaFwdArgs)]
+    lib.swaa_attn_fwd_ex_ws.restype = ctypes.c_int
+    lib.swaa_attn_fwd_ex_ws.argtypes = [ctypes.POINTER(SwaaFwdArgs), ctypes.c_void_p, ctypes.c_longlong]
+    lib.swaa_attn_fwd_ex_workspace_bytes.restype = ctypes.c_longlong
+    lib.swaa_attn_fwd_ex_workspace_bytes.argtypes = [ctypes.POINTER(SwaaFwdArgs)]
     lib.swaa_visible_pairs.restype = ctypes.c_longlong
     lib.swaa_visible_pairs.argtypes = [ctypes.c_longlong] * 3
     lib.swaa_visible_pairs_fa_decode.restype = ctypes.c_longlong
@@ -322,10 +327,19 @@ def swaa_attn_fwd_ex_raw(args: SwaaFwdArgs) -> int:
     return int(load_library().swaa_attn_fwd_ex(ctypes.byref(args)))
 
 
+def swaa_attn_fwd_ex_workspace_bytes(args: SwaaFwdArgs) -> int:
+    """Bytes of workspace with which swaa_attn_fwd_ex splits this call's keys over workgroups (0: it
+    does not); raises SwaaError on invalid arguments."""
+    r = int(load_library().swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(args)))
+    if r < 0:
+        raise SwaaError(r, swaa_status_string(r))
+    return r
+
+
 def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = None, scale: float | None = None,
                      cu_seqlens_q=None, cu_seqlens_k=None, max_seqlen_q: int | None = None,
                      max_seqlen_k: int | None = None, out=None, lse=None, stream=None, block_table=None,
-                     total_rows_q: int | None = None, n_prompts=None):
+                     total_rows_q: int | None = None, n_prompts=None, workspace=None):
     """General forward: strided tensors, Nq <= Nk (the query rows are the newest Nq of Nk
     tokens), packed variable-length batches.
 
@@ -338,7 +352,9 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
     with cu_seqlens the key offsets only give the cache lengths.  total_rows_q (packed batches): the
     rows of the packed q tensor, taken from q by default; 0 makes the launch as large as B times the
     longest sequence (slow for sequences of very different lengths).  n_prompts: int32 [B] GPU tensor of
-    per-sequence prompt lengths, used in place of n_prompt.  bfloat16 or float16 tensors (all of
+    per-sequence prompt lengths, used in place of n_prompt.  workspace: a uint8 tensor of at least
+    swaa_attn_fwd_ex_workspace_bytes(...) bytes for calls whose keys are split over workgroups (allocated
+    here with torch when None and the call needs one).  bfloat16 or float16 tensors (all of
     one type).  out defaults to a new tensor with q's shape in q's memory order;
     lse is fp32 [B, Hq, Nq] ([Hq, Tq] when packed).  Returns (out, lse).
     """
@@ -388,6 +404,7 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
             raise ValueError("out must be a tensor view shaped and typed like q with a contiguous last dimension")
         if tuple(lse.shape) != lse_shape or lse.dtype != torch.float32 or not lse.is_contiguous():
             raise ValueError(f"lse must be a contiguous fp32 tensor of shape {lse_shape}")
+        own_stream = stream is not None
         if stream is None:
             stream = torch.cuda.current_stream(q.device)
 
@@ -418,7 +435,19 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
                     or n_prompts.shape != (B,):
                 raise ValueError("n_prompts must be a contiguous int32 [B] GPU tensor")
             a.n_prompts = n_prompts.data_ptr()
-        rc = swaa_attn_fwd_ex_raw(a)
+        lib = load_library()
+        need = lib.swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(a))
+        if need > 0:
+            if workspace is None:
+                workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+                if own_stream:  # (freed on return: the allocator must know that another stream still uses it)
+                    workspace.record_stream(stream if isinstance(stream, torch.cuda.Stream)
+                                            else torch.cuda.ExternalStream(a.stream))
+            elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
+                raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
+            rc = int(lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), workspace.data_ptr(), workspace.numel()))
+        else:
+            rc = swaa_attn_fwd_ex_raw(a)  # (keys stay whole, or an argument error to be reported)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return out, lse

@@ -67,9 +67,9 @@ bool bad_stride(long long s, bool may_be_zero) {
     return s < 0 || (s % 8) != 0;  // row, head and batch starts stay 16-byte aligned
 }
 
-}  // namespace
-
-int swaa_attn_fwd_ex(const swaa_fwd_args *a) {
+// Argument checks, parameter block and work decomposition of the general forward.  allow_split:
+// the plan may split keys over workgroups; ws_bytes: the workspace that plan needs (0: none).
+int fwd_setup(const swaa_fwd_args *a, bool allow_split, FwdParams &p, long long &ws_bytes) {
     if (!a) return SWAA_ERR_NULL;
     if (!a->q.ptr || !a->k.ptr || !a->v.ptr || !a->out.ptr || !a->lse) return SWAA_ERR_NULL;
     const int B = a->B, Hq = a->Hq, Hkv = a->Hkv, D = a->D, Nq = a->Nq, Nk = a->Nk;
@@ -103,7 +103,6 @@ int swaa_attn_fwd_ex(const swaa_fwd_args *a) {
         return SWAA_ERR_ALIGN;
     if (reinterpret_cast<uintptr_t>(a->n_prompts) & 3u) return SWAA_ERR_ALIGN;
 
-    FwdParams p{};
     p.q = static_cast<const __bf16 *>(a->q.ptr);
     p.k = static_cast<const __bf16 *>(a->k.ptr);
     p.v = static_cast<const __bf16 *>(a->v.ptr);
@@ -136,10 +135,37 @@ int swaa_attn_fwd_ex(const swaa_fwd_args *a) {
     if (a->total_rows_q < 0) return SWAA_ERR_SHAPE;
     if (packed && a->total_rows_q > 0 ? !swaa::plan_work_packed(p, Nq, wg_rows, a->total_rows_q) : !swaa::plan_work(p, Nq, wg_rows))
         return SWAA_ERR_SHAPE;
+    ws_bytes = allow_split && pipelined ? swaa::plan_fwd_split(p) : 0;
+    return SWAA_OK;
+}
 
+int fwd_call(const swaa_fwd_args *a, void *workspace, long long workspace_bytes) {
+    FwdParams p{};
+    long long need = 0;
+    const int rc = fwd_setup(a, workspace != nullptr, p, need);
+    if (rc != SWAA_OK) return rc;
+    if (need > 0) {
+        if (misaligned(workspace) || workspace_bytes < need) return SWAA_ERR_WORKSPACE;
+        swaa::place_fwd_split(p, workspace);
+    }
     hipStream_t s = static_cast<hipStream_t>(a->stream);
-    const hipError_t err = pipelined ? swaa::launch_fwd_pipelined_d128(p, s) : swaa::launch_fwd_simple(p, D, s);
+    const hipError_t err = a->D == 128 ? swaa::launch_fwd_pipelined_d128(p, s) : swaa::launch_fwd_simple(p, a->D, s);
     return err == hipSuccess ? SWAA_OK : SWAA_ERR_LAUNCH;
+}
+
+}  // namespace
+
+int swaa_attn_fwd_ex(const swaa_fwd_args *a) { return fwd_call(a, nullptr, 0); }
+
+int swaa_attn_fwd_ex_ws(const swaa_fwd_args *a, void *workspace, long long workspace_bytes) {
+    return fwd_call(a, workspace, workspace_bytes);
+}
+
+long long swaa_attn_fwd_ex_workspace_bytes(const swaa_fwd_args *a) {
+    FwdParams p{};
+    long long need = 0;
+    const int rc = fwd_setup(a, true, p, need);
+    return rc != SWAA_OK ? rc : need;
 }
 
 int swaa_attn_fwd_fa_decode(const void *q, const void *k, const void *v, void *out, float *lse,

@@ -90,6 +90,16 @@ struct FwdParams {
     // sequence does not have); total_items and chunk are then upper bounds, the workgroups work
     // out the true ones from cu_q / cu_k (decode_work_packed).
     int packed_compact;
+    // Split keys (swaa_fwd_pipelined.hip, split_plan): the tiles of a sequence are cut into
+    // several workgroups along the keys, whose partial results a second kernel merges.
+    // 0: not split; 1: the split counts are worked out on the device from the sequences'
+    // lengths; >= 2: this many for every sequence (fixed-length batches).
+    int split_keys;
+    long long split_items;  // upper bound on the row tiles (times KV heads) of the batch
+    int split_cap;  // partial results the workspace holds
+    float *ws_o;    // [split_cap][4 waves][16][64 lanes][4]: unnormalised O in accumulator order
+    float *ws_ml;   // [split_cap][4 waves][2][32]: reference (log2 units) and row sum
+    int *ws_n;      // [B]: split count of each sequence, for the merge kernel
 };
 
 // One sequence as a workgroup sees it: the query rows are the newest nq of its nk
@@ -323,6 +333,11 @@ __device__ __forceinline__ float half_swap_sum(float x) {
 hipError_t launch_fwd_simple(const FwdParams &p, int D, hipStream_t stream);
 int fwd_simple_wg_rows(int D);
 hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream);
+// Decides whether the call's keys are split over several workgroups per row tile and fills the
+// split_* fields (after plan_work / plan_work_packed, whose launch size it enlarges); the bytes of
+// workspace the plan needs, 0 if the keys stay whole.
+long long plan_fwd_split(FwdParams &p);
+void place_fwd_split(FwdParams &p, void *workspace);
 
 }  // namespace swaa
 

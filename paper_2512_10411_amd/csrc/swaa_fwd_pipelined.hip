@@ -39,6 +39,7 @@
 // all LDS accesses below use plain byte addresses.
 #include <type_traits>
 
+#include "swaa_fwd_split.h"
 #include "swaa_tile_d128.h"
 
 namespace swaa {
@@ -242,10 +243,17 @@ __device__ __forceinline__ void pipelined_substep(const LaneAddr &la, const Half
 // its terms are subnormal or vanish).
 // kPaged: k and v are a paged cache addressed through p.block_table (its own instantiation, so
 // that the contiguous kernel carries none of the table arithmetic).
-template <bool kF16, bool kPaged>
+// kSplit: the keys of a row tile may be split over several workgroups (swaa_fwd_split.h); an
+// instantiation of its own too.
+template <bool kF16, bool kPaged, bool kSplit>
 __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const FwdParams p) {
     WorkItem wi;
-    if (!decode_work(p, wi)) return;
+    SplitItem si{1, 0, 0u};
+    if constexpr (kSplit) {
+        if (!decode_work_split(p, 0u, wi, si)) return;
+    } else {
+        if (!decode_work(p, wi)) return;
+    }
     SeqGeom sg;
     if (!seq_geom(p, wi.b, sg)) return;
     const int hpb = wi.hpb;
@@ -292,12 +300,30 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
     // one); an odd count is padded with a half past the last row, which no row can see.
     const int band_lo = (wg_p1 >= sg.n_prompt) ? 0 : max(0, wg_p0 - p.W + 1);
     const int hb_lo = band_lo >> 5, hb_hi = wg_p1 >> 5;
-    const int n_sink_h = min((min(S, band_lo) + 31) >> 5, hb_lo);
-    const int n_halves = n_sink_h + (hb_hi - hb_lo + 1);
+    const int n_sink_all = min((min(S, band_lo) + 31) >> 5, hb_lo);
+    int n_halves = n_sink_all + (hb_hi - hb_lo + 1);
+    // Split keys: this workgroup visits halves [i0, i0 + n_halves) of that list, i0 and every
+    // split's length but the last one's even (so only the padding of the last is a padding half).
+    int i0 = 0;
+    if constexpr (kSplit) {
+        if (si.n > 1) {
+            const int per = max(((n_halves + si.n - 1) / si.n + 1) & ~1, kSplitMinHalves);
+            i0 = si.s * per;
+            n_halves = min(per, n_halves - i0);
+            if (n_halves <= 0) {  // a tile with fewer halves than the sequence's longest: an empty partial result
+                float *ml = p.ws_ml + (size_t)(si.slot * 4u + (unsigned)wave) * 64;
+                ml[lane] = hf ? 0.f : -INFINITY;
+                return;
+            }
+        }
+    }
+    const int n_sink_h = kSplit ? n_sink_all - i0 : n_sink_all;  // (relative to i0; may be negative)
     const int J = (n_halves + 1) >> 1;  // tiles
     // i-th visited half -> its index among all halves of the sequence (first key / 32); the
     // padding half comes out as hb_hi + 1
-    auto half_of = [&](int i) __attribute__((always_inline)) { return i < n_sink_h ? i : i - n_sink_h + hb_lo; };
+    auto half_of = [&](int i) __attribute__((always_inline)) {
+        return i < n_sink_h ? i + (kSplit ? i0 : 0) : i - n_sink_h + hb_lo;
+    };
 
     const uint32_t k_rsb = (uint32_t)(p.k_sn * 2), v_rsb = (uint32_t)(p.v_sn * 2);  // row strides in bytes
     const __bf16 *kg = p.k + sg.k_batch * p.k_sb + (long long)wi.kvh * p.k_sh + sg.k_row0 * p.k_sn;
@@ -442,7 +468,7 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
     int ja, jb;
     {
         const int g_min = (wbound >> 5) + 1, g_max = (p0 - 31) >> 5;
-        const int i_min = max(n_sink_h, g_min - hb_lo + n_sink_h);  // first unmasked band half
+        const int i_min = max(max(n_sink_h, 0), g_min - hb_lo + n_sink_h);  // first unmasked band half
         const int i_max = min(g_max - hb_lo + n_sink_h, n_halves - 1);  // last one
         ja = (i_min + 2) >> 1;       // 2 t - 1 >= i_min
         jb = max(ja, (i_max >> 1) + 1);  // 2 t <= i_max
@@ -619,6 +645,14 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
     float l_row = half_swap_sum(rs.l);
     float lb_row = rowsum_of_column(lsum, l32_e);
     bool redo;
+    bool row_sees = true;
+    auto row_sees_split = [&](int l32) __attribute__((always_inline)) {
+        const int pos = p0 + l32, window = pos >= sg.n_prompt ? Nk : p.W;
+        const int band0 = max(i0 - n_sink_all, 0) + hb_lo;              // band halves of the split: band0 .. band1
+        const int band1 = i0 + n_halves - 1 - n_sink_all + hb_lo;       // (none if band1 < band0)
+        const bool band = band1 >= band0 && 32 * band0 <= pos && (32 * band1 + 31 > pos - window || 32 * band0 < S);
+        return band || (i0 < n_sink_all && 32 * i0 < S && 32 * i0 <= pos);
+    };
     {
         // a sum inside (kSumFloor, kSumLimit), tested on the bit pattern: positive floats order like
         // unsigned integers, and zero, infinity and every NaN pattern fall outside the interval
@@ -630,7 +664,14 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
         // row whose terms all sank into (or below) the subnormals has a small sum of rounded P
         // (a row that took its reference from a visible key has a term of 2^4)
         const bool p_sound = !kF16 || (__float_as_uint(lb_row) - 0x3c800000u) < (0x7f800000u - 0x3c800000u);  // [2^-6, inf)
-        const int mine = __any(!(in_range && p_sound) && r0 + l32_e < Nq) ? 1 : 0;
+        // (split keys: a row may see no key of this split at all -- a prompt row beside a generated one
+        // in front of its window -- and then has a sum of 0 by right)
+        bool has_say = r0 + l32_e < Nq;
+        if constexpr (kSplit) {
+            row_sees = row_sees_split(l32_e);
+            has_say = has_say && row_sees;
+        }
+        const int mine = __any(!(in_range && p_sound) && has_say) ? 1 : 0;
         const uint32_t flag_base = (uint32_t)(kVRing + (J & 1) * kTileBytes);
         if (lane_e == 0) *(int __attribute__((address_space(3))) *)(uintptr_t)(flag_base + wave * 4) = mine;
         __syncthreads();
@@ -675,7 +716,33 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
             __syncthreads();  // everyone is done with this buffer: tile j + 2 is copied into it next
         }
         row_sums(rs, l_row, lb_row);
+        if constexpr (kSplit) row_sees = row_sees && l_row > 0.f;
         // (after the loop's last barrier the rings are free: they become the O staging area below)
+    }
+
+    // ---- split keys: the partial result, in accumulator order (every store is whole kilobytes);
+    // O scaled by l / (sum of the rounded P), so that the merge divides by the fp32 sums ----
+    if constexpr (kSplit) {
+        if (si.n > 1) {
+            const unsigned ws = si.slot * 4u + (unsigned)wave;
+            if (r0 + l32_e < Nq) {
+                const float fix = row_sees ? l_row / lb_row : 0.f;
+                float *wo = p.ws_o + (size_t)ws * (16 * 64 * 4) + lane_e * 4;
+#pragma unroll
+                for (int db = 0; db < kDB; ++db)
+#pragma unroll
+                    for (int e4 = 0; e4 < 4; ++e4) {
+                        float4 o4;
+                        o4.x = oacc[db][4 * e4 + 0] * fix;
+                        o4.y = oacc[db][4 * e4 + 1] * fix;
+                        o4.z = oacc[db][4 * e4 + 2] * fix;
+                        o4.w = oacc[db][4 * e4 + 3] * fix;
+                        *reinterpret_cast<float4 *>(wo + (4 * db + e4) * 256) = o4;
+                    }
+                p.ws_ml[(size_t)ws * 64 + lane_e] = lane_e < 32 ? (row_sees ? rs.mc : -INFINITY) : (row_sees ? l_row : 0.f);
+            }
+            return;
+        }
     }
 
     // ---- epilogue: O / (sum of the rounded P) -> bf16 through LDS (8 KiB per wave at the start
@@ -711,7 +778,156 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
     }
 }
 
+// ---- merging the splits of a row: out = sum_s 2^(mc_s - m) O_s / sum_s 2^(mc_s - m) l_s with
+// m = max_s mc_s; lse = (m + log2 of the denominator) ln 2 ----
+// A workgroup of 256 threads takes the 32 rows of one wave of one row tile: thread (row l32, q)
+// two of the sixteen 8-element groups of the row, read as the split's wave left them (512
+// contiguous bytes per 32 threads).  Which tile follows from the split counts that the splits left.
+template <bool kF16>
+__global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) {
+    const int tid = threadIdx.x, lane = tid & 63, l32 = tid & 31, q = tid >> 5;
+    const unsigned wave = blockIdx.x & 3u, rank = blockIdx.x >> 2;  // rank: tile among those of split sequences
+    int nq, nk, np;
+    split_lengths(p, lane, nq, nk, np);
+    const SplitSeq me = split_seq(p, nq, nk, np);
+    const unsigned items = (unsigned)(me.tiles * p.Hkv);
+    const unsigned n_mine = items ? (unsigned)p.ws_n[lane] : 1u;  // (items: lane < B, and a split workgroup has been there)
+    const unsigned incl = wave_inclusive_scan(n_mine > 1u ? items : 0u);
+    const unsigned slots = wave_inclusive_scan(n_mine > 1u ? items * n_mine : 0u);
+    if (rank >= wave_read_lane(incl, 63)) return;
+    const int b = __popcll(__ballot(incl <= rank));
+    const unsigned n = wave_read_lane(n_mine, b), tiles = wave_read_lane((unsigned)me.tiles, b);
+    unsigned r = rank - (b ? wave_read_lane(incl, b - 1) : 0u);
+    const unsigned slot_b = b ? wave_read_lane(slots, b - 1) : 0u;
+    const unsigned kvh = r / tiles;
+    r -= kvh * tiles;
+    WorkItem w;
+    split_tile(p, (int)wave_read_lane((unsigned)nq, b), r, w);
+    SeqGeom sg;
+    if (!seq_geom(p, b, sg)) return;
+    const int row = w.pt * (kPWgRows / w.hpb) + ((int)wave / w.hpb) * kPRows + l32;
+    const int head = (int)kvh * p.G + w.h0 + (int)wave % w.hpb;
+    if (row >= sg.nq) return;
+    const unsigned slot0 = slot_b + kvh * n * tiles + r;  // split s: + s * tiles
+
+    // Four splits per round, all their loads in flight together; the reference moves between rounds
+    // (O and l are rescaled).  An empty split may not have written its O, and splits past the last
+    // repeat it: loaded all the same, left out by selection.
+    float acc[2][8], l = 0.f, m = -INFINITY;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[c][e] = 0.f;
+    constexpr int kRound = 4;
+    for (unsigned s0 = 0; s0 < n; s0 += kRound) {
+        float mc[kRound], ls[kRound];
+        float4 o4[kRound][4];
+#pragma unroll
+        for (int u = 0; u < kRound; ++u) {
+            const size_t ws = (size_t)((slot0 + min(s0 + u, n - 1) * tiles) * 4u + wave);
+            mc[u] = p.ws_ml[ws * 64 + l32];
+            ls[u] = p.ws_ml[ws * 64 + 32 + l32];
+            const float *wo = p.ws_o + ws * (16 * 64 * 4) + l32 * 4;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) o4[u][c] = *reinterpret_cast<const float4 *>(wo + (2 * q + c / 2) * 256 + (c & 1) * 128);
+        }
+        float m_new = m;
+#pragma unroll
+        for (int u = 0; u < kRound; ++u) {
+            if (s0 + u >= n) mc[u] = -INFINITY;
+            m_new = fmaxf(m_new, mc[u]);
+        }
+        const float alpha = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+        l *= alpha;
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[c][e] *= alpha;
+        m = m_new;
+#pragma unroll
+        for (int u = 0; u < kRound; ++u) {
+            const bool empty = mc[u] == -INFINITY;
+            const float weight = __builtin_amdgcn_exp2f(mc[u] - m);
+            l += empty ? 0.f : weight * ls[u];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float *a = &acc[c / 2][4 * (c & 1)];
+                a[0] += empty ? 0.f : weight * o4[u][c].x;
+                a[1] += empty ? 0.f : weight * o4[u][c].y;
+                a[2] += empty ? 0.f : weight * o4[u][c].z;
+                a[3] += empty ? 0.f : weight * o4[u][c].w;
+            }
+        }
+    }
+    const float inv = 1.f / l;
+    __bf16 *orow = p.out + sg.q_batch * p.o_sb + (long long)head * p.o_sh + (sg.q_row0 + row) * p.o_sn;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        const bf16x2 a = pack_pair<kF16>(acc[c][0] * inv, acc[c][1] * inv), b2 = pack_pair<kF16>(acc[c][2] * inv, acc[c][3] * inv);
+        const bf16x2 c2 = pack_pair<kF16>(acc[c][4] * inv, acc[c][5] * inv), d2 = pack_pair<kF16>(acc[c][6] * inv, acc[c][7] * inv);
+        const bf16x4 lo = __builtin_shufflevector(a, b2, 0, 1, 2, 3), hi = __builtin_shufflevector(c2, d2, 0, 1, 2, 3);
+        *reinterpret_cast<bf16x8 *>(orow + 8 * (2 * q + c)) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+    if (q == 0)
+        p.lse[sg.q_batch * p.lse_sb + (long long)head * p.lse_sh + sg.q_row0 + row] =
+            (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
+}
+
 }  // namespace
+
+long long plan_fwd_split(FwdParams &p) {
+    p.split_keys = 0;
+    if (p.B > kSplitMaxBatch || p.wg_rows != kPWgRows) return 0;
+    const bool packed = p.cu_q != nullptr;
+    // Whole prompts on themselves: their tiles are many and short enough as they are.
+    if (p.Nq >= p.Nk) return 0;
+    // A packed batch's lengths are known on the device only; Nq and Nk bound them.  With prompt
+    // lengths per sequence any row may be a generated one.
+    const bool maybe_generated = p.n_prompts != nullptr;
+    const SplitSeq longest = split_seq(p, p.Nq, p.Nk, maybe_generated ? 0 : p.P);
+    if (longest.halves <= 2 * kSplitMinHalves) return 0;
+    // (Whether keys are split depends on Nq, Nk, B and the heads only, not on total_rows_q: the
+    // result's bits are the same whichever work list the caller's arguments select.)
+    const long long most = (long long)p.B * p.Hkv * p.tiles_per_pair;
+    // A few chunks that fill the chip twice over are balanced by their number; in a larger batch
+    // single generated tokens on long caches may stand beside them.
+    if (p.B <= 4 && most > 2 * (long long)kSplitResident) return 0;
+    const long long bound = p.packed_compact ? p.total_items : most;
+    int n = 1;
+    if (p.B == 1 || (!packed && !p.n_prompts)) {
+        // sequences of one length (a packed batch of one: of at most this length)
+        if (longest.whole) return 0;
+        const float items = (float)((long long)p.B * p.Hkv * longest.tiles);
+        float best = split_time(items, 0.f, (float)longest.halves, items * (float)longest.average);
+        for (int c = 2; c <= 64; ++c) {
+            if (longest.halves / c < kSplitMinHalves || items * (float)c > (float)kSplitUnits) break;
+            const float t = split_time(items * (float)c, items * (float)c, (float)((longest.halves + c - 1) / c), items * (float)longest.average);
+            if (t < best) {
+                best = t;
+                n = c;
+            }
+        }
+        if (n == 1) return 0;
+    }
+    if (!packed && !p.n_prompts) {
+        p.split_keys = n;
+        p.split_cap = p.B * p.Hkv * p.tiles_per_pair * n;
+        p.chunk = (long long)p.B * (((long long)p.Hkv * p.tiles_per_pair * n + kXcds - 1) / kXcds);
+    } else {
+        p.split_keys = 1;
+        p.split_cap = kSplitUnits;
+        p.chunk = (bound + kSplitUnits + kXcds - 1) / kXcds + p.B;
+    }
+    p.total_items = p.chunk * kXcds;
+    p.split_items = bound;
+    return (long long)p.split_cap * (4 * (16 * 64 * 4 + 64)) * (long long)sizeof(float) + (long long)kSplitMaxBatch * (long long)sizeof(int);
+}
+
+void place_fwd_split(FwdParams &p, void *workspace) {
+    p.ws_o = static_cast<float *>(workspace);
+    p.ws_ml = p.ws_o + (size_t)p.split_cap * (4 * 16 * 64 * 4);
+    p.ws_n = reinterpret_cast<int *>(p.ws_ml + (size_t)p.split_cap * (4 * 64));
+}
 
 hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream) {
     if (p.wg_rows != kPWgRows) return hipErrorInvalidValue;  // the plan must be the one for this kernel's workgroups
@@ -719,14 +935,33 @@ hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream) {
     // (64 KiB of dynamic LDS is what a kernel gets without asking)
     static_assert(kSmemBytes <= 64 * 1024, "more would need hipFuncSetAttribute");
     const bool paged = p.block_table != nullptr;
-    if (p.fp16 && paged)
-        hipLaunchKernelGGL((swaa_fwd_pipelined_kernel<true, true>), dim3(grid), dim3(kPThreads), kSmemBytes, stream, p);
-    else if (p.fp16)
-        hipLaunchKernelGGL((swaa_fwd_pipelined_kernel<true, false>), dim3(grid), dim3(kPThreads), kSmemBytes, stream, p);
-    else if (paged)
-        hipLaunchKernelGGL((swaa_fwd_pipelined_kernel<false, true>), dim3(grid), dim3(kPThreads), kSmemBytes, stream, p);
+    auto launch = [&](auto f16, auto pg, auto split) {
+        hipLaunchKernelGGL((swaa_fwd_pipelined_kernel<decltype(f16)::value, decltype(pg)::value, decltype(split)::value>),
+                           dim3(grid), dim3(kPThreads), kSmemBytes, stream, p);
+    };
+    auto pick_split = [&](auto f16, auto pg) {
+        if (p.split_keys)
+            launch(f16, pg, std::true_type{});
+        else
+            launch(f16, pg, std::false_type{});
+    };
+    auto pick_paged = [&](auto f16) {
+        if (paged)
+            pick_split(f16, std::true_type{});
+        else
+            pick_split(f16, std::false_type{});
+    };
+    if (p.fp16)
+        pick_paged(std::true_type{});
     else
-        hipLaunchKernelGGL((swaa_fwd_pipelined_kernel<false, false>), dim3(grid), dim3(kPThreads), kSmemBytes, stream, p);
+        pick_paged(std::false_type{});
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess || !p.split_keys) return err;
+    const unsigned merges = (unsigned)(4 * (p.split_items < p.split_cap / 2 ? p.split_items : p.split_cap / 2));
+    if (p.fp16)
+        hipLaunchKernelGGL(swaa_fwd_merge_kernel<true>, dim3(merges), dim3(256), 0, stream, p);
+    else
+        hipLaunchKernelGGL(swaa_fwd_merge_kernel<false>, dim3(merges), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 

@@ -1,0 +1,214 @@
+// Split keys of the pipelined forward kernel: the plan, and what a workgroup computes.
+//
+// A chunk of new tokens against a long cache, or single generated tokens in a serving batch, gives
+// the forward kernel few row tiles with many keys each: 512 rows on 32 heads are 128 workgroups of
+// a chip that runs 512 at once, and one generated token on a 12k-token cache is 375 halves of 32
+// keys in a row for one workgroup while the others are long done.  The tiles of a sequence are then
+// cut along the keys into n workgroups, each of which leaves its unnormalised O, its softmax
+// reference and its row sums in the workspace (as the decode kernel's splits do), and
+// swaa_fwd_merge_kernel adds them up.
+//
+// How many splits each sequence gets follows from a cost model in units of one half (the time a
+// workgroup needs for 32 keys with a second one on its compute unit, 0.83 us measured):
+//   * 64 candidates for the longest split, L = h_max / 1 .. h_max / 64 (at least kSplitMinHalves),
+//     one per lane; a sequence whose tiles visit h halves gets ceil(h / L) splits;
+//   * up to 256 units (workgroups) everybody has a compute unit alone and runs 1.6 x as fast, up to
+//     512 they share one in pairs: the longest one is the time.  Above, the chip works through the
+//     total, and the last units run out half a unit late on average;
+//   * a workgroup costs kSplitStart halves outside its loop (8 us measured), and splitting at all
+//     the merge kernel (kSplitMerge, 9-10 us) and the traffic of the partial results (64 KiB per
+//     unit).
+// The lengths of a packed batch are known on the device only: there every workgroup works the plan
+// out for itself (batches of at most 64 sequences: one per lane).  Measured, binary16 and pages of
+// 16 tokens, 32 heads on 8: 512 rows on 24k tokens, full attention, 364 -> 207 us (four splits,
+// 196 + 9 us; 128 workgroups before); 23 generated tokens on caches of 1-12k tokens beside a chunk
+// of 999 rows on a 2k window 213 -> 139 us (bound by HBM: 470 MB, 95 us at the rate of a copy).
+// Calls that the plan leaves whole on the host (prompts on themselves, short windows, chunks that
+// fill the chip) launch the same kernels as without a workspace.
+#ifndef SWAA_FWD_SPLIT_H_
+#define SWAA_FWD_SPLIT_H_
+
+#include "swaa_common.h"
+
+namespace swaa {
+
+constexpr int kSplitMaxBatch = 64;   // one sequence per lane
+constexpr int kSplitMinHalves = 16;  // no split shorter than this many halves
+constexpr int kSplitUnits = 1024;    // most partial results a packed batch may leave (64 KiB each)
+constexpr float kSplitResident = 512.f, kSplitAlone = 256.f, kSplitAloneRate = 0.62f;
+constexpr float kSplitStart = 10.f, kSplitMerge = 12.f, kSplitTraffic = 0.03f;
+
+// Halves a row tile at positions [a, b] visits (as the kernel's prologue counts them).
+__host__ __device__ inline int tile_halves(int a, int b, int W, int S) {
+    const int band_lo = a - W + 1 > 0 ? a - W + 1 : 0;
+    const int lo = band_lo >> 5, hi = b >> 5;
+    const int sink_keys = S < band_lo ? S : band_lo;
+    const int sinks = (sink_keys + 31) >> 5;
+    return (sinks < lo ? sinks : lo) + hi - lo + 1;
+}
+
+// What a sequence brings to the plan.
+struct SplitSeq {
+    int tiles;    // row tiles per (sequence, KV head)
+    int halves;   // visited by the last, longest of them
+    int average;  // by a tile on average
+    bool whole;   // never split: prompt and generated rows mixed, whose tiles differ too much
+};
+__host__ __device__ inline SplitSeq split_seq(const FwdParams &p, int nq, int nk, int n_prompt) {
+    SplitSeq s{0, 0, 0, true};
+    if (nq <= 0) return s;
+    const int r1 = p.wg_rows, r2 = r1 / 2, r4 = r1 / 4;
+    s.tiles = p.n4 * ((nq + r4 - 1) / r4) + p.has2 * ((nq + r2 - 1) / r2) + p.has1 * ((nq + r1 - 1) / r1);
+    const int r = p.n4 ? r4 : p.has2 ? r2 : r1;
+    const int first = nk - nq;
+    const bool some = n_prompt < nk, all = n_prompt <= first;  // generated rows
+    s.halves = tile_halves(nk - (r < nq ? r : nq), nk - 1, some ? nk : p.W, p.S);
+    const int h0 = tile_halves(first, first + (r < nq ? r : nq) - 1, all ? nk : p.W, p.S);
+    s.average = (h0 + s.halves + 1) / 2;
+    s.whole = some && !all;
+    return s;
+}
+
+// Splits of a sequence whose tiles visit h halves, for splits of at most L; rcp = 1 / L.  (Rounded
+// down instead of up where the product comes out just below a whole number: no matter, the same
+// expression is used for the plan and for the work list.)
+__host__ __device__ inline int split_count(int h, int L, float rcp) {
+    const int n = (int)((float)(h + L - 1) * rcp);
+    return n < 1 ? 1 : n;
+}
+// Predicted time of a plan, in halves.
+__host__ __device__ inline float split_time(float units, float split_units, float longest, float total) {
+    const float t = units <= kSplitAlone      ? kSplitAloneRate * (longest + kSplitStart)
+                    : units <= kSplitResident ? longest + kSplitStart
+                                              : (total + kSplitStart * units) * (1.f / kSplitResident) + 0.5f * longest;
+    return split_units > 0.f ? t + kSplitMerge + kSplitTraffic * split_units : t;
+}
+
+// One workgroup's share of the keys.
+struct SplitItem {
+    int n, s;       // the sequence's splits, and which of them this is
+    unsigned slot;  // partial result (n >= 2)
+};
+
+// Sequence b's rows, keys and prompt length (0 rows for b >= B).
+__device__ __forceinline__ void split_lengths(const FwdParams &p, int b, int &nq, int &nk, int &np) {
+    nq = nk = np = 0;
+    if (b >= p.B) return;
+    nq = p.cu_q ? p.cu_q[b + 1] - p.cu_q[b] : p.Nq;
+    nk = p.cu_k ? p.cu_k[b + 1] - p.cu_k[b] : p.Nk;
+    np = p.n_prompts ? max(p.n_prompts[b], 0) : p.P;
+    nq = max(0, min(min(nq, p.Nq), nk));
+    nk = min(nk, p.Nk);
+    nq = min(nq, nk);
+}
+
+// Row tile `t` of a (sequence, KV head) pair with nq query rows (the order of decode_work).
+__device__ __forceinline__ void split_tile(const FwdParams &p, int nq, unsigned t, WorkItem &w) {
+    const unsigned r1 = (unsigned)p.wg_rows, r2 = r1 / 2, r4 = r1 / 4;
+    const unsigned nt4 = ((unsigned)nq + r4 - 1) / r4, nt2 = ((unsigned)nq + r2 - 1) / r2, nt1 = ((unsigned)nq + r1 - 1) / r1;
+    if (t < (unsigned)p.n4 * nt4) {
+        const unsigned g = t / nt4;
+        w.hpb = 4;
+        w.h0 = 4 * (int)g;
+        w.pt = (int)(nt4 - 1 - (t - g * nt4));
+        return;
+    }
+    t -= (unsigned)p.n4 * nt4;
+    if (p.has2 && t < nt2) {
+        w.hpb = 2;
+        w.h0 = 4 * p.n4;
+        w.pt = (int)(nt2 - 1 - t);
+        return;
+    }
+    if (p.has2) t -= nt2;
+    w.hpb = 1;
+    w.h0 = p.G - 1;
+    w.pt = (int)(nt1 - 1 - t);
+}
+
+// The work list with split keys: sequence after sequence, every sequence's units cut into eight
+// contiguous chunks, one per die (as in decode_work_packed); inside a sequence by KV head, then
+// split, then row tile, so that the workgroups side by side on a die read the same keys.  scratch:
+// 3 KiB of LDS of a workgroup of four waves, free again after the caller's next barrier.
+__device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t scratch, WorkItem &w, SplitItem &si) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned xcd = blockIdx.x % kXcds, rank = blockIdx.x / kXcds;
+    int nq, nk, np;
+    split_lengths(p, lane, nq, nk, np);
+    const SplitSeq me = split_seq(p, nq, nk, np);
+    const int items = me.tiles * p.Hkv;
+    int n = 1;
+    if (p.split_keys >= 2) {
+        n = p.split_keys;
+    } else {
+        // the model's terms of candidate `lane`, summed over the sequences: wave w takes every fourth
+        const int splittable = me.whole ? 0 : me.halves;
+        int h_max = splittable;
+        float total = (float)items * (float)me.average;
+#pragma unroll
+        for (int sh = 32; sh > 0; sh >>= 1) {
+            h_max = max(h_max, __shfl_xor(h_max, sh));
+            total += __shfl_xor(total, sh);
+        }
+        const int L = max(kSplitMinHalves, (h_max + lane) / (lane + 1));
+        const float rcp = 1.f / (float)L;
+        float units = 0.f, split_units = 0.f, longest = 0.f;
+        for (int b = wave; b < p.B; b += 4) {
+            const int it = __builtin_amdgcn_readlane(items, b), h = __builtin_amdgcn_readlane(me.halves, b);
+            const int c = __builtin_amdgcn_readlane(splittable, b) ? split_count(h, L, rcp) : 1;
+            const float u = (float)(it * c);
+            units += u;
+            split_units += c > 1 ? u : 0.f;
+            longest = fmaxf(longest, it ? (float)h / (float)c : 0.f);
+        }
+        typedef float __attribute__((address_space(3))) *LdsFloats;
+        const LdsFloats mine = (LdsFloats)(uintptr_t)(scratch + (uint32_t)(wave * 768 + lane * 4));
+        mine[0] = units;
+        mine[64] = split_units;
+        mine[128] = longest;
+        __syncthreads();
+        units = split_units = longest = 0.f;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+            const LdsFloats o = (LdsFloats)(uintptr_t)(scratch + (uint32_t)(x * 768 + lane * 4));
+            units += o[0];
+            split_units += o[64];
+            longest = fmaxf(longest, o[128]);
+        }
+        __syncthreads();  // (the scratch becomes part of a ring)
+        float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, longest, total);
+        float best = t;
+#pragma unroll
+        for (int sh = 32; sh > 0; sh >>= 1) best = fminf(best, __shfl_xor(best, sh));
+        const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
+        const int Lb = __builtin_amdgcn_readlane(L, pick);
+        if (splittable) n = split_count(me.halves, Lb, 1.f / (float)Lb);
+    }
+    if (me.whole) n = 1;
+    const unsigned mine = (unsigned)items * (unsigned)n;
+    const unsigned slots = n > 1 ? mine : 0u;
+    const unsigned slots_incl = wave_inclusive_scan(slots);
+    const unsigned incl = wave_inclusive_scan((mine + kXcds - 1) / kXcds);
+    if (rank >= wave_read_lane(incl, 63)) return false;
+    const int b = __popcll(__ballot(incl <= rank));  // sequences that end at or before the rank
+    const unsigned base = b ? wave_read_lane(incl, b - 1) : 0u;
+    const unsigned u = wave_read_lane(mine, b);
+    const unsigned tiles = wave_read_lane((unsigned)me.tiles, b);
+    const int nq_b = (int)wave_read_lane((unsigned)nq, b);
+    unsigned r = xcd * ((u + kXcds - 1) / kXcds) + (rank - base);
+    if (r >= u) return false;  // (the sequence's last chunks are shorter)
+    si.n = (int)wave_read_lane((unsigned)n, b);
+    si.slot = (b ? wave_read_lane(slots_incl, b - 1) : 0u) + r;
+    if (r == 0) p.ws_n[b] = si.n;  // (by every lane: a branch on the lane id would make what follows lane-dependent)
+    w.b = b;
+    const unsigned per_head = tiles * (unsigned)si.n;
+    w.kvh = (int)(r / per_head);
+    r -= (unsigned)w.kvh * per_head;
+    si.s = (int)(r / tiles);
+    split_tile(p, nq_b, r - (unsigned)si.s * tiles, w);
+    return true;
+}
+
+}  // namespace swaa
+
+#endif  // SWAA_FWD_SPLIT_H_

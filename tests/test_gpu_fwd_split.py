@@ -1,0 +1,100 @@
+"""GPU parity of the forward with keys split over several workgroups (swaa_attn_fwd_ex on few query
+rows and many keys), against the fp64 CPU oracle: split boundaries inside and outside the window,
+ragged last halves, sink halves in the first split only, tiles with fewer halves than the sequence's
+split count has (empty splits), rows that see no key of a split, every head grouping, both formats.
+"""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import input_format, swaa_decode_oracle
+from paper_2512_10411_amd import binding
+from paper_2512_10411_amd.inputs import make_qkv
+from gpu_util import assert_parity, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,Hkv,G,Nq,Nk,W,S,P,fmt", [
+    (1, 1, 4, 1, 1025, 10**9, 4, None, "bf16"),     # 33 halves: the shortest split range, odd last split
+    (1, 1, 4, 33, 3001, 10**9, 0, None, "fp16"),    # two row tiles, ragged last half
+    (1, 2, 5, 130, 4000, 10**9, 4, None, "bf16"),   # groups of four heads and one
+    (2, 1, 7, 65, 2500, 1100, 70, None, "bf16"),    # 4 + 2 + 1 heads, sink halves in front of the band
+    (1, 1, 1, 300, 5000, 1030, 4, None, "fp16"),    # one head per workgroup: 128 positions, band edges apart
+    (1, 1, 4, 700, 2000, 10**9, 4, None, "bf16"),   # causal: tiles with fewer halves than the last
+    (1, 1, 4, 40, 3000, 1, 1500, None, "bf16"),     # nearly all keys are sinks
+    (1, 1, 4, 64, 2100, 40, 4, 2100 - 64, "bf16"),  # generated rows only
+])
+def test_fixed_length_chunks(B, Hkv, G, Nq, Nk, W, S, P, fmt):
+    tag = f"split B{B} Hkv{Hkv} G{G} Nq{Nq} Nk{Nk} W{W} S{S} P{P} {fmt}"
+    print(f"[case] {tag}", flush=True)
+    q, k, v = make_qkv(B, Hkv * G, Hkv, Nk, 128, seed=91000 + Nq + Nk, n_query=Nq, fmt=fmt)
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), W, S, P)
+    torch.cuda.synchronize()
+    with input_format(fmt):
+        ro, rl = swaa_decode_oracle(q, k, v, W, S, 1 / math.sqrt(128), n_prompt=P)
+    assert_parity(out, lse, ro, rl, tag=tag)
+
+
+def test_a_late_spike_in_one_split_takes_the_second_pass():
+    # scores 80 nats above the first keys of a split: that split's workgroups recompute, the others do not
+    q, k, v = make_qkv(1, 4, 1, 3000, 128, seed=92, n_query=40)
+    to_bits = lambda x: np.array([x], dtype=np.float32).view(np.uint32)[0] >> 16
+    q[..., 0], k[..., 0] = to_bits(3.0), to_bits(0.0)
+    k[:, :, 1700, 0] = to_bits(304.0)
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q), to_device(k), to_device(v), 10**9, 4)
+    torch.cuda.synchronize()
+    ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
+    assert_parity(out, lse, ro, rl, tag="split, late spike")
+
+
+@pytest.mark.parametrize("n_singles,W,fmt,page", [(20, 300, "fp16", 16), (62, 40, "bf16", 48), (3, 2000, "bf16", 0)])
+def test_generated_tokens_beside_a_chunk(n_singles, W, fmt, page):
+    # a packed batch: single generated tokens on caches of very different lengths, an empty sequence, a chunk
+    # without generated rows, and a sequence of prompt and generated rows (never split)
+    rng = np.random.Generator(np.random.Philox(93 + n_singles))
+    Hkv, G, S = 2, 4, 4
+    nk = [int(40 * 150 ** rng.random()) for _ in range(n_singles)]
+    nq = [1] * n_singles
+    nk += [500, 3000, 900]
+    nq += [0, 150, 200]
+    if n_singles > 60:
+        nk, nq = nk[2:], nq[2:]  # a batch of 63
+    prompts = [n - 1 for n in nk[:-3]] + [500, 3000, 800]
+    B = len(nk)
+    print(f"[case] {B} sequences, caches {min(nk)}..{max(nk)} W{W} {fmt} page {page}", flush=True)
+    dt = torch.float16 if fmt == "fp16" else torch.bfloat16
+    host = [make_qkv(1, Hkv * G, Hkv, n, 128, 94000 + i, n_query=max(m, 1), fmt=fmt) for i, (m, n) in enumerate(zip(nq, nk))]
+    q = torch.cat([to_device(h[0], fmt)[0, :, :m] for h, m in zip(host, nq)], dim=1).contiguous()
+    offs = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32, device="cuda")
+    args = dict(cu_seqlens_q=offs(nq), cu_seqlens_k=offs(nk), max_seqlen_q=max(nq), max_seqlen_k=max(nk),
+                n_prompts=torch.tensor(prompts, dtype=torch.int32, device="cuda"))
+    dev = [(to_device(h[1], fmt)[0], to_device(h[2], fmt)[0]) for h in host]
+    if page:
+        pages = [(n + page - 1) // page for n in nk]
+        order = rng.permutation(sum(pages))
+        kk, vv = (torch.full((sum(pages), Hkv, page, 128), float("nan"), dtype=dt, device="cuda") for _ in range(2))
+        table, at = np.zeros((B, max(pages)), np.int32), 0
+        for b, n in enumerate(nk):
+            table[b, :pages[b]] = order[at:at + pages[b]]
+            for j in range(pages[b]):
+                rows = slice(j * page, min(n, (j + 1) * page))
+                kk[table[b, j], :, :rows.stop - rows.start] = dev[b][0][:, rows]
+                vv[table[b, j], :, :rows.stop - rows.start] = dev[b][1][:, rows]
+            at += pages[b]
+        args["block_table"] = torch.from_numpy(table).cuda()
+    else:
+        kk, vv = (torch.cat([d[i] for d in dev], dim=1).contiguous() for i in range(2))
+    outs = [tuple(t.clone() for t in binding.swaa_attn_fwd_ex(q, kk, vv, W, S, total_rows_q=t, **args)) for t in (None, None, 0)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(outs[0][0], o) and torch.equal(outs[0][1], l) for o, l in outs[1:])
+    r0 = 0
+    with input_format(fmt):
+        for b, h in enumerate(host):
+            if nq[b]:
+                ro, rl = swaa_decode_oracle(h[0], h[1], h[2], W, S, 1 / math.sqrt(128), n_prompt=prompts[b])
+                assert_parity(outs[0][0][None, :, r0:r0 + nq[b]], outs[0][1][None, :, r0:r0 + nq[b]], ro, rl,
+                              tag=f"seq {b}: {nq[b]} rows on {nk[b]} keys")
+            r0 += nq[b]
