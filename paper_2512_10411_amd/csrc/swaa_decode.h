@@ -12,9 +12,10 @@ namespace swaa {
 // The query rows of one (batch, KV head) pair -- G heads x Nq rows, contiguous
 // in q -- are the columns of 32-wide column tiles.  The visited keys (sink
 // halves, then the halves from the first row's window to the end of the cache;
-// a half is 32 keys; `visited_halves` below) are cut into splits; one single-wave workgroup computes
+// a half is 32 keys; `visited_halves` below) are cut into splits; one workgroup computes
 // one (pair, column tile, split) item and leaves an unnormalised partial result
-// in the workspace; a second kernel merges the splits.
+// in the workspace, which a second kernel merges -- or, where a sequence has one split
+// only, the output itself.
 struct DecodeParams {
     const __bf16 *q;
     const __bf16 *k;
@@ -42,7 +43,7 @@ struct DecodeParams {
     int col_stride;  // min(cols, 32): columns an item stores
     int n_halves;  // upper bound on the halves a sequence of at most Nk tokens visits
     int halves_per_split, n_splits;
-    long long items;  // B * Hkv * n_coltiles * n_splits (ragged: max_units * Hkv * n_coltiles; below 2^31): partial results in the workspace
+    long long items;  // B * Hkv * n_coltiles * (at least n_splits) (ragged: max_units * Hkv * n_coltiles; below 2^31): partial results in the workspace
     // a workgroup computes tiles_per_item (1 or 2) column tiles of one (pair, split) from the same
     // K and V fragments; n_ctgroups = ceil(n_coltiles / tiles_per_item) of them per (pair, split)
     int tiles_per_item, n_ctgroups;

@@ -10,18 +10,22 @@
 //     columns of an MFMA tile (more rows: more column tiles), so one pass over
 //     K and V serves the whole GQA group.  Padding columns cost matrix-core
 //     time only, of which there is plenty.
-//   * The visited keys are cut into splits; a workgroup is ONE wave that owns a
-//     three-stage ring of 32-key half tiles (K 8 KiB + V 8 KiB per stage) in
-//     LDS, filled by global_load_lds_dwordx4 with whole 256-byte rows per 16
-//     lanes.  No barriers: a wave waits on its own copies only.  48 KiB of LDS
-//     per workgroup lets three of them share a CU: 96 KiB of copies in flight
-//     per CU, 24 MiB over the chip.  (Workgroups that compute two column tiles
-//     take a two-stage ring and run four to a CU: decode_stages.)
-//   * Per half: all K and V^T operand fragments go from LDS to registers (V^T
-//     through transposing reads), the copy of the half three ahead is issued into
-//     the stage just emptied, and only then the arithmetic runs: S^T = K Q^T (8
-//     MFMAs), max-based softmax (mask only on halves that are not fully visible),
-//     O^T += V^T P^T (8 MFMAs).  The copies thus never wait for arithmetic.  The
+//   * The visited keys are cut into splits; a workgroup is FOUR waves, each with a quarter of the
+//     split and a ring of 32-key half tiles (K 8 KiB + V 8 KiB per stage) in LDS of its own,
+//     filled by global_load_lds_dwordx4 with whole 256-byte rows per 16 lanes.  No barriers in
+//     the loop: a wave waits on its own copies only.  One stage per wave (64 KiB of LDS per
+//     workgroup, two to a CU: 128 KiB of copies in flight per CU, 32 MiB over the chip): the
+//     registers are the second stage.  Workgroups that compute two column tiles take a two-stage
+//     ring, one to a CU.
+//   * At the end the four waves' results are added up through LDS; a sequence with one split
+//     then writes its output from here, and the merge kernel is not needed.  (Single-wave
+//     workgroups, whose every result went through the workspace: 64 sequences x 2k tokens 101 us,
+//     now 94; 16 x window 2k 30.2 -> 26.9; 1 x window 8k 15.2 -> 13.2; 64 sequences x 4k tokens with
+//     16 new tokens each 230 -> 192; 96 sequences of 0.3-20k tokens 382 -> 338, 5.9 TB/s.)
+//   * Per half: all K and V^T operand fragments go from LDS to registers (V^T through transposing
+//     reads), the copy of the next half is issued into the stage just emptied, and only then the
+//     arithmetic runs: S^T = K Q^T (8 MFMAs), max-based softmax (mask only on halves that are not
+//     fully visible), O^T += V^T P^T (8 MFMAs).  The copies thus never wait for arithmetic.  The
 //     query rows are loaded from HBM in operand layout and parked in AccVGPRs.
 //   * The cache is a contiguous strided tensor or a paged one (a block table of
 //     page numbers per sequence, pages of page_size tokens: the layout of a
@@ -43,15 +47,18 @@ namespace swaa {
 namespace {
 
 constexpr int kDStageBytes = 2 * kHalfBytes;          // K half, then V half
-// Stages of the ring: three (48 KiB, three workgroups per CU) for one column tile per workgroup,
-// where the copies in flight are what counts; two (32 KiB) for two tiles, whose 450 registers
-// leave one wave per SIMD, so that four such workgroups fit a CU: those shapes are bound by the
-// wave's own instruction stream, and a fourth wave per CU is a third more of it.
-constexpr int decode_stages(int tiles) { return tiles == 2 ? 2 : 3; }
-constexpr int decode_wgs_per_cu(int tiles) { return tiles == 2 ? 4 : 3; }
+// Stages of a wave's ring and workgroups per CU: the 450 registers of two column tiles leave one wave
+// per SIMD, so one workgroup, whose waves then take two stages each.
+constexpr int decode_stages(int tiles) { return tiles == 2 ? 2 : 1; }
+constexpr int decode_wgs_per_cu(int tiles) { return tiles == 2 ? 1 : 2; }
+constexpr int kDWaves = 4;
+constexpr int kDThreads = 64 * kDWaves;
+// LDS of a workgroup: every wave's ring, then the waves' references and row sums at the end
+constexpr int decode_wave_bytes(int tiles) { return decode_stages(tiles) * kDStageBytes; }
+constexpr int decode_smem_bytes(int tiles) { return kDWaves * (decode_wave_bytes(tiles) + tiles * 256); }
 constexpr int kCopiesPerHalf = 16;                    // wave instructions per stage: 8 for K, 8 for V
 constexpr int kMergeThreads = 1024;
-constexpr int kRounds = 1;  // rounds of resident workgroups the split plan aims for
+constexpr long long kDResident = 512;                 // workgroups of one column tile that run at once
 
 // ---- the split plan of a batch with per-sequence lengths, worked out by every workgroup of the
 // split kernel (DecodeParams::ragged has the rules) ----
@@ -80,7 +87,9 @@ __device__ __forceinline__ unsigned ragged_halves_per_split(const DecodeParams &
     const unsigned target = (unsigned)p.units_target;
     const unsigned total = sum_over_sequences([](unsigned n) { return n; });
     unsigned hps = (total + target - 1) / target;
-    hps = hps < 4u ? 4u : hps;
+    // (splits of less than 16 halves only where they are needed to have a workgroup per compute unit)
+    const unsigned wide = min((4 * total + target - 1) / target, 16u);
+    hps = (max(max(hps, wide), 4u) + 3u) & ~3u;  // (whole quarters for the four waves)
     // Rounding up per sequence can leave a few units more than the target, i.e. a handful of
     // workgroups in one more round than planned: lengthen the splits until the count fits (a
     // few steps; whatever they end on, the count stays below units_target + B).
@@ -121,7 +130,7 @@ __device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps,
 // kTiles: column tiles a workgroup computes from the same K and V fragments (1, or 2 when a pair
 // has more than 32 query rows: two tiles in two workgroups would read every key twice).
 template <bool kF16, bool kPaged, int kTiles>
-__global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParams p) {
+__global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_decode_split_kernel(const DecodeParams p) {
     // Workgroups reach the eight dies round-robin; the list has fewer than 2^31 items: 32-bit
     // arithmetic, divisions as multiplications.  Sequences of one length: die x takes the x-th
     // contiguous chunk of the item list (a die streams neighbouring memory: 3 % faster on one
@@ -129,7 +138,8 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
     // dies in turn, so that whatever the lengths every die gets its share of the long sequences.
     // Either way the column-tile groups of one (pair, split), which read the same keys, share a die.
     constexpr int kDStages = decode_stages(kTiles);
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned items = (unsigned)p.wg_items;
     unsigned witem;
     if (p.ragged) {
@@ -145,14 +155,13 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
     if (witem >= items) return;
     const unsigned item_ct = fastdiv(witem, p.div_ctgroups);      // witem / n_ctgroups
     const int ctg = (int)(witem - item_ct * (unsigned)p.n_ctgroups);
-    int b, kvh, split, halves_per_split;
+    int b, kvh, split, halves_per_split, n_splits;
     size_t slot0;  // workspace slot of the item's column tile 0
     if (p.ragged) {
         const unsigned unit = fastdiv(item_ct, p.div_hkv);        // (sequence, split) units, KV head innermost
         kvh = (int)(item_ct - unit * (unsigned)p.Hkv);
         const RaggedHalves rh = ragged_halves(p, lane);
         halves_per_split = __builtin_amdgcn_readfirstlane((int)ragged_halves_per_split(p, rh));
-        int n_splits;
         if (!ragged_find(rh, (unsigned)halves_per_split, unit, b, split, n_splits)) return;  // beyond the true list
         slot0 = (size_t)item_ct * p.n_coltiles;
         // the sequence's first workgroup tells the merge kernel where its splits are (all lanes
@@ -168,6 +177,7 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
         b = (int)fastdiv(upair, p.div_hkv);
         kvh = (int)upair - b * p.Hkv;
         halves_per_split = p.halves_per_split;
+        n_splits = p.n_splits;
         slot0 = ((size_t)upair * p.n_splits + split) * p.n_coltiles;
     }
     // this workgroup's column tiles and the workspace slots of their partial results
@@ -205,19 +215,24 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
     const int pos_min = Nk - p.Nq, pos_max = Nk - 1;
 
     const int h_begin = split * halves_per_split;
-    const int n_mine = min(vh.n - h_begin, halves_per_split);
-    if (n_mine <= 0) {
+    const int n_split = min(vh.n - h_begin, halves_per_split);
+    if (n_split <= 0) {
         // a shorter sequence has no keys for this split: an empty partial result (weight 0 in the merge)
 #pragma unroll
         for (int j = 0; j < kTiles; ++j)
-            if (col_valid[j] && hf == 0) {
+            if (col_valid[j] && hf == 0 && wave == 0) {
                 p.ws_ml[item[j] * 64 + l32] = -INFINITY;
                 p.ws_ml[item[j] * 64 + 32 + l32] = 0.f;
             }
         return;
     }
+    // Every wave takes a quarter of the split, contiguous: with the waves' halves interleaved the
+    // streams of all workgroups are a power of two apart (64 halves of 8 KiB on one 128k-token
+    // sequence) and meet on the same memory channels: 117 us instead of 99.
+    const int quarter = (n_split + kDWaves - 1) / kDWaves;
+    const int n_mine = max(0, min(quarter, n_split - wave * quarter));
     auto first_key = [&](int t) {
-        const int h = h_begin + t;
+        const int h = h_begin + quarter * wave + t;
         return 32 * (h < vh.n_sink ? h : h - vh.n_sink + vh.band0);
     };
 
@@ -255,7 +270,7 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
     };
     auto issue_half = [&](int t, int stage, const Pages pg) __attribute__((always_inline)) {
         const int k0 = first_key(t);
-        const uint32_t lds = (uint32_t)(stage * kDStageBytes);
+        const uint32_t lds = (uint32_t)(wave * decode_wave_bytes(kTiles) + stage * kDStageBytes);
         if constexpr (paged) {
             if (pages_per_half == 0) {
                 // page_size is a multiple of 4 only: the four rows of one instruction share a
@@ -345,8 +360,8 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
     const LaneAddr la = make_lane_addr(lane, 0);
 
     // ---- start-up: this lane's Q fragments (B operand of S^T = K Q^T: query row l32, 16 bytes at
-    // 32 ks + 16 hf) straight from HBM with ordinary loads, then the first three halves into the
-    // three stages.  The compiler places the wait for the Q loads in front of their first use,
+    // 32 ks + 16 hf) straight from HBM with ordinary loads, then the first halves into the
+    // stages.  The compiler places the wait for the Q loads in front of their first use,
     // and that wait covers the copies issued behind them as well (it cannot see them): a short
     // item has all its keys in flight at once and starts when they are there; a long one gives
     // away the head start of its first two steps, once. ----
@@ -358,9 +373,8 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
 #pragma unroll
         for (int ks = 0; ks < kKS; ++ks) qf[j][ks] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * ks);
     }
-    issue_half(0, 0, lookup(0));
-    if (n_mine >= 2) issue_half(1, 1, lookup(1));
-    if (kDStages >= 3 && n_mine >= 3) issue_half(2, 2, lookup(2));
+    if (n_mine >= 1) issue_half(0, 0, lookup(0));
+    if (kDStages >= 2 && n_mine >= 2) issue_half(1, 1, lookup(1));
     // (the idle cycles keep the loads two wait states away from the first MFMA that reads them)
 #pragma unroll
     for (int j = 0; j < kTiles; ++j)
@@ -388,22 +402,20 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
     for (int t = 0; t < n_mine; ++t) {
         // half t has landed when at most the copies of the halves issued after it are outstanding
         const int later = min(n_mine - 1 - t, kDStages - 1);
-        if (later >= 2)
-            asm volatile("s_waitcnt vmcnt(32)" ::: "memory");
-        else if (later == 1)
+        if (later == 1)
             asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         else
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        static_assert(kDStages <= 3 && kCopiesPerHalf == 16, "wait counts above");
+        static_assert(kDStages <= 2 && kCopiesPerHalf == 16, "wait counts above");
 
-        const uint32_t so = (uint32_t)(stage * kDStageBytes);
+        const uint32_t so = (uint32_t)(wave * decode_wave_bytes(kTiles) + stage * kDStageBytes);
         const int k0h = first_key(t);
         // no mask when every key of the half is visible to every column: at or below the
         // oldest row's diagonal, and inside the newest row's window or all sinks
         const bool masked = !((k0h + 31 <= pos_min) && ((k0h > pos_max - W) || (k0h + 31 < S)));
 
         // all operand fragments of the half go to registers first; once they are there the
-        // stage is free and the copy of the half three ahead leaves before any arithmetic
+        // stage is free and the copy of a later half leaves before any arithmetic
         bf16x8 kf[kKS], vf[2][kDB];
 #pragma unroll
         for (int ks = 0; ks < kKS; ++ks) kf[ks] = load_k_frag(la, so, ks);
@@ -443,30 +455,78 @@ __global__ __launch_bounds__(64) void swaa_decode_split_kernel(const DecodeParam
         stage = (stage + 1 == kDStages) ? 0 : stage + 1;
     }
 
-    // ---- partial result of the valid columns: O^T accumulators (row d, column l32), reference, sum ----
-    // The merge divides by the fp32 sums it combines; a partial O is the sum over the
-    // rounded P, so it is stored scaled by l / (sum of the rounded P).
+    // ---- the four waves' results are added up through LDS (each wave's O in its own ring, which
+    // only it has used, in accumulator order: conflict-free and without padding), then leave as
+    // the split's partial result -- or, with one split, as the output itself.
+    // The merge divides by the fp32 sums it combines; a wave's O is the sum over the rounded P,
+    // so it enters scaled by l / (sum of the rounded P). ----
+    typedef float __attribute__((address_space(3))) *LdsFloats;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef f32x4 __attribute__((address_space(3))) *LdsQuads;
+    constexpr uint32_t kMl = (uint32_t)(kDWaves * decode_wave_bytes(kTiles));  // [tile][wave][2][32]
+    float fix[kTiles];
 #pragma unroll
     for (int j = 0; j < kTiles; ++j) {
         float l_row, lb_row;
         row_sums(rs[j], l_row, lb_row);
-        const float fix = lb_row > 0.f ? l_row / lb_row : 0.f;  // a column that saw no key: O = 0, l = 0
+        fix[j] = lb_row > 0.f ? l_row / lb_row : 0.f;  // a column that saw no key: O = 0, l = 0
+        ((LdsFloats)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + wave) * 256)))[lane] = hf ? l_row : rs[j].mc;
+    }
+    __syncthreads();
+    float m[kTiles], l[kTiles];
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j) {
+        float mcs[kDWaves];
+        m[j] = -INFINITY;
+#pragma unroll
+        for (int x = 0; x < kDWaves; ++x) {
+            mcs[x] = ((LdsFloats)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + x) * 256)))[l32];
+            m[j] = fmaxf(m[j], mcs[x]);
+        }
+        const float m_use = m[j] == -INFINITY ? 0.f : m[j];
+        l[j] = 0.f;
+#pragma unroll
+        for (int x = 0; x < kDWaves; ++x)
+            l[j] += __builtin_amdgcn_exp2f(mcs[x] - m_use) * ((LdsFloats)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + x) * 256)))[32 + l32];
+        fix[j] *= __builtin_amdgcn_exp2f(rs[j].mc - m_use);
         if (col_valid[j]) {
-            float *wo = p.ws_o + (item[j] * p.col_stride + l32) * kD;
 #pragma unroll
-            for (int db = 0; db < kDB; ++db)
+            for (int c = 0; c < 16; ++c) {
+                f32x4 o4;
 #pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    float4 o4;
-                    o4.x = oacc[j][db][4 * e4 + 0] * fix;
-                    o4.y = oacc[j][db][4 * e4 + 1] * fix;
-                    o4.z = oacc[j][db][4 * e4 + 2] * fix;
-                    o4.w = oacc[j][db][4 * e4 + 3] * fix;
-                    *reinterpret_cast<float4 *>(wo + 32 * db + 8 * e4 + 4 * hf) = o4;
-                }
-            if (hf == 0) {
-                p.ws_ml[item[j] * 64 + l32] = rs[j].mc;
-                p.ws_ml[item[j] * 64 + 32 + l32] = l_row;
+                for (int e = 0; e < 4; ++e) o4[e] = oacc[j][c / 4][4 * (c % 4) + e] * fix[j];
+                *(LdsQuads)(uintptr_t)(wave * decode_wave_bytes(kTiles) + j * kDStageBytes + c * 1024 + lane * 16) = o4;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kTiles; ++j) {
+        if (!col_valid[j]) continue;
+        const size_t row = ((size_t)b * p.Hq + (size_t)kvh * p.G) * p.Nq + cc[j];
+        const float inv_l = 1.f / l[j];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int c = 4 * wave + i;  // this wave's share: head-dimension block `wave`
+            f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int x = 0; x < kDWaves; ++x)
+                o4 += *(LdsQuads)(uintptr_t)(x * decode_wave_bytes(kTiles) + j * kDStageBytes + c * 1024 + lane * 16);
+            const int d = 8 * c + 4 * hf;  // 32 (c / 4) + 8 (c % 4)
+            if (n_splits == 1) {
+                o4 *= inv_l;
+                const bf16x2 lo = pack_pair<kF16>(o4[0], o4[1]), hi = pack_pair<kF16>(o4[2], o4[3]);
+                *reinterpret_cast<bf16x4 *>(p.out + row * kD + d) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+            } else {
+                *reinterpret_cast<f32x4 *>(p.ws_o + (item[j] * p.col_stride + l32) * kD + d) = o4;
+            }
+        }
+        if (wave == 0 && hf == 0) {
+            if (n_splits == 1) {
+                p.lse[row] = (m[j] + __builtin_amdgcn_logf(l[j])) * 0.69314718055994530942f;
+            } else {
+                p.ws_ml[item[j] * 64 + l32] = m[j];
+                p.ws_ml[item[j] * 64 + 32 + l32] = l[j];
             }
         }
     }
@@ -629,7 +689,7 @@ __global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_ragged_kernel
         const long long row = (long long)blockIdx.x * (kMergeThreads / kD) + threadIdx.x / kD;
         if (row >= (long long)p.B * p.Hq * p.Nq) return;
         const MergeRow mr = merge_row(p, row);
-        if (mr.n_splits <= kMergeRowSplits) merge_row_by_group(p, mr, threadIdx.x % kD);
+        if (mr.n_splits > 1 && mr.n_splits <= kMergeRowSplits) merge_row_by_group(p, mr, threadIdx.x % kD);
         return;
     }
     const unsigned k = blockIdx.x - n_small, rows_per_seq = (unsigned)(p.Hq * p.Nq);
@@ -662,8 +722,6 @@ void plan_decode(DecodeParams &p, bool ragged) {
     const int all = (p.Nk + 31) / 32;
     const int bound = (p.S + 31) / 32 + (p.W + p.Nq - 2) / 32 + 2;
     p.n_halves = all < bound ? all : bound;
-    // kRounds rounds of three workgroups per CU (one round measured fastest: every split is
-    // resident at once and streams for the whole launch), but no split shorter than four halves
     p.tiles_per_item = p.n_coltiles >= 2 ? 2 : 1;
     p.n_ctgroups = (p.n_coltiles + p.tiles_per_item - 1) / p.tiles_per_item;
     const long long groups = (long long)p.B * p.Hkv * p.n_ctgroups;
@@ -689,20 +747,35 @@ void plan_decode(DecodeParams &p, bool ragged) {
         p.items = (long long)p.max_units * p.Hkv * p.n_coltiles;
         return;
     }
-    const long long target_items = 256LL * decode_wgs_per_cu(p.tiles_per_item) * kRounds;
-    long long per_group = target_items / groups;
-    // More (pair, column tile) groups than resident workgroups: one item per group would leave a
-    // second round of a few long items streaming alone at the end (100 sequences x 8 KV heads
-    // took 1.5 x the time of 96).  Many short items instead, kTailRounds rounds' worth: the
-    // partly filled tail is then one short item long.
-    constexpr long long kTailRounds = 8;
-    if (per_group < 1) per_group = (kTailRounds * target_items + groups - 1) / groups;
-    long long hps = (p.n_halves + per_group - 1) / per_group;
-    if (hps < 4) hps = 4;
+    // Sequences of one length.  A workgroup draws at most 50 GB/s, so 128 of them come near the
+    // rate of the memory and 256 reach it; more splits than that only cost the merge kernel and its
+    // traffic.  Measured over n splits (us; 8 KV heads, bf16):
+    //   1 sequence x 128k tokens      n = 8: 170, 16: 104, 24: 98, 32: 100, 48: 107, 64: 100
+    //   1 x window 8k                 n = 8: 19.5, 16: 16.0, 32: 14.0, 64: 15.2
+    //   4 x 8k                        n = 2: 42, 4: 29.6, 8: 29.7, 16: 29.4, 32: 35
+    //   16 x window 2k                n = 1: 27.3, 2: 30.4, 4: 30.5    (one split: no merge kernel)
+    //   16 x 16k                      n = 1: 215, 2: 196, 4: 187, 8: 188
+    //   64 x 2k                       n = 1: 96.7, 2: 101, 4: 106
+    //   100 x 4k                      n = 1: 312, 2: 306, 4: 294, 8: 294
+    //   256 x 1k                      n = 1: 183, 2: 196
+    //   64 x 4k, 16 new tokens        n = 1: 204, 2: 247, 4: 266      (two column tiles: 64 KiB of
+    //                                                                  partial results per split)
+    //   1 x 500                       n = 1: 10.1, 4: 10.6
+    long long n = 1;
+    if (groups < 128)
+        n = p.n_halves <= 16 ? 1 : 256 / groups < 32 ? 256 / groups : 32;
+    else if (p.tiles_per_item == 1 && p.n_halves > 96 && groups < 4 * kDResident)
+        n = groups <= 256 ? kDResident / groups : groups <= kDResident ? 1 : 4;
+    // (whole quarters for the four waves: rounded down if that makes at most an eighth more splits, else up)
+    long long hps = n == 1 ? p.n_halves : p.n_halves / n / 4 * 4;
+    if (n > 1 && (hps < 4 || (p.n_halves + hps - 1) / hps > n + n / 8)) hps = (p.n_halves + 4 * n - 1) / (4 * n) * 4;
+    // The workspace is sized for the most splits any smaller number of halves would get: a caller's
+    // workspace for a full-attention layer serves the windowed layers of the same model.
+    const long long most = n == 1 ? 1 : (p.n_halves + 3) / 4 < n + n / 8 ? (p.n_halves + 3) / 4 : n + n / 8;
     p.halves_per_split = (int)hps;
     p.n_splits = (int)((p.n_halves + hps - 1) / hps);
     p.wg_items = groups * p.n_splits;
-    p.items = (long long)p.B * p.Hkv * p.n_coltiles * p.n_splits;
+    p.items = (long long)p.B * p.Hkv * p.n_coltiles * most;
     p.div_splits = make_fastdiv((unsigned)p.n_splits);
 }
 
@@ -745,9 +818,23 @@ hipError_t launch_decode(const DecodeParams &p, hipStream_t stream) {
     const long long wgs = p.ragged ? (p.wg_items + per_round - 1) / per_round * per_round : chunk * kXcds;
     const dim3 grid((unsigned)wgs);
     const bool paged = p.block_table != nullptr;
+    hipError_t err = hipSuccess;
     auto launch = [&](auto f16, auto pg, auto tiles) {
-        hipLaunchKernelGGL((swaa_decode_split_kernel<decltype(f16)::value, decltype(pg)::value, decltype(tiles)::value>), grid,
-                           dim3(64), decode_stages(decltype(tiles)::value) * kDStageBytes, stream, p);
+        constexpr int kT = decltype(tiles)::value;
+        auto kernel = swaa_decode_split_kernel<decltype(f16)::value, decltype(pg)::value, kT>;
+        // more than 64 KiB of LDS per workgroup has to be requested once per device
+        static std::atomic<unsigned long long> configured{0};
+        int dev = 0;
+        err = hipGetDevice(&dev);
+        if (err != hipSuccess) return;
+        const unsigned long long bit = 1ull << (dev & 63);
+        if (!(configured.load(std::memory_order_acquire) & bit)) {
+            err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                      decode_smem_bytes(kT));
+            if (err != hipSuccess) return;
+            configured.fetch_or(bit, std::memory_order_release);
+        }
+        hipLaunchKernelGGL(kernel, grid, dim3(kDThreads), decode_smem_bytes(kT), stream, p);
     };
     auto pick_tiles = [&](auto f16, auto pg) {
         if (p.tiles_per_item == 2)
@@ -763,8 +850,8 @@ hipError_t launch_decode(const DecodeParams &p, hipStream_t stream) {
         pick_tiles(std::false_type{}, std::true_type{});
     else
         pick_tiles(std::false_type{}, std::false_type{});
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
+    if (err == hipSuccess) err = hipGetLastError();
+    if (err != hipSuccess || (!p.ragged && p.n_splits == 1)) return err;
     const long long rows = (long long)p.B * p.Hq * p.Nq;
     constexpr int kRowsPerWg = kMergeThreads / kD;
     const unsigned n_small = (unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg);
