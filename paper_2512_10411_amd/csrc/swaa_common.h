@@ -90,6 +90,7 @@ struct FwdParams {
     // sequence does not have); total_items and chunk are then upper bounds, the workgroups work
     // out the true ones from cu_q / cu_k (decode_work_packed).
     int packed_compact;
+    long long total_rows;  // query rows of the whole packed batch (packed_compact)
     // Split keys (swaa_fwd_pipelined.hip, split_plan): the tiles of a sequence are cut into
     // several workgroups along the keys, whose partial results a second kernel merges.
     // 0: not split; 1: the split counts are worked out on the device from the sequences'
@@ -99,7 +100,7 @@ struct FwdParams {
     int split_cap;  // partial results the workspace holds
     float *ws_o;    // [split_cap][4 waves][16][64 lanes][4]: unnormalised O in accumulator order
     float *ws_ml;   // [split_cap][4 waves][2][32]: reference (log2 units) and row sum
-    int *ws_n;      // [B]: split count of each sequence, for the merge kernel
+    int *ws_n;      // [64]: split count of each sequence, for the merge kernel
 };
 
 // One sequence as a workgroup sees it: the query rows are the newest nq of its nk
@@ -305,6 +306,7 @@ inline bool plan_work_packed(FwdParams &p, int rows, int wg_rows, long long tota
     const long long tiles = p.n4 * bound(wg_rows / 4) + p.has2 * bound(wg_rows / 2) + p.has1 * bound(wg_rows);
     const long long items = (long long)p.Hkv * tiles;
     p.packed_compact = 1;
+    p.total_rows = total_rows;
     p.chunk = (items + kXcds - 1) / kXcds + p.B;
     p.total_items = p.chunk * kXcds;
     return p.total_items <= 0x7fffffffLL;

@@ -787,11 +787,12 @@ template <bool kF16>
 __global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) {
     const int tid = threadIdx.x, lane = tid & 63, l32 = tid & 31, q = tid >> 5;
     const unsigned wave = blockIdx.x & 3u, rank = blockIdx.x >> 2;  // rank: tile among those of split sequences
+    const unsigned n_mine = (unsigned)p.ws_n[lane];
+    if (!__any(n_mine > 1u)) return;  // (the plan has left everything whole)
     int nq, nk, np;
     split_lengths(p, lane, nq, nk, np);
     const SplitSeq me = split_seq(p, nq, nk, np);
     const unsigned items = (unsigned)(me.tiles * p.Hkv);
-    const unsigned n_mine = items ? (unsigned)p.ws_n[lane] : 1u;  // (items: lane < B, and a split workgroup has been there)
     const unsigned incl = wave_inclusive_scan(n_mine > 1u ? items : 0u);
     const unsigned slots = wave_inclusive_scan(n_mine > 1u ? items * n_mine : 0u);
     if (rank >= wave_read_lane(incl, 63)) return;
@@ -893,15 +894,24 @@ long long plan_fwd_split(FwdParams &p) {
     // single generated tokens on long caches may stand beside them.
     if (p.B <= 4 && most > 2 * (long long)kSplitResident) return 0;
     const long long bound = p.packed_compact ? p.total_items : most;
+    // No sequence has fewer rows than are left when the others have Nq each, and all of them together
+    // no fewer tiles than one sequence with all the rows.
+    if (packed && p.packed_compact) {
+        const long long least = p.total_rows - (long long)(p.B - 1) * p.Nq;
+        const int units = p.Hkv * split_seq(p, (int)p.total_rows, (int)p.total_rows, 0).tiles;
+        if (least > 0 && whole_batch(p, (int)least, units)) return 0;
+    }
     int n = 1;
     if (p.B == 1 || (!packed && !p.n_prompts)) {
         // sequences of one length (a packed batch of one: of at most this length)
         if (longest.whole) return 0;
         const float items = (float)((long long)p.B * p.Hkv * longest.tiles);
-        float best = split_time(items, 0.f, (float)longest.halves, items * (float)longest.average);
+        const float memory = longest.tiles <= 2 ? (float)((long long)p.B * p.Hkv * longest.halves) : 0.f;
+        float best = split_time(items, 0.f, (float)longest.halves, items * (float)longest.average, memory);
         for (int c = 2; c <= 64; ++c) {
             if (longest.halves / c < kSplitMinHalves || items * (float)c > (float)kSplitUnits) break;
-            const float t = split_time(items * (float)c, items * (float)c, (float)((longest.halves + c - 1) / c), items * (float)longest.average);
+            const float t = split_time(items * (float)c, items * (float)c, (float)((longest.halves + c - 1) / c),
+                                       items * (float)longest.average, memory);
             if (t < best) {
                 best = t;
                 n = c;

@@ -5,26 +5,36 @@
 // a chip that runs 512 at once, and one generated token on a 12k-token cache is 375 halves of 32
 // keys in a row for one workgroup while the others are long done.  The tiles of a sequence are then
 // cut along the keys into n workgroups, each of which leaves its unnormalised O, its softmax
-// reference and its row sums in the workspace (as the decode kernel's splits do), and
-// swaa_fwd_merge_kernel adds them up.
+// reference and its row sums in the workspace, and swaa_fwd_merge_kernel adds them up.
 //
 // How many splits each sequence gets follows from a cost model in units of one half (the time a
 // workgroup needs for 32 keys with a second one on its compute unit, 0.83 us measured):
 //   * 64 candidates for the longest split, L = h_max / 1 .. h_max / 64 (at least kSplitMinHalves),
 //     one per lane; a sequence whose tiles visit h halves gets ceil(h / L) splits;
-//   * up to 256 units (workgroups) everybody has a compute unit alone and runs 1.6 x as fast, up to
-//     512 they share one in pairs: the longest one is the time.  Above, the chip works through the
-//     total, and the last units run out half a unit late on average;
-//   * a workgroup costs kSplitStart halves outside its loop (8 us measured), and splitting at all
-//     the merge kernel (kSplitMerge, 9-10 us) and the traffic of the partial results (64 KiB per
-//     unit).
+//   * m = (total + start-up) / 512 is the time of a chip kept full.  A unit (workgroup) alone on
+//     its compute unit runs 1 / kSplitAloneRate as fast: up to 256 units all of them are alone, above
+//     the longest one shares its unit for about m and is alone for the rest;
+//   * above 512 units the chip also works through the total, kSplitFull slower than m says, and the
+//     last units run out a share of an average one late;
+//   * sequences of one or two row tiles (generated tokens) read their keys for nobody else: HBM
+//     delivers 300 halves (16 KiB each) in the time of one;
+//   * a workgroup costs kSplitStart halves outside its loop, and splitting at all the merge kernel
+//     (kSplitMerge) and the traffic of the partial results (64 KiB per unit).
+// The constants are a fit to 70 batches of 1-34 sequences (100-2048 new rows beside 0-31 generated
+// tokens, caches of 2-30k tokens, 8-40 heads) at 4-11 plans each: the plan it picks costs 1.1-1.7 % more than
+// the best of them on average (3.2 % with the first model, which took the longest split for the time
+// below 512 units, did not know HBM's rate and split batches that fill the chip).
 // The lengths of a packed batch are known on the device only: there every workgroup works the plan
 // out for itself (batches of at most 64 sequences: one per lane).  Measured, binary16 and pages of
 // 16 tokens, 32 heads on 8: 512 rows on 24k tokens, full attention, 364 -> 207 us (four splits,
 // 196 + 9 us; 128 workgroups before); 23 generated tokens on caches of 1-12k tokens beside a chunk
 // of 999 rows on a 2k window 213 -> 139 us (bound by HBM: 470 MB, 95 us at the rate of a copy).
 // Calls that the plan leaves whole on the host (prompts on themselves, short windows, chunks that
-// fill the chip) launch the same kernels as without a workspace.
+// fill the chip) launch the same kernels as without a workspace: the split kernel takes 4-6 us more
+// for the same plan (the plan itself, a merge without work).
+// So do batches of chunks with little to gain (whole_batch), if the number of packed rows shows on the
+// host that they are that; the device follows the same rule, so that the results do not depend on
+// whether the caller states that number.
 #ifndef SWAA_FWD_SPLIT_H_
 #define SWAA_FWD_SPLIT_H_
 
@@ -35,8 +45,9 @@ namespace swaa {
 constexpr int kSplitMaxBatch = 64;   // one sequence per lane
 constexpr int kSplitMinHalves = 16;  // no split shorter than this many halves
 constexpr int kSplitUnits = 1024;    // most partial results a packed batch may leave (64 KiB each)
-constexpr float kSplitResident = 512.f, kSplitAlone = 256.f, kSplitAloneRate = 0.62f;
-constexpr float kSplitStart = 10.f, kSplitMerge = 12.f, kSplitTraffic = 0.03f;
+constexpr float kSplitResident = 512.f, kSplitAlone = 256.f, kSplitAloneRate = 0.65f;
+constexpr float kSplitStart = 8.f, kSplitMerge = 8.f, kSplitTraffic = 0.015f, kSplitFull = 1.1f, kSplitTail = 0.5f;
+constexpr float kSplitMemory = 1.f / 300.f;
 
 // Halves a row tile at positions [a, b] visits (as the kernel's prologue counts them).
 __host__ __device__ inline int tile_halves(int a, int b, int W, int S) {
@@ -76,12 +87,31 @@ __host__ __device__ inline int split_count(int h, int L, float rcp) {
     const int n = (int)((float)(h + L - 1) * rcp);
     return n < 1 ? 1 : n;
 }
-// Predicted time of a plan, in halves.
-__host__ __device__ inline float split_time(float units, float split_units, float longest, float total) {
-    const float t = units <= kSplitAlone      ? kSplitAloneRate * (longest + kSplitStart)
-                    : units <= kSplitResident ? longest + kSplitStart
-                                              : (total + kSplitStart * units) * (1.f / kSplitResident) + 0.5f * longest;
+// Predicted time of a plan, in halves.  memory: halves read from HBM by sequences of one or two row
+// tiles, over all KV heads.
+__host__ __device__ inline float split_time(float units, float split_units, float longest, float total, float memory) {
+    const float l = longest + kSplitStart, m = (total + kSplitStart * units) * (1.f / kSplitResident);
+    float t = kSplitAloneRate * l;
+    if (units > kSplitAlone) t += (1.f - kSplitAloneRate) * (l < m ? l : m);
+    if (units > kSplitResident) {
+        const float full = kSplitFull * m + kSplitTail * total / units;
+        t = t > full ? t : full;
+    }
+    t = t > memory * kSplitMemory ? t : memory * kSplitMemory;
     return split_units > 0.f ? t + kSplitMerge + kSplitTraffic * split_units : t;
+}
+
+// A batch in which every sequence brings at least `least` rows, `units` row tiles (times KV heads) in all:
+// stays whole where the split kernel does not win its overhead back.  From 64 rows on a sequence is
+// taken for a chunk of a prompt, whose rows see the window.  Measured, whole / best split: 128 - 432
+// units on a window of 1024, 33.3 / 37.0, 47.5 / 52.6 us, of 2048 52.4 / 56.3 (224), 65.8 / 70.9 (288 units); 408 and
+// more units of any length (17 batches) 1 - 5 % faster whole; 48 units on a window of 1024 31.6 / 30.0,
+// 120 on one of 2048 50.1 / 50.3.
+__host__ __device__ inline bool whole_batch(const FwdParams &p, int least, int units) {
+    if (least < 64) return false;
+    const int h = tile_halves(p.Nk - 32, p.Nk - 1, p.W, p.S);
+    return (units >= 400 && p.Hkv * split_seq(p, least, p.Nk, p.Nk).tiles >= 64) || (units >= 160 && h <= 72) ||
+           (units >= 64 && h <= 40);
 }
 
 // One workgroup's share of the keys.
@@ -143,12 +173,16 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     } else {
         // the model's terms of candidate `lane`, summed over the sequences: wave w takes every fourth
         const int splittable = me.whole ? 0 : me.halves;
-        int h_max = splittable;
+        int h_max = splittable, all = items, least = nq > 0 ? nq : p.Nq;
         float total = (float)items * (float)me.average;
+        float memory = me.tiles <= 2 ? (float)(p.Hkv * me.halves) : 0.f;
 #pragma unroll
         for (int sh = 32; sh > 0; sh >>= 1) {
             h_max = max(h_max, __shfl_xor(h_max, sh));
             total += __shfl_xor(total, sh);
+            memory += __shfl_xor(memory, sh);
+            all += __shfl_xor(all, sh);
+            least = min(least, __shfl_xor(least, sh));
         }
         const int L = max(kSplitMinHalves, (h_max + lane) / (lane + 1));
         const float rcp = 1.f / (float)L;
@@ -176,15 +210,16 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
             longest = fmaxf(longest, o[128]);
         }
         __syncthreads();  // (the scratch becomes part of a ring)
-        float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, longest, total);
+        float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, longest, total, memory);
         float best = t;
 #pragma unroll
         for (int sh = 32; sh > 0; sh >>= 1) best = fminf(best, __shfl_xor(best, sh));
         const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
         const int Lb = __builtin_amdgcn_readlane(L, pick);
-        if (splittable) n = split_count(me.halves, Lb, 1.f / (float)Lb);
+        if (splittable > 0 && !whole_batch(p, least, all)) n = split_count(me.halves, Lb, 1.f / (float)Lb);
     }
-    if (me.whole) n = 1;
+    if (me.whole || items == 0) n = 1;
+    if (blockIdx.x == 0) p.ws_n[lane] = n;  // every lane its sequence's, for the merge kernel
     const unsigned mine = (unsigned)items * (unsigned)n;
     const unsigned slots = n > 1 ? mine : 0u;
     const unsigned slots_incl = wave_inclusive_scan(slots);
@@ -199,7 +234,6 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     if (r >= u) return false;  // (the sequence's last chunks are shorter)
     si.n = (int)wave_read_lane((unsigned)n, b);
     si.slot = (b ? wave_read_lane(slots_incl, b - 1) : 0u) + r;
-    if (r == 0) p.ws_n[b] = si.n;  // (by every lane: a branch on the lane id would make what follows lane-dependent)
     w.b = b;
     const unsigned per_head = tiles * (unsigned)si.n;
     w.kvh = (int)(r / per_head);

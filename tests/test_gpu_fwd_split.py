@@ -98,3 +98,25 @@ def test_generated_tokens_beside_a_chunk(n_singles, W, fmt, page):
                 assert_parity(outs[0][0][None, :, r0:r0 + nq[b]], outs[0][1][None, :, r0:r0 + nq[b]], ro, rl,
                               tag=f"seq {b}: {nq[b]} rows on {nk[b]} keys")
             r0 += nq[b]
+
+
+@pytest.mark.parametrize("nq,nk,W", [([333, 400], [1500, 2000], 900),       # 80 units on a short window: whole
+                                     ([64, 640], [2000, 1100], 900),        # the shortest sequence taken for a chunk
+                                     ([63, 640], [2000, 1100], 900)])       # one row less: planned on the device
+def test_chunks_give_the_same_bits_whichever_list_they_run_on(nq, nk, W):
+    # whether the caller states the number of rows or not, a batch is split or left whole alike
+    Hkv, G, S, B = 3, 4, 4, len(nq)
+    print(f"[case] chunks {nq} on {nk} W{W}", flush=True)
+    host = [make_qkv(1, Hkv * G, Hkv, n, 128, 95000 + n, n_query=m) for m, n in zip(nq, nk)]
+    q, kk, vv = (torch.cat([to_device(h[i])[0] for h in host], dim=1).contiguous() for i in range(3))
+    offs = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32, device="cuda")
+    args = dict(cu_seqlens_q=offs(nq), cu_seqlens_k=offs(nk), max_seqlen_q=max(nq), max_seqlen_k=max(nk),
+                n_prompts=torch.tensor(nk, dtype=torch.int32, device="cuda"))
+    (out, lse), (o0, l0) = (tuple(t.clone() for t in binding.swaa_attn_fwd_ex(q, kk, vv, W, S, total_rows_q=t, **args)) for t in (None, 0))
+    torch.cuda.synchronize()
+    assert torch.equal(out, o0) and torch.equal(lse, l0)
+    r0 = 0
+    for b, h in enumerate(host):
+        ro, rl = swaa_decode_oracle(h[0], h[1], h[2], W, S, 1 / math.sqrt(128))
+        assert_parity(out[None, :, r0:r0 + nq[b]], lse[None, :, r0:r0 + nq[b]], ro, rl, tag=f"seq {b}: {nq[b]} rows on {nk[b]} keys")
+        r0 += nq[b]
