@@ -15,8 +15,8 @@
 //     decomposition and tile schedule), walks its visible KV tiles, recomputes
 //     S^T = K Q^T and dP^T = V dO^T and accumulates dQ^T += K^T dS^T.
 //   * swaa_bwd_dkv_kernel: a workgroup owns 128 keys of one KV head, walks
-//     every query head of the GQA group and every 64-row query tile that can
-//     see them, recomputes S = Q K^T and dP = dO V^T and accumulates
+//     every query head of the GQA group and every 64-row query tile (32-row
+//     block) that can see them, recomputes S = Q K^T and dP = dO V^T and accumulates
 //     dV^T += dO^T P and dK^T += Q^T dS.  Key tiles that hold sink
 //     keys are seen by every later row: their rows beyond the band are cut into
 //     segments with a workgroup each, and
@@ -26,10 +26,10 @@
 // consumes them (as in the forward kernels); operands that a product needs
 // transposed are read from row-major LDS tiles with ds_read_b64_tr_b16.
 // P and dS are rounded to bf16 before the second products, sums are fp32.
-// The kernels in this file stage tiles through registers (the templates, used for head
-// dimension 64) or by LDS DMA (dK/dV for head dimension 128) and leave instruction scheduling
-// to the compiler; dQ for head dimension 128 is the hand-pipelined kernel of
-// swaa_bwd_dq_pipelined.hip.  All big kernels run two waves per SIMD.
+// The kernels in this file stage tiles through registers (dQ for head dimension 64) or by LDS DMA
+// (dK/dV) and leave instruction scheduling to the compiler; dQ for head dimension 128 is the
+// hand-pipelined kernel of swaa_bwd_dq_pipelined.hip.  Two waves per SIMD for head dimension 128,
+// three (dK/dV) or four (dQ) for 64.
 #include <atomic>
 #include <cmath>
 
@@ -41,7 +41,6 @@ namespace swaa {
 namespace {
 
 constexpr int kBq = 64;  // query rows per tile of the dK/dV kernel
-constexpr int kDqBlocks = 1;  // 32-row blocks per wave of the dQ kernel
 
 template <int D>
 struct BTile {
@@ -72,12 +71,9 @@ __device__ __forceinline__ bf16x8 col_frag(const __bf16 *tile, int rb, int st, i
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-__device__ __forceinline__ bool visible(int i, int j, int W, int S, int P) {
-    return (j <= i) && ((i >= P) || (j > i - W) || (j < S));
-}
-// The same without short-circuit evaluation, for code that must stay free of branches:
-// per-element branches in the softmax stage of the dK/dV kernels (sixteen elements, several
-// conditions each) cost more than all of the stage's arithmetic.
+// Does row i see key j?  Without short-circuit evaluation, for code that must stay free of branches:
+// per-element branches in the softmax stages (sixteen elements, several conditions each) cost
+// more than all of the stage's arithmetic.
 __device__ __forceinline__ bool visible_in_range(int i, int j, int N, int W, int S, int P) {
     return (i < N) & (j <= i) & ((i >= P) | (j > i - W) | (j < S));
 }
@@ -101,15 +97,18 @@ __global__ __launch_bounds__(kThreads) void swaa_bwd_delta_kernel(const BwdParam
     if (row < rows && c == 0) p.delta[row] = acc;
 }
 
-// ---- dQ ------------------------------------------------------------------------------
-// QB: 32-row blocks per wave.  QB = 1 runs eight waves of 32 rows (two per SIMD, so that one
-// wave's exponentials overlap the other's MFMAs), QB = 2 four waves of 64 rows.
-template <int D, int QB>
-__global__ __launch_bounds__(512 / QB, 1) void swaa_bwd_dq_kernel(const BwdParams p) {
+// ---- dQ, head dimension 64 -------------------------------------------------------------
+// A workgroup is eight waves of 32 query rows; 128 registers per wave, so that two workgroups share
+// a compute unit and one wave's exponentials run under the others' matrix instructions.  (With a
+// whole 64-key tile's scores in registers a wave took 208, a compute unit one workgroup, and every
+// element of every tile its own mask branches: 95 us for two sequences of 4001 tokens, 16 heads on
+// 4, window 1000; now 62.)  A tile's two halves of 32 keys are worked through one after the other;
+// a wave skips the halves that its rows do not see and masks those on an edge.
+template <int D>
+__global__ __launch_bounds__(512, 4) void swaa_bwd_dq_kernel(const BwdParams p) {
     using T = BTile<D>;
     constexpr int KS = D / 16, DB = D / 32;
-    constexpr int TH = 512 / QB;           // threads per workgroup
-    constexpr int kRows = 32 * QB;         // query rows per wave
+    constexpr int TH = 512;                            // threads per workgroup
     constexpr int kCPT = kBk * T::kChunksPerRow / TH;  // 16-byte chunks of a tile per thread
     __shared__ __attribute__((aligned(16))) __bf16 Ks[T::kElems];
     __shared__ __attribute__((aligned(16))) __bf16 Vs[T::kElems];
@@ -119,20 +118,21 @@ __global__ __launch_bounds__(512 / QB, 1) void swaa_bwd_dq_kernel(const BwdParam
     const int hpb = wi.hpb;
     const int rows_per_wg = kWgRows / hpb;
     const int N = p.N, W = p.f.W, S = p.f.S, P = p.f.P;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
 
     const int head = wi.kvh * p.f.G + wi.h0 + (wave % hpb);
     const int wg_p0 = wi.pt * rows_per_wg;
     const int wg_p1 = min(N, wg_p0 + rows_per_wg) - 1;
-    const int p0 = wg_p0 + (wave / hpb) * kRows;
+    const int p0 = wg_p0 + (wave / hpb) * 32;
     const bool wave_active = p0 < N;
-    const int plast = min(p0 + kRows, N) - 1;
+    const int plast = min(p0 + 32, N) - 1;
+    const int qpos = p0 + l32;
 
     const int band_lo = (wg_p1 >= P) ? 0 : max(0, wg_p0 - W + 1);
     const int t_band_lo = band_lo / kBk;
     const int t_hi = wg_p1 / kBk;
     const int n_sink_tiles = min((min(S, band_lo) + kBk - 1) / kBk, t_band_lo);
-    const int wbound = window_bound(p0, kRows, W, P);
+    const int wbound = window_bound(p0, 32, W, P);
 
     const size_t kv_base = ((size_t)wi.b * p.Hkv + wi.kvh) * (size_t)N * D;
     const __bf16 *kg = p.f.k + kv_base;
@@ -141,29 +141,26 @@ __global__ __launch_bounds__(512 / QB, 1) void swaa_bwd_dq_kernel(const BwdParam
     const size_t r_base = ((size_t)wi.b * p.Hq + head) * (size_t)N;
 
     // this wave's Q and dO rows as B operands, its rows' lse (log2 units) and delta
-    bf16x8 qf[QB][KS], dof[QB][KS];
-    float lse2[QB], dl[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int row = min(p0 + 32 * qb + l32, N - 1);
+    bf16x8 qf[KS], dof[KS];
+    float lse2, dl;
+    {
+        const int row = min(qpos, N - 1);
         const __bf16 *qs = p.f.q + q_base + (size_t)row * D + 8 * hf;
         const __bf16 *ds = p.dout + q_base + (size_t)row * D + 8 * hf;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-            qf[qb][ks] = *reinterpret_cast<const bf16x8 *>(qs + 16 * ks);
-            dof[qb][ks] = *reinterpret_cast<const bf16x8 *>(ds + 16 * ks);
+            qf[ks] = *reinterpret_cast<const bf16x8 *>(qs + 16 * ks);
+            dof[ks] = *reinterpret_cast<const bf16x8 *>(ds + 16 * ks);
         }
-        lse2[qb] = p.f.lse[r_base + row] * 1.44269504088896340736f;
-        dl[qb] = p.delta[r_base + row];
+        lse2 = p.f.lse[r_base + row] * 1.44269504088896340736f;
+        dl = p.delta[r_base + row];
     }
 
-    f32x16 dqacc[DB][QB];
+    f32x16 dqacc[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) dqacc[db][qb][e] = 0.f;
+        for (int e = 0; e < 16; ++e) dqacc[db][e] = 0.f;
 
     u32x4 kreg[kCPT], vreg[kCPT];
     auto load_tile = [&](int t) {
@@ -203,64 +200,50 @@ __global__ __launch_bounds__(512 / QB, 1) void swaa_bwd_dq_kernel(const BwdParam
         const bool has_next = tn <= t_hi;
         if (has_next) load_tile(tn);
 
-        const int k0 = t * kBk, k_last = k0 + kBk - 1;
-        const bool in_future = k0 > plast;
-        const bool before_band = (plast < P) && (k_last < p0 - W + 1) && (k0 >= S);
-        if (wave_active && !in_future && !before_band) {
+#pragma unroll 1
+        for (int kb = 0; kb < 2; ++kb) {
+            const int k0 = t * kBk + 32 * kb, k_last = k0 + 31;
+            const bool in_future = k0 > plast;
+            const bool before_band = (plast < P) && (k_last < p0 - W + 1) && (k0 >= S);
+            if (!wave_active || in_future || before_band) continue;  // (uniform)
             const bool unmasked = (k_last <= p0) && ((k0 > wbound) || (k_last < S));
 
-            // S^T = K Q^T and dP^T = V dO^T : [64 keys] x [64 queries]
-            f32x16 sacc[2][QB], dpacc[2][QB];
+            // S^T = K Q^T and dP^T = V dO^T : [32 keys] x [32 queries]
+            f32x16 sacc, dpacc;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int e = 0; e < 16; ++e) {
+                sacc[e] = 0.f;
+                dpacc[e] = 0.f;
+            }
 #pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        sacc[kb][qb][e] = 0.f;
-                        dpacc[kb][qb][e] = 0.f;
-                    }
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    const bf16x8 ka = row_frag<D>(Ks, kb, ks, l32, hf);
-                    const bf16x8 va = row_frag<D>(Vs, kb, ks, l32, hf);
-#pragma unroll
-                    for (int qb = 0; qb < QB; ++qb) {
-                        sacc[kb][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qf[qb][ks], sacc[kb][qb], 0, 0, 0);
-                        dpacc[kb][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, dof[qb][ks], dpacc[kb][qb], 0, 0, 0);
-                    }
-                }
+            for (int ks = 0; ks < KS; ++ks) {
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(Ks, kb, ks, l32, hf), qf[ks], sacc, 0, 0, 0);
+                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(Vs, kb, ks, l32, hf), dof[ks], dpacc, 0, 0, 0);
+                if (ks % 2) __builtin_amdgcn_sched_barrier(0);  // (four operand reads in flight: more do not fit)
+            }
 
-            // P^T = exp2(s c2 - lse2) on visible pairs, dS^T = P^T (dP^T - delta), packed to bf16
-            bf16x8 dsf[2][QB][2];  // [kb][qb][16-key step]
+            // dS^T = P^T (dP^T - delta) with P^T = exp2(s c2 - lse2), packed to bf16; a score that must not
+            // be seen becomes -inf, its P an exact 0
+            if (!unmasked) {
 #pragma unroll
-            for (int qb = 0; qb < QB; ++qb) {
-                const int qpos = p0 + 32 * qb + l32;
+                for (int e = 0; e < 16; ++e) {
+                    const int key = k0 + 8 * (e / 4) + 4 * hf + (e % 4);
+                    sacc[e] = visible_in_range(qpos, key, N, W, S, P) ? sacc[e] : -INFINITY;
+                }
+            }
+            bf16x8 dsf[2];  // [16-key step]
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int key = k0 + 32 * kb + 8 * (e / 4) + 4 * hf + (e % 4);
-                        float pe = __builtin_amdgcn_exp2f(fmaf(sacc[kb][qb][e], c2, -lse2[qb]));
-                        if (!unmasked && !visible(qpos, key, W, S, P)) pe = 0.f;
-                        dsf[kb][qb][e / 8][e % 8] = (__bf16)(pe * (dpacc[kb][qb][e] - dl[qb]));
-                    }
+            for (int e = 0; e < 16; ++e) {
+                const float pe = __builtin_amdgcn_exp2f(fmaf(sacc[e], c2, -lse2));
+                dsf[e / 8][e % 8] = (__bf16)(pe * (dpacc[e] - dl));
             }
 
             // dQ^T += K^T dS^T
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int st = 0; st < 2; ++st)
 #pragma unroll
-                for (int st = 0; st < 2; ++st)
-#pragma unroll
-                    for (int db = 0; db < DB; ++db) {
-                        const bf16x8 a = col_frag<D>(Ks, kb, st, db, lane);
-#pragma unroll
-                        for (int qb = 0; qb < QB; ++qb)
-                            dqacc[db][qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsf[kb][qb][st], dqacc[db][qb], 0, 0, 0);
-                    }
+                for (int db = 0; db < DB; ++db)
+                    dqacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag<D>(Ks, kb, st, db, lane), dsf[st], dqacc[db], 0, 0, 0);
         }
 
         if (!has_next) break;
@@ -270,40 +253,21 @@ __global__ __launch_bounds__(512 / QB, 1) void swaa_bwd_dq_kernel(const BwdParam
         t = tn;
     }
 
-    if (!wave_active) return;
+    if (qpos >= N) return;
+    __bf16 *orow = p.dq + q_base + (size_t)qpos * D;
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-        const int row = p0 + 32 * qb + l32;
-        if (row >= N) continue;
-        __bf16 *orow = p.dq + q_base + (size_t)row * D;
+    for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+        for (int e4 = 0; e4 < 4; ++e4) {
+            bf16x4 o4;
 #pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                bf16x4 o4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(dqacc[db][qb][4 * e4 + e] * p.f.scale);
-                *reinterpret_cast<bf16x4 *>(orow + 32 * db + 8 * e4 + 4 * hf) = o4;
-            }
-    }
+            for (int e = 0; e < 4; ++e) o4[e] = (__bf16)(dqacc[db][4 * e4 + e] * p.f.scale);
+            *reinterpret_cast<bf16x4 *>(orow + 32 * db + 8 * e4 + 4 * hf) = o4;
+        }
 }
 
 // ---- dK, dV --------------------------------------------------------------------------
-// Eight waves, two per SIMD (one wave's exponentials overlap the other's MFMAs): wave w owns
-// the 32 keys 32*(w%4).. of the workgroup's 128 and the 32 rows 32*(w/4).. of every 64-row
-// query tile; the two row halves are added through LDS at the end.  The workgroup's K and V
-// rows stay in LDS for the whole kernel (B operands of S = Q K^T and dP = dO V^T), the query
-// tile's Q and dO are staged per step and read both row-wise and transposed.
-constexpr int kDkvThreads = 512;
-template <int D>
-struct DkvSmem {
-    using T = BTile<D>;
-    static constexpr int kKeyTileBytes = 128 * T::kStride * 2;  // K or V rows of the workgroup's keys
-    static constexpr int kQTileBytes = T::kElems * 2;
-    static constexpr int kK = 0, kV = kKeyTileBytes, kQ = 2 * kKeyTileBytes, kDO = kQ + kQTileBytes,
-                         kL = kDO + kQTileBytes, kDl = kL + kBq * 4, kBytes = kDl + kBq * 4;
-    static_assert(2 * kKeyTileBytes >= 4 * 32 * D * 4, "the K/V area doubles as the buffer of the final sum");
-};
+constexpr int kDkvThreads = 512;  // head dimension 128
 
 // Which key tile's main workgroup is block `bid` (the blocks before n_extra are sink
 // segments)?  Workgroups are dealt to the eight dies round-robin, and each die has its own
@@ -320,22 +284,52 @@ __device__ __forceinline__ int dkv_main_item(unsigned bid, int n_extra) {
     return (int)((bid % kXcds) * per_die + (bid - (unsigned)n_extra) / kXcds);
 }
 
+__device__ __forceinline__ bf16x8 lds16(uint32_t addr) {
+    return *(const bf16x8 __attribute__((address_space(3))) *)(uintptr_t)addr;
+}
+__device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(uintptr_t)addr);
+}
+
+// ---- dK, dV, head dimension 64 ----------------------------------------------------------
+// Wave w owns the 32 keys 32 (w % 4).. of the workgroup's 128, whose K and V rows stay in its registers
+// (B operands of S = Q K^T and dP = dO V^T), and every kDkvParts-th block of 32 query rows of the work
+// list (query head, row block): the four waves of part w / 4 copy that block's Q and dO rows to LDS
+// (global_load_lds_dwordx4, three buffers, one barrier per step) and read them row-wise and
+// transposed.  The parts are added through LDS at the end.  Rows are 128 bytes without padding;
+// 16-byte chunk c of row r lies at chunk c ^ f(r), f(r) = (((r >> 1) & 1) << 2) | ((r >> 2) & 3), applied on
+// the global side of the copy: conflict-free for 16 consecutive rows reading one logical chunk and
+// for 4 consecutive rows reading the same 64 bytes.
+// A short sequence has few key tiles (two of 4001 tokens on 4 KV heads: 256, one per compute
+// unit), so the waves that hide each other's latencies have to come from one workgroup: three per
+// SIMD with 168 registers each.  (Two parts, K and V read from LDS, tiles staged through registers with
+// two barriers a step: 139 us for those sequences; now 125, and 138 with two parts.  Each step is a
+// phase of matrix work, one of vector work and one of matrix work again for all waves at once; the
+// priorities by part pull them apart a little: 133 -> 126.)
+// This kernel declares no static LDS: its dynamic LDS starts at address 0.
+constexpr int kDkvParts = 3;
+constexpr float kLog2e = 1.44269504088896340736f;
 template <int D>
-__global__ __launch_bounds__(kDkvThreads, 1) void swaa_bwd_dkv_kernel(const BwdParams p) {
-    using T = BTile<D>;
+struct DkvSmem {
+    static constexpr int kRowBytes = D * 2;
+    static constexpr int kBlockBytes = 32 * kRowBytes;            // 32 rows of Q, or of dO
+    static constexpr int kPartBytes = 2 * kBlockBytes + 64 * 4;   // Q, dO, lse and delta of the rows
+    static constexpr int kBufferBytes = kDkvParts * kPartBytes;
+    static constexpr int kSumBytes = 4 * 32 * D * 4;              // the final sum: one part's dK or dV
+    static constexpr int kBuffers = 3;
+    static constexpr int kBytes = kBuffers * kBufferBytes > kSumBytes ? kBuffers * kBufferBytes : kSumBytes;
+};
+
+template <int D>
+__global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kernel(const BwdParams p) {
+    static_assert(D == 64, "the swizzle below is for rows of 128 bytes");
     using M = DkvSmem<D>;
     constexpr int KS = D / 16, DB = D / 32;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    __bf16 *Ks = reinterpret_cast<__bf16 *>(smem + M::kK);
-    __bf16 *Vs = reinterpret_cast<__bf16 *>(smem + M::kV);
-    __bf16 *Qs = reinterpret_cast<__bf16 *>(smem + M::kQ);
-    __bf16 *dOs = reinterpret_cast<__bf16 *>(smem + M::kDO);
-    float *Ls = reinterpret_cast<float *>(smem + M::kL);    // lse of the tile's rows, log2 units
-    float *Dls = reinterpret_cast<float *>(smem + M::kDl);  // their delta
 
     const int N = p.N, W = p.f.W, S = p.f.S, P = p.f.P, G = p.f.G;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-    const int kq = wave & 3, qb = wave >> 2;  // key block and row half of this wave
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
+    const int kq = wave & 3, part = wave >> 2;
     // Work list: first the segments of the sink key tiles (rows beyond the band), then one
     // workgroup per key tile of 128 keys (band rows; for key tiles without sinks also the
     // generated rows).  Under a causal mask the first key tiles are seen by the most rows.
@@ -361,16 +355,14 @@ __global__ __launch_bounds__(kDkvThreads, 1) void swaa_bwd_dkv_kernel(const BwdP
     const int key = kw0 + l32;                            // this lane's key column
     const bool wave_active = kw0 < N;
 
-    // the workgroup's K and V rows -> LDS (rows past the end repeat the last key; they stay invisible)
+    // this wave's K and V rows as B operands (rows past the end repeat the last key; they stay invisible)
+    bf16x8 kf[KS], vf[KS];
     {
-        const size_t kv_base = ((size_t)b * p.Hkv + kvh) * (size_t)N * D;
+        const size_t g = (((size_t)b * p.Hkv + kvh) * (size_t)N + min(key, N - 1)) * D + 8 * hf;
 #pragma unroll
-        for (int c = 0; c < 128 * T::kChunksPerRow / kDkvThreads; ++c) {
-            const int id = c * kDkvThreads + tid;
-            const int row = id / T::kChunksPerRow, col = (id % T::kChunksPerRow) * 8;
-            const size_t g = kv_base + (size_t)min(k0 + row, N - 1) * D + col;
-            *reinterpret_cast<u32x4 *>(&Ks[row * T::kStride + col]) = *reinterpret_cast<const u32x4 *>(p.f.k + g);
-            *reinterpret_cast<u32x4 *>(&Vs[row * T::kStride + col]) = *reinterpret_cast<const u32x4 *>(p.f.v + g);
+        for (int ks = 0; ks < KS; ++ks) {
+            kf[ks] = *reinterpret_cast<const bf16x8 *>(p.f.k + g + 16 * ks);
+            vf[ks] = *reinterpret_cast<const bf16x8 *>(p.f.v + g + 16 * ks);
         }
     }
     f32x16 dkacc[DB], dvacc[DB];
@@ -382,77 +374,106 @@ __global__ __launch_bounds__(kDkvThreads, 1) void swaa_bwd_dkv_kernel(const BwdP
             dvacc[db][e] = 0.f;
         }
 
-    // query tiles (64 rows) with a row that sees one of the workgroup's keys: the band tiles
-    // tq_lo .. tq_band_hi, then -- if a key is a sink, or there are generated rows -- the rest.
-    // For a sink key tile the rest is cut into segments: the main workgroup keeps the band.
-    const int tq_last = (N - 1) / kBq;
-    const int tq_band_hi = min(N - 1, k1 + W - 1) / kBq;
-    int tq_lo = k0 / kBq;
-    int n_band = tq_band_hi - tq_lo + 1;
-    int tq_x = tq_last + 1, tq_x_end = tq_last;  // second range
+    // Row blocks (32 rows) with a row that sees one of the workgroup's keys: the band blocks, then
+    // -- if a key is a sink, or there are generated rows -- the rest.  For a sink key tile the
+    // rest is cut into segments of seg_tiles 64-row tiles, and the main workgroup keeps the band.
+    const int last_block = (N - 1) / 32;
+    const int first = k0 / 32;
+    int band_hi = min(N - 1, k1 + W - 1) / 32;
+    int x0 = last_block + 1, x1 = last_block;  // second range
     if (sink_kt) {
+        band_hi = min(band_hi | 1, last_block);  // (the segments start at a whole tile)
         if (seg >= 0) {
-            n_band = 0;
-            tq_x = tq_band_hi + 1 + seg * p.seg_tiles;
-            tq_x_end = min(tq_last, tq_x + p.seg_tiles - 1);
+            x0 = band_hi + 1 + 2 * seg * p.seg_tiles;
+            x1 = min(last_block, x0 + 2 * p.seg_tiles - 1);
         }
     } else if (P < N) {
-        tq_x = max(tq_band_hi + 1, P / kBq);
+        x0 = max(band_hi + 1, P / 32);
     }
-    const int n_tiles = n_band + max(0, tq_x_end - tq_x + 1);
-    auto tile_of = [&](int n) { return n < n_band ? tq_lo + n : tq_x + (n - n_band); };
+    const int n_band = seg >= 0 ? 0 : band_hi - first + 1;
+    const int n_blocks = n_band + max(0, x1 - x0 + 1);  // per query head
+    const int total = G * n_blocks;
+    auto block_of = [&](int i) { return i < n_band ? first + i : x0 + (i - n_band); };
 
     const float c2 = p.f.scale_log2;
-    constexpr int kCPT = kBk * T::kChunksPerRow / kDkvThreads;
-    u32x4 qreg[kCPT], dreg[kCPT];
-    float lreg = 0.f, dlreg = 0.f;
-    auto load_tile = [&](int head, int tq) {
-        const size_t base = ((size_t)b * p.Hq + head) * (size_t)N;
-#pragma unroll
-        for (int c = 0; c < kCPT; ++c) {
-            const int id = c * kDkvThreads + tid;
-            const int row = min(tq * kBq + id / T::kChunksPerRow, N - 1);
-            const int col = (id % T::kChunksPerRow) * 8;
-            qreg[c] = *reinterpret_cast<const u32x4 *>(p.f.q + (base + row) * D + col);
-            dreg[c] = *reinterpret_cast<const u32x4 *>(p.dout + (base + row) * D + col);
+    // A block's rows into LDS: one instruction of 8 rows x 128 bytes per wave for Q and for dO, and one of
+    // 32 lse and 32 delta by the part's first wave (all of them counted together by vmcnt).  Blocks are
+    // asked for two steps ahead, in the order of the list; `at` is the next one's place in it.
+    const int lrow = 8 * kq + (lane >> 3);
+    const uint32_t lchk = (uint32_t)(((lane & 7) ^ ((((lrow >> 1) & 1) << 2) | ((lrow >> 2) & 3))) << 4);
+    int at_head = kvh * G, at = part, at_entry = part, at_buf = 0;
+    auto request_next = [&]() {  // its row block, or -1 behind the end of the list
+        if (at_entry >= total) return -1;
+        while (at >= n_blocks) {
+            at -= n_blocks;
+            ++at_head;
         }
-        if (tid < kBq) {
-            const int row = min(tq * kBq + tid, N - 1);
-            lreg = p.f.lse[base + row] * 1.44269504088896340736f;
-            dlreg = p.delta[base + row];
+        const int block = block_of(at);
+        const size_t base = ((size_t)b * p.Hq + at_head) * (size_t)N;
+        const size_t row = base + min(block * 32 + lrow, N - 1);
+        const char *gq = reinterpret_cast<const char *>(p.f.q + row * D) + lchk;
+        const char *gd = reinterpret_cast<const char *>(p.dout + row * D) + lchk;
+        const uint32_t lds = (uint32_t)(at_buf * M::kBufferBytes + part * M::kPartBytes);
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gq), "s"(lds + (uint32_t)(kq * 1024)) : "memory");
+        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gd), "s"(lds + (uint32_t)(M::kBlockBytes + kq * 1024)) : "memory");
+        if (kq == 0) {
+            const float *gl = (hf ? p.delta : p.f.lse) + base + min(block * 32 + l32, N - 1);
+            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(gl), "s"(lds + (uint32_t)(2 * M::kBlockBytes)) : "memory");
         }
+        at += kDkvParts;
+        at_entry += kDkvParts;
+        at_buf = at_buf == M::kBuffers - 1 ? 0 : at_buf + 1;
+        return block;
     };
-    auto store_tile = [&]() {
-#pragma unroll
-        for (int c = 0; c < kCPT; ++c) {
-            const int id = c * kDkvThreads + tid;
-            const int row = id / T::kChunksPerRow;
-            const int col = (id % T::kChunksPerRow) * 8;
-            *reinterpret_cast<u32x4 *>(&Qs[row * T::kStride + col]) = qreg[c];
-            *reinterpret_cast<u32x4 *>(&dOs[row * T::kStride + col]) = dreg[c];
-        }
-        if (tid < kBq) {
-            Ls[tid] = lreg;
-            Dls[tid] = dlreg;
-        }
+    // The copies of all but the newest block (none, if that was not asked for) have landed: this wave's,
+    // then everybody's.
+    auto step_end = [&](bool newest) {
+        if (!newest)
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        else if (kq == 0)
+            __builtin_amdgcn_s_waitcnt(0x0F73);  // vmcnt(3)
+        else
+            __builtin_amdgcn_s_waitcnt(0x0F72);  // vmcnt(2)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     };
 
-    const int total = G * n_tiles;  // (head, tile) steps, head-major
-    int step = 0;
-    if (total > 0) {
-        load_tile(kvh * G, tile_of(0));
-        store_tile();
-    }
-    __syncthreads();
+    // per-lane fragment addresses inside a block (swizzle folded in)
+    //  * row fragment, k-step ks: row l32, logical chunk 2 ks + hf:  row_lane ^ (ks << 5)
+    //  * transposed fragment, 16-row step st, head-dimension block db: rows 16 st + 4 hf + j16 / 4 (lo) and
+    //    8 further (hi), logical chunk 4 db + 2 (grp & 1) + (j16 & 3) / 2:  col_lane ^ (db << 6), + rows
+    const uint32_t row_lane = (uint32_t)(l32 * M::kRowBytes + ((hf ^ ((((l32 >> 1) & 1) << 2) | ((l32 >> 2) & 3))) << 4));
+    const int grp = lane >> 4, j16 = lane & 15;
+    const int rr = 4 * hf + (j16 >> 2);
+    const int cl = 2 * (grp & 1) + ((j16 & 3) >> 1);
+    const uint32_t col_lo = (uint32_t)(rr * M::kRowBytes + ((((j16 >> 3) << 2) | (cl ^ hf)) << 4) + 8 * (j16 & 1));
+    const uint32_t col_hi = (uint32_t)((rr + 8) * M::kRowBytes + ((((j16 >> 3) << 2) | (cl ^ (hf + 2))) << 4) + 8 * (j16 & 1));
+    auto row_frag_at = [&](uint32_t tile, int ks) { return lds16(tile + (row_lane ^ (uint32_t)(ks << 5))); };
+    auto col_frag_at = [&](uint32_t tile, int st, int db) {
+        const uint32_t off = tile + (uint32_t)(16 * st * M::kRowBytes);
+        const s16x4 lo = lds8_tr(off + (col_lo ^ (uint32_t)(db << 6)));
+        const s16x4 hi = lds8_tr(off + (col_hi ^ (uint32_t)(db << 6)));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
 
-    while (total > 0) {
-        const bool has_next = step + 1 < total;
-        if (has_next) load_tile(kvh * G + (step + 1) / n_tiles, tile_of((step + 1) % n_tiles));
+    const int steps = (total + kDkvParts - 1) / kDkvParts;
+    if (part == 0)
+        __builtin_amdgcn_s_setprio(2);
+    else if (part == 1)
+        __builtin_amdgcn_s_setprio(1);
+    int block = request_next(), next = request_next(), buf = 0;
+    step_end(next >= 0);  // (K and V of the wave are older than both)
 
-        const int tq = tile_of(step % n_tiles);
-        const int i0 = tq * kBq + 32 * qb, i1 = i0 + 31;  // this wave's rows of the tile
-        // can any of them see any key of this wave?
-        const bool sees = (i0 < N) && (i1 >= kw0) && ((i0 < kw1 + W) || (kw0 < S) || (i1 >= P));
+    for (int step = 0; step < steps; ++step) {
+        // (the buffer of the block after next was last read a step ago, in front of that step's barrier)
+        const int after = request_next();
+
+        const uint32_t Qs = (uint32_t)(buf * M::kBufferBytes + part * M::kPartBytes);
+        const uint32_t dOs = Qs + (uint32_t)M::kBlockBytes, Ls = dOs + (uint32_t)M::kBlockBytes;
+        const int i0 = block * 32, i1 = i0 + 31;
+        // can any of the rows see any key of this wave?
+        const bool sees = block >= 0 && (i1 >= kw0) && ((i0 < kw1 + W) || (kw0 < S) || (i1 >= P));
         if (wave_active && sees) {
             // all 32 x 32 pairs visible: rows at or below the keys' diagonal, inside every row's window
             // (or the keys are sinks, or the rows are generated tokens), and no row past the end
@@ -467,87 +488,82 @@ __global__ __launch_bounds__(kDkvThreads, 1) void swaa_bwd_dkv_kernel(const BwdP
             }
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(Qs, qb, ks, l32, hf),
-                                                               row_frag<D>(Ks, kq, ks, l32, hf), sacc, 0, 0, 0);
-                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(dOs, qb, ks, l32, hf),
-                                                                row_frag<D>(Vs, kq, ks, l32, hf), dpacc, 0, 0, 0);
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag_at(Qs, ks), kf[ks], sacc, 0, 0, 0);
+                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag_at(dOs, ks), vf[ks], dpacc, 0, 0, 0);
+                if (ks % 2) __builtin_amdgcn_sched_barrier(0);  // (four operand reads in flight: more do not fit)
             }
 
-            // P and dS in the accumulator layout (row 8 (e/4) + 4 hf + e%4, column = this lane's key)
+            // P and dS in the accumulator layout (row 8 (e/4) + 4 hf + e%4, column = this lane's key); a
+            // score that must not be seen becomes -inf, its P an exact 0
+            if (!unmasked) {
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    sacc[e] = visible_in_range(i0 + 8 * (e / 4) + 4 * hf + e % 4, key, N, W, S, P) ? sacc[e] : -INFINITY;
+            }
             bf16x8 pf[2], dsf[2];  // [16-row step]
-            // (one uniform branch per tile, none per element: see visible_in_range)
-            auto softmax_stage = [&](auto masked) {
 #pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    const int r4 = 32 * qb + 8 * e4 + 4 * hf;
-                    const float4 l4 = *reinterpret_cast<const float4 *>(&Ls[r4]);
-                    const float4 d4 = *reinterpret_cast<const float4 *>(&Dls[r4]);
-                    const float lv[4] = {l4.x, l4.y, l4.z, l4.w};
-                    const float dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+            for (int e4 = 0; e4 < 4; ++e4) {
+                const int r4 = 8 * e4 + 4 * hf;
+                typedef float f32x4 __attribute__((ext_vector_type(4)));
+                const f32x4 lv = *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)(Ls + r4 * 4);
+                const f32x4 dv4 = *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)(Ls + 128 + r4 * 4);
 #pragma unroll
-                    for (int x = 0; x < 4; ++x) {
-                        const int e = 4 * e4 + x;
-                        const int row = tq * kBq + r4 + x;
-                        float pe = __builtin_amdgcn_exp2f(fmaf(sacc[e], c2, -lv[x]));
-                        if (decltype(masked)::value) pe = visible_in_range(row, key, N, W, S, P) ? pe : 0.f;
-                        pf[e / 8][e % 8] = (__bf16)pe;
-                        dsf[e / 8][e % 8] = (__bf16)(pe * (dpacc[e] - dv4[x]));
-                    }
+                for (int x = 0; x < 4; ++x) {
+                    const int e = 4 * e4 + x;
+                    const float pe = __builtin_amdgcn_exp2f(fmaf(sacc[e], c2, -kLog2e * lv[x]));
+                    pf[e / 8][e % 8] = (__bf16)pe;
+                    dsf[e / 8][e % 8] = (__bf16)(pe * (dpacc[e] - dv4[x]));
                 }
-            };
-            if (unmasked)
-                softmax_stage(std::false_type{});
-            else
-                softmax_stage(std::true_type{});
+            }
 
             // dV^T += dO^T P,  dK^T += Q^T dS
 #pragma unroll
             for (int st = 0; st < 2; ++st)
 #pragma unroll
                 for (int db = 0; db < DB; ++db) {
-                    dvacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag<D>(dOs, qb, st, db, lane), pf[st], dvacc[db], 0, 0, 0);
-                    dkacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag<D>(Qs, qb, st, db, lane), dsf[st], dkacc[db], 0, 0, 0);
+                    dvacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag_at(dOs, st, db), pf[st], dvacc[db], 0, 0, 0);
+                    dkacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag_at(Qs, st, db), dsf[st], dkacc[db], 0, 0, 0);
                 }
         }
-
-        if (!has_next) break;
-        __syncthreads();
-        store_tile();
-        __syncthreads();
-        ++step;
+        step_end(after >= 0);
+        block = next;
+        next = after;
+        buf = buf == M::kBuffers - 1 ? 0 : buf + 1;
     }
 
-    // ---- add the two row halves: waves 4..7 hand their sums to waves 0..3 through LDS
-    // (the K/V area, which nobody reads any more), first dK, then dV ----
+    // ---- add the parts: the waves of part 1, 2, .. hand their sums to part 0 through LDS ----
     float *xbuf = reinterpret_cast<float *>(smem);  // [4 key blocks][D][32 key columns]
+#pragma unroll 1
+    for (int from = 1; from < kDkvParts; ++from) {
 #pragma unroll
-    for (int which = 0; which < 2; ++which) {
-        __syncthreads();
-        if (qb == 1) {
+        for (int which = 0; which < 2; ++which) {
+            if (part == from) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int d = 32 * db + 8 * (e / 4) + 4 * hf + (e % 4);
-                    xbuf[(kq * D + d) * 32 + l32] = which == 0 ? dkacc[db][e] : dvacc[db][e];
-                }
-        }
-        __syncthreads();
-        if (qb == 0) {
+                    for (int e = 0; e < 16; ++e) {
+                        const int d = 32 * db + 8 * (e / 4) + 4 * hf + (e % 4);
+                        xbuf[(kq * D + d) * 32 + l32] = which == 0 ? dkacc[db][e] : dvacc[db][e];
+                    }
+            }
+            __syncthreads();
+            if (part == 0) {
 #pragma unroll
-            for (int db = 0; db < DB; ++db)
+                for (int db = 0; db < DB; ++db)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int d = 32 * db + 8 * (e / 4) + 4 * hf + (e % 4);
-                    const float other = xbuf[(kq * D + d) * 32 + l32];
-                    if (which == 0)
-                        dkacc[db][e] += other;
-                    else
-                        dvacc[db][e] += other;
-                }
+                    for (int e = 0; e < 16; ++e) {
+                        const int d = 32 * db + 8 * (e / 4) + 4 * hf + (e % 4);
+                        const float other = xbuf[(kq * D + d) * 32 + l32];
+                        if (which == 0)
+                            dkacc[db][e] += other;
+                        else
+                            dvacc[db][e] += other;
+                    }
+            }
+            __syncthreads();
         }
     }
-    if (qb != 0) return;
+    if (part != 0) return;
 
     if (sink_kt) {
         // fp32 partial sums of all 128 key columns (columns past the end hold zeros)
@@ -581,8 +597,9 @@ __global__ __launch_bounds__(kDkvThreads, 1) void swaa_bwd_dkv_kernel(const BwdP
 }
 
 // ---- dK, dV, head dimension 128: tiles by LDS DMA -------------------------------------------
-// Same decomposition, arithmetic and summation order as swaa_bwd_dkv_kernel; what differs is
-// how the tiles reach LDS and how they lie there.  K, V (once per workgroup) and the query
+// Eight waves, two per SIMD (one wave's exponentials overlap the other's MFMAs): wave w owns
+// the 32 keys 32*(w%4).. of the workgroup's 128 and the 32 rows 32*(w/4).. of every 64-row
+// query tile; the two row halves are added through LDS at the end.  K, V (once per workgroup) and the query
 // tile's Q and dO (per step, two buffers each) travel HBM -> LDS with global_load_lds_dwordx4,
 // no register staging and no store phase: one barrier per step instead of two.  Rows are 256
 // bytes without padding; 16-byte chunk c of row r lies at chunk c ^ g(r), g(r) = ((r & 3) << 2)
@@ -600,12 +617,6 @@ constexpr int kQTileBytes = kBq * kRowBytes;    // 16 KiB
 constexpr int kK = 0, kV = kKeyTileBytes, kQ = 2 * kKeyTileBytes, kDO = kQ + 2 * kQTileBytes, kL = kDO + 2 * kQTileBytes,
               kDl = kL + 2 * kBq * 4, kBytes = kDl + 2 * kBq * 4;
 static_assert(2 * kKeyTileBytes >= 4 * 32 * kD * 4, "the K/V area doubles as the buffer of the final sum");
-__device__ __forceinline__ bf16x8 lds16(uint32_t addr) {
-    return *(const bf16x8 __attribute__((address_space(3))) *)(uintptr_t)addr;
-}
-__device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(uintptr_t)addr);
-}
 }  // namespace dma128
 
 __global__ __launch_bounds__(kDkvThreads, 1) void swaa_bwd_dkv_dma_kernel(const BwdParams p) {
@@ -941,21 +952,21 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     if (err != hipSuccess) return err;
     const unsigned long long bit = 1ull << (dev & 63);
     const bool first_time = !(configured.load(std::memory_order_acquire) & bit);
-    if (D == 128)
+    if constexpr (D == 128)
         err = launch_bwd_dq_pipelined_d128(p, stream);  // swaa_bwd_dq_pipelined.hip
     else
-        hipLaunchKernelGGL((swaa_bwd_dq_kernel<D, kDqBlocks>), dim3((unsigned)(p.f.chunk * kXcds)), dim3(512 / kDqBlocks), 0,
-                           stream, p);
+        hipLaunchKernelGGL(swaa_bwd_dq_kernel<D>, dim3((unsigned)(p.f.chunk * kXcds)), dim3(512), 0, stream, p);
     if (err == hipSuccess) err = hipGetLastError();
     if (err != hipSuccess) return err;
     const long long n_kt = (p.N + 127) / 128;
     const long long pairs = (long long)p.B * p.Hkv;
     if (first_time) {
-        err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_kernel<D>),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, DkvSmem<D>::kBytes);
-        if (err != hipSuccess) return err;
-        err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_dma_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, dma128::kBytes);
+        if constexpr (D == 128)
+            err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_dma_kernel),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, dma128::kBytes);
+        else
+            err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_kernel<D>),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, DkvSmem<D>::kBytes);
         if (err != hipSuccess) return err;
         configured.fetch_or(bit, std::memory_order_release);
     }
@@ -963,10 +974,10 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     // rounded up to a multiple of the die count (dkv_main_item)
     const long long n_main = (pairs * n_kt + kXcds - 1) / kXcds * kXcds;
     const dim3 dkv_grid((unsigned)(pairs * (long long)p.n_sink_kt * p.n_seg + n_main));
-    if (D == 128)
+    if constexpr (D == 128)
         hipLaunchKernelGGL(swaa_bwd_dkv_dma_kernel, dkv_grid, dim3(kDkvThreads), dma128::kBytes, stream, p);
     else
-        hipLaunchKernelGGL(swaa_bwd_dkv_kernel<D>, dkv_grid, dim3(kDkvThreads), DkvSmem<D>::kBytes, stream, p);
+        hipLaunchKernelGGL(swaa_bwd_dkv_kernel<D>, dkv_grid, dim3(256 * kDkvParts), DkvSmem<D>::kBytes, stream, p);
     err = hipGetLastError();
     if (err != hipSuccess || p.n_sink_kt == 0) return err;
     const long long threads = pairs * p.n_sink_kt * (128LL * D / 4);

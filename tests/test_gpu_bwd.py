@@ -116,6 +116,18 @@ def test_gqa_group_sizes_and_batches(G):
     check(1, G, 1, 515, 64, 65, 10, 400, seed=9300 + G)
 
 
+@pytest.mark.parametrize("N,W,S,P,G", [
+    (31, 31, 0, None, 1),     # one row block for three parts
+    (97, 97, 0, None, 2),     # eight entries in the list: the last step is not full
+    (161, 20, 0, None, 3),    # two or three blocks in a key tile's band, a key tile of 33 keys
+    (1037, 90, 10, None, 1),  # sink segments, cut at whole 64-row tiles, the last one short
+    (1037, 90, 140, 900, 4),  # two sink key tiles, generated rows
+    (545, 33, 0, 500, 5),     # a second range that starts inside a block
+])
+def test_row_blocks_of_head_dimension_64(N, W, S, P, G):
+    check(1, 2 * G, 2, N, 64, W, S, P, seed=9600 + N)
+
+
 def test_run_to_run_determinism_and_errors():
     q, k, v = make_qkv(1, 8, 2, 1000, 128, seed=9400)
     qd, kd, vd = to_device(q), to_device(k), to_device(v)
