@@ -149,7 +149,9 @@ int fwd_call(const swaa_fwd_args *a, void *workspace, long long workspace_bytes)
         swaa::place_fwd_split(p, workspace);
     }
     hipStream_t s = static_cast<hipStream_t>(a->stream);
-    const hipError_t err = a->D == 128 ? swaa::launch_fwd_pipelined_d128(p, s) : swaa::launch_fwd_simple(p, a->D, s);
+    const hipError_t err = a->D == 128  ? swaa::launch_fwd_pipelined_d128(p, s)
+                           : a->D == 64 ? swaa::launch_fwd_d64(p, s)
+                                        : swaa::launch_fwd_simple(p, a->D, s);
     return err == hipSuccess ? SWAA_OK : SWAA_ERR_LAUNCH;
 }
 

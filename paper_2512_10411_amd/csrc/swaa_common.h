@@ -330,10 +330,11 @@ __device__ __forceinline__ float half_swap_sum(float x) {
 }
 
 // Launchers (one per kernel family); return the HIP error of the launch.
-// (the plain kernel: head dimensions 32 .. 256 in steps of 32 except 128; its workgroups hold
+// (the plain kernel: head dimensions 32 .. 256 in steps of 32 except 64 and 128; its workgroups hold
 // fwd_simple_wg_rows(D) query rows)
 hipError_t launch_fwd_simple(const FwdParams &p, int D, hipStream_t stream);
 int fwd_simple_wg_rows(int D);
+hipError_t launch_fwd_d64(const FwdParams &p, hipStream_t stream);  // 128 rows per workgroup
 hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream);
 // Decides whether the call's keys are split over several workgroups per row tile and fills the
 // split_* fields (after plan_work / plan_work_packed, whose launch size it enlarges); the bytes of

@@ -7,7 +7,7 @@
 // CDNA4; the paper only says that the mask lives inside a flash-style kernel.
 //
 // This is the plain kernel: it serves every head dimension that is a multiple of
-// 32 up to 256 except 128, which has the software-pipelined kernel of its own.
+// 32 up to 256 except 64 and 128, which have kernels of their own.
 //
 // Shape of the kernel
 //   * One workgroup = 4 wavefronts = 128 "query rows" that share one KV head:
@@ -75,8 +75,8 @@ struct Elem<_Float16> {
 // QB: 32-row blocks of query positions per wave (1 in every instantiation; 2 is possible up to D = 128)
 // Head dimensions up to kSmallD run 32 positions per wave and several workgroups per CU (the
 // registers allow it), so that one wave's softmax runs under another's matrix instructions:
-// measured against 64 positions per wave and one workgroup per CU, D = 64 is 1.25 - 1.37 x as
-// fast, D = 96 1.15 - 1.24 x.  D = 160 still fits two workgroups per CU with a few registers
+// measured against 64 positions per wave and one workgroup per CU, D = 96 is 1.15 - 1.24 x as
+// fast.  D = 160 still fits two workgroups per CU with a few registers
 // spilled outside the loop (1.4 - 1.5 x); from 192 on the spills land inside it and cost more
 // than the second workgroup brings.
 constexpr int kSmallD = 96;
@@ -381,13 +381,12 @@ int fwd_simple_wg_rows(int) { return 128; }
 hipError_t launch_fwd_simple(const FwdParams &p, int D, hipStream_t stream) {
     switch (D) {
         case 32: return launch_format<32>(p, stream);
-        case 64: return launch_format<64>(p, stream);
         case 96: return launch_format<96>(p, stream);
         case 160: return launch_format<160>(p, stream);
         case 192: return launch_format<192>(p, stream);
         case 224: return launch_format<224>(p, stream);
         case 256: return launch_format<256>(p, stream);
-        default: return hipErrorInvalidValue;  // (128 has the pipelined kernel)
+        default: return hipErrorInvalidValue;  // (64 and 128 have kernels of their own)
     }
 }
 
