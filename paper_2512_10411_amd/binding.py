@@ -7,6 +7,7 @@ call raises.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import os
@@ -150,6 +151,28 @@ def swaa_visible_pairs_fa_decode(N: int, window: int, n_sink: int, n_prompt: int
     return r
 
 
+# What surrounds a launch costs more than the smallest kernels run for: a prompt of 64 tokens took 15 us
+# a call, all of it host time.  Switching to the device that is current already and building a stream
+# object only to read its handle were 5 of them.
+_SAME_DEVICE = contextlib.nullcontext()
+
+
+def _on_device_of(t):
+    """A context in which t's device is current."""
+    import torch
+
+    return _SAME_DEVICE if torch._C._cuda_getDevice() == t.get_device() else torch.cuda.device(t.device)
+
+
+def _stream_handle(stream, t) -> int:
+    """The HIP handle of `stream` (a torch stream or a handle), by default of the current stream of t's device."""
+    import torch
+
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(t.get_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+
+
 def swaa_attn_fwd_raw(q_ptr, k_ptr, v_ptr, out_ptr, lse_ptr, B, Hq, Hkv, N, D,
                       window, n_sink, scale, stream_ptr) -> int:
     """The C call itself, on raw addresses; returns the status code."""
@@ -199,18 +222,16 @@ def _fwd(q, k, v, window, n_sink, n_prompt, scale, out, lse, stream):
     Hkv = k.shape[1]
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         if out is None:
             out = torch.empty_like(q)
+        elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
+            raise ValueError("out must be a contiguous bf16 tensor shaped like q")
         if lse is None:
             lse = torch.empty((B, Hq, N), dtype=torch.float32, device=q.device)
-        if out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
-            raise ValueError("out must be a contiguous bf16 tensor shaped like q")
-        if lse.shape != (B, Hq, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
+        elif lse.shape != (B, Hq, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
             raise ValueError("lse must be a contiguous fp32 [B, Hq, N] tensor")
-        if stream is None:
-            stream = torch.cuda.current_stream(q.device)
-        sptr = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+        sptr = _stream_handle(stream, q)
         ptrs = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr())
         if n_prompt is None:
             rc = swaa_attn_fwd_raw(*ptrs, B, Hq, Hkv, N, D, int(window), int(n_sink), float(scale), sptr)
@@ -265,23 +286,22 @@ def swaa_attn_decode(q, k, v, window: int, n_sink: int, scale: float | None = No
     Hkv, Nk = k.shape[1], k.shape[2]
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    need = swaa_attn_decode_workspace_bytes(B, Hq, Hkv, Nq, Nk, D, window, n_sink)
-    with torch.cuda.device(q.device):
+    if workspace is None or q.numel() == 0 or k.numel() == 0:  # (an empty tensor is refused for its shape)
+        need = swaa_attn_decode_workspace_bytes(B, Hq, Hkv, Nq, Nk, D, window, n_sink)
+    with _on_device_of(q):
         if out is None:
             out = torch.empty_like(q)
+        elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
+            raise ValueError("out must be a contiguous bf16 tensor shaped like q")
         if lse is None:
             lse = torch.empty((B, Hq, Nq), dtype=torch.float32, device=q.device)
+        elif lse.shape != (B, Hq, Nq) or lse.dtype != torch.float32 or not lse.is_contiguous():
+            raise ValueError("lse must be a contiguous fp32 [B, Hq, Nq] tensor")
         if workspace is None:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-        if out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
-            raise ValueError("out must be a contiguous bf16 tensor shaped like q")
-        if lse.shape != (B, Hq, Nq) or lse.dtype != torch.float32 or not lse.is_contiguous():
-            raise ValueError("lse must be a contiguous fp32 [B, Hq, Nq] tensor")
-        if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
+        elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
-        if stream is None:
-            stream = torch.cuda.current_stream(q.device)
-        sptr = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+        sptr = _stream_handle(stream, q)
         rc = swaa_attn_decode_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
                                   B, Hq, Hkv, Nq, Nk, D, int(window), int(n_sink), float(scale),
                                   workspace.data_ptr(), workspace.numel(), sptr)
@@ -311,10 +331,7 @@ def swaa_attn_decode_static(q, k, v, out, lse, window: int, n_sink: int, scale: 
     for name, t in (("q", q), ("k", k), ("v", v), ("out", out), ("lse", lse)):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous GPU tensor")
-    if stream is None:
-        import torch
-        stream = torch.cuda.current_stream(q.device)
-    sptr = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    sptr = _stream_handle(stream, q)
     rc = swaa_attn_decode_static_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
                                      B, Hq, Hkv, Nq, Nk, D, int(window), int(n_sink), float(scale), sptr)
     if rc != SWAA_OK:
@@ -395,7 +412,7 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
         if max_seqlen_k is None or k.dim() != 4:
             raise ValueError("a paged cache needs max_seqlen_k and k, v views [num_pages, Hkv, page_size, D]")
         Nk = int(max_seqlen_k)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         if out is None:
             out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
         if lse is None:
@@ -404,9 +421,6 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
             raise ValueError("out must be a tensor view shaped and typed like q with a contiguous last dimension")
         if tuple(lse.shape) != lse_shape or lse.dtype != torch.float32 or not lse.is_contiguous():
             raise ValueError(f"lse must be a contiguous fp32 tensor of shape {lse_shape}")
-        own_stream = stream is not None
-        if stream is None:
-            stream = torch.cuda.current_stream(q.device)
 
         def tensor(t):
             if t.dim() == 3:
@@ -423,7 +437,7 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
         a.window, a.n_sink = int(window), int(n_sink)
         a.n_prompt = 2**31 - 1 if n_prompt is None else int(n_prompt)
         a.scale = float(scale)
-        a.stream = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+        a.stream = _stream_handle(stream, q)
         a.dtype = SWAA_F16 if q.dtype == torch.float16 else SWAA_BF16
         a.block_table = block_table.data_ptr() if paged else None
         a.block_table_stride = block_table.stride(0) if paged else 0
@@ -440,7 +454,7 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
         if need > 0:
             if workspace is None:
                 workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-                if own_stream:  # (freed on return: the allocator must know that another stream still uses it)
+                if stream is not None:  # (freed on return: the allocator must know that another stream still uses it)
                     workspace.record_stream(stream if isinstance(stream, torch.cuda.Stream)
                                             else torch.cuda.ExternalStream(a.stream))
             elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
@@ -490,16 +504,15 @@ def swaa_attn_bwd(q, k, v, out, lse, dout, window: int, n_sink: int, n_prompt: i
         raise ValueError("lse must be a contiguous fp32 [B, Hq, N] tensor")
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    need = swaa_attn_bwd_workspace_bytes(B, Hq, Hkv, N, D, window, n_sink, n_prompt)
-    with torch.cuda.device(q.device):
+    if workspace is None or q.numel() == 0 or k.numel() == 0:  # (an empty tensor is refused for its shape)
+        need = swaa_attn_bwd_workspace_bytes(B, Hq, Hkv, N, D, window, n_sink, n_prompt)
+    with _on_device_of(q):
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         if workspace is None:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-        if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
+        elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
-        if stream is None:
-            stream = torch.cuda.current_stream(q.device)
-        sptr = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+        sptr = _stream_handle(stream, q)
         rc = swaa_attn_bwd_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
                                dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, Hq, Hkv, N, D,
                                int(window), int(n_sink), 2**31 - 1 if n_prompt is None else int(n_prompt),
@@ -560,13 +573,11 @@ def swaa_attn_decode_ex(q, k, v, window: int, n_sink: int, scale: float | None =
         raise ValueError("seq_lens must be a contiguous int32 [B] GPU tensor")
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    with torch.cuda.device(q.device):
+    with _on_device_of(q):
         if out is None:
             out = torch.empty_like(q)
         if lse is None:
             lse = torch.empty((B, Hq, Nq), dtype=torch.float32, device=q.device)
-        if stream is None:
-            stream = torch.cuda.current_stream(q.device)
         a = SwaaDecodeArgs()
         a.q, a.out, a.lse = q.data_ptr(), out.data_ptr(), lse.data_ptr()
         a.k = SwaaTensor(k.data_ptr(), k.stride(0), k.stride(1), k.stride(2))
@@ -582,7 +593,7 @@ def swaa_attn_decode_ex(q, k, v, window: int, n_sink: int, scale: float | None =
             need = swaa_attn_decode_ex_workspace_bytes(a)
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
         a.workspace, a.workspace_bytes = workspace.data_ptr(), workspace.numel()
-        a.stream = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+        a.stream = _stream_handle(stream, q)
         a.dtype = SWAA_F16 if q.dtype == torch.float16 else SWAA_BF16
         rc = swaa_attn_decode_ex_raw(a)
     if rc != SWAA_OK:
