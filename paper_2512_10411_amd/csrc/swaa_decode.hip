@@ -748,11 +748,17 @@ void plan_decode(DecodeParams &p, bool ragged) {
         return;
     }
     // Sequences of one length.  A workgroup draws at most 50 GB/s, so 128 of them come near the
-    // rate of the memory and 256 reach it; more splits than that only cost the merge kernel and its
-    // traffic.  Measured over n splits (us; 8 KV heads, bf16):
-    //   1 sequence x 128k tokens      n = 8: 170, 16: 104, 24: 98, 32: 100, 48: 107, 64: 100
-    //   1 x window 8k                 n = 8: 19.5, 16: 16.0, 32: 14.0, 64: 15.2
-    //   4 x 8k                        n = 2: 42, 4: 29.6, 8: 29.7, 16: 29.4, 32: 35
+    // rate of the memory and 192 reach it; more splits than that only cost the merge kernel and its
+    // traffic, and a power of two of them reads streams that are a power of two apart and meet on
+    // the same memory channels.  Measured over n splits (us; 8 KV heads, bf16):
+    //   1 sequence x 128k tokens      n = 16: 106, 20: 96.7, 24: 96.6, 32: 99.5, 48: 103, 64: 99.7
+    //   1 x 100k                      n = 16: 84.9, 24: 78.2, 32: 90.0, 48: 82.1, 64: 90.5
+    //   2 x 60k                       n = 8: 98, 12: 90.5, 16: 121, 24: 95.0, 32: 105
+    //   4 x 123k, 4 new tokens        n = 4: 370, 6: 330, 8: 437, 12: 350, 16: 354, 32: 367
+    //   5 x 40k                       n = 4: 143, 5: 144, 6: 151, 7: 187, 12: 148
+    //   8 x 32k                       n = 2: 197, 3: 182, 4: 181, 6: 189, 8: 183
+    //   1 x window 8k                 n = 12: 15.7, 16: 15.0, 24: 14.2, 32: 14.3
+    //   4 x 8k                        n = 4: 29.4, 6: 28.3, 8: 28.8, 16: 28.8, 32: 35.4
     //   16 x window 2k                n = 1: 27.3, 2: 30.4, 4: 30.5    (one split: no merge kernel)
     //   16 x 16k                      n = 1: 215, 2: 196, 4: 187, 8: 188
     //   64 x 2k                       n = 1: 96.7, 2: 101, 4: 106
@@ -763,7 +769,7 @@ void plan_decode(DecodeParams &p, bool ragged) {
     //   1 x 500                       n = 1: 10.1, 4: 10.6
     long long n = 1;
     if (groups < 128)
-        n = p.n_halves <= 16 ? 1 : 256 / groups < 32 ? 256 / groups : 32;
+        n = p.n_halves <= 16 ? 1 : (192 + groups / 2) / groups < 48 ? (192 + groups / 2) / groups : 48;
     else if (p.tiles_per_item == 1 && p.n_halves > 96 && groups < 4 * kDResident)
         n = groups <= 256 ? kDResident / groups : groups <= kDResident ? 1 : 4;
     // (whole quarters for the four waves: rounded down if that makes at most an eighth more splits, else up)

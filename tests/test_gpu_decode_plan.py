@@ -20,6 +20,7 @@ pytestmark = pytest.mark.gpu
     (1, 1, 4, 1, 513, 10**9, 0),      # 17: several splits
     (1, 2, 4, 1, 97, 10**9, 0),       # four halves and one key: the last wave has none
     (127, 1, 1, 1, 1100, 10**9, 4),   # 127 pairs: two splits
+    (1, 1, 4, 1, 6177, 10**9, 4),     # 194 halves: the most splits a pair gets
     (128, 1, 2, 1, 3072, 10**9, 4),   # 128 pairs, 96 halves: one split
     (128, 1, 2, 1, 3073, 10**9, 4),   # ... and 97: four
     (257, 1, 1, 1, 3100, 10**9, 0),   # more than 256 pairs: one
