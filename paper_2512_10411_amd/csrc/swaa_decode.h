@@ -57,6 +57,7 @@ struct DecodeParams {
     // halves_per_split and n_splits above are then not used.
     int ragged;
     int units_target, max_units;
+    int min_halves;  // splits get no shorter than this while there is a workgroup per compute unit
     // divisions every workgroup makes, as multiplications (FastDiv)
     FastDiv div_ctgroups, div_splits, div_hkv, div_page, div_per_round;
 };

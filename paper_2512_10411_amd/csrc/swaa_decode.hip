@@ -87,8 +87,8 @@ __device__ __forceinline__ unsigned ragged_halves_per_split(const DecodeParams &
     const unsigned target = (unsigned)p.units_target;
     const unsigned total = sum_over_sequences([](unsigned n) { return n; });
     unsigned hps = (total + target - 1) / target;
-    // (splits of less than 16 halves only where they are needed to have a workgroup per compute unit)
-    const unsigned wide = min((4 * total + target - 1) / target, 16u);
+    // (splits of less than min_halves only where they are needed to have a workgroup per compute unit)
+    const unsigned wide = min((4 * total + target - 1) / target, (unsigned)p.min_halves);
     hps = (max(max(hps, wide), 4u) + 3u) & ~3u;  // (whole quarters for the four waves)
     // Rounding up per sequence can leave a few units more than the target, i.e. a handful of
     // workgroups in one more round than planned: lengthen the splits until the count fits (a
@@ -730,12 +730,26 @@ void plan_decode(DecodeParams &p, bool ragged) {
     p.div_hkv = make_fastdiv((unsigned)p.Hkv);
     p.ragged = ragged && p.B >= 2 && p.B <= kRaggedMaxBatch && (long long)p.B * p.n_halves < 0x7fffffffLL ? 1 : 0;
     if (p.ragged) {
-        // Per-sequence lengths: kRaggedRounds rounds of resident workgroups' worth of (sequence,
-        // split) units, cut on the device in proportion to the sequences' lengths; kTailRounds
-        // with more (pair, column tile) groups than resident workgroups (see below).
-        constexpr long long kRaggedRounds = 2, kRaggedTailRounds = 8;
+        // Per-sequence lengths: about this many workgroups, cut on the device in proportion to the
+        // sequences' lengths.  Up to one per resident place (512; 256 with two column tiles) they are
+        // cut into twice as many; more (pair, column tile) groups than that need some surplus to even
+        // out the lengths, the less the more columns a partial result has.  Measured over the number
+        // of workgroups (us; 8 KV heads, binary16, pages of 16):
+        //   128 sequences of 0.2-8k tokens             1152: 246, 2048: 234, 2304: 233, 4096: 239
+        //   75 of 0.2-17k                               512: 307, 1152: 226, 2048: 222, 4096: 228
+        //   66 of 0.1-4k                                512: 57.5, 1152: 45.3, 2048: 46.1, 4096: 53.1
+        //   92 of 1-9k, window 1k, 20 columns           512: 94.4, 1152: 96.8, 1536: 115, 4096: 129
+        //   65 of 0.2-10k, window 8k, 20 columns        512: 166, 1152: 158, 2048: 170, 4096: 186
+        //   56 of 0.2-23k, window 1k, 16 columns        512: 43.7, 1024: 52.3  (min_halves: three splits of 12)
+        //   80 of 0.3-4k, 36 columns                    288: 145, 576: 148, 1152: 176, 2048: 202
         const long long resident = 256LL * decode_wgs_per_cu(p.tiles_per_item);
-        const long long units = resident * (groups > resident ? kRaggedTailRounds : kRaggedRounds) / ((long long)p.Hkv * p.n_ctgroups);
+        long long wgs = 2 * resident;
+        if (groups > resident && p.tiles_per_item == 1) {
+            wgs = p.cols <= 8 ? 2 * groups : groups;
+            wgs = wgs < 1152 ? 1152 : wgs > 2304 ? 2304 : wgs;
+        }
+        p.min_halves = p.cols <= 8 ? 16 : 40;
+        const long long units = wgs / ((long long)p.Hkv * p.n_ctgroups);
         p.units_target = (int)(units < 1 ? 1 : units);
         // (at most units_target + B units by the rounding of the device's division, and no
         // sequence has more than ceil(n_halves / 4) splits)
