@@ -786,12 +786,17 @@ void plan_decode(DecodeParams &p, bool ragged) {
         n = p.n_halves <= 16 ? 1 : (192 + groups / 2) / groups < 48 ? (192 + groups / 2) / groups : 48;
     else if (p.tiles_per_item == 1 && p.n_halves > 96 && groups < 4 * kDResident)
         n = groups <= 256 ? kDResident / groups : groups <= kDResident ? 1 : 4;
-    // (whole quarters for the four waves: rounded down if that makes at most an eighth more splits, else up)
-    long long hps = n == 1 ? p.n_halves : p.n_halves / n / 4 * 4;
-    if (n > 1 && (hps < 4 || (p.n_halves + hps - 1) / hps > n + n / 8)) hps = (p.n_halves + 4 * n - 1) / (4 * n) * 4;
+    // A call whose partial results fit the library's own scratch array with fewer splits gets no more than fit
+    // (whatever the window, so that the next rule holds).
+    const long long split_bytes = (long long)p.B * p.Hkv * p.n_coltiles * ((long long)p.col_stride * kD + 64) * (long long)sizeof(float);
+    if (split_bytes <= kDecodeStaticScratchBytes)
+        while (n > 1 && (n + n / 8) * split_bytes > kDecodeStaticScratchBytes) --n;
     // The workspace is sized for the most splits any smaller number of halves would get: a caller's
     // workspace for a full-attention layer serves the windowed layers of the same model.
     const long long most = n == 1 ? 1 : (p.n_halves + 3) / 4 < n + n / 8 ? (p.n_halves + 3) / 4 : n + n / 8;
+    // (whole quarters for the four waves: rounded down if that makes at most an eighth more splits, else up)
+    long long hps = n == 1 ? p.n_halves : p.n_halves / n / 4 * 4;
+    if (n > 1 && (hps < 4 || (p.n_halves + hps - 1) / hps > n + n / 8)) hps = (p.n_halves + 4 * n - 1) / (4 * n) * 4;
     p.halves_per_split = (int)hps;
     p.n_splits = (int)((p.n_halves + hps - 1) / hps);
     p.wg_items = groups * p.n_splits;

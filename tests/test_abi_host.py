@@ -243,3 +243,12 @@ def test_general_decode_argument_errors():
     for B in (1, 300):
         assert binding.swaa_attn_decode_ex_workspace_bytes(args(B=B, seq_lens=p)) == \
             binding.swaa_attn_decode_workspace_bytes(B, 8, 2, 1, 1024, 128, 1024, 0)
+
+
+@pytest.mark.parametrize("B,Hkv,G,Nq,Nk", [(586, 1, 2, 8, 18690), (75, 8, 4, 8, 6679), (39, 16, 5, 4, 45205), (1, 1, 4, 1, 131072)])
+def test_decode_calls_that_fit_the_static_scratch_with_fewer_splits_do(B, Hkv, G, Nq, Nk):
+    def need(window):
+        return binding.swaa_attn_decode_workspace_bytes(B, G * Hkv, Hkv, Nq, Nk, 128, window, 4)
+
+    assert need(10**9) <= binding.SWAA_DECODE_STATIC_SCRATCH_BYTES
+    assert all(need(w) <= need(10**9) for w in (1, 100, 1000, 10000))  # one workspace serves windowed layers too
