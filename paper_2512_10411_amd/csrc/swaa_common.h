@@ -319,6 +319,15 @@ __device__ __forceinline__ int window_bound(int p0, int rows, int W, int P) {
     return p0 >= P ? -(1 << 30) : min(p0 + rows - 1, P - 1) - W;
 }
 
+// Is x infinite or not a number?  On the bits, and behind the optimiser's back: the build does not honour NaNs
+// (-fno-honor-nans), and a comparison, or a test of the bits that the compiler recognises, would be folded.
+__device__ __forceinline__ uint32_t opaque_bits(float x) {
+    uint32_t bits = __float_as_uint(x);
+    asm("" : "+v"(bits));
+    return bits;
+}
+__device__ __forceinline__ bool non_finite(float x) { return (opaque_bits(x) & 0x7fffffffu) >= 0x7f800000u; }
+
 // Lanes l and l^32 hold partial results for the same query column.
 __device__ __forceinline__ float half_swap_max(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);

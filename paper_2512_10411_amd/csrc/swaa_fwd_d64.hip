@@ -255,9 +255,12 @@ __global__ __launch_bounds__(kThreads, 4) void swaa_fwd_d64_kernel(const FwdPara
     }
 
     // ---- epilogue: O / (sum of the rounded P) -> 16 bit; lse = (mc + log2 l) ln 2 ----
+    // (Query columns j and 16 + j share a column of lsum's products, kept apart by zeros, and 0 NaN is NaN: where one
+    // of the two rows sees a key that is not a number, the other divides by its own fp32 sum of the unrounded P.)
     l = half_swap_sum(l);
     const float lb_lo = __shfl(lsum[0], l32 & 15), lb_hi = __shfl(lsum[1], l32 & 15);
-    const float inv = 1.f / (l32 < 16 ? lb_lo : lb_hi);
+    const float lb = l32 < 16 ? lb_lo : lb_hi;
+    const float inv = 1.f / (non_finite(lb) ? l : lb);
     const int row = r0 + l32;
     if (row >= Nq) return;
     __bf16 *orow = p.out + sg.q_batch * p.o_sb + (long long)head * p.o_sh + (sg.q_row0 + row) * p.o_sn;

@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import input_format, swaa_decode_oracle
+from oracle import input_format, swaa_attn_oracle, swaa_decode_oracle
 from paper_2512_10411_amd import binding
 from paper_2512_10411_amd.inputs import f32_to_bf16_bits, make_qkv
 from gpu_util import assert_parity, to_device
@@ -45,3 +45,26 @@ def test_a_spike_moves_the_reference(key, height):
     torch.cuda.synchronize()
     ro, rl = swaa_decode_oracle(q, k, v, 300, 4, 1 / math.sqrt(64))
     assert_parity(out, lse, ro, rl, tag=f"d64 spike {height} at {key}")
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+def test_non_finite_key_rows_reach_only_the_rows_that_see_them(fmt):
+    # NaN and infinities in a few key rows (as at head dimension 128, test_gpu_parity.py): a row that does not see
+    # such a key comes out as the oracle has it, although rows 16 above or below it, which share columns of the
+    # row sums' products with it, do see the key
+    B, Hq, Hkv, N, W, S = 1, 8, 2, 1500, 100, 4
+    q, k, v = make_qkv(B, Hq, Hkv, N, 64, seed=4964, fmt=fmt)
+    nan, inf = (0x7FC0, 0x7F80) if fmt == "bf16" else (0x7E00, 0x7C00)
+    poisoned = {500: nan, 777: inf, 778: 0x8000 | inf, 1290: 0x8000 | nan}
+    for j, bits in poisoned.items():
+        k[:, :, j, 5::7] = np.uint16(bits)
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), W, S)
+    torch.cuda.synchronize()
+    touched = sorted({i for j in poisoned for i in range(j, min(N, j + W))})
+    rows = np.array([i for i in range(N) if i not in set(touched)], dtype=np.int32)
+    with input_format(fmt):
+        ro, rl = swaa_attn_oracle(q, k, v, W, S, 1 / math.sqrt(64), rows=rows)
+    assert np.isfinite(ro).all() and np.isfinite(rl).all()
+    assert_parity(out, lse, ro, rl, rows=rows, tag=f"d64 non-finite invisible keys {fmt}")
+    for j in (500, 1290):  # and the rows that see a NaN show it
+        assert not torch.isfinite(out[:, :, j:j + W].float()).any() and not torch.isfinite(lse[:, :, j:j + W]).any()
