@@ -716,7 +716,9 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
             __syncthreads();  // everyone is done with this buffer: tile j + 2 is copied into it next
         }
         row_sums(rs, l_row, lb_row);
-        if constexpr (kSplit) row_sees = row_sees && l_row > 0.f;
+        // (a row whose keys of this split all have probability zero counts as one that sees none of them; NaN is no
+        // such sum)
+        if constexpr (kSplit) row_sees = row_sees && (opaque_bits(l_row) << 1) != 0u;
         // (after the loop's last barrier the rings are free: they become the O staging area below)
     }
 
@@ -739,7 +741,10 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
                         o4.w = oacc[db][4 * e4 + 3] * fix;
                         *reinterpret_cast<float4 *>(wo + (4 * db + e4) * 256) = o4;
                     }
-                p.ws_ml[(size_t)ws * 64 + lane_e] = lane_e < 32 ? (row_sees ? rs.mc : -INFINITY) : (row_sees ? l_row : 0.f);
+                // (a sum that is not a number travels with a finite reference: one of -inf would mark the split as
+                // empty, and the merge would leave it out)
+                const float ref = !row_sees ? -INFINITY : non_finite(l_row) ? 0.f : rs.mc;
+                p.ws_ml[(size_t)ws * 64 + lane_e] = lane_e < 32 ? ref : row_sees ? l_row : 0.f;
             }
             return;
         }

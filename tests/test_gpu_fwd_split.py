@@ -120,3 +120,21 @@ def test_chunks_give_the_same_bits_whichever_list_they_run_on(nq, nk, W):
         ro, rl = swaa_decode_oracle(h[0], h[1], h[2], W, S, 1 / math.sqrt(128))
         assert_parity(out[None, :, r0:r0 + nq[b]], lse[None, :, r0:r0 + nq[b]], ro, rl, tag=f"seq {b}: {nq[b]} rows on {nk[b]} keys")
         r0 += nq[b]
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+@pytest.mark.parametrize("what", ["nan", "inf"])
+def test_a_non_finite_key_of_one_split_reaches_the_rows_that_see_it(what, fmt):
+    # the merge must not take a split whose sums are not numbers for one without keys
+    q, k, v = make_qkv(1, 4, 1, 5000, 128, seed=9650, n_query=300, fmt=fmt)
+    bits = {("nan", "bf16"): 0x7FC0, ("inf", "bf16"): 0x7F80, ("nan", "fp16"): 0x7E00, ("inf", "fp16"): 0x7C00}[what, fmt]
+    q[..., 5] = {"bf16": 0x3F80, "fp16": 0x3C00}[fmt]  # 1: the score of an infinite component is +infinity
+    W, key = 1030, 3900  # seen by positions 3900 .. 4929, the chunk's first 230 rows
+    k[:, :, key, 5] = np.uint16(bits)
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), W, 4)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(out[:, :, :230].float()).any() and not torch.isfinite(lse[:, :, :230]).any()
+    rows = np.arange(230, 300)
+    with input_format(fmt):
+        ro, rl = swaa_decode_oracle(q, k, v, W, 4, 1 / math.sqrt(128))
+    assert_parity(out[:, :, rows], lse[:, :, rows], ro[:, :, rows], rl[:, :, rows], tag=f"split, {what} key, rows that do not see it")
