@@ -495,7 +495,14 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
 
             // P and dS in the accumulator layout (row 8 (e/4) + 4 hf + e%4, column = this lane's key); a
             // score that must not be seen becomes -inf, its P an exact 0
+            // (A row whose lse is not a number, or -inf, must not reach keys that it does not see, and exp2(-inf - NaN) is
+            // NaN: with an lse of -1e38 in its place, P is 0 there and infinite where the row does see the key.  In
+            // LDS, where all waves of the part write the same.)
             if (!unmasked) {
+                const auto lse = (uint32_t __attribute__((address_space(3))) *)(uintptr_t)(Ls + 4 * l32);
+                const uint32_t bits = *lse;
+                if ((bits & 0x7fffffffu) > 0x7f800000u || bits == 0xff800000u) *lse = 0xfe967699u;
+                asm volatile("" ::: "memory");
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     sacc[e] = visible_in_range(i0 + 8 * (e / 4) + 4 * hf + e % 4, key, N, W, S, P) ? sacc[e] : -INFINITY;

@@ -128,6 +128,26 @@ def test_row_blocks_of_head_dimension_64(N, W, S, P, G):
     check(1, 2 * G, 2, N, 64, W, S, P, seed=9600 + N)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_a_row_without_a_number_reaches_only_the_keys_it_sees(D):
+    # NaN in one row's log-sum-exp: P = 0 where the row does not see the key, whatever the row holds
+    N, W, row = 700, 90, 333
+    q, k, v = make_qkv(1, 4, 1, N, D, seed=9700)
+    qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(make_dout(q.shape, 9701))
+    out, lse = binding.swaa_attn_fwd(qd, kd, vd, W, 4)
+    want = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
+    lse[:, :, row] = float("nan")
+    got = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
+    torch.cuda.synchronize()
+    seen = torch.zeros(N, dtype=torch.bool, device="cuda")
+    seen[:4], seen[row - W + 1:row + 1] = True, True
+    rows = torch.arange(N, device="cuda") != row
+    assert torch.equal(got[0][:, :, rows], want[0][:, :, rows])
+    for x, y in zip(got[1:], want[1:]):  # dK, dV
+        assert torch.equal(x[:, :, ~seen], y[:, :, ~seen])
+        assert not torch.isfinite(x[:, :, seen].float()).any()
+
+
 def test_run_to_run_determinism_and_errors():
     q, k, v = make_qkv(1, 8, 2, 1000, 128, seed=9400)
     qd, kd, vd = to_device(q), to_device(k), to_device(v)
