@@ -173,6 +173,21 @@ def _stream_handle(stream, t) -> int:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
+def _pool_of(stream, t):
+    """A context in which torch allocates from the pool of `stream` (None: the current stream): memory that the
+    pool hands out was last used by work in front of this call's on that stream, and what is freed on return is not
+    handed out again before the call's kernels are done with it."""
+    import torch
+
+    device = t.get_device()
+    handle = _stream_handle(stream, t)
+    if handle == torch._C._cuda_getCurrentRawStream(device):
+        return _SAME_DEVICE
+    if not isinstance(stream, torch.cuda.Stream):  # a handle (0: the default stream)
+        stream = torch.cuda.ExternalStream(handle, device) if handle else torch.cuda.default_stream(device)
+    return torch.cuda.stream(stream)
+
+
 def swaa_attn_fwd_raw(q_ptr, k_ptr, v_ptr, out_ptr, lse_ptr, B, Hq, Hkv, N, D,
                       window, n_sink, scale, stream_ptr) -> int:
     """The C call itself, on raw addresses; returns the status code."""
@@ -453,10 +468,8 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
         need = lib.swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(a))
         if need > 0:
             if workspace is None:
-                workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-                if stream is not None:  # (freed on return: the allocator must know that another stream still uses it)
-                    workspace.record_stream(stream if isinstance(stream, torch.cuda.Stream)
-                                            else torch.cuda.ExternalStream(a.stream))
+                with _pool_of(stream, q):
+                    workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
             elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
                 raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
             rc = int(lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), workspace.data_ptr(), workspace.numel()))
