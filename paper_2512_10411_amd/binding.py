@@ -173,19 +173,29 @@ def _stream_handle(stream, t) -> int:
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
 
-def _pool_of(stream, t):
-    """A context in which torch allocates from the pool of `stream` (None: the current stream): memory that the
-    pool hands out was last used by work in front of this call's on that stream, and what is freed on return is not
-    handed out again before the call's kernels are done with it."""
+def _launching_on(stream, t):
+    """A context in which t's device and `stream` are current.  What a call allocates, it allocates there, from that
+    stream's pool: such memory was last used by work in front of this call's on the same stream, and scratch that
+    is freed on return is not handed out again before the call's kernels are done with it."""
     import torch
 
-    device = t.get_device()
     handle = _stream_handle(stream, t)
-    if handle == torch._C._cuda_getCurrentRawStream(device):
-        return _SAME_DEVICE
+    if stream is None or handle == torch._C._cuda_getCurrentRawStream(t.get_device()):
+        return _on_device_of(t)
     if not isinstance(stream, torch.cuda.Stream):  # a handle (0: the default stream)
-        stream = torch.cuda.ExternalStream(handle, device) if handle else torch.cuda.default_stream(device)
+        stream = torch.cuda.ExternalStream(handle, t.device) if handle else torch.cuda.default_stream(t.device)
     return torch.cuda.stream(stream)
+
+
+def _returned_to(caller, *tensors):
+    """Tells the allocator that the caller's stream (a handle) uses `tensors`, too, if it is not the current one."""
+    import torch
+
+    device = tensors[0].get_device()
+    if caller != torch._C._cuda_getCurrentRawStream(device):
+        used_by = torch.cuda.ExternalStream(caller, device) if caller else torch.cuda.default_stream(device)
+        for t in tensors:
+            t.record_stream(used_by)
 
 
 def swaa_attn_fwd_raw(q_ptr, k_ptr, v_ptr, out_ptr, lse_ptr, B, Hq, Hkv, N, D,
@@ -208,7 +218,9 @@ def swaa_attn_fwd(q, k, v, window: int, n_sink: int, scale: float | None = None,
 
     q: bf16 [B, Hq, N, D]; k, v: bf16 [B, Hkv, N, D]; all contiguous CUDA/HIP
     tensors on one device.  Returns (out bf16 [B, Hq, N, D], lse fp32 [B, Hq, N]).
-    The call is asynchronous on `stream` (default: torch's current stream).
+    The call is asynchronous on `stream` (a torch stream or a HIP handle; default: torch's current stream),
+    here and in all calls below; results allocated for the caller may be used on torch's current stream once that
+    has waited for `stream`.
     """
     return _fwd(q, k, v, window, n_sink, None, scale, out, lse, stream)
 
@@ -237,7 +249,8 @@ def _fwd(q, k, v, window, n_sink, n_prompt, scale, out, lse, stream):
     Hkv = k.shape[1]
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    with _on_device_of(q):
+    caller = _stream_handle(None, q)
+    with _launching_on(stream, q):
         if out is None:
             out = torch.empty_like(q)
         elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
@@ -253,6 +266,8 @@ def _fwd(q, k, v, window, n_sink, n_prompt, scale, out, lse, stream):
         else:
             rc = swaa_attn_fwd_fa_decode_raw(*ptrs, B, Hq, Hkv, N, D, int(window), int(n_sink), n_prompt,
                                              float(scale), sptr)
+        if stream is not None:
+            _returned_to(caller, out, lse)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return out, lse
@@ -303,7 +318,8 @@ def swaa_attn_decode(q, k, v, window: int, n_sink: int, scale: float | None = No
         scale = 1.0 / math.sqrt(D)
     if workspace is None or q.numel() == 0 or k.numel() == 0:  # (an empty tensor is refused for its shape)
         need = swaa_attn_decode_workspace_bytes(B, Hq, Hkv, Nq, Nk, D, window, n_sink)
-    with _on_device_of(q):
+    caller = _stream_handle(None, q)
+    with _launching_on(stream, q):
         if out is None:
             out = torch.empty_like(q)
         elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
@@ -320,6 +336,8 @@ def swaa_attn_decode(q, k, v, window: int, n_sink: int, scale: float | None = No
         rc = swaa_attn_decode_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
                                   B, Hq, Hkv, Nq, Nk, D, int(window), int(n_sink), float(scale),
                                   workspace.data_ptr(), workspace.numel(), sptr)
+        if stream is not None:
+            _returned_to(caller, out, lse)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return out, lse
@@ -427,7 +445,8 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
         if max_seqlen_k is None or k.dim() != 4:
             raise ValueError("a paged cache needs max_seqlen_k and k, v views [num_pages, Hkv, page_size, D]")
         Nk = int(max_seqlen_k)
-    with _on_device_of(q):
+    caller = _stream_handle(None, q)
+    with _launching_on(stream, q):
         if out is None:
             out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
         if lse is None:
@@ -468,13 +487,14 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
         need = lib.swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(a))
         if need > 0:
             if workspace is None:
-                with _pool_of(stream, q):
-                    workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+                workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
             elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
                 raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
             rc = int(lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), workspace.data_ptr(), workspace.numel()))
         else:
             rc = swaa_attn_fwd_ex_raw(a)  # (keys stay whole, or an argument error to be reported)
+        if stream is not None:
+            _returned_to(caller, out, lse)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return out, lse
@@ -519,7 +539,8 @@ def swaa_attn_bwd(q, k, v, out, lse, dout, window: int, n_sink: int, n_prompt: i
         scale = 1.0 / math.sqrt(D)
     if workspace is None or q.numel() == 0 or k.numel() == 0:  # (an empty tensor is refused for its shape)
         need = swaa_attn_bwd_workspace_bytes(B, Hq, Hkv, N, D, window, n_sink, n_prompt)
-    with _on_device_of(q):
+    caller = _stream_handle(None, q)
+    with _launching_on(stream, q):
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         if workspace is None:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
@@ -530,6 +551,8 @@ def swaa_attn_bwd(q, k, v, out, lse, dout, window: int, n_sink: int, n_prompt: i
                                dout.data_ptr(), dq.data_ptr(), dk.data_ptr(), dv.data_ptr(), B, Hq, Hkv, N, D,
                                int(window), int(n_sink), 2**31 - 1 if n_prompt is None else int(n_prompt),
                                float(scale), workspace.data_ptr(), workspace.numel(), sptr)
+        if stream is not None:
+            _returned_to(caller, dq, dk, dv)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return dq, dk, dv
@@ -586,7 +609,8 @@ def swaa_attn_decode_ex(q, k, v, window: int, n_sink: int, scale: float | None =
         raise ValueError("seq_lens must be a contiguous int32 [B] GPU tensor")
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    with _on_device_of(q):
+    caller = _stream_handle(None, q)
+    with _launching_on(stream, q):
         if out is None:
             out = torch.empty_like(q)
         if lse is None:
@@ -609,6 +633,8 @@ def swaa_attn_decode_ex(q, k, v, window: int, n_sink: int, scale: float | None =
         a.stream = _stream_handle(stream, q)
         a.dtype = SWAA_F16 if q.dtype == torch.float16 else SWAA_BF16
         rc = swaa_attn_decode_ex_raw(a)
+        if stream is not None:
+            _returned_to(caller, out, lse)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return out, lse
