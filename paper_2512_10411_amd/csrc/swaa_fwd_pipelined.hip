@@ -929,9 +929,12 @@ long long plan_fwd_split(FwdParams &p) {
         p.split_cap = p.B * p.Hkv * p.tiles_per_pair * n;
         p.chunk = (long long)p.B * (((long long)p.Hkv * p.tiles_per_pair * n + kXcds - 1) / kXcds);
     } else {
+        // (room for the shortest splits a plan may have, of every row tile the batch can have: one half more than the
+        // longest sequence visits, for a band that straddles one more, and one split more for split_count's rounding)
+        const long long room = bound * ((longest.halves + 1 + kSplitMinHalves - 1) / kSplitMinHalves + 1);
         p.split_keys = 1;
-        p.split_cap = kSplitUnits;
-        p.chunk = (bound + kSplitUnits + kXcds - 1) / kXcds + p.B;
+        p.split_cap = room < kSplitUnits ? (int)room : kSplitUnits;
+        p.chunk = (bound + p.split_cap + kXcds - 1) / kXcds + p.B;
     }
     p.total_items = p.chunk * kXcds;
     p.split_items = bound;

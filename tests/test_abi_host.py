@@ -252,3 +252,50 @@ def test_decode_calls_that_fit_the_static_scratch_with_fewer_splits_do(B, Hkv, G
 
     assert need(10**9) <= binding.SWAA_DECODE_STATIC_SCRATCH_BYTES
     assert all(need(w) <= need(10**9) for w in (1, 100, 1000, 10000))  # one workspace serves windowed layers too
+
+
+def _chunk_args(B, Nq, Nk, total_rows=0, packed=True, Hq=8, Hkv=2, window=1 << 30, n_prompts=True):
+    p = 4096  # fake aligned address; never dereferenced on these paths
+    a = binding.SwaaFwdArgs()
+    a.q = a.out = binding.SwaaTensor(p, 0 if packed else Hq * Nq * 128, (total_rows or B * Nq) * 128, 128)
+    a.k = a.v = binding.SwaaTensor(p, 0 if packed else Hkv * Nk * 128, B * Nk * 128, 128)
+    a.lse, a.lse_stride_b, a.lse_stride_h = p, 0 if packed else Hq * Nq, total_rows or B * Nq
+    a.B, a.Hq, a.Hkv, a.D, a.Nq, a.Nk, a.total_rows_q = B, Hq, Hkv, 128, Nq, Nk, total_rows
+    a.window, a.n_sink, a.n_prompt, a.scale = window, 4, (1 << 31) - 1, 0.1
+    if packed:
+        a.cu_seqlens_q = a.cu_seqlens_k = p
+        a.n_prompts = p if n_prompts else None
+    return a
+
+
+SPLIT_UNIT = 4 * (16 * 64 * 4 + 64) * 4  # bytes of one partial result: four waves of O, references and sums
+
+
+@pytest.mark.parametrize("B,Nq,Nk,total_rows,most", [
+    (2, 32, 1200, 33, 150),      # two short sequences: three row tiles at most, 38 halves
+    (2, 32, 1200, 0, 150),       # the number of rows not stated
+    (24, 999, 12000, 1022, 1024),
+    (64, 1, 100000, 64, 1024),
+])
+def test_the_forwards_workspace_is_no_larger_than_its_plan_can_fill(B, Nq, Nk, total_rows, most):
+    need = binding.swaa_attn_fwd_ex_workspace_bytes(_chunk_args(B, Nq, Nk, total_rows))
+    assert 0 < need <= most * SPLIT_UNIT + 64 * 4
+
+
+def test_the_forwards_workspace_argument():
+    lib = binding.load_library()
+    call = lambda a, ws, n: lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), ws, n)
+    a = _chunk_args(1, 64, 6000, packed=False)
+    need = binding.swaa_attn_fwd_ex_workspace_bytes(a)
+    assert need > 0
+    assert call(a, 4096, need - 1) == binding.SWAA_ERR_WORKSPACE
+    assert call(a, 4096 + 8, need) == binding.SWAA_ERR_WORKSPACE
+    assert lib.swaa_attn_fwd_ex_workspace_bytes(None) == lib.swaa_attn_fwd_ex_ws(None, 4096, need) == binding.SWAA_ERR_NULL
+    # keys that stay whole need none: prompts on themselves, short caches, other head dimensions
+    whole = [_chunk_args(1, 6000, 6000, packed=False), _chunk_args(1, 64, 1000, packed=False)]
+    b = _chunk_args(1, 64, 6000, packed=False)
+    b.D = 64
+    assert all(binding.swaa_attn_fwd_ex_workspace_bytes(x) == 0 for x in whole + [b])
+    b.D = 80
+    with pytest.raises(binding.SwaaError):
+        binding.swaa_attn_fwd_ex_workspace_bytes(b)
