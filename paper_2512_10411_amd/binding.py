@@ -404,7 +404,7 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
     longest sequence (slow for sequences of very different lengths).  n_prompts: int32 [B] GPU tensor of
     per-sequence prompt lengths, used in place of n_prompt.  workspace: a uint8 tensor of at least
     swaa_attn_fwd_ex_workspace_bytes(...) bytes for calls whose keys are split over workgroups (allocated
-    here with torch when None and the call needs one).  bfloat16 or float16 tensors (all of
+    here with torch when None and the call needs one; where there is no memory for it the keys stay whole).  bfloat16 or float16 tensors (all of
     one type).  out defaults to a new tensor with q's shape in q's memory order;
     lse is fp32 [B, Hq, Nq] ([Hq, Tq] when packed).  Returns (out, lse).
     """
@@ -485,10 +485,13 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
             a.n_prompts = n_prompts.data_ptr()
         lib = load_library()
         need = lib.swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(a))
-        if need > 0:
-            if workspace is None:
+        if need > 0 and workspace is None:
+            try:
                 workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-            elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
+            except torch.cuda.OutOfMemoryError:
+                need = 0  # (the call itself needs no scratch: whole keys are slower, not refused)
+        if need > 0:
+            if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
                 raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
             rc = int(lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), workspace.data_ptr(), workspace.numel()))
         else:

@@ -138,3 +138,21 @@ def test_a_non_finite_key_of_one_split_reaches_the_rows_that_see_it(what, fmt):
     with input_format(fmt):
         ro, rl = swaa_decode_oracle(q, k, v, W, 4, 1 / math.sqrt(128))
     assert_parity(out[:, :, rows], lse[:, :, rows], ro[:, :, rows], rl[:, :, rows], tag=f"split, {what} key, rows that do not see it")
+
+
+def test_without_memory_for_scratch_the_keys_stay_whole(monkeypatch):
+    q, k, v = make_qkv(1, 4, 1, 3001, 128, seed=9670, n_query=33)
+    qd, kd, vd = to_device(q), to_device(k), to_device(v)
+    empty = torch.empty
+
+    def no_scratch(*args, **kwargs):
+        if kwargs.get("dtype") == torch.uint8:
+            raise torch.cuda.OutOfMemoryError("no memory")
+        return empty(*args, **kwargs)
+
+    monkeypatch.setattr(torch, "empty", no_scratch)
+    out, lse = binding.swaa_attn_fwd_ex(qd, kd, vd, 10**9, 4)
+    torch.cuda.synchronize()
+    monkeypatch.undo()
+    ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
+    assert_parity(out, lse, ro, rl, tag="no scratch")
