@@ -180,7 +180,7 @@ def _launching_on(stream, t):
     import torch
 
     handle = _stream_handle(stream, t)
-    if stream is None or handle == torch._C._cuda_getCurrentRawStream(t.get_device()):
+    if handle == torch._C._cuda_getCurrentRawStream(t.get_device()):
         return _on_device_of(t)
     if not isinstance(stream, torch.cuda.Stream):  # a handle (0: the default stream)
         stream = torch.cuda.ExternalStream(handle, t.device) if handle else torch.cuda.default_stream(t.device)
@@ -249,8 +249,8 @@ def _fwd(q, k, v, window, n_sink, n_prompt, scale, out, lse, stream):
     Hkv = k.shape[1]
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    caller = _stream_handle(None, q)
-    with _launching_on(stream, q):
+    caller = None if stream is None else _stream_handle(None, q)
+    with _on_device_of(q) if stream is None else _launching_on(stream, q):
         if out is None:
             out = torch.empty_like(q)
         elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
@@ -318,8 +318,8 @@ def swaa_attn_decode(q, k, v, window: int, n_sink: int, scale: float | None = No
         scale = 1.0 / math.sqrt(D)
     if workspace is None or q.numel() == 0 or k.numel() == 0:  # (an empty tensor is refused for its shape)
         need = swaa_attn_decode_workspace_bytes(B, Hq, Hkv, Nq, Nk, D, window, n_sink)
-    caller = _stream_handle(None, q)
-    with _launching_on(stream, q):
+    caller = None if stream is None else _stream_handle(None, q)
+    with _on_device_of(q) if stream is None else _launching_on(stream, q):
         if out is None:
             out = torch.empty_like(q)
         elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
@@ -445,8 +445,8 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
         if max_seqlen_k is None or k.dim() != 4:
             raise ValueError("a paged cache needs max_seqlen_k and k, v views [num_pages, Hkv, page_size, D]")
         Nk = int(max_seqlen_k)
-    caller = _stream_handle(None, q)
-    with _launching_on(stream, q):
+    caller = None if stream is None else _stream_handle(None, q)
+    with _on_device_of(q) if stream is None else _launching_on(stream, q):
         if out is None:
             out = torch.empty_strided(q.shape, q.stride(), dtype=q.dtype, device=q.device)
         if lse is None:
@@ -542,8 +542,8 @@ def swaa_attn_bwd(q, k, v, out, lse, dout, window: int, n_sink: int, n_prompt: i
         scale = 1.0 / math.sqrt(D)
     if workspace is None or q.numel() == 0 or k.numel() == 0:  # (an empty tensor is refused for its shape)
         need = swaa_attn_bwd_workspace_bytes(B, Hq, Hkv, N, D, window, n_sink, n_prompt)
-    caller = _stream_handle(None, q)
-    with _launching_on(stream, q):
+    caller = None if stream is None else _stream_handle(None, q)
+    with _on_device_of(q) if stream is None else _launching_on(stream, q):
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         if workspace is None:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
@@ -612,8 +612,8 @@ def swaa_attn_decode_ex(q, k, v, window: int, n_sink: int, scale: float | None =
         raise ValueError("seq_lens must be a contiguous int32 [B] GPU tensor")
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    caller = _stream_handle(None, q)
-    with _launching_on(stream, q):
+    caller = None if stream is None else _stream_handle(None, q)
+    with _on_device_of(q) if stream is None else _launching_on(stream, q):
         if out is None:
             out = torch.empty_like(q)
         if lse is None:
