@@ -319,9 +319,10 @@ long long swaa_attn_decode_ex_workspace_bytes(const swaa_decode_args *args);
  * on the first call on each GPU (each GPU the library runs on holds its own copy
  * until the process ends).
  *
- *   - a shape whose swaa_attn_decode_workspace_bytes exceeds
- *     SWAA_DECODE_STATIC_SCRATCH_BYTES is refused with SWAA_ERR_WORKSPACE before
- *     anything is launched (use swaa_attn_decode with a workspace for those);
+ *   - a shape whose partial results exceed SWAA_DECODE_STATIC_SCRATCH_BYTES is refused
+ *     with SWAA_ERR_WORKSPACE before anything is launched (use swaa_attn_decode with a
+ *     workspace for those); where fewer key splits fit than swaa_attn_decode takes
+ *     (swaa_attn_decode_workspace_bytes exceeds the array), the call runs on those;
  *   - every call on a GPU shares that GPU's array: calls that may overlap on one
  *     GPU (two streams, two host threads) race on it and must be serialised by
  *     the caller; consecutive calls on one stream are fine.  The array keeps the

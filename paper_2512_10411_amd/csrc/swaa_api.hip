@@ -208,7 +208,8 @@ int swaa_attn_fwd(const void *q, const void *k, const void *v, void *out, float 
 namespace {
 
 // Shape checks shared by the two decode entry points; fills the shape fields and the plan.
-int decode_plan(swaa::DecodeParams &p, int B, int Hq, int Hkv, int Nq, int Nk, int D, int window, int n_sink, bool ragged) {
+int decode_plan(swaa::DecodeParams &p, int B, int Hq, int Hkv, int Nq, int Nk, int D, int window, int n_sink, bool ragged,
+                bool own_scratch = false) {
     if (B < 1 || Hq < 1 || Hkv < 1 || Nq < 1 || Nk < 1 || D < 1) return SWAA_ERR_SHAPE;
     if (Hq % Hkv != 0 || Nq > Nk) return SWAA_ERR_SHAPE;
     if (window < 1 || n_sink < 0) return SWAA_ERR_SHAPE;
@@ -218,7 +219,7 @@ int decode_plan(swaa::DecodeParams &p, int B, int Hq, int Hkv, int Nq, int Nk, i
     p.W = window < Nk ? window : Nk;
     p.S = n_sink < Nk ? n_sink : Nk;
     if ((long long)p.G * Nq > 0x7fffffffLL / 256) return SWAA_ERR_SHAPE;
-    swaa::plan_decode(p, ragged);
+    swaa::plan_decode(p, ragged, own_scratch);
     if (p.items + 64 > 0x7fffffffLL || (long long)B * Hq * Nq > 0x7fffffffLL)
         return SWAA_ERR_SHAPE;
     return SWAA_OK;
@@ -247,7 +248,8 @@ int decode_call(const swaa_decode_args *a, bool own_scratch) {
     if (!a) return SWAA_ERR_NULL;
     if (!a->q || !a->k.ptr || !a->v.ptr || !a->out || !a->lse) return SWAA_ERR_NULL;
     swaa::DecodeParams p{};
-    const int rc = decode_plan(p, a->B, a->Hq, a->Hkv, a->Nq, a->Nk, a->D, a->window, a->n_sink, a->seq_lens != nullptr);
+    const int rc =
+        decode_plan(p, a->B, a->Hq, a->Hkv, a->Nq, a->Nk, a->D, a->window, a->n_sink, a->seq_lens != nullptr, own_scratch);
     if (rc != SWAA_OK) return rc;
     if (!positive_finite(a->scale)) return SWAA_ERR_SHAPE;
     if (a->dtype != SWAA_BF16 && a->dtype != SWAA_F16) return SWAA_ERR_UNSUPPORTED;

@@ -80,8 +80,9 @@ __host__ __device__ inline VisitedHalves visited_halves(int nk, int nq, int W, i
 // Fills the plan fields (everything from `cols` on) from the shape fields.  ragged: the sequences
 // may hold far fewer than Nk tokens each (seq_lens is given): the device-side plan described at
 // DecodeParams::ragged, for batches of 2 .. kRaggedMaxBatch sequences (else the plan for Nk).
+// own_scratch: no more splits than the library's own scratch array has room for, if fewer fit.
 constexpr int kRaggedMaxBatch = 256;
-void plan_decode(DecodeParams &p, bool ragged);
+void plan_decode(DecodeParams &p, bool ragged, bool own_scratch);
 // Floats the workspace must hold for this plan.
 long long decode_workspace_floats(const DecodeParams &p);
 

@@ -59,6 +59,7 @@ constexpr int decode_smem_bytes(int tiles) { return kDWaves * (decode_wave_bytes
 constexpr int kCopiesPerHalf = 16;                    // wave instructions per stage: 8 for K, 8 for V
 constexpr int kMergeThreads = 1024;
 constexpr long long kDResident = 512;                 // workgroups of one column tile that run at once
+constexpr long long kDResidentPairs = 256;            // ... of two
 
 // ---- the split plan of a batch with per-sequence lengths, worked out by every workgroup of the
 // split kernel (DecodeParams::ragged has the rules) ----
@@ -713,7 +714,7 @@ __global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_ragged_kernel
 
 }  // namespace
 
-void plan_decode(DecodeParams &p, bool ragged) {
+void plan_decode(DecodeParams &p, bool ragged, bool own_scratch) {
     p.cols = p.G * p.Nq;
     p.n_coltiles = (p.cols + 31) / 32;
     p.col_stride = p.cols < 32 ? p.cols : 32;
@@ -722,13 +723,25 @@ void plan_decode(DecodeParams &p, bool ragged) {
     const int all = (p.Nk + 31) / 32;
     const int bound = (p.S + 31) / 32 + (p.W + p.Nq - 2) / 32 + 2;
     p.n_halves = all < bound ? all : bound;
-    p.tiles_per_item = p.n_coltiles >= 2 ? 2 : 1;
+    p.ragged = ragged && p.B >= 2 && p.B <= kRaggedMaxBatch && (long long)p.B * p.n_halves < 0x7fffffffLL ? 1 : 0;
+    // Two column tiles per workgroup read every key once, but only one such workgroup fits a compute unit.  One
+    // tile each where that makes one round of workgroups alone on their compute units (at least 128 pairs of
+    // tiles, up to 256 tiles), or 1.5 rounds at most instead of two (257 pairs of tiles and more, up to 768 tiles).
+    // (128 pairs of at most 192 tiles on long keys: two splits of two tiles each are one round as well, and the
+    // keys are read once.)  Measured, two tiles / one tile (us; 8 KV heads, bf16, 40 columns or, *, 80; one split):
+    //   16 x 2k 36.7 / 25.4    16 x 16k 216 / 191     8 x 8k* 115 / 71.3    10 x 8k* 114 / 86.2
+    //   20 x 4k 69.0 / 84.8    28 x 16k 319 / 370    12 x 8k* 115 / 139     16 x 8k* 126 / 150
+    //   33 x 1k 47.5 / 33.8    33 x 8k 286 / 247     40 x 4k 158 / 135      17 x 8k* 222 / 148
+    //   48 x 4k 162 / 150      48 x 16k 577 / 570    56 x 4k 174 / 189      24 x 8k* 225 / 223
+    const long long tiles = (long long)p.B * p.Hkv * p.n_coltiles, tile_pairs = (long long)p.B * p.Hkv * ((p.n_coltiles + 1) / 2);
+    const bool two_splits = tile_pairs == 128 && tiles <= 192 && p.n_halves >= 384;
+    const bool one_each = !p.ragged && !two_splits && tile_pairs >= 128 && (tiles <= 256 || (tile_pairs > 256 && tiles <= 768));
+    p.tiles_per_item = p.n_coltiles >= 2 && !one_each ? 2 : 1;
     p.n_ctgroups = (p.n_coltiles + p.tiles_per_item - 1) / p.tiles_per_item;
     const long long groups = (long long)p.B * p.Hkv * p.n_ctgroups;
     p.div_ctgroups = make_fastdiv((unsigned)p.n_ctgroups);
     p.div_per_round = make_fastdiv((unsigned)(kXcds * p.n_ctgroups));
     p.div_hkv = make_fastdiv((unsigned)p.Hkv);
-    p.ragged = ragged && p.B >= 2 && p.B <= kRaggedMaxBatch && (long long)p.B * p.n_halves < 0x7fffffffLL ? 1 : 0;
     if (p.ragged) {
         // Per-sequence lengths: about this many workgroups, cut on the device in proportion to the
         // sequences' lengths.  Up to one per resident place (512; 256 with two column tiles) they are
@@ -764,7 +777,9 @@ void plan_decode(DecodeParams &p, bool ragged) {
     // Sequences of one length.  A workgroup draws at most 50 GB/s, so 128 of them come near the
     // rate of the memory and 192 reach it; more splits than that only cost the merge kernel and its
     // traffic, and a power of two of them reads streams that are a power of two apart and meet on
-    // the same memory channels.  Measured over n splits (us; 8 KV heads, bf16):
+    // the same memory channels.  What also counts is how full the last round of workgroups is, and whether
+    // few compute units have one workgroup more than the others.  Measured over n splits (us; 8 KV heads, bf16).
+    // One column tile:
     //   1 sequence x 128k tokens      n = 16: 106, 20: 96.7, 24: 96.6, 32: 99.5, 48: 103, 64: 99.7
     //   1 x 100k                      n = 16: 84.9, 24: 78.2, 32: 90.0, 48: 82.1, 64: 90.5
     //   2 x 60k                       n = 8: 98, 12: 90.5, 16: 121, 24: 95.0, 32: 105
@@ -773,23 +788,57 @@ void plan_decode(DecodeParams &p, bool ragged) {
     //   8 x 32k                       n = 2: 197, 3: 182, 4: 181, 6: 189, 8: 183
     //   1 x window 8k                 n = 12: 15.7, 16: 15.0, 24: 14.2, 32: 14.3
     //   4 x 8k                        n = 4: 29.4, 6: 28.3, 8: 28.8, 16: 28.8, 32: 35.4
+    //   1 x 500                       n = 1: 10.1, 4: 10.6
     //   16 x window 2k                n = 1: 27.3, 2: 30.4, 4: 30.5    (one split: no merge kernel)
-    //   16 x 16k                      n = 1: 215, 2: 196, 4: 187, 8: 188
+    //   16 x 4k                       n = 1: 43.4, 2: 47.9, 4: 47.9
+    //   16 x 20k                      n = 1: 236, 2: 224, 4: 226
+    //   22 x 20k                      n = 1: 295, 2: 333, 3: 351, 4: 307
+    //   32 x 20k                      n = 1: 432, 2: 437, 4: 440
+    //   28 x 16k, 8 new tokens        n = 1: 306, 2: 330, 3: 333
+    //   33 x 2k                       n = 1: 60.2, 4: 52.4    33 x 16k   n = 1: 495, 2: 427, 4: 396
+    //   40 x 4k                       n = 1: 135, 4: 122      48 x 4k    n = 1: 144, 2: 145, 4: 147
+    //   33 x 2k, 8 new tokens         n = 1: 61.3, 3: 63.9    33 x 16k, 8 new tokens   n = 1: 496, 3: 442
     //   64 x 2k                       n = 1: 96.7, 2: 101, 4: 106
     //   100 x 4k                      n = 1: 312, 2: 306, 4: 294, 8: 294
     //   256 x 1k                      n = 1: 183, 2: 196
-    //   64 x 4k, 16 new tokens        n = 1: 204, 2: 247, 4: 266      (two column tiles: 64 KiB of
-    //                                                                  partial results per split)
-    //   1 x 500                       n = 1: 10.1, 4: 10.6
+    // Two column tiles (or, *, three: 80 columns) per workgroup, 64 KiB of partial results per split:
+    //   4 x 8k*                       n = 2: 68.0, 3: 53.1, 4: 46.0, 5: 63.2
+    //   5 x 16k*                      n = 2: 120, 3: 89.4, 4: 127      7 x 16k*   n = 1: 212, 2: 124, 4: 131
+    //   5 x 16k                       n = 4: 72.4, 5: 68.8, 6: 70.9    8 x 16k    n = 2: 124, 3: 107, 4: 108
+    //   4 x 10k                       n = 6: 39.2, 8: 58.4             1 x 13k*   n = 12: 30.1, 16: 43.4
+    //   64 x 4k, 16 new tokens        n = 1: 204, 2: 247, 4: 266
+    //   65 x 16k                      n = 1: 900, 4: 823              72 x 24k   n = 1: 1353, 4: 1261
+    //   65 x 8k                       n = 1: 461, 4: 454              80 x 16k   n = 1: 933, 4: 972
+    // Several column tiles, one per workgroup (40 columns):
+    //   33 x 8k                       n = 1: 247, 2: 237, 3: 232, 4: 228    40 x 8k   n = 1: 261, 2: 256, 3: 266
+    //   36 x 8k                       n = 1: 258, 2: 247, 3: 243, 4: 252    44 x 8k   n = 1: 267, 2: 296
+    const long long few = p.n_halves <= 16 ? 1 : (192 + groups / 2) / groups < 48 ? (192 + groups / 2) / groups : 48;
     long long n = 1;
-    if (groups < 128)
-        n = p.n_halves <= 16 ? 1 : (192 + groups / 2) / groups < 48 ? (192 + groups / 2) / groups : 48;
-    else if (p.tiles_per_item == 1 && p.n_halves > 96 && groups < 4 * kDResident)
-        n = groups <= 256 ? kDResident / groups : groups <= kDResident ? 1 : 4;
+    bool may_exceed = false;  // the static array, where a workspace is given
+    if (p.tiles_per_item == 2) {
+        const long long last = (groups - 1) % kDResidentPairs + 1;  // workgroups in the last round
+        if (groups <= 128) {
+            n = few;
+            if (groups >= 64 && kDResidentPairs / groups > n && p.n_halves > 16) n = kDResidentPairs / groups;
+        }
+        if (groups > kDResidentPairs && last <= kDResidentPairs / 4 && p.n_halves >= 384)
+            n = 4;
+        may_exceed = groups > 128;
+    } else if (p.n_coltiles >= 2) {
+        if (groups > kDResident && p.n_halves >= 128) n = groups <= 544 ? 4 : p.n_halves < 192 ? 1 : groups <= 608 ? 3 : groups <= 656 ? 2 : 1;
+        may_exceed = true;
+    } else if (groups < 128) {
+        n = few;
+    } else if (groups <= kDResident) {
+        if (groups == 128 && p.cols <= 8 && p.n_halves >= 256) n = 4;  // (one workgroup per compute unit at half of them draws too little)
+        if (groups > 256 && groups <= 320 && p.n_halves >= (p.cols <= 8 ? 64 : 192)) n = 4;
+    } else if (groups < 4 * kDResident && p.n_halves > 96) {
+        n = 4;
+    }
     // A call whose partial results fit the library's own scratch array with fewer splits gets no more than fit
     // (whatever the window, so that the next rule holds).
     const long long split_bytes = (long long)p.B * p.Hkv * p.n_coltiles * ((long long)p.col_stride * kD + 64) * (long long)sizeof(float);
-    if (split_bytes <= kDecodeStaticScratchBytes)
+    if (split_bytes <= kDecodeStaticScratchBytes && (own_scratch || !may_exceed))
         while (n > 1 && (n + n / 8) * split_bytes > kDecodeStaticScratchBytes) --n;
     // The workspace is sized for the most splits any smaller number of halves would get: a caller's
     // workspace for a full-attention layer serves the windowed layers of the same model.

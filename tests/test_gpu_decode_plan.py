@@ -22,11 +22,19 @@ pytestmark = pytest.mark.gpu
     (127, 1, 1, 1, 1100, 10**9, 4),   # 127 pairs: two splits
     (1, 1, 4, 1, 6177, 10**9, 4),     # 194 halves: the most splits a pair gets
     (128, 1, 2, 1, 3072, 10**9, 4),   # 128 pairs, 96 halves: one split
-    (128, 1, 2, 1, 3073, 10**9, 4),   # ... and 97: four
-    (257, 1, 1, 1, 3100, 10**9, 0),   # more than 256 pairs: one
+    (128, 1, 2, 1, 3073, 10**9, 4),   # ... and 97
+    (257, 1, 1, 1, 3100, 10**9, 0),   # more than 256 pairs: four
     (513, 1, 1, 1, 3100, 10**9, 0),   # more than the workgroups that run at once: four
     (64, 2, 4, 9, 600, 10**9, 4),     # two column tiles, one split
     (3, 2, 5, 13, 2000, 900, 40),     # three column tiles (one workgroup with a single one), many splits, window + sinks
+    (16, 8, 5, 8, 300, 10**9, 4),     # 128 pairs of column tiles: a workgroup for each tile
+    (64, 2, 3, 21, 300, 100, 4),      # ... with window; the second tile has 31 columns
+    (86, 3, 5, 8, 300, 10**9, 0),     # 258 pairs: a workgroup for each tile again
+    (65, 2, 5, 16, 300, 10**9, 0),    # three tiles, 260 pairs
+    (257, 1, 4, 1, 2048, 10**9, 4),   # 257 pairs of one tile, 64 halves: four splits
+    (257, 1, 4, 1, 2016, 10**9, 4),   # ... and 63: one
+    (321, 1, 4, 1, 2048, 10**9, 4),   # 321 pairs: one
+    (42, 3, 5, 8, 2000, 10**9, 4),    # 126 pairs of column tiles: two tiles a workgroup, two splits
 ])
 def test_borders_of_the_split_plan(B, Hkv, G, Nq, Nk, W, S):
     tag = f"decode B{B} Hkv{Hkv} G{G} Nq{Nq} Nk{Nk} W{W} S{S}"
@@ -54,3 +62,30 @@ def test_sequences_of_one_split_beside_long_ones():
         for b, h in enumerate(host):
             ro, rl = swaa_decode_oracle(*h, W, 4, 1 / math.sqrt(128))
             assert_parity(out[b:b + 1], lse[b:b + 1], ro, rl, tag=f"seq {b} of {lens[b]} W{W}")
+
+
+def test_several_splits_of_single_column_tiles_and_the_static_array():
+    # 264 pairs of column tiles on 4.1k tokens: four splits in a workspace, fewer where the library's own array must do
+    B, G, Nq, Nk = 264, 5, 8, 4100
+    assert binding.swaa_attn_decode_workspace_bytes(B, G, 1, Nq, Nk, 128, Nk, 4) > binding.SWAA_DECODE_STATIC_SCRATCH_BYTES
+    q, k, v = make_qkv(B, G, 1, Nk, 128, seed=97800, n_query=Nq)
+    qd, kd, vd = to_device(q), to_device(k), to_device(v)
+    out, lse = binding.swaa_attn_decode(qd, kd, vd, Nk, 4)
+    out1, lse1 = torch.full_like(out, float("nan")), torch.full_like(lse, float("nan"))
+    binding.swaa_attn_decode_static(qd, kd, vd, out1, lse1, Nk, 4)
+    torch.cuda.synchronize()
+    some = slice(0, B, 29)
+    ro, rl = swaa_decode_oracle(q[some], k[some], v[some], Nk, 4, 1 / math.sqrt(128))
+    assert_parity(out[some], lse[some], ro, rl, tag="splits in a workspace")
+    assert_parity(out1[some], lse1[some], ro, rl, tag="static array")
+
+
+def test_several_splits_of_two_column_tiles_where_the_last_round_is_nearly_empty():
+    B, G, Nq, Nk = 17, 4, 512, 12300  # 17 x 32 pairs of column tiles
+    q, k, v = make_qkv(B, G, 1, Nk, 128, seed=97810, n_query=Nq)
+    out, lse = binding.swaa_attn_decode(to_device(q), to_device(k), to_device(v), Nk, 4)
+    torch.cuda.synchronize()
+    for b in (0, B - 1):
+        one = slice(b, b + 1)
+        ro, rl = swaa_decode_oracle(q[one], k[one], v[one], Nk, 4, 1 / math.sqrt(128))
+        assert_parity(out[one], lse[one], ro, rl, tag=f"sequence {b}")
