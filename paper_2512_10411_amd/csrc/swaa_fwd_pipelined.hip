@@ -934,7 +934,7 @@ long long plan_fwd_split(FwdParams &p) {
         const long long room = bound * ((longest.halves + 1 + kSplitMinHalves - 1) / kSplitMinHalves + 1);
         p.split_keys = 1;
         p.split_cap = room < kSplitUnits ? (int)room : kSplitUnits;
-        p.chunk = (bound + p.split_cap + kXcds - 1) / kXcds + p.B;
+        p.chunk = (bound + (p.split_cap < kSplitExtra ? p.split_cap : kSplitExtra) + kXcds - 1) / kXcds + p.B;
     }
     p.total_items = p.chunk * kXcds;
     p.split_items = bound;

@@ -30,8 +30,12 @@
 // 196 + 9 us; 128 workgroups before); 23 generated tokens on caches of 1-12k tokens beside a chunk
 // of 999 rows on a 2k window 213 -> 139 us (bound by HBM: 470 MB, 95 us at the rate of a copy).
 // Calls that the plan leaves whole on the host (prompts on themselves, short windows, chunks that
-// fill the chip) launch the same kernels as without a workspace: the split kernel takes 4-6 us more
-// for the same plan (the plan itself, a merge without work).
+// fill the chip) launch the same kernels as without a workspace: the split kernel takes about 4 us more
+// for the same plan (the plan itself, a merge without work).  The launch has kSplitExtra workgroups beyond one
+// per row tile, and plans with more are not considered: those that the plan has no work for work it out all the
+// same, beside workgroups that have (31 generated tokens on 8k tokens beside a chunk of 512 rows, left whole: 216 us
+// with 1024 of them and reductions through the LDS crossbar, 203 now; without a workspace 199).  Of 600 drawn
+// batches the limit changes 28 plans, for a predicted 4 % at most.
 // So do batches of chunks with little to gain (whole_batch), if the number of packed rows shows on the
 // host that they are that; the device follows the same rule, so that the results do not depend on
 // whether the caller states that number.
@@ -45,6 +49,7 @@ namespace swaa {
 constexpr int kSplitMaxBatch = 64;   // one sequence per lane
 constexpr int kSplitMinHalves = 16;  // no split shorter than this many halves
 constexpr int kSplitUnits = 1024;    // most partial results a packed batch may leave (64 KiB each)
+constexpr int kSplitExtra = 512;     // most workgroups it may have beyond one per row tile
 constexpr float kSplitResident = 512.f, kSplitAlone = 256.f, kSplitAloneRate = 0.65f;
 constexpr float kSplitStart = 8.f, kSplitMerge = 8.f, kSplitTraffic = 0.015f, kSplitFull = 1.1f, kSplitTail = 0.5f;
 constexpr float kSplitMemory = 1.f / 300.f;
@@ -156,6 +161,26 @@ __device__ __forceinline__ void split_tile(const FwdParams &p, int nq, unsigned 
     w.pt = (int)(nt1 - 1 - t);
 }
 
+// Sum and largest of x over the 64 lanes (the data-parallel-primitive steps of wave_inclusive_scan).
+__device__ __forceinline__ unsigned wave_max(unsigned x) {
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false));
+    x = max(x, (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false));
+    return wave_read_lane(x, 63);
+}
+__device__ __forceinline__ float wave_sum(float x) {
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x111, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x112, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x114, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x118, 0xf, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x142, 0xa, 0xf, false));
+    x += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x143, 0xc, 0xf, false));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
+}
+
 // The work list with split keys: sequence after sequence, every sequence's units cut into eight
 // contiguous chunks, one per die (as in decode_work_packed); inside a sequence by KV head, then
 // split, then row tile, so that the workgroups side by side on a die read the same keys.  scratch:
@@ -176,14 +201,11 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
         int h_max = splittable, all = items, least = nq > 0 ? nq : p.Nq;
         float total = (float)items * (float)me.average;
         float memory = me.tiles <= 2 ? (float)(p.Hkv * me.halves) : 0.f;
-#pragma unroll
-        for (int sh = 32; sh > 0; sh >>= 1) {
-            h_max = max(h_max, __shfl_xor(h_max, sh));
-            total += __shfl_xor(total, sh);
-            memory += __shfl_xor(memory, sh);
-            all += __shfl_xor(all, sh);
-            least = min(least, __shfl_xor(least, sh));
-        }
+        h_max = (int)wave_max((unsigned)h_max);
+        total = wave_sum(total);
+        memory = wave_sum(memory);
+        all = (int)wave_read_lane(wave_inclusive_scan((unsigned)all), 63);
+        least = 0x7fffffff - (int)wave_max((unsigned)(0x7fffffff - least));
         const int L = max(kSplitMinHalves, (h_max + lane) / (lane + 1));
         const float rcp = 1.f / (float)L;
         float units = 0.f, split_units = 0.f, longest = 0.f;
@@ -210,10 +232,8 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
             longest = fmaxf(longest, o[128]);
         }
         __syncthreads();  // (the scratch becomes part of a ring)
-        float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, longest, total, memory);
-        float best = t;
-#pragma unroll
-        for (int sh = 32; sh > 0; sh >>= 1) best = fminf(best, __shfl_xor(best, sh));
+        float t = split_units > (float)p.split_cap || units > (float)(p.split_items + kSplitExtra) ? 3.0e38f : split_time(units, split_units, longest, total, memory);
+        const float best = __uint_as_float(~wave_max(~__float_as_uint(t)));  // (positive floats order like their bits)
         const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
         const int Lb = __builtin_amdgcn_readlane(L, pick);
         if (splittable > 0 && !whole_batch(p, least, all)) n = split_count(me.halves, Lb, 1.f / (float)Lb);
