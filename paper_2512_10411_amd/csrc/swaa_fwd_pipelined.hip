@@ -898,18 +898,21 @@ long long plan_fwd_split(FwdParams &p) {
     // A few chunks that fill the chip twice over are balanced by their number; in a larger batch
     // single generated tokens on long caches may stand beside them.
     if (p.B <= 4 && most > 2 * (long long)kSplitResident) return 0;
-    const long long bound = p.packed_compact ? p.total_items : most;
-    // No sequence has fewer rows than are left when the others have Nq each, and all of them together
-    // no fewer tiles than one sequence with all the rows.
+    // (every sequence adds at most one partly filled tile per head group to those that its rows fill)
+    auto tiles_of_all = [&](int tile_rows) { return (p.total_rows + tile_rows - 1) / tile_rows + p.B; };
+    const long long bound = !p.packed_compact ? most
+                                              : p.Hkv * (p.n4 * tiles_of_all(p.wg_rows / 4) + p.has2 * tiles_of_all(p.wg_rows / 2) +
+                                                         p.has1 * tiles_of_all(p.wg_rows));
+    // No sequence has fewer rows than are left when the others have Nq each.
     if (packed && p.packed_compact) {
         const long long least = p.total_rows - (long long)(p.B - 1) * p.Nq;
-        const int units = p.Hkv * split_seq(p, (int)p.total_rows, (int)p.total_rows, 0).tiles;
-        if (least > 0 && whole_batch(p, (int)least, units)) return 0;
+        if (least > 0 && whole_batch(p, (int)least, least_units(p, (int)p.total_rows))) return 0;
     }
     int n = 1;
     if (p.B == 1 || (!packed && !p.n_prompts)) {
         // sequences of one length (a packed batch of one: of at most this length)
         if (longest.whole) return 0;
+        if (!packed && p.P >= p.Nk && whole_batch(p, p.Nq, p.B * p.Hkv * longest.tiles)) return 0;
         const float items = (float)((long long)p.B * p.Hkv * longest.tiles);
         const float memory = longest.tiles <= 2 ? (float)((long long)p.B * p.Hkv * longest.halves) : 0.f;
         float best = split_time(items, 0.f, (float)longest.halves, items * (float)longest.average, memory);
@@ -934,7 +937,7 @@ long long plan_fwd_split(FwdParams &p) {
         const long long room = bound * ((longest.halves + 1 + kSplitMinHalves - 1) / kSplitMinHalves + 1);
         p.split_keys = 1;
         p.split_cap = room < kSplitUnits ? (int)room : kSplitUnits;
-        p.chunk = (bound + (p.split_cap < kSplitExtra ? p.split_cap : kSplitExtra) + kXcds - 1) / kXcds + p.B;
+        p.chunk = (bound + p.split_cap + kXcds - 1) / kXcds + p.B;
     }
     p.total_items = p.chunk * kXcds;
     p.split_items = bound;

@@ -31,11 +31,9 @@
 // of 999 rows on a 2k window 213 -> 139 us (bound by HBM: 470 MB, 95 us at the rate of a copy).
 // Calls that the plan leaves whole on the host (prompts on themselves, short windows, chunks that
 // fill the chip) launch the same kernels as without a workspace: the split kernel takes about 4 us more
-// for the same plan (the plan itself, a merge without work).  The launch has kSplitExtra workgroups beyond one
-// per row tile, and plans with more are not considered: those that the plan has no work for work it out all the
-// same, beside workgroups that have (31 generated tokens on 8k tokens beside a chunk of 512 rows, left whole: 216 us
-// with 1024 of them and reductions through the LDS crossbar, 203 now; without a workspace 199).  Of 600 drawn
-// batches the limit changes 28 plans, for a predicted 4 % at most.
+// for the same plan (the plan itself, also in the workgroups that it then has no work for, and a merge without
+// work: 31 generated tokens on 3k tokens beside a chunk of 256 rows, 8 heads on 8, 77.5 us without a workspace, 81.5
+// with one, 80.6 since the launch follows a closer bound and the plan's sums no longer cross LDS).
 // So do batches of chunks with little to gain (whole_batch), if the number of packed rows shows on the
 // host that they are that; the device follows the same rule, so that the results do not depend on
 // whether the caller states that number.
@@ -49,7 +47,6 @@ namespace swaa {
 constexpr int kSplitMaxBatch = 64;   // one sequence per lane
 constexpr int kSplitMinHalves = 16;  // no split shorter than this many halves
 constexpr int kSplitUnits = 1024;    // most partial results a packed batch may leave (64 KiB each)
-constexpr int kSplitExtra = 512;     // most workgroups it may have beyond one per row tile
 constexpr float kSplitResident = 512.f, kSplitAlone = 256.f, kSplitAloneRate = 0.65f;
 constexpr float kSplitStart = 8.f, kSplitMerge = 8.f, kSplitTraffic = 0.015f, kSplitFull = 1.1f, kSplitTail = 0.5f;
 constexpr float kSplitMemory = 1.f / 300.f;
@@ -106,18 +103,34 @@ __host__ __device__ inline float split_time(float units, float split_units, floa
     return split_units > 0.f ? t + kSplitMerge + kSplitTraffic * split_units : t;
 }
 
-// A batch in which every sequence brings at least `least` rows, `units` row tiles (times KV heads) in all:
+// A batch in which every sequence brings at least `least` rows, with at least `units` row tiles (times KV heads):
 // stays whole where the split kernel does not win its overhead back.  From 64 rows on a sequence is
-// taken for a chunk of a prompt, whose rows see the window.  Measured, whole / best split: 128 - 432
-// units on a window of 1024, 33.3 / 37.0, 47.5 / 52.6 us, of 2048 52.4 / 56.3 (224), 65.8 / 70.9 (288 units); 408 and
-// more units of any length (17 batches) 1 - 5 % faster whole; 48 units on a window of 1024 31.6 / 30.0,
-// 120 on one of 2048 50.1 / 50.3.
+// taken for a chunk of a prompt, whose rows see the window.  The more tiles there are, the longer the windows
+// (h halves) for which that holds; from 400 tiles on there are enough for any.  Measured, whole / as planned (us;
+// 32 heads on 8, binary16, pages of 16; bfloat16, pages of 64 and contiguous keys alike):
+//    64 tiles   window 1250 28.6 / 29.3   1500 33.2 / 30.0   2048 38.7 / 31.6
+//    96         window 1250 28.8 / 32.4   1500 33.2 / 34.3   1750 36.7 / 36.1   2500 47.6 / 41.0
+//   128         window 1500 33.2 / 36.7   2048 39.1 / 40.1   2500 47.7 / 43.9   3000 53.4 / 46.2
+//   160         window 2048 39.6 / 44.4   2500 48.0 / 49.1   3000 54.3 / 52.8   4096 68.6 / 61.5
+//   192         window 2500 50.4 / 52.9   3000 57.8 / 61.7   4096 74.9 / 74.9   6000 104 / 97.7
+//   240         window 3000 58.2 / 60.9   4096 76.0 / 82.2   6000 109 / 110     8192 144 / 141
+//   304         window 3000 84.2 / 88.4   8192 201 / 206     24k, full attention 546 / 476
+// Groups of fewer than four heads share less, and their tiles of 64 or 128 positions take longer (8 heads on 8,
+// 112 tiles: window 1250 35.6 / 35.2, 1500 38.8 / 36.1).  Fewer tiles gain on every window that is long enough to be
+// split (16 tiles: window 700 20.7 / 23.6, 1250 28.4 / 24.0).  (These are chunks on 12k tokens.)  With full
+// attention, and on caches shorter than a long window, the tiles differ, by sequence and along its rows, and splits
+// even them out: three chunks of 735 rows, 276 tiles, on 3-6k tokens 113 / 109; two of 339, 224 tiles, window 4096, on
+// 3-10k tokens 81.0 / 75.5.  So the rule ends at windows of 3000.
 __host__ __device__ inline bool whole_batch(const FwdParams &p, int least, int units) {
     if (least < 64) return false;
+    if (units >= 400 && p.Hkv * split_seq(p, least, p.Nk, p.Nk).tiles >= 64) return true;
     const int h = tile_halves(p.Nk - 32, p.Nk - 1, p.W, p.S);
-    return (units >= 400 && p.Hkv * split_seq(p, least, p.Nk, p.Nk).tiles >= 64) || (units >= 160 && h <= 72) ||
-           (units >= 64 && h <= 40);
+    if (units < 64) return h <= 2 * kSplitMinHalves;
+    if (p.n4 == 0 || p.W >= p.Nk) return h <= (units < 160 ? 42 : 72);
+    return h <= (units < 160 ? 42 + (units - 64) * 9 / 20 : 100);
 }
+// Row tiles (times KV heads) of a batch of so many rows: no fewer than one sequence with all of them has.
+__host__ __device__ inline int least_units(const FwdParams &p, int rows) { return p.Hkv * split_seq(p, rows, rows, 0).tiles; }
 
 // One workgroup's share of the keys.
 struct SplitItem {
@@ -198,13 +211,13 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     } else {
         // the model's terms of candidate `lane`, summed over the sequences: wave w takes every fourth
         const int splittable = me.whole ? 0 : me.halves;
-        int h_max = splittable, all = items, least = nq > 0 ? nq : p.Nq;
+        int h_max = splittable, rows = nq, least = nq > 0 ? nq : p.Nq;
         float total = (float)items * (float)me.average;
         float memory = me.tiles <= 2 ? (float)(p.Hkv * me.halves) : 0.f;
         h_max = (int)wave_max((unsigned)h_max);
         total = wave_sum(total);
         memory = wave_sum(memory);
-        all = (int)wave_read_lane(wave_inclusive_scan((unsigned)all), 63);
+        rows = (int)wave_read_lane(wave_inclusive_scan((unsigned)rows), 63);
         least = 0x7fffffff - (int)wave_max((unsigned)(0x7fffffff - least));
         const int L = max(kSplitMinHalves, (h_max + lane) / (lane + 1));
         const float rcp = 1.f / (float)L;
@@ -232,11 +245,11 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
             longest = fmaxf(longest, o[128]);
         }
         __syncthreads();  // (the scratch becomes part of a ring)
-        float t = split_units > (float)p.split_cap || units > (float)(p.split_items + kSplitExtra) ? 3.0e38f : split_time(units, split_units, longest, total, memory);
+        const float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, longest, total, memory);
         const float best = __uint_as_float(~wave_max(~__float_as_uint(t)));  // (positive floats order like their bits)
         const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
         const int Lb = __builtin_amdgcn_readlane(L, pick);
-        if (splittable > 0 && !whole_batch(p, least, all)) n = split_count(me.halves, Lb, 1.f / (float)Lb);
+        if (splittable > 0 && !whole_batch(p, least, least_units(p, rows))) n = split_count(me.halves, Lb, 1.f / (float)Lb);
     }
     if (me.whole || items == 0) n = 1;
     if (blockIdx.x == 0) p.ws_n[lane] = n;  // every lane its sequence's, for the merge kernel
