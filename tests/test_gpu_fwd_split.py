@@ -17,6 +17,28 @@ from gpu_util import assert_parity, to_device
 pytestmark = pytest.mark.gpu
 
 
+@pytest.fixture
+def scratch(monkeypatch):
+    """The workspace bytes of every swaa_attn_fwd_ex call (0: its keys stay whole); the workspaces hold 0xFF bytes,
+    NaN patterns that show if a partial result is read that was not written."""
+    lib, sizes = binding.load_library(), []
+    query, launch = lib.swaa_attn_fwd_ex_workspace_bytes, lib.swaa_attn_fwd_ex_ws
+
+    def recording(args):
+        sizes.append(int(query(args)))
+        return sizes[-1]
+
+    def filled(args, workspace, workspace_bytes):
+        full = torch.full((workspace_bytes,), 255, dtype=torch.uint8, device="cuda")
+        kept.append(full)
+        return launch(args, full.data_ptr(), workspace_bytes)
+
+    kept = []
+    monkeypatch.setattr(lib, "swaa_attn_fwd_ex_workspace_bytes", recording)
+    monkeypatch.setattr(lib, "swaa_attn_fwd_ex_ws", filled)
+    return sizes
+
+
 @pytest.mark.parametrize("B,Hkv,G,Nq,Nk,W,S,P,fmt", [
     (1, 1, 4, 1, 1025, 10**9, 4, None, "bf16"),     # 33 halves: the shortest split range, odd last split
     (1, 1, 4, 33, 3001, 10**9, 0, None, "fp16"),    # two row tiles, ragged last half
@@ -27,18 +49,19 @@ pytestmark = pytest.mark.gpu
     (1, 1, 4, 40, 3000, 1, 1500, None, "bf16"),     # nearly all keys are sinks
     (1, 1, 4, 64, 2100, 40, 4, 2100 - 64, "bf16"),  # generated rows only
 ])
-def test_fixed_length_chunks(B, Hkv, G, Nq, Nk, W, S, P, fmt):
+def test_fixed_length_chunks(scratch, B, Hkv, G, Nq, Nk, W, S, P, fmt):
     tag = f"split B{B} Hkv{Hkv} G{G} Nq{Nq} Nk{Nk} W{W} S{S} P{P} {fmt}"
     print(f"[case] {tag}", flush=True)
     q, k, v = make_qkv(B, Hkv * G, Hkv, Nk, 128, seed=91000 + Nq + Nk, n_query=Nq, fmt=fmt)
     out, lse = binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), W, S, P)
     torch.cuda.synchronize()
+    assert scratch[0] > 0
     with input_format(fmt):
         ro, rl = swaa_decode_oracle(q, k, v, W, S, 1 / math.sqrt(128), n_prompt=P)
     assert_parity(out, lse, ro, rl, tag=tag)
 
 
-def test_a_late_spike_in_one_split_takes_the_second_pass():
+def test_a_late_spike_in_one_split_takes_the_second_pass(scratch):
     # scores 80 nats above the first keys of a split: that split's workgroups recompute, the others do not
     q, k, v = make_qkv(1, 4, 1, 3000, 128, seed=92, n_query=40)
     to_bits = lambda x: np.array([x], dtype=np.float32).view(np.uint32)[0] >> 16
@@ -46,12 +69,13 @@ def test_a_late_spike_in_one_split_takes_the_second_pass():
     k[:, :, 1700, 0] = to_bits(304.0)
     out, lse = binding.swaa_attn_fwd_ex(to_device(q), to_device(k), to_device(v), 10**9, 4)
     torch.cuda.synchronize()
+    assert scratch[0] > 0
     ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
     assert_parity(out, lse, ro, rl, tag="split, late spike")
 
 
 @pytest.mark.parametrize("n_singles,W,fmt,page", [(20, 300, "fp16", 16), (62, 40, "bf16", 48), (3, 2000, "bf16", 0)])
-def test_generated_tokens_beside_a_chunk(n_singles, W, fmt, page):
+def test_generated_tokens_beside_a_chunk(scratch, n_singles, W, fmt, page):
     # a packed batch: single generated tokens on caches of very different lengths, an empty sequence, a chunk
     # without generated rows, and a sequence of prompt and generated rows (never split)
     rng = np.random.Generator(np.random.Philox(93 + n_singles))
@@ -89,6 +113,7 @@ def test_generated_tokens_beside_a_chunk(n_singles, W, fmt, page):
         kk, vv = (torch.cat([d[i] for d in dev], dim=1).contiguous() for i in range(2))
     outs = [tuple(t.clone() for t in binding.swaa_attn_fwd_ex(q, kk, vv, W, S, total_rows_q=t, **args)) for t in (None, None, 0)]
     torch.cuda.synchronize()
+    assert all(n > 0 for n in scratch)
     assert all(torch.equal(outs[0][0], o) and torch.equal(outs[0][1], l) for o, l in outs[1:])
     r0 = 0
     with input_format(fmt):
@@ -100,10 +125,13 @@ def test_generated_tokens_beside_a_chunk(n_singles, W, fmt, page):
             r0 += nq[b]
 
 
-@pytest.mark.parametrize("nq,nk,W", [([333, 400], [1500, 2000], 900),       # 80 units on a short window: whole
-                                     ([64, 640], [2000, 1100], 900),        # the shortest sequence taken for a chunk
-                                     ([63, 640], [2000, 1100], 900)])       # one row less: planned on the device
-def test_chunks_give_the_same_bits_whichever_list_they_run_on(nq, nk, W):
+@pytest.mark.parametrize("nq,nk,W,whole", [
+    ([333, 400], [1500, 2000], 900, True),    # 72 units on a short window: whole
+    ([64, 640], [2000, 1100], 900, True),     # the shortest sequence taken for a chunk
+    ([63, 640], [2000, 1100], 900, False),    # one row less: planned on the device
+    ([333, 400], [1500, 2000], 1500, False),  # a longer window
+])
+def test_chunks_give_the_same_bits_whichever_list_they_run_on(scratch, nq, nk, W, whole):
     # whether the caller states the number of rows or not, a batch is split or left whole alike
     Hkv, G, S, B = 3, 4, 4, len(nq)
     print(f"[case] chunks {nq} on {nk} W{W}", flush=True)
@@ -114,6 +142,7 @@ def test_chunks_give_the_same_bits_whichever_list_they_run_on(nq, nk, W):
                 n_prompts=torch.tensor(nk, dtype=torch.int32, device="cuda"))
     (out, lse), (o0, l0) = (tuple(t.clone() for t in binding.swaa_attn_fwd_ex(q, kk, vv, W, S, total_rows_q=t, **args)) for t in (None, 0))
     torch.cuda.synchronize()
+    assert (scratch[0] == 0) == whole and scratch[1] > 0
     assert torch.equal(out, o0) and torch.equal(lse, l0)
     r0 = 0
     for b, h in enumerate(host):
@@ -124,7 +153,7 @@ def test_chunks_give_the_same_bits_whichever_list_they_run_on(nq, nk, W):
 
 @pytest.mark.parametrize("fmt", ["bf16", "fp16"])
 @pytest.mark.parametrize("what", ["nan", "inf"])
-def test_a_non_finite_key_of_one_split_reaches_the_rows_that_see_it(what, fmt):
+def test_a_non_finite_key_of_one_split_reaches_the_rows_that_see_it(scratch, what, fmt):
     # the merge must not take a split whose sums are not numbers for one without keys
     q, k, v = make_qkv(1, 4, 1, 5000, 128, seed=9650, n_query=300, fmt=fmt)
     bits = {("nan", "bf16"): 0x7FC0, ("inf", "bf16"): 0x7F80, ("nan", "fp16"): 0x7E00, ("inf", "fp16"): 0x7C00}[what, fmt]
@@ -133,6 +162,7 @@ def test_a_non_finite_key_of_one_split_reaches_the_rows_that_see_it(what, fmt):
     k[:, :, key, 5] = np.uint16(bits)
     out, lse = binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), W, 4)
     torch.cuda.synchronize()
+    assert scratch[0] > 0
     assert not torch.isfinite(out[:, :, :230].float()).any() and not torch.isfinite(lse[:, :, :230]).any()
     rows = np.arange(230, 300)
     with input_format(fmt):
@@ -140,7 +170,7 @@ def test_a_non_finite_key_of_one_split_reaches_the_rows_that_see_it(what, fmt):
     assert_parity(out[:, :, rows], lse[:, :, rows], ro[:, :, rows], rl[:, :, rows], tag=f"split, {what} key, rows that do not see it")
 
 
-def test_without_memory_for_scratch_the_keys_stay_whole(monkeypatch):
+def test_without_memory_for_scratch_the_keys_stay_whole(scratch, monkeypatch):
     q, k, v = make_qkv(1, 4, 1, 3001, 128, seed=9670, n_query=33)
     qd, kd, vd = to_device(q), to_device(k), to_device(v)
     empty = torch.empty
@@ -153,6 +183,7 @@ def test_without_memory_for_scratch_the_keys_stay_whole(monkeypatch):
     monkeypatch.setattr(torch, "empty", no_scratch)
     out, lse = binding.swaa_attn_fwd_ex(qd, kd, vd, 10**9, 4)
     torch.cuda.synchronize()
+    assert scratch[0] > 0
     monkeypatch.undo()
     ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
     assert_parity(out, lse, ro, rl, tag="no scratch")
