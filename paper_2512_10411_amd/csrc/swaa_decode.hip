@@ -526,7 +526,9 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
             if (n_splits == 1) {
                 p.lse[row] = (m[j] + __builtin_amdgcn_logf(l[j])) * 0.69314718055994530942f;
             } else {
-                p.ws_ml[item[j] * 64 + l32] = m[j];
+                // (a sum that is not a number travels with a finite reference: -inf, the largest score of a column that
+                // sees NaN only, would mark the split as empty, and the merge would leave it out)
+                p.ws_ml[item[j] * 64 + l32] = non_finite(l[j]) ? 0.f : m[j];
                 p.ws_ml[item[j] * 64 + 32 + l32] = l[j];
             }
         }

@@ -4,6 +4,7 @@ where some of the workgroup's four waves have no keys; against the fp64 CPU orac
 """
 import math
 
+import numpy as np
 import pytest
 import torch
 
@@ -89,3 +90,16 @@ def test_several_splits_of_two_column_tiles_where_the_last_round_is_nearly_empty
         one = slice(b, b + 1)
         ro, rl = swaa_decode_oracle(q[one], k[one], v[one], Nk, 4, 1 / math.sqrt(128))
         assert_parity(out[one], lse[one], ro, rl, tag=f"sequence {b}")
+
+
+@pytest.mark.parametrize("first,last", [(2560, 3072), (5, 6), (0, 8000)])  # splits of 256 keys: two whole ones
+def test_keys_that_are_no_numbers_show_in_the_rows_that_see_them(first, last):
+    # whole splits of NaN among them: the merge must not take those for splits without keys
+    q, k, v = make_qkv(1, 4, 1, 8000, 128, seed=97820, n_query=1)
+    k[:, :, first:last, 7] = np.uint16(0x7FC0)
+    out, lse = binding.swaa_attn_decode(to_device(q), to_device(k), to_device(v), 8000, 4)
+    seen = binding.swaa_attn_decode_ex(to_device(q), to_device(k), to_device(v), 8000, 4,
+                                       seq_lens=torch.tensor([8000], dtype=torch.int32, device="cuda"))
+    torch.cuda.synchronize()
+    for o, l in ((out, lse), seen):
+        assert not torch.isfinite(o.float()).any() and not torch.isfinite(l).any()
