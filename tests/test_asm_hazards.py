@@ -164,25 +164,25 @@ def test_no_vector_write_within_two_instructions_of_an_mfma_that_reads_it(tmp_pa
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
                     reason="hipcc not available")
-def test_backward_dma_kernels_own_all_lds(tmp_path):
-    """The LDS-DMA dK/dV kernel addresses LDS with plain byte addresses from 0 (its MFMAs go
-    through compiler builtins, so the wait-state rules above are the compiler's)."""
+@pytest.mark.parametrize("src,kernels", [("swaa_bwd.hip", ("dkv_dma", "bwd_dkv_kernelILi64")), ("swaa_fwd_d64.hip", ("fwd_d64",))])
+def test_lds_dma_kernels_own_all_lds(tmp_path, src, kernels):
+    """The LDS-DMA kernels whose MFMAs go through compiler builtins (the wait-state rules above are the
+    compiler's there) address LDS with plain byte addresses from 0, too."""
     out = tmp_path / "b.s"
     flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
-    cmd = [build.hipcc_path(), *flags, "--cuda-device-only", "-S", "-o", str(out), os.path.join(build.CSRC, "swaa_bwd.hip")]
+    cmd = [build.hipcc_path(), *flags, "--cuda-device-only", "-S", "-o", str(out), os.path.join(build.CSRC, src)]
     subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
     text = open(out).read()
     sizes = re.findall(r"\.amdhsa_group_segment_fixed_size\s+(\d+)", text)
+    spills = re.findall(r"\.amdhsa_private_segment_fixed_size\s+(\d+)", text)
     names = re.findall(r"\.amdhsa_kernel\s+(\S+)", text)
-    assert names and len(sizes) == len(names)
+    assert names and len(sizes) == len(names) == len(spills)
     seen = set()
-    for name, size in zip(names, sizes):
-        for k in ("dkv_dma",):
+    for name, size, spill in zip(names, sizes, spills):
+        for k in kernels:
             if k in name:
                 seen.add(k)
                 assert int(size) == 0, (name, size)
-    assert seen == {"dkv_dma"}
-    # and they do not spill (a spill would also mean scratch traffic inside the key loop)
-    for name, spill in zip(names, re.findall(r"\.amdhsa_private_segment_fixed_size\s+(\d+)", text)):
-        if "dma" in name:
-            assert int(spill) == 0, (name, spill)
+                # and no spills (their reloads would wait for the copies, inside the loop)
+                assert int(spill) == 0, (name, spill)
+    assert seen == set(kernels)
