@@ -43,11 +43,11 @@ MEASURED_TRAFFIC_BYTES = {
     "pair32k_full": (2.64e9, "profiles/swaa_fwd_pipelined_pair32k_full.txt"),
     "long128k_swa": (6.807e9, "profiles/swaa_fwd_pipelined_long128k_swa.txt"),
     "long128k_full": (2.669e11, "profiles/swaa_fwd_pipelined_long128k_full.txt"),
-    "decode128k_full": (5.411e8, "profiles/swaa_decode_decode128k_full.txt"),
-    "decode16k_b16": (1.079e9, "profiles/swaa_decode_decode16k_b16.txt"),
-    "decode128k_swa": (3.665e7, "profiles/swaa_decode_decode128k_swa.txt"),
-    "decode_skewed_b16": (6.081e8, "profiles/swaa_decode_decode_skewed_b16.txt"),
-    "decode_mixed_b32": (1.078e9, "profiles/swaa_decode_decode_mixed_b32.txt"),
+    "decode128k_full": (5.382e8, "profiles/swaa_decode_decode128k_full.txt"),
+    "decode16k_b16": (1.076e9, "profiles/swaa_decode_decode16k_b16.txt"),
+    "decode128k_swa": (3.491e7, "profiles/swaa_decode_decode128k_swa.txt"),
+    "decode_skewed_b16": (6.050e8, "profiles/swaa_decode_decode_skewed_b16.txt"),
+    "decode_mixed_b32": (1.075e9, "profiles/swaa_decode_decode_mixed_b32.txt"),
     "mid_bwd": (1.63e9, "profiles/swaa_bwd_mid_bwd.txt"),
 }
 MIN_WARMUP_S = 0.05  # the clocks settle only after some tens of ms of continuous work

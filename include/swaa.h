@@ -56,7 +56,7 @@ typedef enum swaa_status {
  *   B, Hq, Hkv, N >= 1; Hq a multiple of Hkv (query head h reads KV head
  *        h / (Hq/Hkv)); N * D * max(Hq, Hkv) * B must fit in 2^62 elements
  *   D    head dimension: a multiple of 32 up to 256 (128 has the tuned, software-pipelined
- *        kernel; the others run on a plain tiled kernel)
+ *        kernel, 64 one of its own; the others run on a plain tiled kernel)
  *   window  >= 1; any value >= N means full causal attention
  *   n_sink  >= 0; values >= N behave as N
  *   scale   finite and > 0 (callers normally pass 1/sqrt(D))
@@ -121,7 +121,7 @@ int swaa_attn_fwd_fa_decode(const void *q, const void *k, const void *v, void *o
  * dtype selects the 16-bit element format of q, k, v and out: SWAA_BF16 (the
  * format of every other call) or SWAA_F16, which computes the same thing on
  * binary16 operands and rounds the probabilities and the output to binary16
- * (fp32 accumulation; runs on the plain kernel).
+ * (fp32 accumulation).
  *
  * Paged key/value cache (prefill of a chunk against a serving engine's cache, as
  * swaa_attn_decode_ex reads it): with block_table given, token j of sequence b

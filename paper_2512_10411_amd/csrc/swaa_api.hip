@@ -58,7 +58,7 @@ const char *swaa_status_string(int status) {
     }
 }
 
-int swaa_version(void) { return 130; }
+int swaa_version(void) { return 131; }
 
 namespace {
 
@@ -128,14 +128,13 @@ int fwd_setup(const swaa_fwd_args *a, bool allow_split, FwdParams &p, long long 
     p.G = Hq / Hkv;
     p.scale = a->scale;
     p.scale_log2 = a->scale * 1.44269504088896340736f;
-    // the pipelined kernel (head dimension 128, either 16-bit format) runs workgroups of 128
-    // rows, two per compute unit; other head dimensions run on the plain kernel
-    const bool pipelined = D == 128;
-    const int wg_rows = pipelined ? 128 : swaa::fwd_simple_wg_rows(D);
+    // head dimensions 128 (the pipelined kernel) and 64 have kernels of their own, the others run on the plain one;
+    // all of them run workgroups of as many rows
+    const int wg_rows = swaa::kFwdWgRows;
     if (a->total_rows_q < 0) return SWAA_ERR_SHAPE;
     if (packed && a->total_rows_q > 0 ? !swaa::plan_work_packed(p, Nq, wg_rows, a->total_rows_q) : !swaa::plan_work(p, Nq, wg_rows))
         return SWAA_ERR_SHAPE;
-    ws_bytes = allow_split && pipelined ? swaa::plan_fwd_split(p) : 0;
+    ws_bytes = allow_split && D == 128 ? swaa::plan_fwd_split(p) : 0;
     return SWAA_OK;
 }
 

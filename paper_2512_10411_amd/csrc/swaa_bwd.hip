@@ -45,7 +45,6 @@ constexpr int kBq = 64;  // query rows per tile of the dK/dV kernel
 template <int D>
 struct BTile {
     static constexpr int kChunksPerRow = D / 8;
-    static constexpr int kChunksPerThread = kBk * kChunksPerRow / kThreads;  // 64-row tile, 256 threads
     static constexpr int kStride = D + 8;  // bf16 elements per LDS row
     static constexpr int kElems = kBk * kStride;
 };
@@ -303,7 +302,7 @@ __device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
 // A short sequence has few key tiles (two of 4001 tokens on 4 KV heads: 256, one per compute
 // unit), so the waves that hide each other's latencies have to come from one workgroup: three per
 // SIMD with 168 registers each.  (Two parts, K and V read from LDS, tiles staged through registers with
-// two barriers a step: 139 us for those sequences; now 125, and 138 with two parts.  Each step is a
+// two barriers a step: 139 us for those sequences; now 126, and 138 with two parts.  Each step is a
 // phase of matrix work, one of vector work and one of matrix work again for all waves at once; the
 // priorities by part pull them apart a little: 133 -> 126.)
 // This kernel declares no static LDS: its dynamic LDS starts at address 0.

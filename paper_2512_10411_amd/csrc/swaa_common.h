@@ -17,9 +17,9 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBk = 64;        // keys per KV tile
-constexpr int kThreads = 256;  // plain kernels: 4 waves per workgroup ...
-constexpr int kWaveRows = 64;  // ... of 64 query rows each (the pipelined kernel: 8 waves of 32)
-constexpr int kWgRows = 256;   // query rows (head x position) per workgroup of the plain and backward kernels
+constexpr int kThreads = 256;  // per workgroup of the forward kernels that leave scheduling to the compiler
+constexpr int kWgRows = 256;   // query rows (head x position) per workgroup of the dQ kernels
+constexpr int kFwdWgRows = 128;  // query rows (head x position) per workgroup of the forward kernels
 constexpr int kXcds = 8;       // accelerator dies; workgroups are dealt to them round-robin
 
 // Division of a number below 2^31 by a divisor fixed at launch, as a multiplication: with
@@ -67,7 +67,7 @@ struct FwdParams {
     // at page 0 and k_sb, v_sb are the page strides.  page_size is a multiple of 16.
     const int *block_table;
     int bt_stride, page_size, num_pages;
-    int fp16;  // the 16-bit elements of q, k, v, out are IEEE binary16 instead of bfloat16 (plain kernel only)
+    int fp16;  // the 16-bit elements of q, k, v, out are IEEE binary16 instead of bfloat16
     int B, Hq, Hkv;
     int Nq, Nk;  // query rows and keys per sequence (the largest ones when cu_q / cu_k are given)
     int W, S;    // clamped to [1, Nk] and [0, Nk]
@@ -78,7 +78,7 @@ struct FwdParams {
     // cut into n4 groups of 4 heads, at most one group of 2 heads and at most
     // one single head; a workgroup is wg_rows query rows (head x position) on one
     // KV head: 4 heads x wg_rows/4 positions, 2 x wg_rows/2 or 1 x wg_rows.
-    int wg_rows;  // 128 (forward kernels) or 256 (backward kernels)
+    int wg_rows;  // kFwdWgRows (forward kernels) or 256 (backward kernels)
     int n4, has2, has1;
     int nt_h4, nt_h2, nt_h1;  // row tiles of a sequence of Nq rows for workgroups of 4, 2 and 1 heads
     FastDiv div_tiles_per_pair, div_hkv, div_nt_h4;  // for the work-list decode of every workgroup
@@ -91,7 +91,7 @@ struct FwdParams {
     // out the true ones from cu_q / cu_k (decode_work_packed).
     int packed_compact;
     long long total_rows;  // query rows of the whole packed batch (packed_compact)
-    // Split keys (swaa_fwd_pipelined.hip, split_plan): the tiles of a sequence are cut into
+    // Split keys (plan_fwd_split, and swaa_fwd_split.h on the device): the tiles of a sequence are cut into
     // several workgroups along the keys, whose partial results a second kernel merges.
     // 0: not split; 1: the split counts are worked out on the device from the sequences'
     // lengths; >= 2: this many for every sequence (fixed-length batches).
@@ -339,11 +339,9 @@ __device__ __forceinline__ float half_swap_sum(float x) {
 }
 
 // Launchers (one per kernel family); return the HIP error of the launch.
-// (the plain kernel: head dimensions 32 .. 256 in steps of 32 except 64 and 128; its workgroups hold
-// fwd_simple_wg_rows(D) query rows)
+// (the plain kernel: head dimensions 32 .. 256 in steps of 32 except 64 and 128)
 hipError_t launch_fwd_simple(const FwdParams &p, int D, hipStream_t stream);
-int fwd_simple_wg_rows(int D);
-hipError_t launch_fwd_d64(const FwdParams &p, hipStream_t stream);  // 128 rows per workgroup
+hipError_t launch_fwd_d64(const FwdParams &p, hipStream_t stream);
 hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream);
 // Decides whether the call's keys are split over several workgroups per row tile and fills the
 // split_* fields (after plan_work / plan_work_packed, whose launch size it enlarges); the bytes of

@@ -47,7 +47,7 @@ namespace swaa {
 namespace {
 
 constexpr int kDStageBytes = 2 * kHalfBytes;          // K half, then V half
-// Stages of a wave's ring and workgroups per CU: the 450 registers of two column tiles leave one wave
+// Stages of a wave's ring and workgroups per CU: the 382 registers of two column tiles leave one wave
 // per SIMD, so one workgroup, whose waves then take two stages each.
 constexpr int decode_stages(int tiles) { return tiles == 2 ? 2 : 1; }
 constexpr int decode_wgs_per_cu(int tiles) { return tiles == 2 ? 1 : 2; }
@@ -128,8 +128,8 @@ __device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps,
 }
 
 // kPaged: k and v are a paged cache addressed through p.block_table (its own instantiation).
-// kTiles: column tiles a workgroup computes from the same K and V fragments (1, or 2 when a pair
-// has more than 32 query rows: two tiles in two workgroups would read every key twice).
+// kTiles: column tiles a workgroup computes from the same K and V fragments (1, or 2 when a pair has more than 32
+// query rows: two tiles in two workgroups read every key twice, which only some sizes make up for, see plan_decode).
 template <bool kF16, bool kPaged, int kTiles>
 __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_decode_split_kernel(const DecodeParams p) {
     // Workgroups reach the eight dies round-robin; the list has fewer than 2^31 items: 32-bit

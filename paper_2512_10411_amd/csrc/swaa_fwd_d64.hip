@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kThreads, 4) void swaa_fwd_d64_kernel(const FwdPara
     SeqGeom sg;
     if (!seq_geom(p, wi.b, sg)) return;
     const int hpb = wi.hpb;
-    const int rows_per_wg = 128 / hpb;
+    const int rows_per_wg = kFwdWgRows / hpb;
     const int wg_r0 = wi.pt * rows_per_wg;  // first query row of the workgroup
     if (wg_r0 >= sg.nq) return;             // a shorter sequence of a packed batch
     const int Nq = sg.nq, Nk = sg.nk, S = p.S, P = sg.n_prompt;
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kThreads, 4) void swaa_fwd_d64_kernel(const FwdPara
 }  // namespace
 
 hipError_t launch_fwd_d64(const FwdParams &p, hipStream_t stream) {
-    if (p.wg_rows != 128) return hipErrorInvalidValue;  // the plan must be the one for this kernel's workgroups
+    if (p.wg_rows != kFwdWgRows) return hipErrorInvalidValue;  // the plan must be the one for this kernel's workgroups
     const dim3 grid((unsigned)(p.chunk * kXcds));
     if (p.fp16)
         hipLaunchKernelGGL(swaa_fwd_d64_kernel<true>, grid, dim3(kThreads), kSmem64, stream, p);

@@ -49,6 +49,7 @@ constexpr int kPWaves = 4;    // waves per workgroup
 constexpr int kPThreads = 64 * kPWaves;
 constexpr int kPRows = 32;    // query positions per wave
 constexpr int kPWgRows = kPWaves * kPRows;            // query rows (head x position) per workgroup
+static_assert(kPWgRows == kFwdWgRows, "the plan's workgroups");
 constexpr int kStages = 2;                            // tiles per ring
 constexpr int kTileBytes = kBk * kD * 2;              // 16 KiB
 constexpr int kVRing = kStages * kTileBytes;          // V ring follows the K ring

@@ -89,8 +89,8 @@ __global__ __launch_bounds__(kThreads, min_blocks(D)) void swaa_fwd_kernel(const
     using x4 = typename X::x4;
     constexpr int KS = D / 16;  // k-steps of the QK^T contraction
     constexpr int DB = D / 32;  // 32-wide blocks of the head dimension
-    constexpr int kWaveRows = 32 * QB;           // (hides the namespace's constants of the same names)
-    constexpr int kWgRows = 4 * kWaveRows;
+    constexpr int kWaveRows = 32 * QB;
+    constexpr int kWgRows = 4 * kWaveRows;  // (hides the namespace's constant of the same name)
 
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     E *Ks = reinterpret_cast<E *>(smem_raw);
@@ -375,8 +375,6 @@ hipError_t launch_format(const FwdParams &p, hipStream_t stream) {
 }
 
 }  // namespace
-
-int fwd_simple_wg_rows(int) { return 128; }
 
 hipError_t launch_fwd_simple(const FwdParams &p, int D, hipStream_t stream) {
     switch (D) {
