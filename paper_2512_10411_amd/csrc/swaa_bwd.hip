@@ -316,7 +316,9 @@ struct DkvSmem {
     static constexpr int kBufferBytes = kDkvParts * kPartBytes;
     static constexpr int kSumBytes = 4 * 32 * D * 4;              // the final sum: one part's dK or dV
     static constexpr int kBuffers = 3;
-    static constexpr int kBytes = kBuffers * kBufferBytes > kSumBytes ? kBuffers * kBufferBytes : kSumBytes;
+    static constexpr int kLse = kBuffers * kBufferBytes;          // every wave's copy of a block's lse (edge blocks)
+    static constexpr int kEnd = kLse + 4 * kDkvParts * 32 * 4;
+    static constexpr int kBytes = kEnd > kSumBytes ? kEnd : kSumBytes;
 };
 
 template <int D>
@@ -495,12 +497,14 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
             // P and dS in the accumulator layout (row 8 (e/4) + 4 hf + e%4, column = this lane's key); a
             // score that must not be seen becomes -inf, its P an exact 0
             // (A row whose lse is not a number, or -inf, must not reach keys that it does not see, and exp2(-inf - NaN) is
-            // NaN: with an lse of -1e38 in its place, P is 0 there and infinite where the row does see the key.  In
-            // LDS, where all waves of the part write the same.)
+            // NaN: with an lse of -1e38 in its place, P is 0 there and infinite where the row does see the key.  A
+            // copy of the wave's own takes it.)
+            uint32_t lse_at = Ls;
             if (!unmasked) {
-                const auto lse = (uint32_t __attribute__((address_space(3))) *)(uintptr_t)(Ls + 4 * l32);
-                const uint32_t bits = *lse;
-                if ((bits & 0x7fffffffu) > 0x7f800000u || bits == 0xff800000u) *lse = 0xfe967699u;
+                lse_at = (uint32_t)(M::kLse + wave * 128);
+                const uint32_t bits = *(const uint32_t __attribute__((address_space(3))) *)(uintptr_t)(Ls + 4 * l32);
+                const bool sound = (bits & 0x7fffffffu) <= 0x7f800000u && bits != 0xff800000u;
+                *(uint32_t __attribute__((address_space(3))) *)(uintptr_t)(lse_at + 4 * l32) = sound ? bits : 0xfe967699u;
                 asm volatile("" ::: "memory");
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
@@ -511,7 +515,7 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
             for (int e4 = 0; e4 < 4; ++e4) {
                 const int r4 = 8 * e4 + 4 * hf;
                 typedef float f32x4 __attribute__((ext_vector_type(4)));
-                const f32x4 lv = *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)(Ls + r4 * 4);
+                const f32x4 lv = *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)(lse_at + r4 * 4);
                 const f32x4 dv4 = *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)(Ls + 128 + r4 * 4);
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
