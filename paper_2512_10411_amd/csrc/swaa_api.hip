@@ -121,6 +121,7 @@ int fwd_setup(const swaa_fwd_args *a, bool allow_split, FwdParams &p, long long 
     p.bt_stride = paged ? a->block_table_stride : 0;
     p.page_size = paged ? a->page_size : 1;
     p.num_pages = paged ? a->num_pages : 1;
+    p.div_page = swaa::make_fastdiv((unsigned)p.page_size);
     p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.Nq = Nq; p.Nk = Nk;
     p.W = a->window < Nk ? a->window : Nk;
     p.S = a->n_sink < Nk ? a->n_sink : Nk;
@@ -144,8 +145,13 @@ int fwd_call(const swaa_fwd_args *a, void *workspace, long long workspace_bytes)
     const int rc = fwd_setup(a, workspace != nullptr, p, need);
     if (rc != SWAA_OK) return rc;
     if (need > 0) {
-        if (misaligned(workspace) || workspace_bytes < need) return SWAA_ERR_WORKSPACE;
-        swaa::place_fwd_split(p, workspace);
+        if (misaligned(workspace) || workspace_bytes < need) {
+            if (!p.few_only) return SWAA_ERR_WORKSPACE;
+            p = FwdParams{};  // (needs no workspace in row tiles)
+            fwd_setup(a, false, p, need);
+        } else {
+            swaa::place_fwd_split(p, workspace);
+        }
     }
     hipStream_t s = static_cast<hipStream_t>(a->stream);
     const hipError_t err = a->D == 128  ? swaa::launch_fwd_pipelined_d128(p, s)

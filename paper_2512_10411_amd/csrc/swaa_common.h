@@ -82,6 +82,7 @@ struct FwdParams {
     int n4, has2, has1;
     int nt_h4, nt_h2, nt_h1;  // row tiles of a sequence of Nq rows for workgroups of 4, 2 and 1 heads
     FastDiv div_tiles_per_pair, div_hkv, div_nt_h4;  // for the work-list decode of every workgroup
+    FastDiv div_page;  // page_size (paged caches)
     int tiles_per_pair;
     long long total_items;
     long long chunk;  // work items per XCD
@@ -94,8 +95,10 @@ struct FwdParams {
     // Split keys (plan_fwd_split, and swaa_fwd_split.h on the device): the tiles of a sequence are cut into
     // several workgroups along the keys, whose partial results a second kernel merges.
     // 0: not split; 1: the split counts are worked out on the device from the sequences'
-    // lengths; >= 2: this many for every sequence (fixed-length batches).
+    // lengths; >= 2: this many for every sequence (fixed-length batches); -1: whole keys, and no merge
+    // (fixed-length batches of few rows, swaa_fwd_few_rows.h).
     int split_keys;
+    int few_only;  // the host expects no splits: the plan is for the sake of few rows, and may be dropped
     long long split_items;  // upper bound on the row tiles (times KV heads) of the batch
     int split_cap;  // partial results the workspace holds
     float *ws_o;    // [split_cap][4 waves][16][64 lanes][4]: unnormalised O in accumulator order

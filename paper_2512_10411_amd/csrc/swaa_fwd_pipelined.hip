@@ -39,6 +39,7 @@
 // all LDS accesses below use plain byte addresses.
 #include <type_traits>
 
+#include "swaa_fwd_few_rows.h"
 #include "swaa_fwd_split.h"
 #include "swaa_tile_d128.h"
 
@@ -257,6 +258,12 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
     }
     SeqGeom sg;
     if (!seq_geom(p, wi.b, sg)) return;
+    if constexpr (kSplit) {
+        if (few_rows(p, sg.nq)) {
+            few_rows_item<kF16, kPaged>(p, wi, si, sg);
+            return;
+        }
+    }
     const int hpb = wi.hpb;
     const int rows_per_wg = kPWgRows / hpb;
     const int wg_r0 = wi.pt * rows_per_wg;  // first query row of the workgroup
@@ -812,8 +819,13 @@ __global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) 
     split_tile(p, (int)wave_read_lane((unsigned)nq, b), r, w);
     SeqGeom sg;
     if (!seq_geom(p, b, sg)) return;
-    const int row = w.pt * (kPWgRows / w.hpb) + ((int)wave / w.hpb) * kPRows + l32;
-    const int head = (int)kvh * p.G + w.h0 + (int)wave % w.hpb;
+    int row = w.pt * (kPWgRows / w.hpb) + ((int)wave / w.hpb) * kPRows + l32;
+    int head = (int)kvh * p.G + w.h0 + (int)wave % w.hpb;
+    if (few_rows(p, sg.nq)) {  // one column tile, in the first wave's place
+        if (wave != 0 || l32 >= p.G * sg.nq) return;
+        row = l32 % sg.nq;
+        head = (int)kvh * p.G + l32 / sg.nq;
+    }
     if (row >= sg.nq) return;
     const unsigned slot0 = slot_b + kvh * n * tiles + r;  // split s: + s * tiles
 
@@ -883,7 +895,7 @@ __global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) 
 }  // namespace
 
 long long plan_fwd_split(FwdParams &p) {
-    p.split_keys = 0;
+    p.split_keys = p.few_only = 0;
     if (p.B > kSplitMaxBatch || p.wg_rows != kPWgRows) return 0;
     const bool packed = p.cu_q != nullptr;
     // Whole prompts on themselves: their tiles are many and short enough as they are.
@@ -916,21 +928,23 @@ long long plan_fwd_split(FwdParams &p) {
         if (!packed && p.P >= p.Nk && whole_batch(p, p.Nq, p.B * p.Hkv * longest.tiles)) return 0;
         const float items = (float)((long long)p.B * p.Hkv * longest.tiles);
         const float memory = longest.tiles <= 2 ? (float)((long long)p.B * p.Hkv * longest.halves) : 0.f;
-        float best = split_time(items, 0.f, (float)longest.halves, items * (float)longest.average, memory);
+        float best = split_time(items, 0.f, longest.start * items, (float)longest.cost + longest.start, items * (float)longest.average, memory);
         for (int c = 2; c <= 64; ++c) {
-            if (longest.halves / c < kSplitMinHalves || items * (float)c > (float)kSplitUnits) break;
-            const float t = split_time(items * (float)c, items * (float)c, (float)((longest.halves + c - 1) / c),
+            if (longest.cost / c < kSplitMinHalves || items * (float)c > (float)kSplitUnits) break;
+            const float t = split_time(items * (float)c, items * (float)c, longest.start * items * (float)c,
+                                       (float)((longest.cost + c - 1) / c) + longest.start,
                                        items * (float)longest.average, memory);
             if (t < best) {
                 best = t;
                 n = c;
             }
         }
-        if (n == 1) return 0;
+        if (n == 1 && !few_rows(p, p.Nq)) return 0;
+        p.few_only = n == 1;
     }
     if (!packed && !p.n_prompts) {
-        p.split_keys = n;
-        p.split_cap = p.B * p.Hkv * p.tiles_per_pair * n;
+        p.split_keys = n > 1 ? n : -1;
+        p.split_cap = n > 1 ? p.B * p.Hkv * p.tiles_per_pair * n : 0;
         p.chunk = (long long)p.B * (((long long)p.Hkv * p.tiles_per_pair * n + kXcds - 1) / kXcds);
     } else {
         // (room for the shortest splits a plan may have, of every row tile the batch can have: one half more than the
@@ -978,7 +992,7 @@ hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream) {
     else
         pick_paged(std::false_type{});
     const hipError_t err = hipGetLastError();
-    if (err != hipSuccess || !p.split_keys) return err;
+    if (err != hipSuccess || p.split_keys <= 0) return err;
     const unsigned merges = (unsigned)(4 * (p.split_items < p.split_cap / 2 ? p.split_items : p.split_cap / 2));
     if (p.fp16)
         hipLaunchKernelGGL(swaa_fwd_merge_kernel<true>, dim3(merges), dim3(256), 0, stream, p);

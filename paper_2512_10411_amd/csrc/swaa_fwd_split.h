@@ -17,18 +17,21 @@
 //   * above 512 units the chip also works through the total, kSplitFull slower than m says, and the
 //     last units run out a share of an average one late;
 //   * sequences of one or two row tiles (generated tokens) read their keys for nobody else: HBM
-//     delivers 300 halves (16 KiB each) in the time of one;
+//     delivers 350 halves (16 KiB each) in the time of one, and 0.3 of the shorter of the two times shows;
+//   * where a sequence's rows fit one column tile (swaa_fwd_few_rows.h) the four waves share the keys: a half
+//     costs kSplitFewRate, a workgroup kSplitFewStart outside its loop;
 //   * a workgroup costs kSplitStart halves outside its loop, and splitting at all the merge kernel
 //     (kSplitMerge) and the traffic of the partial results (64 KiB per unit).
 // The constants are a fit to 70 batches of 1-34 sequences (100-2048 new rows beside 0-31 generated
 // tokens, caches of 2-30k tokens, 8-40 heads) at 4-11 plans each: the plan it picks costs 1.1-1.7 % more than
 // the best of them on average (3.2 % with the first model, which took the longest split for the time
-// below 512 units, did not know HBM's rate and split batches that fill the chip).
+// below 512 units, did not know HBM's rate and split batches that fill the chip).  The terms of few rows, and of
+// HBM beside them, are a fit to 230 batches of 7 or 31 generated tokens beside chunks at 81 plans each: 4 % behind the best.
 // The lengths of a packed batch are known on the device only: there every workgroup works the plan
 // out for itself (batches of at most 64 sequences: one per lane).  Measured, binary16 and pages of
 // 16 tokens, 32 heads on 8: 512 rows on 24k tokens, full attention, 364 -> 207 us (four splits,
 // 196 + 9 us; 128 workgroups before); 23 generated tokens on caches of 1-12k tokens beside a chunk
-// of 999 rows on a 2k window 213 -> 139 us (bound by HBM: 470 MB, 95 us at the rate of a copy).
+// of 999 rows on a 2k window 213 -> 139 us in row tiles, 118 with the few rows of a token in one column tile.
 // Calls that the plan leaves whole on the host (prompts on themselves, short windows, chunks that
 // fill the chip) launch the same kernels as without a workspace: the split kernel takes about 4 us more
 // for the same plan (the plan itself, also in the workgroups that it then has no work for, and a merge without
@@ -49,7 +52,8 @@ constexpr int kSplitMinHalves = 16;  // no split shorter than this many halves
 constexpr int kSplitUnits = 1024;    // most partial results a packed batch may leave (64 KiB each)
 constexpr float kSplitResident = 512.f, kSplitAlone = 256.f, kSplitAloneRate = 0.65f;
 constexpr float kSplitStart = 8.f, kSplitMerge = 8.f, kSplitTraffic = 0.015f, kSplitFull = 1.1f, kSplitTail = 0.5f;
-constexpr float kSplitMemory = 1.f / 300.f;
+constexpr float kSplitMemory = 1.f / 350.f, kSplitOverlap = 0.3f;
+constexpr float kSplitFewRate = 0.65f, kSplitFewStart = 12.f;  // a workgroup of few rows (swaa_fwd_few_rows.h)
 
 // Halves a row tile at positions [a, b] visits (as the kernel's prologue counts them).
 __host__ __device__ inline int tile_halves(int a, int b, int W, int S) {
@@ -60,22 +64,35 @@ __host__ __device__ inline int tile_halves(int a, int b, int W, int S) {
     return (sinks < lo ? sinks : lo) + hi - lo + 1;
 }
 
+// A sequence whose rows fit one column tile of a KV head: a single tile, see swaa_fwd_few_rows.h.
+__host__ __device__ inline bool few_rows(const FwdParams &p, int nq) { return p.G * nq <= 32; }
+
 // What a sequence brings to the plan.
 struct SplitSeq {
     int tiles;    // row tiles per (sequence, KV head)
     int halves;   // visited by the last, longest of them
-    int average;  // by a tile on average
+    int cost;     // what that takes, in halves of a row tile
+    int average;  // the same of a tile on average
+    float start;  // what a workgroup costs outside its loop
     bool whole;   // never split: prompt and generated rows mixed, whose tiles differ too much
 };
 __host__ __device__ inline SplitSeq split_seq(const FwdParams &p, int nq, int nk, int n_prompt) {
-    SplitSeq s{0, 0, 0, true};
+    SplitSeq s{0, 0, 0, 0, kSplitStart, true};
     if (nq <= 0) return s;
-    const int r1 = p.wg_rows, r2 = r1 / 2, r4 = r1 / 4;
+    constexpr int r1 = kFwdWgRows, r2 = r1 / 2, r4 = r1 / 4;  // (the rows of p's plan; known here, so no divisions)
     s.tiles = p.n4 * ((nq + r4 - 1) / r4) + p.has2 * ((nq + r2 - 1) / r2) + p.has1 * ((nq + r1 - 1) / r1);
     const int r = p.n4 ? r4 : p.has2 ? r2 : r1;
     const int first = nk - nq;
     const bool some = n_prompt < nk, all = n_prompt <= first;  // generated rows
-    s.halves = tile_halves(nk - (r < nq ? r : nq), nk - 1, some ? nk : p.W, p.S);
+    if (few_rows(p, nq)) {
+        s.tiles = 1;
+        s.halves = tile_halves(first, nk - 1, some ? nk : p.W, p.S);
+        s.cost = s.average = (int)((float)s.halves * kSplitFewRate) + 1;
+        s.start = kSplitFewStart;
+        s.whole = false;
+        return s;
+    }
+    s.halves = s.cost = tile_halves(nk - (r < nq ? r : nq), nk - 1, some ? nk : p.W, p.S);
     const int h0 = tile_halves(first, first + (r < nq ? r : nq) - 1, all ? nk : p.W, p.S);
     s.average = (h0 + s.halves + 1) / 2;
     s.whole = some && !all;
@@ -89,17 +106,18 @@ __host__ __device__ inline int split_count(int h, int L, float rcp) {
     const int n = (int)((float)(h + L - 1) * rcp);
     return n < 1 ? 1 : n;
 }
-// Predicted time of a plan, in halves.  memory: halves read from HBM by sequences of one or two row
-// tiles, over all KV heads.
-__host__ __device__ inline float split_time(float units, float split_units, float longest, float total, float memory) {
-    const float l = longest + kSplitStart, m = (total + kSplitStart * units) * (1.f / kSplitResident);
+// Predicted time of a plan, in halves.  starts: of all units together; longest: with its own.  memory: halves read
+// from HBM by sequences of one or two row tiles, over all KV heads.
+__host__ __device__ inline float split_time(float units, float split_units, float starts, float longest, float total, float memory) {
+    const float l = longest, m = (total + starts) * (1.f / kSplitResident);
     float t = kSplitAloneRate * l;
     if (units > kSplitAlone) t += (1.f - kSplitAloneRate) * (l < m ? l : m);
     if (units > kSplitResident) {
         const float full = kSplitFull * m + kSplitTail * total / units;
         t = t > full ? t : full;
     }
-    t = t > memory * kSplitMemory ? t : memory * kSplitMemory;
+    const float read = memory * kSplitMemory;
+    t = t > read ? t + kSplitOverlap * read : read + kSplitOverlap * t;
     return split_units > 0.f ? t + kSplitMerge + kSplitTraffic * split_units : t;
 }
 
@@ -152,7 +170,7 @@ __device__ __forceinline__ void split_lengths(const FwdParams &p, int b, int &nq
 
 // Row tile `t` of a (sequence, KV head) pair with nq query rows (the order of decode_work).
 __device__ __forceinline__ void split_tile(const FwdParams &p, int nq, unsigned t, WorkItem &w) {
-    const unsigned r1 = (unsigned)p.wg_rows, r2 = r1 / 2, r4 = r1 / 4;
+    constexpr unsigned r1 = kFwdWgRows, r2 = r1 / 2, r4 = r1 / 4;
     const unsigned nt4 = ((unsigned)nq + r4 - 1) / r4, nt2 = ((unsigned)nq + r2 - 1) / r2, nt1 = ((unsigned)nq + r1 - 1) / r1;
     if (t < (unsigned)p.n4 * nt4) {
         const unsigned g = t / nt4;
@@ -197,7 +215,7 @@ __device__ __forceinline__ float wave_sum(float x) {
 // The work list with split keys: sequence after sequence, every sequence's units cut into eight
 // contiguous chunks, one per die (as in decode_work_packed); inside a sequence by KV head, then
 // split, then row tile, so that the workgroups side by side on a die read the same keys.  scratch:
-// 3 KiB of LDS of a workgroup of four waves, free again after the caller's next barrier.
+// 4 KiB of LDS of a workgroup of four waves, free again after the caller's next barrier.
 __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t scratch, WorkItem &w, SplitItem &si) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned xcd = blockIdx.x % kXcds, rank = blockIdx.x / kXcds;
@@ -206,11 +224,11 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     const SplitSeq me = split_seq(p, nq, nk, np);
     const int items = me.tiles * p.Hkv;
     int n = 1;
-    if (p.split_keys >= 2) {
-        n = p.split_keys;
+    if (p.split_keys != 1) {
+        n = p.split_keys;  // (-1: one)
     } else {
         // the model's terms of candidate `lane`, summed over the sequences: wave w takes every fourth
-        const int splittable = me.whole ? 0 : me.halves;
+        const int splittable = me.whole ? 0 : me.cost;
         int h_max = splittable, rows = nq, least = nq > 0 ? nq : p.Nq;
         float total = (float)items * (float)me.average;
         float memory = me.tiles <= 2 ? (float)(p.Hkv * me.halves) : 0.f;
@@ -219,51 +237,66 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
         memory = wave_sum(memory);
         rows = (int)wave_read_lane(wave_inclusive_scan((unsigned)rows), 63);
         least = 0x7fffffff - (int)wave_max((unsigned)(0x7fffffff - least));
-        const int L = max(kSplitMinHalves, (h_max + lane) / (lane + 1));
+        // (an approximate quotient will do: every workgroup comes to the same, and nobody else needs it)
+        const int L = max(kSplitMinHalves, (int)((float)(h_max + lane) * __builtin_amdgcn_rcpf((float)(lane + 1))));
         const float rcp = 1.f / (float)L;
-        float units = 0.f, split_units = 0.f, longest = 0.f;
+        float units = 0.f, split_units = 0.f, starts = 0.f, longest = 0.f;
         for (int b = wave; b < p.B; b += 4) {
-            const int it = __builtin_amdgcn_readlane(items, b), h = __builtin_amdgcn_readlane(me.halves, b);
+            const int it = __builtin_amdgcn_readlane(items, b), h = __builtin_amdgcn_readlane(me.cost, b);
             const int c = __builtin_amdgcn_readlane(splittable, b) ? split_count(h, L, rcp) : 1;
             const float u = (float)(it * c);
             units += u;
             split_units += c > 1 ? u : 0.f;
-            longest = fmaxf(longest, it ? (float)h / (float)c : 0.f);
+            const float start = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(me.start), b));
+            starts += u * start;
+            longest = fmaxf(longest, it ? (float)h / (float)c + start : 0.f);
         }
         typedef float __attribute__((address_space(3))) *LdsFloats;
-        const LdsFloats mine = (LdsFloats)(uintptr_t)(scratch + (uint32_t)(wave * 768 + lane * 4));
+        const LdsFloats mine = (LdsFloats)(uintptr_t)(scratch + (uint32_t)(wave * 1024 + lane * 4));
         mine[0] = units;
         mine[64] = split_units;
         mine[128] = longest;
+        mine[192] = starts;
         __syncthreads();
-        units = split_units = longest = 0.f;
+        units = split_units = starts = longest = 0.f;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-            const LdsFloats o = (LdsFloats)(uintptr_t)(scratch + (uint32_t)(x * 768 + lane * 4));
+            const LdsFloats o = (LdsFloats)(uintptr_t)(scratch + (uint32_t)(x * 1024 + lane * 4));
             units += o[0];
             split_units += o[64];
             longest = fmaxf(longest, o[128]);
+            starts += o[192];
         }
         __syncthreads();  // (the scratch becomes part of a ring)
-        const float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, longest, total, memory);
+        const float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, starts, longest, total, memory);
         const float best = __uint_as_float(~wave_max(~__float_as_uint(t)));  // (positive floats order like their bits)
         const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
         const int Lb = __builtin_amdgcn_readlane(L, pick);
-        if (splittable > 0 && !whole_batch(p, least, least_units(p, rows))) n = split_count(me.halves, Lb, 1.f / (float)Lb);
+        if (splittable > 0 && !whole_batch(p, least, least_units(p, rows))) n = split_count(me.cost, Lb, 1.f / (float)Lb);
     }
-    if (me.whole || items == 0) n = 1;
+    if (me.whole || items == 0 || n < 1) n = 1;
     if (blockIdx.x == 0) p.ws_n[lane] = n;  // every lane its sequence's, for the merge kernel
     const unsigned mine = (unsigned)items * (unsigned)n;
     const unsigned slots = n > 1 ? mine : 0u;
     const unsigned slots_incl = wave_inclusive_scan(slots);
-    const unsigned incl = wave_inclusive_scan((mine + kXcds - 1) / kXcds);
-    if (rank >= wave_read_lane(incl, 63)) return false;
-    const int b = __popcll(__ballot(incl <= rank));  // sequences that end at or before the rank
+    // Units of row tiles, which compute, and of few rows, which read, take turns while there are both, so that neither is
+    // left alone with the chip -- and the other way round every 32 units of a die, so that the two workgroups of a
+    // compute unit are one of each (20 batches against row tiles: 15.0 % faster, 13.2 % without that, 12.6 % in the order of the batch).
+    const unsigned chunk = (mine + kXcds - 1) / kXcds;
+    const bool few = few_rows(p, nq);
+    const unsigned incl_rows = wave_inclusive_scan(few ? 0u : chunk), incl_few = wave_inclusive_scan(few ? chunk : 0u);
+    const unsigned n_rows = wave_read_lane(incl_rows, 63), n_few = wave_read_lane(incl_few, 63), turns = min(n_rows, n_few);
+    if (rank >= n_rows + n_few) return false;
+    const bool both = rank < 2 * turns;
+    const bool take_few = both ? ((rank ^ (rank >> 5)) & 1u) != 0 : n_few > n_rows;
+    const unsigned at = both ? rank >> 1 : rank - turns;  // among the units of its kind
+    const unsigned incl = take_few ? incl_few : incl_rows;
+    const int b = __popcll(__ballot(incl <= at));  // sequences that end at or before it
     const unsigned base = b ? wave_read_lane(incl, b - 1) : 0u;
     const unsigned u = wave_read_lane(mine, b);
     const unsigned tiles = wave_read_lane((unsigned)me.tiles, b);
     const int nq_b = (int)wave_read_lane((unsigned)nq, b);
-    unsigned r = xcd * ((u + kXcds - 1) / kXcds) + (rank - base);
+    unsigned r = xcd * ((u + kXcds - 1) / kXcds) + (at - base);
     if (r >= u) return false;  // (the sequence's last chunks are shorter)
     si.n = (int)wave_read_lane((unsigned)n, b);
     si.slot = (b ? wave_read_lane(slots_incl, b - 1) : 0u) + r;

@@ -187,3 +187,69 @@ def test_without_memory_for_scratch_the_keys_stay_whole(scratch, monkeypatch):
     monkeypatch.undo()
     ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
     assert_parity(out, lse, ro, rl, tag="no scratch")
+
+
+@pytest.mark.parametrize("Hkv,G,nq,nk,W,S,P,fmt,page", [
+    (2, 4, 8, 3001, 10**9, 4, None, "bf16", 0),       # 32 columns, a full tile
+    (1, 4, 9, 3001, 10**9, 4, None, "bf16", 0),       # one row more: a row tile again
+    (1, 1, 32, 2500, 900, 70, None, "fp16", 16),      # one head, sinks in front of the band
+    (2, 5, 6, 5003, 10**9, 0, None, "fp16", 48),      # 30 columns, pages that are no multiple of a half
+    (1, 8, 1, 1040, 10**9, 4, None, "bf16", 16),      # 33 halves, the last of 16 keys: ends inside a page pair
+    (1, 8, 4, 1025, 10**9, 4, None, "bf16", 64),      # ... of one key
+    (1, 32, 1, 4000, 1500, 1000, None, "bf16", 0),    # 32 heads on one
+    (2, 4, 5, 4000, 1100, 40, 3998, "bf16", 32),      # prompt and generated rows in one tile
+    (1, 4, 3, 40000, 10**9, 4, None, "fp16", 16),     # many splits
+])
+def test_few_rows_share_one_column_tile(scratch, Hkv, G, nq, nk, W, S, P, fmt, page):
+    # beside a sequence of more rows, so that the batch is planned on the device
+    print(f"[case] few rows Hkv{Hkv} G{G} nq{nq} nk{nk} W{W} S{S} P{P} {fmt} page {page}", flush=True)
+    lens, rows = [nk, 700, 2000], [nq, 1, 70]
+    host = [make_qkv(1, Hkv * G, Hkv, n, 128, 97000 + n + m, n_query=m, fmt=fmt) for m, n in zip(rows, lens)]
+    dt = torch.float16 if fmt == "fp16" else torch.bfloat16
+    q = torch.cat([to_device(h[0], fmt)[0] for h in host], dim=1).contiguous()
+    offs = lambda x: torch.tensor(np.concatenate([[0], np.cumsum(x)]), dtype=torch.int32, device="cuda")
+    prompts = [n if P is None else min(n, P) for n in lens]
+    args = dict(cu_seqlens_q=offs(rows), cu_seqlens_k=offs(lens), max_seqlen_q=max(rows), max_seqlen_k=max(lens),
+                n_prompts=torch.tensor(prompts, dtype=torch.int32, device="cuda"))
+    dev = [(to_device(h[1], fmt)[0], to_device(h[2], fmt)[0]) for h in host]
+    if page:
+        pages = [(n + page - 1) // page for n in lens]
+        order = np.random.Generator(np.random.Philox(98)).permutation(sum(pages))
+        kk, vv = (torch.full((sum(pages), Hkv, page, 128), float("nan"), dtype=dt, device="cuda") for _ in range(2))
+        table, at = np.full((3, max(pages)), 10**9, np.int32), 0
+        for b, n in enumerate(lens):
+            table[b, :pages[b]] = order[at:at + pages[b]]
+            at += pages[b]
+            for j in range(pages[b]):
+                part = slice(j * page, min(n, (j + 1) * page))
+                kk[table[b, j], :, :part.stop - part.start] = dev[b][0][:, part]
+                vv[table[b, j], :, :part.stop - part.start] = dev[b][1][:, part]
+        args["block_table"] = torch.from_numpy(table).cuda()
+    else:
+        kk, vv = (torch.cat([d[i] for d in dev], dim=1).contiguous() for i in range(2))
+    out, lse = binding.swaa_attn_fwd_ex(q, kk, vv, W, S, **args)
+    torch.cuda.synchronize()
+    assert scratch[0] > 0
+    r0 = 0
+    with input_format(fmt):
+        for b, h in enumerate(host):
+            ro, rl = swaa_decode_oracle(h[0], h[1], h[2], W, S, 1 / math.sqrt(128), n_prompt=prompts[b])
+            assert_parity(out[None, :, r0:r0 + rows[b]], lse[None, :, r0:r0 + rows[b]], ro, rl,
+                          tag=f"few rows, seq {b}: {rows[b]} rows on {lens[b]} keys")
+            r0 += rows[b]
+
+
+@pytest.mark.parametrize("B,Hkv,Nq,Nk", [(40, 8, 1, 1500), (40, 8, 8, 1500)])
+def test_few_rows_of_sequences_of_one_length(scratch, B, Hkv, Nq, Nk):
+    # enough of them that no keys are split: 256 bytes of scratch, no merge; without even those the row tiles run
+    q, k, v = make_qkv(B, Hkv * 4, Hkv, Nk, 128, seed=9680 + Nq, n_query=Nq)
+    qd, kd, vd = to_device(q), to_device(k), to_device(v)
+    print(f"[case] {B} x {Nq} rows on {Nk} keys", flush=True)
+    out, lse = (t.clone() for t in binding.swaa_attn_fwd_ex(qd, kd, vd, 10**9, 4))
+    assert scratch == [256]
+    small = torch.empty(128, dtype=torch.uint8, device="cuda")
+    out2, lse2 = binding.swaa_attn_fwd_ex(qd, kd, vd, 10**9, 4, workspace=small)
+    torch.cuda.synchronize()
+    ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
+    assert_parity(out, lse, ro, rl, tag="few rows of one length")
+    assert_parity(out2, lse2, ro, rl, tag="few rows of one length, no scratch")
