@@ -186,3 +186,44 @@ def test_lds_dma_kernels_own_all_lds(tmp_path, src, kernels):
                 # and no spills (their reloads would wait for the copies, inside the loop)
                 assert int(spill) == 0, (name, spill)
     assert seen == set(kernels)
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
+                    reason="hipcc not available")
+def test_dkv_kernel_of_head_dimension_128_keeps_the_wait_states_and_its_accumulators(tmp_path):
+    """swaa_bwd_dkv_dma_kernel names its 256 accumulator registers in the instructions: nothing else may live
+    there (not even for a moment), and the two rules above hold for its MFMAs."""
+    out = tmp_path / "b.s"
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    cmd = [build.hipcc_path(), *flags, "--cuda-device-only", "-S", "-o", str(out), os.path.join(build.CSRC, "swaa_bwd.hip")]
+    subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    lines = open(out).read().splitlines()
+    first = next(i for i, ln in enumerate(lines) if re.match(r"_Z\S*dkv_dma_kernel\S*:", ln))
+    insts, labels, written_out = [], {}, []  # written_out: does the instruction come from inline assembly?
+    inside = False
+    for ln in lines[first:next(i for i in range(first, len(lines)) if lines[i].startswith(".Lfunc_end"))]:
+        inside = (inside or "#ASMSTART" in ln) and "#ASMEND" not in ln
+        m = re.match(r"^(\.LBB\d+_\d+):", ln)
+        if m:
+            labels[m.group(1)] = len(insts)
+        p = parse(ln)
+        if p:
+            insts.append(p)
+            written_out.append(inside)
+    mfmas = [i for i, (op, _) in enumerate(insts) if op.startswith("v_mfma")]
+    assert len(mfmas) >= 140  # a prologue of 16 and two versions of a step
+    for i, (op, ops) in enumerate(insts):
+        if written_out[i]:
+            continue
+        assert not any(r[0] == "a" for t in ops for r in reg_set(t)), insts[i]
+        assert not op.startswith("scratch_"), insts[i]
+    for i in mfmas:
+        srcs = set().union(*[reg_set(t) for t in insts[i][1][1:]])
+        wait_states = 0
+        for pop, pops in reversed(insts[max(0, i - 3):i]):
+            if wait_states >= 2:
+                break
+            assert not (is_valu_write(pop) and pops and reg_set(pops[0]) & srcs), ((pop, pops), insts[i])
+            wait_states += int(pops[0]) + 1 if pop == "s_nop" else 1
+    late = result_hazards(insts, labels)
+    assert not late, late[:5]

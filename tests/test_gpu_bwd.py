@@ -128,6 +128,38 @@ def test_row_blocks_of_head_dimension_64(N, W, S, P, G):
     check(1, 2 * G, 2, N, 64, W, S, P, seed=9600 + N)
 
 
+@pytest.mark.parametrize("N,W,S,P,G", [
+    (33, 33, 0, None, 1),      # one tile, its second row half one row long
+    (193, 31, 0, None, 2),     # a window inside a 32-key unit, a key tile of 65 keys
+    (259, 97, 0, None, 3),     # three tiles of query rows in a band, the last key tile has three keys
+    (1029, 64, 33, None, 1),   # sinks that end inside the second unit: segments, one of them short
+    (1029, 160, 130, 901, 4),  # two sink key tiles, generated rows that start inside a tile
+    (545, 545, 0, 511, 5),     # no window; the row before a tile is generated
+])
+def test_units_and_tiles_of_head_dimension_128(N, W, S, P, G):
+    check(1, 2 * G, 2, N, 128, W, S, P, seed=9800 + N)
+
+
+def test_an_upstream_row_without_a_number_stays_in_its_blocks():
+    # head dimension 128: 32 rows x 32 keys are computed together, so NaN in one row of dO may reach the keys of
+    # those blocks in which some row of its 32 sees some key, and no others
+    N, W, row = 700, 90, 333
+    q, k, v = make_qkv(1, 4, 1, N, 128, seed=9710)
+    qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(make_dout(q.shape, 9711))
+    out, lse = binding.swaa_attn_fwd(qd, kd, vd, W, 4)
+    want = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
+    dd[:, :, row] = float("nan")
+    got = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
+    torch.cuda.synchronize()
+    first = row // 32 * 32
+    reached = torch.zeros(N, dtype=torch.bool, device="cuda")
+    reached[:32], reached[(first - W + 1) // 32 * 32:first + 32] = True, True
+    rows = torch.arange(N, device="cuda") != row
+    assert torch.equal(got[0][:, :, rows], want[0][:, :, rows])
+    for x, y in zip(got[1:], want[1:]):  # dK, dV
+        assert torch.equal(x[:, :, ~reached], y[:, :, ~reached])
+
+
 @pytest.mark.parametrize("D", [64, 128])
 def test_a_row_without_a_number_reaches_only_the_keys_it_sees(D):
     # NaN in one row's log-sum-exp: P = 0 where the row does not see the key, whatever the row holds
