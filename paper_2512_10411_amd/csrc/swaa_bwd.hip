@@ -9,11 +9,10 @@
 //   dS_ij = P_ij (dP_ij - delta_i)
 //   dQ_i = scale sum_j dS_ij k_j               dK_j = scale sum_i dS_ij q_i
 //
-// Four kernels, no atomics, results independent of scheduling:
-//   * swaa_bwd_delta_kernel: delta, one pass over dO and O.
+// Three kernels, no atomics, results independent of scheduling:
 //   * swaa_bwd_dq_kernel: a workgroup owns 256 query rows (the forward's work
 //     decomposition and tile schedule), walks its visible KV tiles, recomputes
-//     S^T = K Q^T and dP^T = V dO^T and accumulates dQ^T += K^T dS^T.
+//     S^T = K Q^T and dP^T = V dO^T and accumulates dQ^T += K^T dS^T.  It forms delta on the way.
 //   * swaa_bwd_dkv_kernel: a workgroup owns 128 keys of one KV head, walks
 //     every query head of the GQA group and every 64-row query tile (32-row
 //     block) that can see them, recomputes S = Q K^T and dP = dO V^T and accumulates
@@ -77,25 +76,6 @@ __device__ __forceinline__ bool visible_in_range(int i, int j, int N, int W, int
     return (i < N) & (j <= i) & ((i >= P) | (j > i - W) | (j < S));
 }
 
-// ---- delta_i = <dO_i, O_i> ---------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(kThreads) void swaa_bwd_delta_kernel(const BwdParams p) {
-    constexpr int L = D / 8;  // lanes per row
-    const long long rows = (long long)p.B * p.Hq * p.N;
-    const long long row = (long long)blockIdx.x * (kThreads / L) + threadIdx.x / L;
-    const int c = threadIdx.x % L;
-    float acc = 0.f;
-    if (row < rows) {
-        const bf16x8 a = *reinterpret_cast<const bf16x8 *>(p.dout + row * D + 8 * c);
-        const bf16x8 b = *reinterpret_cast<const bf16x8 *>(p.out + row * D + 8 * c);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc += (float)a[e] * (float)b[e];
-    }
-#pragma unroll
-    for (int w = L / 2; w > 0; w >>= 1) acc += __shfl_xor(acc, w, L);
-    if (row < rows && c == 0) p.delta[row] = acc;
-}
-
 // ---- dQ, head dimension 64 -------------------------------------------------------------
 // A workgroup is eight waves of 32 query rows; 128 registers per wave, so that two workgroups share
 // a compute unit and one wave's exponentials run under the others' matrix instructions.  (With a
@@ -152,7 +132,8 @@ __global__ __launch_bounds__(512, 4) void swaa_bwd_dq_kernel(const BwdParams p) 
             dof[ks] = *reinterpret_cast<const bf16x8 *>(ds + 16 * ks);
         }
         lse2 = p.f.lse[r_base + row] * 1.44269504088896340736f;
-        dl = p.delta[r_base + row];
+        dl = row_delta<KS>(p.out + q_base + (size_t)row * D + 8 * hf, dof);
+        if (qpos < N && hf == 0) p.delta[r_base + row] = dl;  // for the dK/dV kernel
     }
 
     f32x16 dqacc[DB];
@@ -644,16 +625,10 @@ __global__ __launch_bounds__(kThreads) void swaa_bwd_sink_sum_kernel(const BwdPa
 
 template <int D>
 hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
-    const long long rows = (long long)p.B * p.Hq * p.N;
-    const int rows_per_block = kThreads / (D / 8);
-    hipLaunchKernelGGL(swaa_bwd_delta_kernel<D>, dim3((unsigned)((rows + rows_per_block - 1) / rows_per_block)),
-                       dim3(kThreads), 0, stream, p);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
     // more than 64 KiB of LDS per workgroup has to be requested once per device
     static std::atomic<unsigned long long> configured{0};
     int dev = 0;
-    err = hipGetDevice(&dev);
+    hipError_t err = hipGetDevice(&dev);
     if (err != hipSuccess) return err;
     const unsigned long long bit = 1ull << (dev & 63);
     const bool first_time = !(configured.load(std::memory_order_acquire) & bit);

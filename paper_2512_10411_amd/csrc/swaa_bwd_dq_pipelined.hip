@@ -220,7 +220,7 @@ __global__ __launch_bounds__(kQThreads, 2) void swaa_bwd_dq_pipelined_kernel(con
     issue_tile(2, 2);
 
     // ---- this wave's Q and dO rows (B operands of stage A), parked in AccVGPRs; its rows'
-    // lse (log2 units) and delta ----
+    // lse (log2 units) and delta (formed here: see row_delta) ----
     bf16x8 qf[kKS], dof[kKS];
     float lse2, dl;
     {
@@ -233,7 +233,8 @@ __global__ __launch_bounds__(kQThreads, 2) void swaa_bwd_dq_pipelined_kernel(con
             dof[ks] = *reinterpret_cast<const bf16x8 *>(ds + 16 * ks);
         }
         lse2 = p.f.lse[r_base + row] * 1.44269504088896340736f;
-        dl = p.delta[r_base + row];
+        dl = row_delta<kKS>(p.out + q_base + (size_t)row * kD + 8 * hf, dof);
+        if (p0 + l32 < N && hf == 0) p.delta[r_base + row] = dl;  // for the dK/dV kernel
     }
     // the idle cycles keep the copies two wait states away from the first MFMA that reads them
     asm volatile("s_nop 1"
