@@ -48,7 +48,7 @@ MEASURED_TRAFFIC_BYTES = {
     "decode128k_swa": (3.491e7, "profiles/swaa_decode_decode128k_swa.txt"),
     "decode_skewed_b16": (6.050e8, "profiles/swaa_decode_decode_skewed_b16.txt"),
     "decode_mixed_b32": (1.075e9, "profiles/swaa_decode_decode_mixed_b32.txt"),
-    "mid_bwd": (1.63e9, "profiles/swaa_bwd_mid_bwd.txt"),
+    "mid_bwd": (1.54e9, "profiles/swaa_bwd_mid_bwd.txt"),
 }
 MIN_WARMUP_S = 0.05  # the clocks settle only after some tens of ms of continuous work
 
