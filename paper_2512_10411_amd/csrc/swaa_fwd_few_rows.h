@@ -25,6 +25,7 @@ namespace swaa {
 template <bool kF16, bool kPaged>
 __device__ __forceinline__ void few_rows_item(const FwdParams &p, const WorkItem &wi, const SplitItem &si, const SeqGeom &sg) {
     constexpr uint32_t kRing = 2 * kHalfBytes;  // a wave's: K half, then V half
+    constexpr int kBelow = kF16 ? 4 : 0;  // as the row tiles' reference: terms keep full precision down to 2^-18 of it
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int l32 = lane & 31, hf = lane >> 5;
     const int Nk = sg.nk, S = p.S, nq = sg.nq, cols = p.G * nq;
@@ -171,9 +172,9 @@ __device__ __forceinline__ void few_rows_item(const FwdParams &p, const WorkItem
         for (int ks = 1; ks < kKS - 1; ++ks) mfma_s<kF16>(s, kf[ks], qf[ks]);
         mfma_s_settled<kF16>(s, kf[kKS - 1], qf[kKS - 1]);
         if (masked)
-            softmax_half<true, kF16>(s, k0h, qpos, W, S, hf, c2, rs, pf, alpha);
+            softmax_half<true, kF16, kBelow>(s, k0h, qpos, W, S, hf, c2, rs, pf, alpha);
         else
-            softmax_half<false, kF16>(s, k0h, qpos, W, S, hf, c2, rs, pf, alpha);
+            softmax_half<false, kF16, kBelow>(s, k0h, qpos, W, S, hf, c2, rs, pf, alpha);
         rescale(oacc, alpha);
 #pragma unroll
         for (int st = 0; st < 2; ++st)

@@ -216,8 +216,10 @@ __device__ __forceinline__ void row_sums(const RowState &st, float &l, float &lb
 // half whose row sums outgrow the reference): optional mask, reference update
 // with slack, exponentials, row sum, bf16 P^T fragments.  alpha is the factor
 // the O accumulator must be multiplied with (1 when the reference stays).  The
-// scores must be settled (qk_half leaves them so).
-template <bool kMask, bool kF16 = false>
+// scores must be settled (qk_half leaves them so).  kBelow: the reference is set so many log2 units below the
+// largest score, for binary16, whose P lose precision below 2^-14 and vanish below 2^-25 (and end at 65504: they come
+// up to 2^(kBelow + kRefSlack)).
+template <bool kMask, bool kF16 = false, int kBelow = 0>
 __device__ __forceinline__ void softmax_half(f32x16 &s, int k0h, int qpos, int W, int S, int hf, float c2, RowState &st,
                                              bf16x8 (&pf)[2], float &alpha) {
     if (kMask) {
@@ -233,7 +235,7 @@ __device__ __forceinline__ void softmax_half(f32x16 &s, int k0h, int qpos, int W
     for (int e = 1; e < 16; ++e) mx = fmaxf(mx, s[e]);
     mx = half_swap_max(mx);
     const float mc_old = st.mc;
-    const float m_new = fmaxf(mc_old, mx * c2);
+    const float m_new = fmaxf(mc_old, mx * c2 - (float)kBelow);
     const bool move = m_new > mc_old + kRefSlack;  // -inf never moves to -inf
     st.mc = move ? m_new : mc_old;
     const float mc_use = (kMask && st.mc == -INFINITY) ? 0.f : st.mc;

@@ -253,3 +253,27 @@ def test_few_rows_of_sequences_of_one_length(scratch, B, Hkv, Nq, Nk):
     ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
     assert_parity(out, lse, ro, rl, tag="few rows of one length")
     assert_parity(out2, lse2, ro, rl, tag="few rows of one length, no scratch")
+
+
+@pytest.mark.parametrize("nats", [10.0, 13.0, 14.284, 16.0])
+@pytest.mark.parametrize("nk", [1100, 5000])  # whole keys (one split), and split
+def test_few_rows_in_binary16_keep_the_terms_below_a_sink(scratch, nk, nats):
+    # One key `nats` above all the others, and the others alone have values: P of those is p = 2^4 e^-nats beside the
+    # reference (2^4 below the largest score), and rounds to a multiple of 2^-24 below 2^-14: off by at most 2^-25 / p
+    # of itself there, by 2^-11 above.  2^-11 more for the result's own rounding (values of 32 keep it out of the
+    # subnormals), and 2^-11 for the sums of 32-bit terms and the other splits' and waves' weights.
+    bits = lambda x: np.array([x], dtype=np.float16).view(np.uint16)[0]
+    q, k, v = (np.zeros((1, h, n, 128), dtype=np.uint16) for h, n in ((4, 2), (1, nk), (1, nk)))
+    q[..., 0], k[:, :, 0, 0] = bits(1.0), bits(1.0)
+    v[:, :, 1:128] = bits(32.0)  # (the keys of the sink's own wave)
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q, "fp16"), to_device(k, "fp16"), to_device(v, "fp16"), 10**9, 4, scale=nats)
+    torch.cuda.synchronize()
+    assert scratch[0] > 0
+    with input_format("fp16"):
+        ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, nats)
+    p = 16 * math.exp(-nats)
+    bound = max(2.0**-25 / p, 2.0**-11) + 2.0**-10
+    rel = np.abs(out.float().cpu().numpy() / ro - 1).max()
+    print(f"[few rows, sink] {nk} keys, {nats} nats: {rel:.2e} of at most {bound:.2e}", flush=True)
+    assert rel <= bound
+    assert np.abs(lse.cpu().numpy() - rl).max() <= 1e-3
