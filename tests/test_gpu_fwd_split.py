@@ -277,3 +277,56 @@ def test_few_rows_in_binary16_keep_the_terms_below_a_sink(scratch, nk, nats):
     print(f"[few rows, sink] {nk} keys, {nats} nats: {rel:.2e} of at most {bound:.2e}", flush=True)
     assert rel <= bound
     assert np.abs(lse.cpu().numpy() - rl).max() <= 1e-3
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+@pytest.mark.parametrize("nk,at", [(1100, 40), (1100, 300), (1100, 600), (1100, 1060), (5000, 40), (5000, 300), (5000, 2600), (5000, 4990)])
+def test_few_rows_with_references_far_apart(scratch, nk, at, fmt):
+    # One key 40 nats above the rest, in each of the four waves' quarters of whole keys, in some split and in the last:
+    # the others' results have to vanish beside that wave's.
+    q, k, v = make_qkv(1, 8, 2, nk, 128, seed=9700 + at, n_query=2, fmt=fmt)
+    bits = lambda x: np.array([x], dtype=np.float16).view(np.uint16)[0] if fmt == "fp16" else np.array([x], dtype=np.float32).view(np.uint32)[0] >> 16
+    q[..., 0], k[..., 0] = bits(3.0), bits(0.0)
+    k[:, :, at, 0] = bits(152.0)
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), 10**9, 4)
+    torch.cuda.synchronize()
+    assert scratch[0] > 0
+    with input_format(fmt):
+        ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
+    assert_parity(out, lse, ro, rl, tag=f"few rows, {nk} keys, spike at {at} {fmt}")
+
+
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+@pytest.mark.parametrize("what", ["nan", "inf"])
+@pytest.mark.parametrize("nk", [1100, 5000])
+def test_few_rows_and_what_is_not_a_number(scratch, nk, what, fmt):
+    bits = {("nan", "bf16"): 0x7FC0, ("inf", "bf16"): 0x7F80, ("nan", "fp16"): 0x7E00, ("inf", "fp16"): 0x7C00}[what, fmt]
+    q, k, v = make_qkv(1, 8, 2, nk, 128, seed=9710, n_query=3, fmt=fmt)
+    q[..., 5] = {"bf16": 0x3F80, "fp16": 0x3C00}[fmt]  # 1: the score of an infinite component is +infinity
+    run = lambda q, k: tuple(t.clone() for t in binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), 10**9, 4))
+    want, want_l = run(q, k)
+    # a query row that is not a number: it alone, its neighbours in the column tile bit for bit as without it
+    bad = q.copy()
+    bad[:, 6, 1, 5] = np.uint16(bits)
+    out, lse = run(bad, k)
+    torch.cuda.synchronize()
+    assert scratch[0] > 0
+    assert not torch.isfinite(out[0, 6, 1].float()).any() and not torch.isfinite(lse[0, 6, 1])
+    out[0, 6, 1], lse[0, 6, 1] = want[0, 6, 1], want_l[0, 6, 1]
+    assert torch.equal(out, want) and torch.equal(lse, want_l)
+    # a key, in every wave's quarter and in other splits: all rows of its head, and the other head's as before
+    for at in [40, 300, 560, 840, 1060, 2600, 4900]:
+        if at < nk:
+            bad = k.copy()
+            bad[:, 1, at, 5] = np.uint16(bits)
+            out, lse = run(q, bad)
+            torch.cuda.synchronize()
+            assert not torch.isfinite(out[0, 4:].float()).any() and not torch.isfinite(lse[0, 4:]).any(), at
+            assert torch.equal(out[0, :4], want[0, :4]) and torch.equal(lse[0, :4], want_l[0, :4]), at
+    # the newest key: only the row that sees it
+    bad = k.copy()
+    bad[:, 1, nk - 1, 5] = np.uint16(bits)
+    out, lse = run(q, bad)
+    torch.cuda.synchronize()
+    assert not torch.isfinite(out[0, 4:, 2].float()).any() and not torch.isfinite(lse[0, 4:, 2]).any()
+    assert torch.equal(out[0, :, :2], want[0, :, :2]) and torch.equal(lse[0, :, :2], want_l[0, :, :2])
