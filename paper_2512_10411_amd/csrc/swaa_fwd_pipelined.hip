@@ -907,15 +907,17 @@ long long plan_fwd_split(FwdParams &p) {
     if (longest.halves <= 2 * kSplitMinHalves) return 0;
     // (Whether keys are split depends on Nq, Nk, B and the heads only, not on total_rows_q: the
     // result's bits are the same whichever work list the caller's arguments select.)
-    const long long most = (long long)p.B * p.Hkv * p.tiles_per_pair;
+    // (few rows are one tile per KV head however many heads share it; no sequence has more tiles than one of Nq rows)
+    const long long most = (long long)p.B * p.Hkv * longest.tiles;
     // A few chunks that fill the chip twice over are balanced by their number; in a larger batch
     // single generated tokens on long caches may stand beside them.
     if (p.B <= 4 && most > 2 * (long long)kSplitResident) return 0;
     // (every sequence adds at most one partly filled tile per head group to those that its rows fill)
     auto tiles_of_all = [&](int tile_rows) { return (p.total_rows + tile_rows - 1) / tile_rows + p.B; };
-    const long long bound = !p.packed_compact ? most
-                                              : p.Hkv * (p.n4 * tiles_of_all(p.wg_rows / 4) + p.has2 * tiles_of_all(p.wg_rows / 2) +
-                                                         p.has1 * tiles_of_all(p.wg_rows));
+    const long long bound = !p.packed_compact || few_rows(p, p.Nq)
+                                ? most
+                                : p.Hkv * (p.n4 * tiles_of_all(p.wg_rows / 4) + p.has2 * tiles_of_all(p.wg_rows / 2) +
+                                           p.has1 * tiles_of_all(p.wg_rows));
     // No sequence has fewer rows than are left when the others have Nq each.
     if (packed && p.packed_compact) {
         const long long least = p.total_rows - (long long)(p.B - 1) * p.Nq;
@@ -944,8 +946,8 @@ long long plan_fwd_split(FwdParams &p) {
     }
     if (!packed && !p.n_prompts) {
         p.split_keys = n > 1 ? n : -1;
-        p.split_cap = n > 1 ? p.B * p.Hkv * p.tiles_per_pair * n : 0;
-        p.chunk = (long long)p.B * (((long long)p.Hkv * p.tiles_per_pair * n + kXcds - 1) / kXcds);
+        p.split_cap = n > 1 ? p.B * p.Hkv * longest.tiles * n : 0;
+        p.chunk = (long long)p.B * (((long long)p.Hkv * longest.tiles * n + kXcds - 1) / kXcds);
     } else {
         // (room for the shortest splits a plan may have, of every row tile the batch can have: one half more than the
         // longest sequence visits, for a band that straddles one more, and one split more for split_count's rounding)

@@ -282,6 +282,15 @@ def test_the_forwards_workspace_is_no_larger_than_its_plan_can_fill(B, Nq, Nk, t
     assert 0 < need <= most * SPLIT_UNIT + 64 * 4
 
 
+@pytest.mark.parametrize("packed", [False, True])
+@pytest.mark.parametrize("B,Hkv,G,Nq", [(16, 8, 5, 1), (16, 8, 7, 1), (2, 8, 32, 1), (32, 8, 31, 1), (4, 8, 10, 3), (40, 1, 32, 1)])
+def test_the_workspace_of_few_rows_does_not_grow_with_the_heads_of_a_group(B, Hkv, G, Nq, packed):
+    # G Nq <= 32 rows of a KV head are one tile: as many partial results as with one head, 1024 at most (and below 72 MiB)
+    need, one = (binding.swaa_attn_fwd_ex_workspace_bytes(_chunk_args(B, Nq, 131072, packed=packed, Hq=g * Hkv, Hkv=Hkv)) for g in (G, 1))
+    assert 0 < need <= 1024 * SPLIT_UNIT + 64 * 4 < 72 << 20
+    assert need == one
+
+
 def test_the_forwards_workspace_argument():
     lib = binding.load_library()
     call = lambda a, ws, n: lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), ws, n)

@@ -255,6 +255,17 @@ def test_few_rows_of_sequences_of_one_length(scratch, B, Hkv, Nq, Nk):
     assert_parity(out2, lse2, ro, rl, tag="few rows of one length, no scratch")
 
 
+@pytest.mark.parametrize("B,Hkv,G,Nq,Nk", [(1, 2, 5, 6, 3001), (2, 1, 7, 4, 2600), (3, 2, 32, 1, 5000), (1, 1, 31, 1, 40000)])
+def test_few_rows_of_large_groups_and_one_length(scratch, B, Hkv, G, Nq, Nk):
+    # groups whose row tiles would be two to eight: the workspace, the grid and the merge are those of one tile
+    q, k, v = make_qkv(B, Hkv * G, Hkv, Nk, 128, seed=9690 + G, n_query=Nq)
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q), to_device(k), to_device(v), 10**9, 4)
+    torch.cuda.synchronize()
+    assert scratch[0] > 256
+    ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
+    assert_parity(out, lse, ro, rl, tag=f"few rows, {B} x {Hkv} x {G}, {Nq} on {Nk}")
+
+
 @pytest.mark.parametrize("nats", [10.0, 13.0, 14.284, 16.0])
 @pytest.mark.parametrize("nk", [1100, 5000])  # whole keys (one split), and split
 def test_few_rows_in_binary16_keep_the_terms_below_a_sink(scratch, nk, nats):
