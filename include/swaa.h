@@ -185,20 +185,27 @@ int swaa_attn_fwd_ex(const swaa_fwd_args *args);
  * prompt, single generated tokens in a packed batch (paper App. D) -- are too few workgroups
  * for the chip; with a workspace the keys of such rows are split over several workgroups
  * and a second kernel merges their partial results.  Which calls gain is decided from the
- * sizes in args (and, for packed batches, from the sequences' lengths on the device).
+ * sizes in args (and, for packed batches, from the sequences' lengths on the device).  Sequences
+ * of few rows -- Hq / Hkv * rows <= 32, generated tokens -- run on a tile of their own kind with a
+ * workspace, whether their keys are split or not.
  *
  *   workspace        device scratch memory owned by the caller, 16-byte aligned, of at least
  *                    swaa_attn_fwd_ex_workspace_bytes(args) bytes; contents before and after
  *                    the call are meaningless, and calls that may overlap on the device need
  *                    separate workspaces.  NULL: the call is swaa_attn_fwd_ex.
  *
- * Returns SWAA_OK or a negative swaa_status (SWAA_ERR_WORKSPACE: misaligned or too small).
+ * Returns SWAA_OK or a negative swaa_status (SWAA_ERR_WORKSPACE: misaligned or too small).  Batches of
+ * few rows (Hq / Hkv * Nq <= 32) and one length, and packed batches of one such sequence, whose
+ * keys the sizes in args leave whole do without: a workspace that is misaligned or too small is
+ * no error there, and the call is swaa_attn_fwd_ex.
  */
 int swaa_attn_fwd_ex_ws(const swaa_fwd_args *args, void *workspace, long long workspace_bytes);
 
 /*
- * Bytes of workspace swaa_attn_fwd_ex_ws needs for this argument block (0 if its keys are not
- * split; below 72 MiB), or a negative swaa_status if the arguments are invalid.  Host-only
+ * Bytes of workspace swaa_attn_fwd_ex_ws has use for with this argument block (below 72 MiB), or a
+ * negative swaa_status if the arguments are invalid.  0 if its keys are not split -- save for
+ * batches of few rows and one length, which ask for 256 bytes then (see above), and a packed
+ * batch of one such sequence, which asks for what the plan on the device may use.  Host-only
  * arithmetic: no device memory is read, and the tensors' contents do not matter.
  */
 long long swaa_attn_fwd_ex_workspace_bytes(const swaa_fwd_args *args);

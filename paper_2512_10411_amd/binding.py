@@ -378,8 +378,8 @@ def swaa_attn_fwd_ex_raw(args: SwaaFwdArgs) -> int:
 
 
 def swaa_attn_fwd_ex_workspace_bytes(args: SwaaFwdArgs) -> int:
-    """Bytes of workspace with which swaa_attn_fwd_ex splits this call's keys over workgroups (0: it
-    does not); raises SwaaError on invalid arguments."""
+    """Bytes of workspace with which swaa_attn_fwd_ex splits this call's keys over workgroups, or runs
+    its few rows on a tile of their own kind (0: neither); raises SwaaError on invalid arguments."""
     r = int(load_library().swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(args)))
     if r < 0:
         raise SwaaError(r, swaa_status_string(r))
@@ -403,8 +403,9 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
     rows of the packed q tensor, taken from q by default; 0 makes the launch as large as B times the
     longest sequence (slow for sequences of very different lengths).  n_prompts: int32 [B] GPU tensor of
     per-sequence prompt lengths, used in place of n_prompt.  workspace: a uint8 tensor of at least
-    swaa_attn_fwd_ex_workspace_bytes(...) bytes for calls whose keys are split over workgroups (allocated
-    here with torch when None and the call needs one; where there is no memory for it the keys stay whole).  bfloat16 or float16 tensors (all of
+    swaa_attn_fwd_ex_workspace_bytes(...) bytes for calls whose keys are split over workgroups or whose
+    rows are few (allocated here with torch when None and the call has use for one; where there is no memory for it the
+    keys stay whole).  bfloat16 or float16 tensors (all of
     one type).  out defaults to a new tensor with q's shape in q's memory order;
     lse is fp32 [B, Hq, Nq] ([Hq, Tq] when packed).  Returns (out, lse).
     """

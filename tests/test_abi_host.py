@@ -291,6 +291,15 @@ def test_the_workspace_of_few_rows_does_not_grow_with_the_heads_of_a_group(B, Hk
     assert need == one
 
 
+def test_few_rows_whose_keys_stay_whole_ask_for_little():
+    # batches of one length: the 256 bytes that select their kernel; of more rows: nothing
+    bytes_of = lambda B, Nq, Nk, **kw: binding.swaa_attn_fwd_ex_workspace_bytes(_chunk_args(B, Nq, Nk, **kw))
+    assert [bytes_of(B, Nq, Nk, packed=False, Hkv=h, Hq=4 * h) for B, Nq, Nk, h in ((40, 1, 1500, 8), (1, 2, 1100, 2), (40, 8, 1500, 8))] == [256] * 3
+    assert bytes_of(1, 9, 1100, packed=False, Hkv=8, Hq=32) > 256 and bytes_of(40, 9, 1500, packed=False, Hkv=8, Hq=32) == 0
+    # a packed batch of one: its length on the device may be shorter than stated, and its plan another
+    assert 256 < bytes_of(1, 1, 1100) <= 64 * SPLIT_UNIT + 256
+
+
 def test_the_forwards_workspace_argument():
     lib = binding.load_library()
     call = lambda a, ws, n: lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), ws, n)

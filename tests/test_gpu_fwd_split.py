@@ -40,7 +40,8 @@ def scratch(monkeypatch):
 
 
 @pytest.mark.parametrize("B,Hkv,G,Nq,Nk,W,S,P,fmt", [
-    (1, 1, 4, 1, 1025, 10**9, 4, None, "bf16"),     # 33 halves: the shortest split range, odd last split
+    (1, 1, 4, 1, 1025, 10**9, 4, None, "bf16"),     # 33 halves of few rows: a tile of their own kind, whole
+    (1, 1, 4, 9, 1025, 10**9, 4, None, "bf16"),     # 33 halves: the shortest split range, odd last split
     (1, 1, 4, 33, 3001, 10**9, 0, None, "fp16"),    # two row tiles, ragged last half
     (1, 2, 5, 130, 4000, 10**9, 4, None, "bf16"),   # groups of four heads and one
     (2, 1, 7, 65, 2500, 1100, 70, None, "bf16"),    # 4 + 2 + 1 heads, sink halves in front of the band
@@ -242,6 +243,7 @@ def test_few_rows_share_one_column_tile(scratch, Hkv, G, nq, nk, W, S, P, fmt, p
 @pytest.mark.parametrize("B,Hkv,Nq,Nk", [(40, 8, 1, 1500), (40, 8, 8, 1500)])
 def test_few_rows_of_sequences_of_one_length(scratch, B, Hkv, Nq, Nk):
     # enough of them that no keys are split: 256 bytes of scratch, no merge; without even those the row tiles run
+    # (a workspace that is too small is no error where the call needs none)
     q, k, v = make_qkv(B, Hkv * 4, Hkv, Nk, 128, seed=9680 + Nq, n_query=Nq)
     qd, kd, vd = to_device(q), to_device(k), to_device(v)
     print(f"[case] {B} x {Nq} rows on {Nk} keys", flush=True)
@@ -253,6 +255,8 @@ def test_few_rows_of_sequences_of_one_length(scratch, B, Hkv, Nq, Nk):
     ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
     assert_parity(out, lse, ro, rl, tag="few rows of one length")
     assert_parity(out2, lse2, ro, rl, tag="few rows of one length, no scratch")
+    plain = binding.swaa_attn_fwd_ex(qd, kd, vd, 10**9, 4, workspace=torch.empty(0, dtype=torch.uint8, device="cuda"))
+    assert torch.equal(out2, plain[0]) and torch.equal(lse2, plain[1])  # the call without a workspace
 
 
 @pytest.mark.parametrize("B,Hkv,G,Nq,Nk", [(1, 2, 5, 6, 3001), (2, 1, 7, 4, 2600), (3, 2, 32, 1, 5000), (1, 1, 31, 1, 40000)])
