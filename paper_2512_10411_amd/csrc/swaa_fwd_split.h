@@ -99,6 +99,14 @@ __host__ __device__ inline SplitSeq split_seq(const FwdParams &p, int nq, int nk
     return s;
 }
 
+// Candidate i for the longest split, h_max / (i + 1) rounded up; rcp: about 1 / (i + 1).  (An approximate quotient
+// will do: every workgroup comes to the same, and nobody else needs it.  Candidate 0 is the exception: it is the one
+// plan that splits nothing, and so fits every workspace.)
+__host__ __device__ inline int split_length(int h_max, int i, float rcp) {
+    const int L = i == 0 ? h_max : (int)((float)(h_max + i) * rcp);
+    return L > kSplitMinHalves ? L : kSplitMinHalves;
+}
+
 // Splits of a sequence whose tiles visit h halves, for splits of at most L; rcp = 1 / L.  (Rounded
 // down instead of up where the product comes out just below a whole number: no matter, the same
 // expression is used for the plan and for the work list.)
@@ -237,8 +245,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
         memory = wave_sum(memory);
         rows = (int)wave_read_lane(wave_inclusive_scan((unsigned)rows), 63);
         least = 0x7fffffff - (int)wave_max((unsigned)(0x7fffffff - least));
-        // (an approximate quotient will do: every workgroup comes to the same, and nobody else needs it)
-        const int L = max(kSplitMinHalves, (int)((float)(h_max + lane) * __builtin_amdgcn_rcpf((float)(lane + 1))));
+        const int L = split_length(h_max, lane, __builtin_amdgcn_rcpf((float)(lane + 1)));
         const float rcp = 1.f / (float)L;
         float units = 0.f, split_units = 0.f, starts = 0.f, longest = 0.f;
         for (int b = wave; b < p.B; b += 4) {
@@ -272,7 +279,9 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
         const float best = __uint_as_float(~wave_max(~__float_as_uint(t)));  // (positive floats order like their bits)
         const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
         const int Lb = __builtin_amdgcn_readlane(L, pick);
-        if (splittable > 0 && !whole_batch(p, least, least_units(p, rows))) n = split_count(me.cost, Lb, 1.f / (float)Lb);
+        // (no candidate fits the workspace only if candidate 0 splits as well: caches of 2^27 keys, whose halves
+        // split_count can no longer tell apart)
+        if (splittable > 0 && best < 3.0e38f && !whole_batch(p, least, least_units(p, rows))) n = split_count(me.cost, Lb, 1.f / (float)Lb);
     }
     if (me.whole || items == 0 || n < 1) n = 1;
     if (blockIdx.x == 0) p.ws_n[lane] = n;  // every lane its sequence's, for the merge kernel

@@ -1,0 +1,39 @@
+// Host-side check of the split plan's candidates (swaa::split_length, swaa::split_count): the first one splits nothing,
+// however far off the approximate reciprocal is.  Built and run by tests/test_host_split_plan.py; needs no GPU.
+#include <cstdio>
+#include <cstring>
+
+#include "swaa_fwd_split.h"
+
+int main() {
+    long bad = 0, checked = 0;
+    auto ulps = [](float x, int n) {
+        unsigned u;
+        std::memcpy(&u, &x, 4);
+        u += (unsigned)n;
+        std::memcpy(&x, &u, 4);
+        return x;
+    };
+    // longest sequences of 1 .. 2^20 halves (33 million keys): no sequence of the batch is split by candidate 0
+    for (int h_max = 1; h_max <= 1 << 20; h_max += h_max < 4096 ? 1 : 37)
+        for (int off = -2; off <= 2; ++off) {
+            const int L = swaa::split_length(h_max, 0, ulps(1.f, off));
+            for (int h : {1, h_max / 2, h_max - 1, h_max}) {
+                ++checked;
+                if (h < 1 || swaa::split_count(h, L, 1.f / (float)L) == 1) continue;
+                if (bad++ < 10) std::printf("candidate 0: %d of %d halves, reciprocal %d ulps off: L = %d\n", h, h_max, off, L);
+            }
+        }
+    // the others are at least the shortest split, and no longer than an exact quotient by more than one
+    for (int h_max = 1; h_max <= 20000; h_max += 7)
+        for (int i = 1; i < 64; ++i)
+            for (int off = -1; off <= 1; ++off) {
+                const int L = swaa::split_length(h_max, i, ulps(1.f / (float)(i + 1), off)), exact = (h_max + i) / (i + 1);
+                ++checked;
+                const int want = exact > swaa::kSplitMinHalves ? exact : swaa::kSplitMinHalves;
+                if (L >= swaa::kSplitMinHalves && L <= want + 1 && L >= want - 1) continue;
+                if (bad++ < 10) std::printf("candidate %d of %d halves: L = %d, not %d\n", i, h_max, L, want);
+            }
+    std::printf("checked %ld candidates, %ld wrong\n", checked, bad);
+    return bad != 0;
+}
