@@ -1,5 +1,5 @@
 // Host-side check of the split plan's candidates (swaa::split_length, swaa::split_count): the first one splits nothing,
-// however far off the approximate reciprocal is.  Built and run by tests/test_host_split_plan.py; needs no GPU.
+// however far off the approximate reciprocal is; and of the dies' shares of the units (swaa::die_share).  Built and run by tests/test_host_split_plan.py; needs no GPU.
 #include <cstdio>
 #include <cstring>
 
@@ -34,6 +34,24 @@ int main() {
                 if (L >= swaa::kSplitMinHalves && L <= want + 1 && L >= want - 1) continue;
                 if (bad++ < 10) std::printf("candidate %d of %d halves: L = %d, not %d\n", i, h_max, L, want);
             }
-    std::printf("checked %ld candidates, %ld wrong\n", checked, bad);
+    // the dies' shares: every unit once, and over sequences of as many units each no die gets more than one unit more
+    for (unsigned units = 0; units <= 70; ++units) {
+        unsigned of_die[swaa::kXcds] = {};
+        for (unsigned b = 0; b < swaa::kSplitMaxBatch; ++b) {
+            unsigned most = 0, least = ~0u;
+            bool whole = swaa::die_share(units, b * units, 0) == 0 && swaa::die_share(units, b * units, swaa::kXcds) == units;
+            for (unsigned x = 0; x < swaa::kXcds; ++x) {
+                const int share = (int)(swaa::die_share(units, b * units, x + 1) - swaa::die_share(units, b * units, x));
+                whole = whole && share >= 0 && share <= (int)((units + swaa::kXcds - 1) / swaa::kXcds);
+                of_die[x] += (unsigned)share;
+                most = of_die[x] > most ? of_die[x] : most;
+                least = of_die[x] < least ? of_die[x] : least;
+            }
+            ++checked;
+            if (whole && most - least <= 1) continue;
+            if (bad++ < 10) std::printf("%u sequences of %u units: dies get %u to %u\n", b + 1, units, least, most);
+        }
+    }
+    std::printf("checked %ld cases, %ld wrong\n", checked, bad);
     return bad != 0;
 }
