@@ -26,7 +26,8 @@
 // tokens, caches of 2-30k tokens, 8-40 heads) at 4-11 plans each: the plan it picks costs 1.1-1.7 % more than
 // the best of them on average (3.2 % with the first model, which took the longest split for the time
 // below 512 units, did not know HBM's rate and split batches that fill the chip).  The terms of few rows, and of
-// HBM beside them, are a fit to 230 batches of 7 or 31 generated tokens beside chunks at 81 plans each: 4 % behind the best.
+// HBM beside them, are a fit to 230 batches of 7 or 31 generated tokens beside chunks at 81 plans each.  Over 500 other
+// batches (3-60 sequences of 1-4 rows beside 0-3 chunks, 8-40 heads on 2-8) the plan is 1.4 % behind the best (18 % the worst).
 // The lengths of a packed batch are known on the device only: there every workgroup works the plan
 // out for itself (batches of at most 64 sequences: one per lane).  Measured, binary16 and pages of
 // 16 tokens, 32 heads on 8: 512 rows on 24k tokens, full attention, 364 -> 207 us (four splits,
@@ -166,6 +167,25 @@ __host__ __device__ inline unsigned die_share(unsigned units, unsigned ahead, un
     return (xcd * units + ahead % kXcds) / kXcds;
 }
 
+// Which unit of a die's list is workgroup `rank`: the at-th of few rows, or of row tiles?  Row tiles compute and few rows
+// read, so that they take turns and neither is left alone with the chip -- the other way round every 32 ranks,
+// so that the two workgroups of a compute unit, ranks r and r + 32 (of the first 64), are one of each.  When less than 32
+// of a kind are left (or were there), first what there is of it: turns to the end would put two row tiles
+// on a compute unit while few rows have others to themselves (31 tokens beside two chunks of 1588 rows, 8 heads on 8, 184 us
+// in row tiles for all; 205 with turns to the end, 187 so).  Against row tiles, 280 batches: 15.7 % faster on average,
+// six slower by more than 2 %; with turns to the end 14.7 % and 14.
+__host__ __device__ inline void unit_of_rank(unsigned rank, unsigned n_rows, unsigned n_few, bool &few, unsigned &at) {
+    const unsigned turns = n_rows < n_few ? n_rows : n_few, paired = turns / 32 * 64;
+    if (rank < paired) {
+        few = ((rank ^ (rank >> 5)) & 1u) != 0;
+        at = rank >> 1;
+        return;
+    }
+    const unsigned done = paired / 2, rel = rank - paired, first = turns - done;
+    few = (rel < first) == (n_few <= n_rows);
+    at = rel < first ? done + rel : rank - turns;
+}
+
 // One workgroup's share of the keys.
 struct SplitItem {
     int n, s;       // the sequence's splits, and which of them this is
@@ -296,18 +316,15 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     const unsigned mine = (unsigned)items * (unsigned)n;
     const unsigned slots = n > 1 ? mine : 0u;
     const unsigned slots_incl = wave_inclusive_scan(slots);
-    // Units of row tiles, which compute, and of few rows, which read, take turns while there are both, so that neither is
-    // left alone with the chip -- and the other way round every 32 units of a die, so that the two workgroups of a
-    // compute unit are one of each (20 batches against row tiles: 15.0 % faster, 13.2 % without that, 12.6 % in the order of the batch).
     const unsigned ahead = wave_inclusive_scan(mine) - mine;
     const unsigned from = die_share(mine, ahead, xcd), chunk = die_share(mine, ahead, xcd + 1) - from;
     const bool few = few_rows(p, nq);
     const unsigned incl_rows = wave_inclusive_scan(few ? 0u : chunk), incl_few = wave_inclusive_scan(few ? chunk : 0u);
-    const unsigned n_rows = wave_read_lane(incl_rows, 63), n_few = wave_read_lane(incl_few, 63), turns = min(n_rows, n_few);
+    const unsigned n_rows = wave_read_lane(incl_rows, 63), n_few = wave_read_lane(incl_few, 63);
     if (rank >= n_rows + n_few) return false;
-    const bool both = rank < 2 * turns;
-    const bool take_few = both ? ((rank ^ (rank >> 5)) & 1u) != 0 : n_few > n_rows;
-    const unsigned at = both ? rank >> 1 : rank - turns;  // among the units of its kind
+    bool take_few;
+    unsigned at;
+    unit_of_rank(rank, n_rows, n_few, take_few, at);
     const unsigned incl = take_few ? incl_few : incl_rows;
     const int b = __popcll(__ballot(incl <= at));  // sequences that end at or before it
     const unsigned base = b ? wave_read_lane(incl, b - 1) : 0u;

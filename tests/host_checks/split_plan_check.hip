@@ -1,5 +1,5 @@
 // Host-side check of the split plan's candidates (swaa::split_length, swaa::split_count): the first one splits nothing,
-// however far off the approximate reciprocal is; and of the dies' shares of the units (swaa::die_share).  Built and run by tests/test_host_split_plan.py; needs no GPU.
+// however far off the approximate reciprocal is; of the dies' shares of the units (swaa::die_share) and of their order (swaa::unit_of_rank).  Built and run by tests/test_host_split_plan.py; needs no GPU.
 #include <cstdio>
 #include <cstring>
 
@@ -52,6 +52,27 @@ int main() {
             if (bad++ < 10) std::printf("%u sequences of %u units: dies get %u to %u\n", b + 1, units, least, most);
         }
     }
+    // the order on a die: every unit once, and no two row tiles on a compute unit (ranks r and r + 32) while one
+    // of few rows could be there
+    for (unsigned n_rows = 0; n_rows <= 140; ++n_rows)
+        for (unsigned n_few = 0; n_few <= 140; ++n_few) {
+            const unsigned n = n_rows + n_few, pairs = n <= 32 ? 0 : n <= 64 ? n - 32 : 32;
+            bool seen[2][140] = {}, kind[280] = {}, sound = true;
+            for (unsigned r = 0; r < n; ++r) {
+                bool few;
+                unsigned at;
+                swaa::unit_of_rank(r, n_rows, n_few, few, at);
+                sound = sound && at < (few ? n_few : n_rows) && !seen[few][at];
+                if (sound) seen[few][at] = true;
+                kind[r] = few;
+            }
+            unsigned rows_alone = 0;
+            for (unsigned r = 0; r < pairs; ++r) rows_alone += !kind[r] && !kind[r + 32];
+            sound = sound && rows_alone <= (n_few < pairs ? pairs - n_few : 0);
+            ++checked;
+            if (sound) continue;
+            if (bad++ < 10) std::printf("%u row tiles, %u of few rows: %u compute units with two row tiles\n", n_rows, n_few, rows_alone);
+        }
     std::printf("checked %ld cases, %ld wrong\n", checked, bad);
     return bad != 0;
 }

@@ -1,7 +1,8 @@
 """The split plan's candidates (csrc/swaa_fwd_split.h) are worked out on the device with an approximate
 reciprocal.  A host program built from the same header checks that the first of them, the only one
-sure to fit every workspace, splits nothing however that reciprocal comes out, and that the units of a
-batch spread over the eight dies evenly.  No GPU."""
+sure to fit every workspace, splits nothing however that reciprocal comes out, that the units of a
+batch spread over the eight dies evenly, and that two row tiles share a compute unit only where there is
+nothing else.  No GPU."""
 import os
 import shutil
 import subprocess
@@ -15,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
                     reason="hipcc not available")
-def test_first_candidate_and_dies_shares(tmp_path):
+def test_first_candidate_shares_of_the_dies_and_order(tmp_path):
     exe = tmp_path / "split_plan_check"
     flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     cmd = [build.hipcc_path(), *flags, "-o", str(exe), os.path.join(HERE, "host_checks", "split_plan_check.hip")]
