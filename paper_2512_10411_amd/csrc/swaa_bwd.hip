@@ -262,6 +262,58 @@ __device__ __forceinline__ int dkv_main_item(unsigned bid, int n_extra) {
     return (int)((bid % kXcds) * per_die + (bid - (unsigned)n_extra) / kXcds);
 }
 
+// The work list of the dK/dV kernels: first the segments of the sink key tiles (rows beyond the band), then one
+// workgroup per key tile of 128 keys (band rows; for key tiles without sinks also the generated rows).  Under a causal mask
+// the first key tiles are seen by the most rows.
+struct DkvItem {
+    int kt, pair;  // key tile, (batch, KV head)
+    int seg;       // -1 for a key tile's main workgroup
+};
+__device__ __forceinline__ bool dkv_item(const BwdParams &p, DkvItem &w) {
+    const int n_kt = (p.N + 127) / 128;
+    const int n_extra = p.B * p.Hkv * p.n_sink_kt * p.n_seg;
+    const unsigned bid = blockIdx.x;
+    if ((int)bid < n_extra) {
+        w.seg = bid % p.n_seg;
+        w.kt = (bid / p.n_seg) % p.n_sink_kt;
+        w.pair = bid / (p.n_seg * p.n_sink_kt);
+        return true;
+    }
+    const int id = dkv_main_item(bid, n_extra);
+    if (id >= p.B * p.Hkv * n_kt) return false;  // (the grid is rounded up to a multiple of eight)
+    w.seg = -1;
+    w.kt = id % n_kt;
+    w.pair = id / n_kt;
+    return true;
+}
+
+// Its tiles of kBq query rows (head dimension 128): the band, then -- if a key is a sink, or there are generated rows --
+// the rest.  For a sink key tile the rest is cut into segments, and the main workgroup keeps the band.
+struct DkvTiles {
+    int lo, n_band;  // the band's first tile, and how many
+    int x;           // the first tile of the rest
+    int n;           // all of them
+    __device__ __forceinline__ int at(int i) const { return i < n_band ? lo + i : x + (i - n_band); }
+};
+__device__ __forceinline__ DkvTiles dkv_tiles(const BwdParams &p, const DkvItem &w) {
+    const int N = p.N, k0 = w.kt * 128, k1 = min(k0 + 127, N - 1);
+    const int last = (N - 1) / kBq, band_hi = min(N - 1, k1 + p.f.W - 1) / kBq;
+    DkvTiles t{k0 / kBq, 0, last + 1, 0};
+    t.n_band = band_hi - t.lo + 1;
+    int x_end = last;
+    if (w.kt < p.n_sink_kt) {
+        if (w.seg >= 0) {
+            t.n_band = 0;
+            t.x = band_hi + 1 + w.seg * p.seg_tiles;
+            x_end = min(last, t.x + p.seg_tiles - 1);
+        }
+    } else if (p.f.P < N) {
+        t.x = max(band_hi + 1, p.f.P / kBq);
+    }
+    t.n = t.n_band + max(0, x_end - t.x + 1);
+    return t;
+}
+
 __device__ __forceinline__ bf16x8 lds16(uint32_t addr) {
     return *(const bf16x8 __attribute__((address_space(3))) *)(uintptr_t)addr;
 }
@@ -310,24 +362,9 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
     const int N = p.N, W = p.f.W, S = p.f.S, P = p.f.P, G = p.f.G;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
     const int kq = wave & 3, part = wave >> 2;
-    // Work list: first the segments of the sink key tiles (rows beyond the band), then one
-    // workgroup per key tile of 128 keys (band rows; for key tiles without sinks also the
-    // generated rows).  Under a causal mask the first key tiles are seen by the most rows.
-    const int n_kt = (N + 127) / 128;
-    const int n_extra = p.B * p.Hkv * p.n_sink_kt * p.n_seg;
-    const unsigned bid = blockIdx.x;
-    int kt, pair, seg;  // seg: -1 for a key tile's main workgroup
-    if ((int)bid < n_extra) {
-        seg = bid % p.n_seg;
-        kt = (bid / p.n_seg) % p.n_sink_kt;
-        pair = bid / (p.n_seg * p.n_sink_kt);
-    } else {
-        const int id = dkv_main_item(bid, n_extra);
-        if (id >= p.B * p.Hkv * n_kt) return;  // (the grid is rounded up to a multiple of eight)
-        seg = -1;
-        kt = id % n_kt;
-        pair = id / n_kt;
-    }
+    DkvItem item;
+    if (!dkv_item(p, item)) return;
+    const int kt = item.kt, pair = item.pair, seg = item.seg;
     const bool sink_kt = kt < p.n_sink_kt;  // results go to the partial-sum workspace
     const int b = pair / p.Hkv, kvh = pair % p.Hkv;
     const int k0 = kt * 128, k1 = min(k0 + 127, N - 1);  // the workgroup's keys
