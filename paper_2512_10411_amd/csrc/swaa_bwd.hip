@@ -26,9 +26,10 @@
 // transposed are read from row-major LDS tiles with ds_read_b64_tr_b16.
 // P and dS are rounded to bf16 before the second products, sums are fp32.
 // The kernels in this file stage tiles through registers (dQ for head dimension 64) or by LDS DMA
-// (dK/dV) and leave instruction scheduling to the compiler; for head dimension 128 dQ
-// (swaa_bwd_dq_pipelined.hip) and dK/dV (swaa_bwd_dkv_d128.h) are pipelined by hand.  Waves per SIMD: two
-// (dQ) or one (dK/dV) for head dimension 128, four or three for 64.
+// (dK/dV) and leave instruction scheduling to the compiler, as does dK/dV for head dimension 128 where a key tile is
+// seen by few query tiles (swaa_bwd_dkv_d128_short.h); otherwise dQ (swaa_bwd_dq_pipelined.hip) and dK/dV
+// (swaa_bwd_dkv_d128.h) of head dimension 128 are pipelined by hand.  Waves per SIMD: two (dQ, short dK/dV) or one
+// (dK/dV) for head dimension 128, four or three for 64.
 #include <atomic>
 #include <cmath>
 
@@ -625,7 +626,8 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
 }  // namespace
 }  // namespace swaa
 
-#include "swaa_bwd_dkv_d128.h"  // dK, dV, head dimension 128
+#include "swaa_bwd_dkv_d128.h"        // dK, dV, head dimension 128
+#include "swaa_bwd_dkv_d128_short.h"  // ... of few query tiles per key tile
 
 namespace swaa {
 namespace {
@@ -660,6 +662,28 @@ __global__ __launch_bounds__(kThreads) void swaa_bwd_sink_sum_kernel(const BwdPa
     *reinterpret_cast<bf16x4 *>(p.dv + row) = v4;
 }
 
+// Is a key tile seen by so few query tiles that eight waves with less around their loop, which leave out every block
+// without a visible pair, beat one wave per SIMD, whose steps are faster?  Backward of head dimension 128, one wave per
+// SIMD / eight waves (us; 32 heads on 8 unless stated):
+//    tiles                                   4096 tokens (256 workgroups), window    16384 tokens (1024), window
+//    100 tokens   2   42.9 / 39.2             64   3   86.1 / 81.8                    128   4   409 / 390
+//    300          5   69.6 / 66.9            256   6  118.6 / 115.9                   256   6   498 / 482
+//    384          6   75.9 / 75.9            384   8  138.9 / 138.1                   512  10   672 / 675  (4 sinks 794 / 782)
+//    640         10  106.9 / 110.8           512  10  160.0 / 160.2                  1024  18  1032 / 1054
+//    (8 heads on 8)                          (8 on 8)                                 (16 heads on 8)
+//    500          8   53.8 / 52.0            512  10   71.4 / 69.9                    512  10   377 / 374
+//    1000        16   80.1 / 80.1            768  14   84.2 / 83.4                    768  14   469 / 472
+// With few workgroups the longest one is the time, and where sinks see many rows that is a segment, in which the eight
+// waves keep two busy: 16 heads on 2, 4 sinks, 4096 tokens: window 64 97.8 / 94.9, 128 113 / 112, 256 144 / 148.
+// Generated rows see every key, and their blocks have few edges: they count half.
+bool dkv_short(const BwdParams &p) {
+    const long long n_main = (long long)p.B * p.Hkv * ((p.N + 127) / 128);
+    const int G = p.f.G, all = (p.N + kBq - 1) / kBq, band = (p.f.W + 127) / kBq + 1;
+    const int tiles = (band < all ? band : all) + (p.N - p.f.P) / (2 * kBq);
+    if (n_main >= 256) return tiles <= (G <= 2 ? 13 : n_main >= 512 ? 10 : 9);
+    return tiles <= (G == 1 ? 12 : p.n_seg > 0 ? 4 : G <= 3 ? 8 : 6);
+}
+
 template <int D>
 hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     // more than 64 KiB of LDS per workgroup has to be requested once per device
@@ -678,12 +702,16 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     const long long n_kt = (p.N + 127) / 128;
     const long long pairs = (long long)p.B * p.Hkv;
     if (first_time) {
-        if constexpr (D == 128)
+        if constexpr (D == 128) {
             err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_dma_kernel),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, dkv128::kBytes);
-        else
+            if (err == hipSuccess)
+                err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_dma_short_kernel),
+                                          hipFuncAttributeMaxDynamicSharedMemorySize, dkv128short::kBytes);
+        } else {
             err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_kernel<D>),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, DkvSmem<D>::kBytes);
+        }
         if (err != hipSuccess) return err;
         configured.fetch_or(bit, std::memory_order_release);
     }
@@ -691,9 +719,12 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     // rounded up to a multiple of the die count (dkv_main_item)
     const long long n_main = (pairs * n_kt + kXcds - 1) / kXcds * kXcds;
     const dim3 dkv_grid((unsigned)(pairs * (long long)p.n_sink_kt * p.n_seg + n_main));
-    if constexpr (D == 128)
-        hipLaunchKernelGGL(swaa_bwd_dkv_dma_kernel, dkv_grid, dim3(dkv128::kThreads), dkv128::kBytes, stream, p);
-    else
+    if constexpr (D == 128) {
+        if (dkv_short(p))
+            hipLaunchKernelGGL(swaa_bwd_dkv_dma_short_kernel, dkv_grid, dim3(dkv128short::kThreads), dkv128short::kBytes, stream, p);
+        else
+            hipLaunchKernelGGL(swaa_bwd_dkv_dma_kernel, dkv_grid, dim3(dkv128::kThreads), dkv128::kBytes, stream, p);
+    } else
         hipLaunchKernelGGL(swaa_bwd_dkv_kernel<D>, dkv_grid, dim3(256 * kDkvParts), DkvSmem<D>::kBytes, stream, p);
     err = hipGetLastError();
     if (err != hipSuccess || p.n_sink_kt == 0) return err;

@@ -20,8 +20,8 @@
 //     3      dV^T += dO^T P, dK^T += Q^T dS, rows lo     P, dS of (s, 1) hi
 //     4      the same, rows hi                           P, dS of (s + 1, 0) lo
 // Measured, 16384 tokens, 32 heads on 8, window 2048, 512 generated rows: 1.36 ms with eight waves, now 1.27
-// (1.15 if no step had an edge: 18 % of them do); 4000 tokens, window 2048: the whole backward 847 -> 807 us; every
-// shape tried gained 1 to 6 %.  Asking for operands earlier, or for the tiles in another phase, changes nothing.
+// (1.15 if no step had an edge: 18 % of them do); 4000 tokens, window 2048: the whole backward 847 -> 807 us.  Short
+// sequences and narrow windows stay with the eight waves (swaa_bwd_dkv_d128_short.h, dkv_short).  Asking for operands earlier, or for the tiles in another phase, changes nothing.
 // S = Q K^T starts from zero, dP = dO V^T from -delta.  An invisible pair's P and dS are cleared
 // after packing, in steps with an edge only (a second version of the step).
 //

@@ -135,15 +135,33 @@ def test_row_blocks_of_head_dimension_64(N, W, S, P, G):
     (1029, 64, 33, None, 1),   # sinks that end inside the second unit: segments, one of them short
     (1029, 160, 130, 901, 4),  # two sink key tiles, generated rows that start inside a tile
     (545, 545, 0, 511, 5),     # no window; the row before a tile is generated
+    # (more query tiles per key tile than the short sequences' dK/dV kernel takes, as the last two)
+    (449, 449, 0, None, 4),    # a key tile of 65 keys
+    (515, 515, 4, None, 4),    # the last key tile has three keys
+    (1029, 150, 33, None, 2),  # sinks that end inside the second unit, a window that ends inside a unit
+    (1029, 135, 4, 700, 3),    # the same with generated rows
+    (929, 139, 1, None, 8),    # a window two rows longer than a whole number of units, a key tile of 33 keys
 ])
 def test_units_and_tiles_of_head_dimension_128(N, W, S, P, G):
     check(1, 2 * G, 2, N, 128, W, S, P, seed=9800 + N)
 
 
-def test_an_upstream_row_without_a_number_stays_in_its_blocks():
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P", [
+    (1, 2, 4, 384, 384, 0, None), (1, 2, 4, 385, 385, 0, None),      # few workgroups, on both sides of the rule
+    (1, 2, 4, 1024, 192, 4, None), (1, 2, 4, 1024, 193, 4, None),    # with segments of sinks: six tiles run on the other kernel
+    (1, 2, 1, 768, 768, 0, None), (1, 2, 1, 769, 769, 0, None),      # one head per KV head
+    (8, 16, 4, 256, 256, 0, None),                                   # a full chip
+    (1, 2, 4, 640, 64, 0, 256), (1, 2, 4, 640, 64, 0, 200),          # generated rows count half
+])
+def test_both_kernels_of_head_dimension_128_at_the_line_between_them(B, Hkv, G, N, W, S, P):
+    check(B, Hkv * G, Hkv, N, 128, W, S, P, seed=9900 + N + W)
+
+
+@pytest.mark.parametrize("W", [90, 140])  # eight waves, and one wave per SIMD
+def test_an_upstream_row_without_a_number_stays_in_its_blocks(W):
     # head dimension 128: 32 rows x 32 keys are computed together, so NaN in one row of dO may reach the keys of
     # those blocks in which some row of its 32 sees some key, and no others
-    N, W, row = 700, 90, 333
+    N, row = 700, 333
     q, k, v = make_qkv(1, 4, 1, N, 128, seed=9710)
     qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(make_dout(q.shape, 9711))
     out, lse = binding.swaa_attn_fwd(qd, kd, vd, W, 4)
@@ -160,10 +178,10 @@ def test_an_upstream_row_without_a_number_stays_in_its_blocks():
         assert torch.equal(x[:, :, ~reached], y[:, :, ~reached])
 
 
-@pytest.mark.parametrize("D", [64, 128])
-def test_a_row_without_a_number_reaches_only_the_keys_it_sees(D):
+@pytest.mark.parametrize("D,W", [(64, 90), (128, 90), (128, 140)])
+def test_a_row_without_a_number_reaches_only_the_keys_it_sees(D, W):
     # NaN in one row's log-sum-exp: P = 0 where the row does not see the key, whatever the row holds
-    N, W, row = 700, 90, 333
+    N, row = 700, 333
     q, k, v = make_qkv(1, 4, 1, N, D, seed=9700)
     qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(make_dout(q.shape, 9701))
     out, lse = binding.swaa_attn_fwd(qd, kd, vd, W, 4)
