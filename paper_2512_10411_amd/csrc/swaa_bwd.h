@@ -12,14 +12,21 @@ namespace swaa {
 // on 32 heads), is saved: backwards of 1000 to 9000 tokens are 1 to 2.6 % faster, longer ones 0.5.
 template <int kSteps>
 __device__ __forceinline__ float row_delta(const __bf16 *o, const bf16x8 (&dof)[kSteps]) {
-    float acc = 0.f;
+    // eight products in a row, then pairs of sums: twelve additions deep for 128 elements, as far as the sums of a tree
+    // over the lanes (64 in a row lose what is small beside a large product)
+    float part[kSteps];
 #pragma unroll
     for (int ks = 0; ks < kSteps; ++ks) {
         const bf16x8 of = *reinterpret_cast<const bf16x8 *>(o + 16 * ks);
+        part[ks] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc += (float)dof[ks][e] * (float)of[e];
+        for (int e = 0; e < 8; ++e) part[ks] += (float)dof[ks][e] * (float)of[e];
     }
-    return half_swap_sum(acc);
+#pragma unroll
+    for (int w = kSteps / 2; w > 0; w /= 2)
+#pragma unroll
+        for (int ks = 0; ks < w; ++ks) part[ks] += part[ks + w];
+    return half_swap_sum(part[0]);
 }
 
 struct BwdParams {

@@ -198,6 +198,29 @@ def test_a_row_without_a_number_reaches_only_the_keys_it_sees(D, W):
         assert not torch.isfinite(x[:, :, seen].float()).any()
 
 
+@pytest.mark.parametrize("D,N", [(64, 97), (128, 97), (128, 500)])
+def test_the_sums_of_delta_are_no_deeper_than_a_tree(D, N):
+    # delta = <dO, O> stands at the front of the workspace.  Products of bf16 are exact in fp32; a sum of additions at most
+    # 12 deep (eight in a row, then pairs) is off by at most 12 u of the sum of the absolute values, u = 2^-24.
+    # One product of 2^24 in front of 127 of 0.75: adding those one by one loses them all, 47 u and more.
+    Hq, Hkv = 4, 2
+    q, k, v = make_qkv(1, Hq, Hkv, N, D, seed=9720)
+    qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(make_dout(q.shape, 9721))
+    out, lse = binding.swaa_attn_fwd(qd, kd, vd, 64, 4)
+    dd[:, 1], out[:, 1] = 1.0, 0.75
+    dd[:, 1, :, 0], out[:, 1, :, 0] = 4096.0, 4096.0
+    dd[:, 2], out[:, 2] = 1.0, 0.75
+    dd[:, 2, :, 24], out[:, 2, :, 24] = 4096.0, -4096.0
+    ws = torch.empty(binding.swaa_attn_bwd_workspace_bytes(1, Hq, Hkv, N, D, 64, 4), dtype=torch.uint8, device="cuda")
+    binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, 64, 4, workspace=ws)
+    torch.cuda.synchronize()
+    delta = ws[:4 * Hq * N].view(torch.float32).view(Hq, N).double()
+    x = dd[0].double() * out[0].double()
+    off = (delta - x.sum(-1)).abs() / x.abs().sum(-1) * 2.0**24
+    print(f"[delta] D{D}: off by {[round(o, 2) for o in off.amax(-1).tolist()]} u", flush=True)
+    assert off.max().item() <= 12
+
+
 def test_run_to_run_determinism_and_errors():
     q, k, v = make_qkv(1, 8, 2, 1000, 128, seed=9400)
     qd, kd, vd = to_device(q), to_device(k), to_device(v)
