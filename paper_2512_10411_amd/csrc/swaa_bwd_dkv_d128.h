@@ -130,19 +130,48 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
     const int N = p.N, W = p.f.W, S = p.f.S, P = p.f.P, G = p.f.G;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
     const int kq = wave & 1, qb = wave >> 1;  // key block and row half of this wave
-    DkvItem item;
-    if (!dkv_item(p, item)) return;
-    const int kt = item.kt, pair = item.pair, seg = item.seg;
+    // (dkv_item and dkv_tiles, written out: called, they left this kernel with more scalar registers moved to vector ones, and
+    // 3000 to 4096 tokens with sinks took 1 % longer)
+    const int n_kt = (N + 127) / 128;
+    const int n_extra = p.B * p.Hkv * p.n_sink_kt * p.n_seg;
+    const unsigned bid = blockIdx.x;
+    int kt, pair, seg;  // seg: -1 for a key tile's main workgroup
+    if ((int)bid < n_extra) {
+        seg = bid % p.n_seg;
+        kt = (bid / p.n_seg) % p.n_sink_kt;
+        pair = bid / (p.n_seg * p.n_sink_kt);
+    } else {
+        const int id = dkv_main_item(bid, n_extra);
+        if (id >= p.B * p.Hkv * n_kt) return;  // (the grid is rounded up to a multiple of eight)
+        seg = -1;
+        kt = id % n_kt;
+        pair = id / n_kt;
+    }
     const bool sink_kt = kt < p.n_sink_kt;  // results go to the partial-sum workspace
     const int b = pair / p.Hkv, kvh = pair % p.Hkv;
-    const int k0 = kt * 128;                              // the workgroup's first key
+    const int k0 = kt * 128, k1 = min(k0 + 127, N - 1);  // the workgroup's keys
     const int kw0 = k0 + 64 * kq;                         // this wave's first key
     const size_t kv_base = ((size_t)b * p.Hkv + kvh) * (size_t)N * kD;
 
-    const DkvTiles tiles = dkv_tiles(p, item);
-    const int n_band = tiles.n_band, n_tiles = tiles.n;
+    // query tiles: the band, then -- if a key is a sink, or there are generated rows -- the rest.  For a
+    // sink key tile the rest is cut into segments, and the main workgroup keeps the band.
+    const int tq_last = (N - 1) / kRows;
+    const int tq_band_hi = min(N - 1, k1 + W - 1) / kRows;
+    const int tq_lo = k0 / kRows;
+    int n_band = tq_band_hi - tq_lo + 1;
+    int tq_x = tq_last + 1, tq_x_end = tq_last;  // second range
+    if (sink_kt) {
+        if (seg >= 0) {
+            n_band = 0;
+            tq_x = tq_band_hi + 1 + seg * p.seg_tiles;
+            tq_x_end = min(tq_last, tq_x + p.seg_tiles - 1);
+        }
+    } else if (P < N) {
+        tq_x = max(tq_band_hi + 1, P / kRows);
+    }
+    const int n_tiles = n_band + max(0, tq_x_end - tq_x + 1);
     const int total = G * n_tiles;  // (head, tile) steps, head-major
-    auto first_row = [&](int n) { return tiles.at(n) * kRows; };
+    auto first_row = [&](int n) { return (n < n_band ? tq_lo + n : tq_x + (n - n_band)) * kRows; };
 
     unrolled<256>([](auto r) { acc_clear<decltype(r)::value>(); });
     asm volatile("s_nop 1" ::: SWAA_ALL_ACC);
