@@ -14,13 +14,16 @@ template <int kSteps>
 __device__ __forceinline__ float row_delta(const __bf16 *o, const bf16x8 (&dof)[kSteps]) {
     // eight products in a row, then pairs of sums: twelve additions deep for 128 elements, as far as the sums of a tree
     // over the lanes (64 in a row lose what is small beside a large product)
+    bf16x8 of[kSteps];
+#pragma unroll
+    for (int ks = 0; ks < kSteps; ++ks) of[ks] = *reinterpret_cast<const bf16x8 *>(o + 16 * ks);
+    __builtin_amdgcn_sched_barrier(0);  // (all of them asked for before the first is used)
     float part[kSteps];
 #pragma unroll
     for (int ks = 0; ks < kSteps; ++ks) {
-        const bf16x8 of = *reinterpret_cast<const bf16x8 *>(o + 16 * ks);
         part[ks] = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) part[ks] += (float)dof[ks][e] * (float)of[e];
+        for (int e = 0; e < 8; ++e) part[ks] += (float)dof[ks][e] * (float)of[ks][e];
     }
 #pragma unroll
     for (int w = kSteps / 2; w > 0; w /= 2)
