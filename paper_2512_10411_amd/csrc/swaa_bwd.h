@@ -9,7 +9,8 @@ namespace swaa {
 // delta_i = <dO_i, O_i> of the dQ kernels' rows: a lane holds 8 kSteps elements of its row's dO as B operands and
 // reads the same of O at `o`; lanes l and l + 32 share a row.  The dQ kernels have every row's dO in
 // registers once, so a launch of its own, which read dO and O for nothing else (268 MB in 42 us for 16384 tokens
-// on 32 heads), is saved: backwards of 1000 to 9000 tokens are 1 to 2.6 % faster, longer ones 0.5.
+// on 32 heads), is saved: backwards of 1000 to 9000 tokens are 1 to 2.6 % faster, longer ones 0.5 (100 tokens take 0.4 us
+// longer: O is one more wait in the chain of a single workgroup).
 template <int kSteps>
 __device__ __forceinline__ float row_delta(const __bf16 *o, const bf16x8 (&dof)[kSteps]) {
     // eight products in a row, then pairs of sums: twelve additions deep for 128 elements, as far as the sums of a tree

@@ -3,8 +3,10 @@
 //
 // A workgroup owns 128 keys and walks tiles of 64 query rows; four waves, one per SIMD: wave w owns
 // the 64 keys 64 (w % 2).. in two units of 32 and the 32 rows 32 (w / 2).. of every tile; the two row
-// halves are added through LDS at the end.  It runs at 1.1 PFLOP/s, 80 % of what a large product reaches on this
-// card; the steps with an edge and the issue rate of the one wave have the rest.
+// halves are added through LDS at the end.  It runs at 1.0 PFLOP/s counted by visible pairs, 72 % of what a large product
+// reaches on this card (1.06, 77 %, with the masked and dead products of its edges).  The issue rate of the one wave has the
+// rest: 3.7 vector, 1.4 scalar and 1.7 LDS instructions per MFMA, the matrix pipe busy 44 % of the cycles at 2.1 GHz, no bank
+// conflicts (16384 tokens, window 2048; profiles/swaa_bwd_mid_bwd_sq_counters.txt).
 // Eight waves of 32 keys x 32 rows, two per SIMD, drew 48 KiB of operands from LDS for their 32
 // MFMAs and were in the same phase (products, exponentials, products) most of the time; a wave of
 // 64 keys draws 72 KiB for 64 MFMAs, because a transposed fragment of Q or dO serves both units and

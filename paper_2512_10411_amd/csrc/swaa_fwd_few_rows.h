@@ -6,13 +6,16 @@
 // G x nq rows of a (sequence, KV head) pair fit one column tile (few_rows), the pair is ONE tile, as in
 // the decode kernel: all rows are columns of the same 32 x 32 products, the four waves take a quarter of
 // the split's keys each, with a ring of one half (K 8 KiB + V 8 KiB) of their own and no barriers in the
-// loop, and their results are added up through LDS.  What bounds it is HBM; the softmax is max-based, so there is
+// loop, and their results are added up through LDS.  What bounds it is reading: every key once (466 MB fetched, 470
+// by count), at 4.1 TB/s beside a chunk and 5.0 alone of 6.4 for large reads; asking for a half's K before its V is read
+// changed nothing.  The softmax is max-based, so there is
 // no second pass.  The registers (two workgroups per CU) and the 64 KiB of LDS are those of the forward.
 // Measured, row tiles -> this (binary16, pages of 16 tokens): 23 tokens on 1-12k keys beside a chunk of 999 rows on a
-// window of 2k, 32 heads on 8, 133-138 -> 117-120 us (470 MB: 74 us at the rate of large reads); 31 tokens on 3-24k keys
-// beside three chunks of 273 rows, 40 heads on 8 (five heads were two tiles, each reading the keys) 540 -> 370; 7 tokens
-// beside 256 rows, 16 heads on 4, 63 -> 43.  Calls already bound by HBM gain nothing (31 tokens on 3-28k keys, 32 heads on 8,
-// 342 -> 353; one head per KV head 195 -> 195).
+// window of 2k, 32 heads on 8, 141 -> 123 us (470 MB: 74 us at the rate of large reads); 31 tokens on 3-28k keys
+// beside 500 rows, 40 heads on 8 (five heads were two tiles, each reading the keys) 362 -> 268, 32 heads on 8 266 -> 247;
+// 23 tokens alone, 16 heads on 4, 52 -> 48.  Calls that read at HBM's rate in row tiles gain nothing (31 tokens alone, 8 heads on
+// 8: 233 -> 233), and whole keys of one length may lose: 64 sequences on 8000 keys 346 -> 350, 40 on 1500 51.7 -> 53.7 (64 on 1100
+// 57 -> 53, 16 heads on 4 35 -> 26).
 #ifndef SWAA_FWD_FEW_ROWS_H_
 #define SWAA_FWD_FEW_ROWS_H_
 

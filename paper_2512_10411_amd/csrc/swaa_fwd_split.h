@@ -27,7 +27,8 @@
 // the best of them on average (3.2 % with the first model, which took the longest split for the time
 // below 512 units, did not know HBM's rate and split batches that fill the chip).  The terms of few rows, and of
 // HBM beside them, are a fit to 230 batches of 7 or 31 generated tokens beside chunks at 81 plans each.  Over 500 other
-// batches (3-60 sequences of 1-4 rows beside 0-3 chunks, 8-40 heads on 2-8) the plan is 1.4 % behind the best (18 % the worst).
+// batches (3-60 sequences of 1-4 rows beside 0-3 chunks, 8-40 heads on 2-8) the plan is 1.7 % behind the best of its candidates
+// on average, 30 % the worst; against row tiles they take 0.837 of the time, ten more than 1.02 (the worst 1.12).
 // The lengths of a packed batch are known on the device only: there every workgroup works the plan
 // out for itself (batches of at most 64 sequences: one per lane).  Measured, binary16 and pages of
 // 16 tokens, 32 heads on 8: 512 rows on 24k tokens, full attention, 364 -> 207 us (four splits,
