@@ -187,7 +187,7 @@ int swaa_attn_fwd_ex(const swaa_fwd_args *args);
  * and a second kernel merges their partial results.  Which calls gain is decided from the
  * sizes in args (and, for packed batches, from the sequences' lengths on the device).  Sequences
  * of few rows -- Hq / Hkv * rows <= 32, generated tokens -- run on a tile of their own kind with a
- * workspace, whether their keys are split or not.
+ * workspace, whether their keys are split or not (where it is the faster one).
  *
  *   workspace        device scratch memory owned by the caller, 16-byte aligned, of at least
  *                    swaa_attn_fwd_ex_workspace_bytes(args) bytes; contents before and after

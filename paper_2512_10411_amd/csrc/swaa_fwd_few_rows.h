@@ -14,8 +14,9 @@
 // window of 2k, 32 heads on 8, 141 -> 123 us (470 MB: 74 us at the rate of large reads); 31 tokens on 3-28k keys
 // beside 500 rows, 40 heads on 8 (five heads were two tiles, each reading the keys) 362 -> 268, 32 heads on 8 266 -> 247;
 // 23 tokens alone, 16 heads on 4, 52 -> 48.  Calls that read at HBM's rate in row tiles gain nothing (31 tokens alone, 8 heads on
-// 8: 233 -> 233), and whole keys of one length may lose: 64 sequences on 8000 keys 346 -> 350, 40 on 1500 51.7 -> 53.7 (64 on 1100
-// 57 -> 53, 16 heads on 4 35 -> 26).
+// 8: 233 -> 233), and whole keys may lose by the way their units fall on the compute units (few_in_row_tiles has the worst of
+// it, up to 21 %): 64 sequences on 8000 keys 346 -> 350, 49 on 16 KV heads and 3840 keys 278 -> 293 (64 on 1100 57 -> 53, 16 heads on
+// 4 35 -> 26).
 #ifndef SWAA_FWD_FEW_ROWS_H_
 #define SWAA_FWD_FEW_ROWS_H_
 

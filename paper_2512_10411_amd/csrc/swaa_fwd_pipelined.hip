@@ -259,10 +259,11 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
     SeqGeom sg;
     if (!seq_geom(p, wi.b, sg)) return;
     if constexpr (kSplit) {
-        if (few_rows(p, sg.nq)) {
+        if (few_rows(p, sg.nq) && si.n > 0) {
             few_rows_item<kF16, kPaged>(p, wi, si, sg);
             return;
         }
+        si.n = max(si.n, 1);
     }
     const int hpb = wi.hpb;
     const int rows_per_wg = kPWgRows / hpb;

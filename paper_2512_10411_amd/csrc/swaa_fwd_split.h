@@ -187,9 +187,23 @@ __host__ __device__ inline void unit_of_rank(unsigned rank, unsigned n_rows, uns
     at = rel < first ? done + rel : rank - turns;
 }
 
+// A batch of few rows on whole keys, `units` (times KV heads) of about one length: do row tiles, which are as many where the
+// heads of a group share one, run them faster?  Two workgroups of few rows on a compute unit read no more than one alone
+// does (32 KB/us), two of row tiles 37, and from 257 units on the doubled ones are the time, until all are.  Row tiles / few
+// rows (us; 32 heads on 8, bfloat16, caches that no cache of the chip has seen; pages of 16 and other groups alike):
+//    units    256          272          288          320          352          384          448          512
+//    1504     41.0 / 39.0  46.2 / 52.2  47.5 / 52.8  50.5 / 54.2  53.8 / 56.3  56.6 / 57.9  64.1 / 63.8  72.3 / 72.1
+//    4000     96.9 / 96.5   110 / 130    114 / 132    123 / 136    131 / 141    140 / 145    161 / 162    183 / 185
+//    16000     349 / 354    407 / 491    423 / 497    455 / 507    490 / 523    522 / 543    602 / 608    687 / 690
+// In drawn batches the two are even from 377 units on, and in any number where the lengths differ by a factor of four, so
+// that the longest ones are the time (272 units on 2-9k keys: 0.97).
+__host__ __device__ inline bool few_in_row_tiles(const FwdParams &p, unsigned units) {
+    return p.n4 + p.has2 + p.has1 == 1 && units > 256 && units <= 376;
+}
+
 // One workgroup's share of the keys.
 struct SplitItem {
-    int n, s;       // the sequence's splits, and which of them this is
+    int n, s;       // the sequence's splits (0: none, and few rows on a row tile all the same), and which of them this is
     unsigned slot;  // partial result (n >= 2)
 };
 
@@ -261,6 +275,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     const SplitSeq me = split_seq(p, nq, nk, np);
     const int items = me.tiles * p.Hkv;
     int n = 1;
+    float total_all = 1.f, longest_all = 0.f;  // of the halves (as sequences of one length have)
     if (p.split_keys != 1) {
         n = p.split_keys;  // (-1: one)
     } else {
@@ -304,6 +319,8 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
             starts += o[192];
         }
         __syncthreads();  // (the scratch becomes part of a ring)
+        longest_all = (float)h_max;
+        total_all = total;
         const float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, starts, longest, total, memory);
         const float best = __uint_as_float(~wave_max(~__float_as_uint(t)));  // (positive floats order like their bits)
         const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
@@ -320,6 +337,8 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     const unsigned ahead = wave_inclusive_scan(mine) - mine;
     const unsigned from = die_share(mine, ahead, xcd), chunk = die_share(mine, ahead, xcd + 1) - from;
     const bool few = few_rows(p, nq);
+    const unsigned units = wave_read_lane(ahead + mine, 63);
+    const bool in_rows = few_in_row_tiles(p, units) && total_all >= 0.8f * longest_all * (float)units && !__any(n > 1 || !few);
     const unsigned incl_rows = wave_inclusive_scan(few ? 0u : chunk), incl_few = wave_inclusive_scan(few ? chunk : 0u);
     const unsigned n_rows = wave_read_lane(incl_rows, 63), n_few = wave_read_lane(incl_few, 63);
     if (rank >= n_rows + n_few) return false;
@@ -340,6 +359,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     r -= (unsigned)w.kvh * per_head;
     si.s = (int)(r / tiles);
     split_tile(p, nq_b, r - (unsigned)si.s * tiles, w);
+    if (in_rows) si.n = 0;  // (said in another field, it cost other batches 1 us: scalar registers move to vector ones)
     return true;
 }
 

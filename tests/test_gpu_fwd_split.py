@@ -259,6 +259,39 @@ def test_few_rows_of_sequences_of_one_length(scratch, B, Hkv, Nq, Nk):
     assert torch.equal(out2, plain[0]) and torch.equal(lse2, plain[1])  # the call without a workspace
 
 
+@pytest.mark.parametrize("B,Hkv,G,nq,nk,packed,rows", [
+    (33, 8, 4, 1, 1500, False, True), (47, 8, 1, 3, 1100, False, True), (19, 16, 2, 2, 1100, False, True),
+    (32, 8, 4, 1, 1500, False, False), (48, 8, 4, 1, 1100, False, False),  # 256 and 384 units
+    (33, 8, 3, 1, 1100, False, False),                                     # a group of two row tiles
+    (33, 8, 4, 1, 1500, True, True), (47, 8, 2, 2, 1100, True, True), (32, 8, 4, 1, 1500, True, False),
+])
+def test_few_rows_that_fill_more_than_every_compute_unit_once(scratch, B, Hkv, G, nq, nk, packed, rows):
+    # 257 to 376 units of whole keys run on row tiles, bit for bit as without a workspace
+    q, k, v = make_qkv(B, Hkv * G, Hkv, nk, 128, seed=9695 + B, n_query=nq)
+    qd, kd, vd = to_device(q), to_device(k), to_device(v)
+    print(f"[case] {B} x {nq} rows on {nk} keys, {Hkv} x {G} heads, packed {packed}", flush=True)
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    if packed:
+        cu = lambda n: torch.arange(0, (B + 1) * n, n, dtype=torch.int32, device="cuda")
+        pack = lambda x: x.permute(1, 0, 2, 3).reshape(x.shape[1], -1, 128).contiguous()
+        run = lambda ws: binding.swaa_attn_fwd_ex(pack(qd), pack(kd), pack(vd), 10**9, 4, cu_seqlens_q=cu(nq), cu_seqlens_k=cu(nk),
+                                                  max_seqlen_q=nq, max_seqlen_k=nk, workspace=ws)
+        plain = binding.swaa_attn_fwd_ex(qd, kd, vd, 10**9, 4, workspace=none)
+        plain = pack(plain[0]), plain[1].permute(1, 0, 2).reshape(Hkv * G, -1)
+    else:
+        run = lambda ws: binding.swaa_attn_fwd_ex(qd, kd, vd, 10**9, 4, workspace=ws)
+        plain = run(none)
+    out, lse = run(None)
+    torch.cuda.synchronize()
+    assert scratch[-1] > 0
+    assert (torch.equal(out, plain[0]) and torch.equal(lse, plain[1])) == rows
+    if packed:
+        out, lse = (x.view(Hkv * G, B, nq, -1).permute(1, 0, 2, 3) for x in (out, lse))
+        lse = lse[..., 0]
+    ro, rl = swaa_decode_oracle(q, k, v, 10**9, 4, 1 / math.sqrt(128))
+    assert_parity(out, lse, ro, rl, tag=f"few rows, {B * Hkv} units")
+
+
 @pytest.mark.parametrize("B,Hkv,G,Nq,Nk", [(1, 2, 5, 6, 3001), (2, 1, 7, 4, 2600), (3, 2, 32, 1, 5000), (1, 1, 31, 1, 40000)])
 def test_few_rows_of_large_groups_and_one_length(scratch, B, Hkv, G, Nq, Nk):
     # groups whose row tiles would be two to eight: the workspace, the grid and the merge are those of one tile
