@@ -942,6 +942,7 @@ long long plan_fwd_split(FwdParams &p) {
                 n = c;
             }
         }
+        if (few_rows(p, p.Nq) && few_stay_whole((unsigned)items)) n = 1;
         if (n == 1 && !few_rows(p, p.Nq)) return 0;
         p.few_only = n == 1;
     }

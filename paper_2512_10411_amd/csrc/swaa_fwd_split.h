@@ -201,6 +201,14 @@ __host__ __device__ inline bool few_in_row_tiles(const FwdParams &p, unsigned un
     return p.n4 + p.has2 + p.has1 == 1 && units > 256 && units <= 376;
 }
 
+// Does such a batch stay whole because its units have a compute unit each, and most of those have one?  Splits share
+// compute units, which read no more for it; the model, whose row tiles do, splits from about 13000 keys on.  Whole / the best
+// of two to eight splits / row tiles (us; 13440 keys, 16 heads on 4; 2500 to 24000 keys and 32 heads on 8 alike):
+//    units    128              144              160              176              192              208              240
+//             163 / 158 / 164  171 / 180 / 189  184 / 198 / 207  200 / 217 / 222  219 / 237 / 260  239 / 251 / 267  277 / 285 / 283
+// Up to 160 it depends on where the keys lie (144 units on 10270 keys, packed: 160 / 151).
+__host__ __device__ inline bool few_stay_whole(unsigned units) { return units > 160 && units <= 256; }
+
 // One workgroup's share of the keys.
 struct SplitItem {
     int n, s;       // the sequence's splits (0: none, and few rows on a row tile all the same), and which of them this is
@@ -275,7 +283,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     const SplitSeq me = split_seq(p, nq, nk, np);
     const int items = me.tiles * p.Hkv;
     int n = 1;
-    float total_all = 1.f, longest_all = 0.f;  // of the halves (as sequences of one length have)
+    bool few_even = true;  // few rows only, of about one length: the average is 0.8 of the longest and more
     if (p.split_keys != 1) {
         n = p.split_keys;  // (-1: one)
     } else {
@@ -319,8 +327,6 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
             starts += o[192];
         }
         __syncthreads();  // (the scratch becomes part of a ring)
-        longest_all = (float)h_max;
-        total_all = total;
         const float t = split_units > (float)p.split_cap ? 3.0e38f : split_time(units, split_units, starts, longest, total, memory);
         const float best = __uint_as_float(~wave_max(~__float_as_uint(t)));  // (positive floats order like their bits)
         const int pick = __builtin_ctzll(__ballot(t == best) | (1ull << 63));
@@ -328,6 +334,9 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
         // (no candidate fits the workspace only if candidate 0 splits as well: caches of 2^27 keys, whose halves
         // split_count can no longer tell apart)
         if (splittable > 0 && best < 3.0e38f && !whole_batch(p, least, least_units(p, rows))) n = split_count(me.cost, Lb, 1.f / (float)Lb);
+        const float whole_units = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(units), 0));  // (candidate 0's)
+        few_even = total >= 0.8f * (float)h_max * whole_units && !__any(!few_rows(p, nq));
+        if (few_even && few_stay_whole((unsigned)whole_units)) n = 1;
     }
     if (me.whole || items == 0 || n < 1) n = 1;
     if (blockIdx.x == 0) p.ws_n[lane] = n;  // every lane its sequence's, for the merge kernel
@@ -337,8 +346,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     const unsigned ahead = wave_inclusive_scan(mine) - mine;
     const unsigned from = die_share(mine, ahead, xcd), chunk = die_share(mine, ahead, xcd + 1) - from;
     const bool few = few_rows(p, nq);
-    const unsigned units = wave_read_lane(ahead + mine, 63);
-    const bool in_rows = few_in_row_tiles(p, units) && total_all >= 0.8f * longest_all * (float)units && !__any(n > 1 || !few);
+    const bool in_rows = few_even && few_in_row_tiles(p, wave_read_lane(ahead + mine, 63)) && !__any(n > 1);
     const unsigned incl_rows = wave_inclusive_scan(few ? 0u : chunk), incl_few = wave_inclusive_scan(few ? chunk : 0u);
     const unsigned n_rows = wave_read_lane(incl_rows, 63), n_few = wave_read_lane(incl_few, 63);
     if (rank >= n_rows + n_few) return false;

@@ -292,6 +292,29 @@ def test_few_rows_that_fill_more_than_every_compute_unit_once(scratch, B, Hkv, G
     assert_parity(out, lse, ro, rl, tag=f"few rows, {B * Hkv} units")
 
 
+@pytest.mark.parametrize("B,Hkv,whole", [(40, 4, False), (41, 4, True), (64, 4, True)])
+def test_few_rows_with_a_compute_unit_each_stay_whole(scratch, B, Hkv, whole):
+    # 161 to 256 units: 256 bytes of scratch where the sequences are of one length, and the same bits packed
+    nk = 14000 if B < 64 else 24000
+    q = to_device(make_qkv(B, Hkv, Hkv, 16, 128, seed=9697, n_query=1)[0])
+    gen = torch.Generator(device="cuda").manual_seed(B)
+    k, v = (torch.randn(B, Hkv, nk, 128, device="cuda", generator=gen).bfloat16() for _ in range(2))
+    print(f"[case] {B} x 1 row on {nk} keys, {Hkv} heads", flush=True)
+    out, lse = (t.clone() for t in binding.swaa_attn_fwd_ex(q, k, v, 10**9, 4))
+    assert (scratch[-1] == 256) == whole
+    cu = lambda n: torch.arange(0, (B + 1) * n, n, dtype=torch.int32, device="cuda")
+    pack = lambda x: x.permute(1, 0, 2, 3).reshape(Hkv, -1, x.shape[-1]).contiguous()
+    out2, lse2 = binding.swaa_attn_fwd_ex(pack(q), pack(k), pack(v), 10**9, 4, cu_seqlens_q=cu(1), cu_seqlens_k=cu(nk),
+                                          max_seqlen_q=1, max_seqlen_k=nk)
+    torch.cuda.synchronize()
+    if whole:
+        assert torch.equal(pack(out), out2) and torch.equal(pack(lse[..., None])[..., 0], lse2)
+    s = torch.einsum("bhd,bhkd->bhk", q[:, :, 0].float(), k.float()) / math.sqrt(128)
+    ro = torch.einsum("bhk,bhkd->bhd", s.softmax(-1), v.float())[:, :, None].cpu().numpy()
+    rl = torch.logsumexp(s, -1)[:, :, None].cpu().numpy()
+    assert_parity(out, lse, ro, rl, tag=f"few rows, {B * Hkv} units on {nk} keys")
+
+
 @pytest.mark.parametrize("B,Hkv,G,Nq,Nk", [(1, 2, 5, 6, 3001), (2, 1, 7, 4, 2600), (3, 2, 32, 1, 5000), (1, 1, 31, 1, 40000)])
 def test_few_rows_of_large_groups_and_one_length(scratch, B, Hkv, G, Nq, Nk):
     # groups whose row tiles would be two to eight: the workspace, the grid and the merge are those of one tile
