@@ -7,6 +7,7 @@
 #include "swaa_common.h"
 #include "swaa_bwd.h"
 #include "swaa_decode.h"
+#include "swaa_fwd_short.h"
 
 using swaa::FwdParams;
 using swaa::kXcds;
@@ -154,7 +155,9 @@ int fwd_call(const swaa_fwd_args *a, void *workspace, long long workspace_bytes)
         }
     }
     hipStream_t s = static_cast<hipStream_t>(a->stream);
-    const hipError_t err = a->D == 128  ? swaa::launch_fwd_pipelined_d128(p, s)
+    swaa::FwdShortParams sp;
+    const hipError_t err = a->D == 128  ? (swaa::plan_fwd_short(p, sp) ? swaa::launch_fwd_short_d128(sp, s)
+                                                                       : swaa::launch_fwd_pipelined_d128(p, s))
                            : a->D == 64 ? swaa::launch_fwd_d64(p, s)
                                         : swaa::launch_fwd_simple(p, a->D, s);
     return err == hipSuccess ? SWAA_OK : SWAA_ERR_LAUNCH;

@@ -21,7 +21,7 @@ import pytest
 from paper_2512_10411_amd import build
 
 # source file, substring of the kernel that addresses LDS absolutely, fewest MFMAs expected
-CASES = [("swaa_fwd_pipelined.hip", "pipelined", 60), ("swaa_decode.hip", "decode_split", 16),
+CASES = [("swaa_fwd_pipelined.hip", "pipelined", 60), ("swaa_decode.hip", "decode_split", 16), ("swaa_fwd_short.hip", "fwd_short", 16),
          ("swaa_bwd_dq_pipelined.hip", "dq_pipelined", 100)]
 
 
