@@ -42,6 +42,7 @@ struct BwdParams {
     __bf16 *dv;          // [B, Hkv, N, D]
     float *delta;        // workspace, [B, Hq, N]
     int B, Hq, Hkv, N;
+    int die_shift;  // of the dK/dV kernels' work list (dkv_main_item)
     // Key tiles (128 keys) that hold sink keys are seen by every later row.  Their rows
     // beyond the band are cut into n_seg segments of seg_tiles query tiles, each computed
     // by a workgroup of its own; the band part and the segments leave fp32 partial sums in
@@ -50,7 +51,7 @@ struct BwdParams {
     float *partial;  // workspace, after delta
 };
 
-// Fills n_sink_kt, n_seg, seg_tiles from the shape and mask fields.
+// Fills die_shift, n_sink_kt, n_seg, seg_tiles from the shape and mask fields.
 void plan_bwd(BwdParams &p);
 // Floats of workspace the plan needs (delta + partial sums).
 long long bwd_workspace_floats(const BwdParams &p, int D);

@@ -143,7 +143,7 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
         kt = (bid / p.n_seg) % p.n_sink_kt;
         pair = bid / (p.n_seg * p.n_sink_kt);
     } else {
-        const int id = dkv_main_item(bid, n_extra);
+        const int id = dkv_main_item(p, bid, n_extra, n_kt);
         if (id >= p.B * p.Hkv * n_kt) return;  // (the grid is rounded up to a multiple of eight)
         seg = -1;
         kt = id % n_kt;

@@ -84,6 +84,7 @@ struct FwdParams {
     FastDiv div_tiles_per_pair, div_hkv, div_nt_h4;  // for the work-list decode of every workgroup
     FastDiv div_page;  // page_size (paged caches)
     int tiles_per_pair;
+    int die_shift, die_items;  // which items a die takes (plan_work)
     long long total_items;
     long long chunk;  // work items per XCD
     // Packed batches whose total number of query rows the caller has stated: the work list holds
@@ -242,15 +243,16 @@ __device__ __forceinline__ bool decode_work_packed(const FwdParams &p, WorkItem 
 
 // Workgroups reach the 8 XCDs round-robin; XCD x takes the x-th contiguous
 // chunk of the work list, so the position tiles of one KV head, whose K/V
-// bands overlap, run behind the same L2.  Inside a pair, long rows go first.
+// bands overlap, run behind the same L2.  Inside a pair, long rows go first; where several XCDs
+// share a pair whose tiles differ in length, they take them in turn (plan_work).
 __device__ __forceinline__ bool decode_work(const FwdParams &p, WorkItem &w) {
     if (p.packed_compact) return decode_work_packed(p, w);
     // (the entry points refuse work lists of 2^31 items or more: 32-bit arithmetic, whose
     // divisions cost a fraction of the 64-bit ones -- every wave of every workgroup pays them)
     const unsigned bid = blockIdx.x;
-    const unsigned slot = bid / kXcds, chunk = (unsigned)p.chunk;
-    const unsigned item = (bid % kXcds) * chunk + slot;
-    if (slot >= chunk || item >= (unsigned)p.total_items) return false;
+    const unsigned xcd = bid % kXcds, sub = xcd & ((1u << p.die_shift) - 1u);
+    const unsigned off = ((bid / kXcds) << p.die_shift) + sub, item = (xcd >> p.die_shift) * (unsigned)p.die_items + off;
+    if (off >= (unsigned)p.die_items || item >= (unsigned)p.total_items) return false;
     const unsigned tpp = (unsigned)p.tiles_per_pair, hkv = (unsigned)p.Hkv;
     const unsigned pair = fastdiv(item, p.div_tiles_per_pair);
     unsigned r = item - pair * tpp;
@@ -278,8 +280,15 @@ __device__ __forceinline__ bool decode_work(const FwdParams &p, WorkItem &w) {
     return true;
 }
 
+// log2 of the dies that share a (batch, KV head) pair, where they share one evenly: eight to one pair, four to two, two to four.
+inline int die_shift(long long pairs) { return pairs == 1 ? 3 : pairs == 2 ? 2 : pairs == 4 ? 1 : 0; }
+
 // Fills the work-decomposition fields (everything from wg_rows on) for sequences of
-// `rows` query rows; needs B, Hkv and G.  False if the work list does not fit 31 bits.
+// `rows` query rows; needs B, Hkv, G, Nk, W and P.  False if the work list does not fit 31 bits.
+// Dies that share a pair take its tiles in turn if the rows differ much in length (a window of half the keys and more, or
+// generated rows behind a prompt): with a contiguous part each, one has the long rows and the others are done
+// early (16 heads on 4, full attention, 8192 tokens 281 us, in turn 254; window 8192 of 16384 776, 716).  Rows of one length stay
+// in contiguous parts, whose bands one L2 holds (4 heads on 1, window 2048, 65536 tokens 250 us, in turn 305).
 inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     p.wg_rows = wg_rows;
     p.n4 = p.G / 4;
@@ -291,10 +300,14 @@ inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     p.tiles_per_pair = p.n4 * p.nt_h4 + p.has2 * p.nt_h2 + p.has1 * p.nt_h1;
     p.packed_compact = 0;
     p.total_items = (long long)p.B * p.Hkv * p.tiles_per_pair;
+    const bool rows_differ = 2LL * p.W >= p.Nk || p.P < p.Nk || p.n_prompts;
     p.div_tiles_per_pair = make_fastdiv((unsigned)p.tiles_per_pair);
     p.div_hkv = make_fastdiv((unsigned)p.Hkv);
     p.div_nt_h4 = make_fastdiv((unsigned)p.nt_h4);
     p.chunk = (p.total_items + kXcds - 1) / kXcds;
+    const int shift = die_shift((long long)p.B * p.Hkv);
+    p.die_shift = rows_differ ? shift : 0;
+    p.die_items = p.die_shift ? p.tiles_per_pair : (int)p.chunk;  // (ceil(die_items / dies) is chunk)
     return p.chunk * kXcds <= 0x7fffffffLL;
 }
 
