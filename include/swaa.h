@@ -374,8 +374,11 @@ int swaa_attn_bwd(const void *q, const void *k, const void *v, const void *out, 
                   float scale, void *workspace, long long workspace_bytes, void *stream);
 
 /*
- * Bytes of workspace swaa_attn_bwd needs (one float per query row, plus partial
- * sums for the key tiles that hold sink keys), or a negative swaa_status.
+ * Bytes of workspace swaa_attn_bwd uses (one float per query row, plus partial
+ * sums for the key tiles that hold sink keys, or, of short sequences whose key tiles
+ * are shared out over several workgroups each, for all of them: 128 MiB at most), or a
+ * negative swaa_status.  With less, down to what key tiles that are not shared out need, the
+ * call runs without sharing them out.
  */
 long long swaa_attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int D, int window, int n_sink, int n_prompt);
 

@@ -365,7 +365,7 @@ int bwd_plan(swaa::BwdParams &p, int B, int Hq, int Hkv, int N, int D, int windo
     f.G = Hq / Hkv;
     if (!swaa::plan_work(f, N, swaa::kWgRows) || (long long)B * Hq * N > 0x7fffffffLL * 16) return SWAA_ERR_SHAPE;
     p.B = B; p.Hq = Hq; p.Hkv = Hkv; p.N = N;
-    swaa::plan_bwd(p);
+    swaa::plan_bwd(p, D, true);
     return SWAA_OK;
 }
 
@@ -390,9 +390,12 @@ int swaa_attn_bwd(const void *q, const void *k, const void *v, const void *out, 
     for (const void *ptr : {q, k, v, out, dout, (const void *)dq, (const void *)dk, (const void *)dv})
         if (misaligned(ptr)) return SWAA_ERR_ALIGN;
     if ((reinterpret_cast<uintptr_t>(lse) & 3u) != 0) return SWAA_ERR_ALIGN;
-    if (!workspace || misaligned(workspace) ||
-        workspace_bytes < swaa::bwd_workspace_floats(p, D) * (long long)sizeof(float))
-        return SWAA_ERR_WORKSPACE;
+    if (!workspace || misaligned(workspace)) return SWAA_ERR_WORKSPACE;
+    auto fits = [&]() { return workspace_bytes >= swaa::bwd_workspace_floats(p, D) * (long long)sizeof(float); };
+    if (!fits()) {
+        swaa::plan_bwd(p, D, false);  // (whole key tiles need less)
+        if (!fits()) return SWAA_ERR_WORKSPACE;
+    }
 
     FwdParams &f = p.f;
     f.q = static_cast<const __bf16 *>(q);

@@ -46,13 +46,24 @@ struct BwdParams {
     // Key tiles (128 keys) that hold sink keys are seen by every later row.  Their rows
     // beyond the band are cut into n_seg segments of seg_tiles query tiles, each computed
     // by a workgroup of its own; the band part and the segments leave fp32 partial sums in
-    // `partial` ([B*Hkv][n_sink_kt][n_seg + 1][2 (dK, dV)][128][D]) and a last kernel adds them.
+    // `partial` and a last kernel adds them.
     int n_sink_kt, n_seg, seg_tiles;
+    // Where the key tiles are too few for the chip, the (head, query tile) steps of every one are cut into n_split pieces
+    // (plan_bwd), each a workgroup's; then all key tiles leave partial sums: [B*Hkv][key tile][parts][2 (dK, dV)][128][D], the
+    // parts being the pieces, then the segments (of key tiles that have them).
+    int n_split;
+    __host__ __device__ int parts(int kt) const { return kt < n_sink_kt ? n_split + n_seg : n_split > 1 ? n_split : 0; }
+    __host__ __device__ long long first_part(int pair, int kt) const {
+        const int sinks = kt < n_sink_kt ? kt : n_sink_kt, rest = n_split > 1 ? n_split : 0;
+        const int n_kt = (N + 127) / 128;
+        return (long long)pair * (n_sink_kt * (n_split + n_seg) + (n_kt - n_sink_kt) * rest) + sinks * (n_split + n_seg) + (kt - sinks) * rest;
+    }
     float *partial;  // workspace, after delta
 };
 
-// Fills die_shift, n_sink_kt, n_seg, seg_tiles from the shape and mask fields.
-void plan_bwd(BwdParams &p);
+// Fills die_shift, n_sink_kt, n_seg, seg_tiles and n_split from the shape and mask fields.  pieces: key tiles may be cut into
+// pieces (their partial sums take workspace).
+void plan_bwd(BwdParams &p, int D, bool pieces);
 // Floats of workspace the plan needs (delta + partial sums).
 long long bwd_workspace_floats(const BwdParams &p, int D);
 

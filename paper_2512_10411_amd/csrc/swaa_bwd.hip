@@ -19,7 +19,8 @@
 //     dV^T += dO^T P and dK^T += Q^T dS.  Key tiles that hold sink
 //     keys are seen by every later row: their rows beyond the band are cut into
 //     segments with a workgroup each, and
-//   * swaa_bwd_sink_sum_kernel adds the fp32 partial sums of those key tiles.
+//   * swaa_bwd_part_sum_kernel adds the fp32 partial sums of those key tiles.  Where the key tiles are too few for the chip,
+//     their steps are cut into pieces with a workgroup each, and all key tiles have partial sums (plan_pieces).
 // Each product is a v_mfma_f32_32x32x16_bf16 with the accumulator oriented so
 // that the probabilities come out in the B-operand layout of the product that
 // consumes them (as in the forward kernels); operands that a product needs
@@ -271,26 +272,42 @@ __device__ __forceinline__ int dkv_main_item(const BwdParams &p, unsigned bid, i
 // The work list of the dK/dV kernels: first the segments of the sink key tiles (rows beyond the band), then one
 // workgroup per key tile of 128 keys (band rows; for key tiles without sinks also the generated rows).  Under a causal mask
 // the first key tiles are seen by the most rows.
+// Pieces of a key tile (BwdParams::n_split) come in the order key tile, piece, pair: the first key tiles, which are the longest,
+// first, and where the pairs are a multiple of eight each die keeps to its own.
 struct DkvItem {
     int kt, pair;  // key tile, (batch, KV head)
-    int seg;       // -1 for a key tile's main workgroup
+    int seg;       // -1 for a key tile's main workgroups
+    int piece;     // which of them
 };
 __device__ __forceinline__ bool dkv_item(const BwdParams &p, DkvItem &w) {
     const int n_kt = (p.N + 127) / 128;
     const int n_extra = p.B * p.Hkv * p.n_sink_kt * p.n_seg;
     const unsigned bid = blockIdx.x;
+    w.piece = 0;
     if ((int)bid < n_extra) {
         w.seg = bid % p.n_seg;
         w.kt = (bid / p.n_seg) % p.n_sink_kt;
         w.pair = bid / (p.n_seg * p.n_sink_kt);
         return true;
     }
+    w.seg = -1;
+    if (p.n_split > 1) {
+        const unsigned pairs = (unsigned)(p.B * p.Hkv), id = bid - (unsigned)n_extra;
+        w.pair = (int)(id % pairs);
+        w.piece = (int)(id / pairs % (unsigned)p.n_split);
+        w.kt = (int)(id / pairs / (unsigned)p.n_split);
+        return w.kt < n_kt;
+    }
     const int id = dkv_main_item(p, bid, n_extra, n_kt);
     if (id >= p.B * p.Hkv * n_kt) return false;  // (the grid is rounded up to a multiple of eight)
-    w.seg = -1;
     w.kt = id % n_kt;
     w.pair = id / n_kt;
     return true;
+}
+
+// A piece's share [from, to) of its key tile's steps.
+__device__ __forceinline__ int dkv_piece_start(const BwdParams &p, const DkvItem &w, int total, int next) {
+    return w.seg >= 0 ? next * total : (int)((long long)total * (w.piece + next) / p.n_split);
 }
 
 // Its tiles of kBq query rows (head dimension 128): the band, then -- if a key is a sink, or there are generated rows --
@@ -371,7 +388,7 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
     DkvItem item;
     if (!dkv_item(p, item)) return;
     const int kt = item.kt, pair = item.pair, seg = item.seg;
-    const bool sink_kt = kt < p.n_sink_kt;  // results go to the partial-sum workspace
+    const bool sink_kt = kt < p.n_sink_kt;
     const int b = pair / p.Hkv, kvh = pair % p.Hkv;
     const int k0 = kt * 128, k1 = min(k0 + 127, N - 1);  // the workgroup's keys
     const int kw0 = k0 + 32 * kq, kw1 = kw0 + 31;         // this wave's keys
@@ -415,7 +432,7 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
     }
     const int n_band = seg >= 0 ? 0 : band_hi - first + 1;
     const int n_blocks = n_band + max(0, x1 - x0 + 1);  // per query head
-    const int total = G * n_blocks;
+    const int all_blocks = G * n_blocks, from = dkv_piece_start(p, item, all_blocks, 0), total = dkv_piece_start(p, item, all_blocks, 1) - from;
     auto block_of = [&](int i) { return i < n_band ? first + i : x0 + (i - n_band); };
 
     const float c2 = p.f.scale_log2;
@@ -424,7 +441,7 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
     // asked for two steps ahead, in the order of the list; `at` is the next one's place in it.
     const int lrow = 8 * kq + (lane >> 3);
     const uint32_t lchk = (uint32_t)(((lane & 7) ^ ((((lrow >> 1) & 1) << 2) | ((lrow >> 2) & 3))) << 4);
-    int at_head = kvh * G, at = part, at_entry = part, at_buf = 0;
+    int at_head = kvh * G, at = from + part, at_entry = part, at_buf = 0;
     auto request_next = [&]() {  // its row block, or -1 behind the end of the list
         if (at_entry >= total) return -1;
         while (at >= n_blocks) {
@@ -597,9 +614,9 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
     }
     if (part != 0) return;
 
-    if (sink_kt) {
+    if (p.parts(kt) > 0) {
         // fp32 partial sums of all 128 key columns (columns past the end hold zeros)
-        float *slot = p.partial + ((((size_t)pair * p.n_sink_kt + kt) * (p.n_seg + 1) + (seg + 1)) * 2) * (size_t)(128 * D);
+        float *slot = p.partial + (size_t)(p.first_part(pair, kt) + (seg >= 0 ? p.n_split + seg : item.piece)) * (2 * 128 * D);
         float *pk = slot + (size_t)(32 * kq + l32) * D, *pv = pk + 128 * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -637,24 +654,26 @@ __global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kerne
 namespace swaa {
 namespace {
 
-// dK, dV of the sink key tiles: sum of the band part and the segments, in a fixed order.
+// dK, dV of the key tiles that have partial sums (all of them, or those with sinks): pieces, then segments, in this order.
 template <int D>
-__global__ __launch_bounds__(kThreads) void swaa_bwd_sink_sum_kernel(const BwdParams p) {
+__global__ __launch_bounds__(kThreads) void swaa_bwd_part_sum_kernel(const BwdParams p) {
     // one thread per 4 consecutive head-dimension elements of one key
+    const int n_kt = p.n_split > 1 ? (p.N + 127) / 128 : p.n_sink_kt;
     const long long per_kt = 128LL * D / 4;
     const long long idx = (long long)blockIdx.x * kThreads + threadIdx.x;
-    const long long total = (long long)p.B * p.Hkv * p.n_sink_kt * per_kt;
+    const long long total = (long long)p.B * p.Hkv * n_kt * per_kt;
     if (idx >= total) return;
     const int e = (int)(idx % per_kt);
-    const long long kt_id = idx / per_kt;  // pair * n_sink_kt + kt
-    const int kt = (int)(kt_id % p.n_sink_kt);
-    const long long pair = kt_id / p.n_sink_kt;
+    const long long kt_id = idx / per_kt;  // pair * n_kt + kt
+    const int kt = (int)(kt_id % n_kt), pair = (int)(kt_id / n_kt);
     const int key = kt * 128 + e / (D / 4);
     const int d = (e % (D / 4)) * 4;
     if (key >= p.N) return;
-    const float *slot = p.partial + (kt_id * (p.n_seg + 1) * 2) * (size_t)(128 * D) + (size_t)(e / (D / 4)) * D + d;
+    const float *slot = p.partial + (size_t)p.first_part(pair, kt) * (2 * 128 * D) + (size_t)(e / (D / 4)) * D + d;
     float4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s <= p.n_seg; ++s) {
+    const int n = p.parts(kt);
+#pragma unroll 4
+    for (int s = 0; s < n; ++s) {
         const float4 a = *reinterpret_cast<const float4 *>(slot + (size_t)s * 2 * 128 * D);
         const float4 c = *reinterpret_cast<const float4 *>(slot + (size_t)s * 2 * 128 * D + 128 * D);
         sk.x += a.x; sk.y += a.y; sk.z += a.z; sk.w += a.w;
@@ -681,10 +700,13 @@ __global__ __launch_bounds__(kThreads) void swaa_bwd_sink_sum_kernel(const BwdPa
 // With few workgroups the longest one is the time, and where sinks see many rows that is a segment, in which the eight
 // waves keep two busy: 16 heads on 2, 4 sinks, 4096 tokens: window 64 97.8 / 94.9, 128 113 / 112, 256 144 / 148.
 // Generated rows see every key, and their blocks have few edges: they count half.
+// A piece of a key tile (plan_pieces) has a part of its tiles: 500 tokens in six 63.4 / 61.5, 700 in six 71.7 / 70.8, 1000 in four
+// 90.6 / 91.2, 2048 in three 178 / 184; 8 heads on 8, 1000 tokens in two 78.0 / 76.6, 1500 in two 98.3 / 94.1, 2048 120 / 122.
 bool dkv_short(const BwdParams &p) {
     const long long n_main = (long long)p.B * p.Hkv * ((p.N + 127) / 128);
     const int G = p.f.G, all = (p.N + kBq - 1) / kBq, band = (p.f.W + 127) / kBq + 1;
     const int tiles = (band < all ? band : all) + (p.N - p.f.P) / (2 * kBq);
+    if (p.n_split > 1) return tiles <= (G == 1 ? 12 : 3) * p.n_split;
     if (n_main >= 256) return tiles <= (G <= 2 ? 13 : n_main >= 512 ? 10 : 9);
     return tiles <= (G == 1 ? 12 : p.n_seg > 0 ? 4 : G <= 3 ? 8 : 6);
 }
@@ -722,7 +744,7 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     }
     // sink segments first (the longest items), then the key tiles' main workgroups, their number
     // rounded up to a multiple of the die count (dkv_main_item)
-    const long long n_main = (pairs * n_kt + kXcds - 1) / kXcds * kXcds;
+    const long long n_main = p.n_split > 1 ? pairs * n_kt * p.n_split : (pairs * n_kt + kXcds - 1) / kXcds * kXcds;
     const dim3 dkv_grid((unsigned)(pairs * (long long)p.n_sink_kt * p.n_seg + n_main));
     if constexpr (D == 128) {
         if (dkv_short(p))
@@ -732,18 +754,16 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     } else
         hipLaunchKernelGGL(swaa_bwd_dkv_kernel<D>, dkv_grid, dim3(256 * kDkvParts), DkvSmem<D>::kBytes, stream, p);
     err = hipGetLastError();
-    if (err != hipSuccess || p.n_sink_kt == 0) return err;
-    const long long threads = pairs * p.n_sink_kt * (128LL * D / 4);
-    hipLaunchKernelGGL(swaa_bwd_sink_sum_kernel<D>, dim3((unsigned)((threads + kThreads - 1) / kThreads)), dim3(kThreads),
+    if (err != hipSuccess || (p.n_sink_kt == 0 && p.n_split == 1)) return err;
+    const long long threads = pairs * (p.n_split > 1 ? n_kt : p.n_sink_kt) * (128LL * D / 4);
+    hipLaunchKernelGGL(swaa_bwd_part_sum_kernel<D>, dim3((unsigned)((threads + kThreads - 1) / kThreads)), dim3(kThreads),
                        0, stream, p);
     return hipGetLastError();
 }
 
-}  // namespace
-
-void plan_bwd(BwdParams &p) {
+// The segments of the sink key tiles, about as long as an ordinary key tile's band or a piece of it, but at most 512 of them in all.
+void plan_sink_segments(BwdParams &p) {
     const int N = p.N, W = p.f.W, S = p.f.S;
-    p.die_shift = die_shift((long long)p.B * p.Hkv);
     p.n_sink_kt = 0;
     p.n_seg = 0;
     p.seg_tiles = 1;
@@ -753,18 +773,68 @@ void plan_bwd(BwdParams &p) {
     if (S == 0 || first_beyond > tq_last) return;
     p.n_sink_kt = (min(S, N) + 127) / 128;
     const int range = tq_last - first_beyond + 1;
-    // segments about as long as an ordinary key tile's band, but at most 512 of them in all
-    const int band_tiles = (W + 127) / kBq + 1;
-    long long seg = band_tiles;
+    long long seg = ((W + 127) / kBq + p.n_split) / p.n_split;
     const long long groups = (long long)p.B * p.Hkv * p.n_sink_kt;
     while ((range + seg - 1) / seg * groups > 512) seg *= 2;
     p.seg_tiles = (int)seg;
     p.n_seg = (int)((range + seg - 1) / seg);
 }
 
+// Into how many pieces are the key tiles' steps cut?  One workgroup runs on a compute unit, so 64 key tiles (1000 tokens on 8
+// KV heads) leave three quarters of the chip idle, and causal key tiles differ: the first is seen by all rows, the last by few.
+// But every piece leaves 128 KiB of partial sums (head dimension 128) for the last kernel.  The time of a plan, in us: pieces that
+// have a compute unit each take as long as the longest; more of them share the chip evenly but for a third of the longest;
+// a step takes 1.67 (head dimension 64: 1.13), a workgroup six of them outside its loop; the last kernel 4, and a piece's partial sums
+// 0.04 while compute units are idle, then 0.03.  The backward, one piece / as planned / the best of 1 to 8 (us; 4 sinks):
+//    head dimension 128           500 tokens        1000              2048              4096              2048, window 512
+//      32 heads on 8              94 / 61 / 59      156 / 91 / 91     281 / 174 / 174   594 / 471 / 471   135 / 130 / 125
+//      16 heads on 4              95 / 58 / 58      155 / 77 / 77     277 / 136 / 136   528 / 296 / 296   129 / 91 / 91
+//      8 heads on 8               54 / 53 / 53      81 / 79 / 77      134 / 122 / 122   240 / 225 / 225   79 / 79 / 79
+//    head dimension 64
+//      32 heads on 8              65 / 45 / 45      109 / 69 / 69     203 / 124 / 124   409 / 312 / 312   100 / 87 / 82
+//      16 heads on 4              65 / 40 / 40      110 / 61 / 61     201 / 103 / 103   386 / 208 / 208   97 / 66 / 64
+// With 512 key tiles and more the best of one to four is at most 1 % ahead of whole ones, or behind.  Windows without
+// sinks have no partial sums, and callers that know their workspace as delta alone.
+int plan_pieces(BwdParams &p, int D) {
+    const int n_kt = (p.N + 127) / 128, pairs = p.B * p.Hkv, G = p.f.G;
+    if ((long long)pairs * n_kt >= 512 || (p.f.S == 0 && p.f.W < p.N)) return 1;
+    const int all = (p.N + kBq - 1) / kBq, generated = (p.N - p.f.P) / kBq;
+    const int band = min(all, (p.f.W + 126) / kBq + 1), longest = min(all, band + generated);  // query tiles that see a key tile
+    const int full = min(n_kt, (all - band) / 2 + 1);  // key tiles with a whole band; the others have two tiles fewer each time
+    const float tiles = (float)(full * band) + (float)(n_kt - full) * (0.5f * (float)band + 1.f) + (float)(n_kt * generated);
+    float best = 0.f;
+    int pick = 1;
+    for (int n = 1; n <= 8 && (n == 1 || pairs * n_kt * n <= 1024); ++n) {
+        p.n_split = n;
+        plan_sink_segments(p);
+        constexpr float kStart = 6.f;
+        const int units = pairs * (n_kt * n + p.n_sink_kt * p.n_seg);
+        const float seg = p.n_seg ? (float)(p.seg_tiles * G) : 0.f, piece = (float)(longest * G) / (float)n;
+        const float one = (seg > piece ? seg : piece) + kStart;
+        const float steps = (float)(pairs * G) * (tiles + (float)(p.n_sink_kt * p.n_seg * p.seg_tiles));
+        const float shared = (steps + kStart * (float)units) * (1.f / 256.f) + 0.3f * one;
+        float t = (D == 128 ? 1.67f : 1.13f) * (units <= 256 || one > shared ? one : shared);
+        if (n > 1) t += 4.f + (units <= 256 ? 0.04f : 0.03f) * (float)units * (float)D * (1.f / 128.f);
+        // (more pieces than the best so far have to gain 2 %, and any at all 2 us)
+        if (n == 1 || t < 0.98f * best - (pick == 1 ? 2.f : 0.f)) {
+            best = t;
+            pick = n;
+        }
+    }
+    return pick;
+}
+
+}  // namespace
+
+void plan_bwd(BwdParams &p, int D, bool pieces) {
+    p.die_shift = die_shift((long long)p.B * p.Hkv);
+    p.n_split = pieces ? plan_pieces(p, D) : 1;
+    plan_sink_segments(p);
+}
+
 long long bwd_workspace_floats(const BwdParams &p, int D) {
     const long long rows = ((long long)p.B * p.Hq * p.N + 3) / 4 * 4;  // the partial sums start 16-byte aligned
-    return rows + (long long)p.B * p.Hkv * p.n_sink_kt * (p.n_seg + 1) * 2 * 128 * D;
+    return rows + p.first_part(p.B * p.Hkv, 0) * 2 * 128 * D;
 }
 
 hipError_t launch_bwd(const BwdParams &p, int D, hipStream_t stream) {

@@ -137,11 +137,18 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
     const int n_kt = (N + 127) / 128;
     const int n_extra = p.B * p.Hkv * p.n_sink_kt * p.n_seg;
     const unsigned bid = blockIdx.x;
-    int kt, pair, seg;  // seg: -1 for a key tile's main workgroup
+    int kt, pair, seg, piece = 0;  // seg: -1 for a key tile's main workgroups
     if ((int)bid < n_extra) {
         seg = bid % p.n_seg;
         kt = (bid / p.n_seg) % p.n_sink_kt;
         pair = bid / (p.n_seg * p.n_sink_kt);
+    } else if (p.n_split > 1) {
+        const unsigned pairs = (unsigned)(p.B * p.Hkv), id = bid - (unsigned)n_extra;
+        seg = -1;
+        pair = (int)(id % pairs);
+        piece = (int)(id / pairs % (unsigned)p.n_split);
+        kt = (int)(id / pairs / (unsigned)p.n_split);
+        if (kt >= n_kt) return;
     } else {
         const int id = dkv_main_item(p, bid, n_extra, n_kt);
         if (id >= p.B * p.Hkv * n_kt) return;  // (the grid is rounded up to a multiple of eight)
@@ -149,7 +156,7 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
         kt = id % n_kt;
         pair = id / n_kt;
     }
-    const bool sink_kt = kt < p.n_sink_kt;  // results go to the partial-sum workspace
+    const bool sink_kt = kt < p.n_sink_kt;
     const int b = pair / p.Hkv, kvh = pair % p.Hkv;
     const int k0 = kt * 128, k1 = min(k0 + 127, N - 1);  // the workgroup's keys
     const int kw0 = k0 + 64 * kq;                         // this wave's first key
@@ -172,7 +179,11 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
         tq_x = max(tq_band_hi + 1, P / kRows);
     }
     const int n_tiles = n_band + max(0, tq_x_end - tq_x + 1);
-    const int total = G * n_tiles;  // (head, tile) steps, head-major
+    int total = G * n_tiles, from = 0;  // (head, tile) steps, head-major
+    if (p.n_split > 1 && seg < 0) {  // (dkv_piece_start)
+        from = (int)((long long)total * piece / p.n_split);
+        total = (int)((long long)total * (piece + 1) / p.n_split) - from;
+    }
     auto first_row = [&](int n) { return (n < n_band ? tq_lo + n : tq_x + (n - n_band)) * kRows; };
 
     unrolled<256>([](auto r) { acc_clear<decltype(r)::value>(); });
@@ -191,8 +202,8 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
         };
         // The next tile to ask for: its place in its head's list, its first row, its head's rows, where it
         // begins.  Behind the end of the list the last one is asked for again, into buffers that nobody reads any more.
-        int rq_left = total, rq_n = 0, rq_row = first_row(0);
-        size_t rq_base = ((size_t)b * p.Hq + kvh * G) * (size_t)N;
+        int rq_left = total, rq_n = from % n_tiles, rq_row = first_row(rq_n);
+        size_t rq_base = ((size_t)b * p.Hq + kvh * G + from / n_tiles) * (size_t)N;
         const __bf16 *rq_q = p.f.q + (rq_base + rq_row) * kD, *rq_do = p.dout + (rq_base + rq_row) * kD;
         float lreg = 0.f, dlreg = 0.f;
         uint32_t rq_off = 0;
@@ -604,7 +615,8 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
     else
         hand_over(std::integral_constant<int, 0>{});
     __syncthreads();
-    float *slot = p.partial + ((((size_t)pair * p.n_sink_kt + kt) * (p.n_seg + 1) + (seg + 1)) * 2 + (1 - keep)) * (size_t)(128 * kD);
+    const bool partial = p.parts(kt) > 0;
+    float *slot = p.partial + ((size_t)(p.first_part(pair, kt) + (seg >= 0 ? p.n_split + seg : piece)) * 2 + (1 - keep)) * (size_t)(128 * kD);
     const float factor = keep == 1 ? p.f.scale : 1.f;
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
@@ -619,7 +631,7 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
                 for (int e = 0; e < 4; ++e)
                     x[e] = mine[u][db][4 * e4 + e] +
                            *(const float __attribute__((address_space(3))) *)(uintptr_t)(take + (uint32_t)(((d + e) * 64 + 32 * u) * 4));
-                if (sink_kt) {  // fp32 partial sums of all 128 key columns (columns past the end hold zeros)
+                if (partial) {  // fp32 partial sums of all 128 key columns (columns past the end hold zeros)
                     const float4 x4 = {x[0], x[1], x[2], x[3]};
                     *reinterpret_cast<float4 *>(slot + (size_t)col * kD + d) = x4;
                 } else if (key < N) {

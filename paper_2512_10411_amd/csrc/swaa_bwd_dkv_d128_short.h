@@ -47,7 +47,6 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
     DkvItem item;
     if (!dkv_item(p, item)) return;
     const int kt = item.kt, pair = item.pair, seg = item.seg;
-    const bool sink_kt = kt < p.n_sink_kt;  // results go to the partial-sum workspace
     const int b = pair / p.Hkv, kvh = pair % p.Hkv;
     const int k0 = kt * 128;                             // the workgroup's first key
     const int kw0 = k0 + 32 * kq, kw1 = kw0 + 31;         // this wave's keys
@@ -87,12 +86,14 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
 
     const DkvTiles tiles = dkv_tiles(p, item);
     const int n_tiles = tiles.n;
+    const int from = dkv_piece_start(p, item, G * n_tiles, 0);  // this workgroup's (head, tile) steps, head-major
+    const int total = dkv_piece_start(p, item, G * n_tiles, 1) - from;
 
     const float c2 = p.f.scale_log2;
     float lreg = 0.f, dlreg = 0.f;
     // step `st` = (head, query tile): its Q and dO rows into buffer `buf`, its lse and delta into registers
     auto request_tile = [&](int st, int buf) {
-        const int head = kvh * G + st / n_tiles, tq = tiles.at(st % n_tiles);
+        const int head = kvh * G + (from + st) / n_tiles, tq = tiles.at((from + st) % n_tiles);
         const size_t base = ((size_t)b * p.Hq + head) * (size_t)N;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -135,7 +136,6 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
     };
 
-    const int total = G * n_tiles;  // (head, tile) steps, head-major
     if (total > 0) {
         request_tile(0, 0);
         publish_rows(0);
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
         if (has_next) request_tile(step + 1, buf ^ 1);
 
         const uint32_t Qs = (uint32_t)(kQ + buf * kQTileBytes), dOs = (uint32_t)(kDO + buf * kQTileBytes);
-        const int tq = tiles.at(step % n_tiles);
+        const int tq = tiles.at((from + step) % n_tiles);
         const int i0 = tq * kBq + 32 * qb, i1 = i0 + 31;  // this wave's rows of the tile
         // can any of them see any key of this wave?
         const bool sees = (i0 < N) && (i1 >= kw0) && ((i0 < kw1 + W) || (kw0 < S) || (i1 >= P));
@@ -266,9 +266,9 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
     }
     if (qb != 0) return;
 
-    if (sink_kt) {
+    if (p.parts(kt) > 0) {
         // fp32 partial sums of all 128 key columns (columns past the end hold zeros)
-        float *slot = p.partial + ((((size_t)pair * p.n_sink_kt + kt) * (p.n_seg + 1) + (seg + 1)) * 2) * (size_t)(128 * D);
+        float *slot = p.partial + (size_t)(p.first_part(pair, kt) + (seg >= 0 ? p.n_split + seg : item.piece)) * (2 * 128 * D);
         float *pk = slot + (size_t)(32 * kq + l32) * D, *pv = pk + 128 * D;
 #pragma unroll
         for (int db = 0; db < DB; ++db)

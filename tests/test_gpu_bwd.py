@@ -268,3 +268,28 @@ def test_benchmark_workload_at_full_size_two_kv_heads():
         assert_grad("dq", dq[:, hs], rq, tag)
         assert_grad("dk", dk[:, kvh:kvh + 1], rk, tag)
         assert_grad("dv", dv[:, kvh:kvh + 1], rv, tag)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P", [
+    (1, 1, 4, 100, 100, 0, None),    # a single key tile, its pieces shorter than a head's list
+    (1, 2, 5, 129, 129, 4, None),    # the last key tile has one key, and fewer steps than there are pieces
+    (2, 2, 4, 1000, 128, 200, None),  # two key tiles with sinks: pieces and segments
+    (1, 4, 4, 600, 200, 4, 500),     # generated rows behind the band
+    (1, 1, 1, 1500, 1500, 0, None),  # one head: pieces of its list of tiles
+])
+def test_key_tiles_in_pieces(B, Hkv, G, N, W, S, P, D):
+    args = (B, G * Hkv, Hkv, N, D, W, S, N if P is None else P)
+    whole = 4 * (B * G * Hkv * N + 3) // 4 * 4
+    need = binding.swaa_attn_bwd_workspace_bytes(*args)
+    assert need > whole  # partial sums of all key tiles
+    check(B, G * Hkv, Hkv, N, D, W, S, P, seed=9800 + N + D)
+    # a workspace full of NaN patterns gives the same, and so, but for the order of the sums, does one too small for pieces
+    q, k, v, dd = (to_device(x) for x in (*make_qkv(B, G * Hkv, Hkv, N, D, seed=9800 + N + D), make_dout((B, G * Hkv, N, D), 9801 + N + D)))
+    out, lse = binding.swaa_attn_fwd_fa_decode(q, k, v, W, S, args[7])
+    runs = [binding.swaa_attn_bwd(q, k, v, out, lse, dd, W, S, args[7], workspace=torch.full((n,), 255, dtype=torch.uint8, device="cuda"))
+            for n in (need, need, need - 1)]
+    torch.cuda.synchronize()
+    assert all(torch.equal(x, y) for x, y in zip(runs[0], runs[1]))
+    for x, y in zip(runs[0], runs[2]):  # fp32 sums in another order, then one rounding each to bf16
+        assert (x.float() - y.float()).norm() <= 2.0 ** -8 * x.float().norm()
