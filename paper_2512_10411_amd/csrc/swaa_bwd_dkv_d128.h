@@ -577,14 +577,22 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
         // units, the answer is no).
         const int lean_from = kw0 + 63, lean_to = min(N - 32, kw0 + 63 < S ? N : kw0 + W - 32);
         auto lean = [&](int first) { return first >= lean_from && (first <= lean_to || (first >= P && first + 31 < N)); };
+        // (Steps without an edge loop among themselves: where the two versions of the step meet, what they keep in different
+        // registers is moved, 59 instructions that every step paid.  The whole backward, 16384 tokens, 32 heads on 8, window
+        // 2048, 512 generated rows: 2182 -> 2140 us; 8192 tokens, full attention: 1720 -> 1662.)
+        int left = total;
         bool lean_now = lean(i0);
-        for (int left = total; left > 0; --left) {
-            const bool lean_next = lean(i0n);  // (behind the last tile: never used)
-            if (lean_now && lean_next)
-                step(std::false_type{}, left > 1);
-            else
+        while (left > 0) {
+            if (lean_now && lean(i0n)) {
+                do {
+                    step(std::false_type{}, left > 1);
+                    --left;
+                } while (left > 0 && lean(i0n));  // (behind the last tile: never used)
+            } else {
                 step(std::true_type{}, left > 1);
-            lean_now = lean_next;
+                --left;
+                lean_now = lean(i0);
+            }
         }
     }
 
