@@ -26,11 +26,11 @@
 // consumes them (as in the forward kernels); operands that a product needs
 // transposed are read from row-major LDS tiles with ds_read_b64_tr_b16.
 // P and dS are rounded to bf16 before the second products, sums are fp32.
-// The kernels in this file stage tiles through registers (dQ for head dimension 64) or by LDS DMA
-// (dK/dV) and leave instruction scheduling to the compiler, as does dK/dV for head dimension 128 where a key tile is
-// seen by few query tiles (swaa_bwd_dkv_d128_short.h); otherwise dQ (swaa_bwd_dq_pipelined.hip) and dK/dV
-// (swaa_bwd_dkv_d128.h) of head dimension 128 are pipelined by hand.  Waves per SIMD: two (dQ, short dK/dV) or one
-// (dK/dV) for head dimension 128, four or three for 64.
+// dQ for head dimension 64, in this file, stages tiles through registers and leaves instruction scheduling to the compiler,
+// as does dK/dV for head dimension 128 where a key tile is seen by few query tiles (swaa_bwd_dkv_d128_short.h, LDS DMA);
+// otherwise dQ (swaa_bwd_dq_pipelined.hip) and dK/dV (swaa_bwd_dkv_d128.h) of head dimension 128 and dK/dV of 64
+// (swaa_bwd_dkv_d64.h) are pipelined by hand.  Waves per SIMD: two (dQ, short dK/dV) or one (dK/dV) for head
+// dimension 128, four (dQ) and two (dK/dV) for 64.
 #include <atomic>
 #include <cmath>
 
@@ -344,312 +344,12 @@ __device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(uintptr_t)addr);
 }
 
-// ---- dK, dV, head dimension 64 ----------------------------------------------------------
-// Wave w owns the 32 keys 32 (w % 4).. of the workgroup's 128, whose K and V rows stay in its registers
-// (B operands of S = Q K^T and dP = dO V^T), and every kDkvParts-th block of 32 query rows of the work
-// list (query head, row block): the four waves of part w / 4 copy that block's Q and dO rows to LDS
-// (global_load_lds_dwordx4, three buffers, one barrier per step) and read them row-wise and
-// transposed.  The parts are added through LDS at the end.  Rows are 128 bytes without padding;
-// 16-byte chunk c of row r lies at chunk c ^ f(r), f(r) = (((r >> 1) & 1) << 2) | ((r >> 2) & 3), applied on
-// the global side of the copy: conflict-free for 16 consecutive rows reading one logical chunk and
-// for 4 consecutive rows reading the same 64 bytes.
-// A short sequence has few key tiles (two of 4001 tokens on 4 KV heads: 256, one per compute
-// unit), so the waves that hide each other's latencies have to come from one workgroup: three per
-// SIMD with 168 registers each.  (Two parts, K and V read from LDS, tiles staged through registers with
-// two barriers a step: 139 us for those sequences; now 126, and 138 with two parts.  Each step is a
-// phase of matrix work, one of vector work and one of matrix work again for all waves at once; the
-// priorities by part pull them apart a little: 133 -> 126.)
-// This kernel declares no static LDS: its dynamic LDS starts at address 0.
-constexpr int kDkvParts = 3;
-constexpr float kLog2e = 1.44269504088896340736f;
-template <int D>
-struct DkvSmem {
-    static constexpr int kRowBytes = D * 2;
-    static constexpr int kBlockBytes = 32 * kRowBytes;            // 32 rows of Q, or of dO
-    static constexpr int kPartBytes = 2 * kBlockBytes + 64 * 4;   // Q, dO, lse and delta of the rows
-    static constexpr int kBufferBytes = kDkvParts * kPartBytes;
-    static constexpr int kSumBytes = 4 * 32 * D * 4;              // the final sum: one part's dK or dV
-    static constexpr int kBuffers = 3;
-    static constexpr int kLse = kBuffers * kBufferBytes;          // every wave's copy of a block's lse (edge blocks)
-    static constexpr int kEnd = kLse + 4 * kDkvParts * 32 * 4;
-    static constexpr int kBytes = kEnd > kSumBytes ? kEnd : kSumBytes;
-};
-
-template <int D>
-__global__ __launch_bounds__(256 * kDkvParts, kDkvParts) void swaa_bwd_dkv_kernel(const BwdParams p) {
-    static_assert(D == 64, "the swizzle below is for rows of 128 bytes");
-    using M = DkvSmem<D>;
-    constexpr int KS = D / 16, DB = D / 32;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-    const int N = p.N, W = p.f.W, S = p.f.S, P = p.f.P, G = p.f.G;
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
-    const int kq = wave & 3, part = wave >> 2;
-    DkvItem item;
-    if (!dkv_item(p, item)) return;
-    const int kt = item.kt, pair = item.pair, seg = item.seg;
-    const bool sink_kt = kt < p.n_sink_kt;
-    const int b = pair / p.Hkv, kvh = pair % p.Hkv;
-    const int k0 = kt * 128, k1 = min(k0 + 127, N - 1);  // the workgroup's keys
-    const int kw0 = k0 + 32 * kq, kw1 = kw0 + 31;         // this wave's keys
-    const int key = kw0 + l32;                            // this lane's key column
-    const bool wave_active = kw0 < N;
-
-    // this wave's K and V rows as B operands (rows past the end repeat the last key; they stay invisible)
-    bf16x8 kf[KS], vf[KS];
-    {
-        const size_t g = (((size_t)b * p.Hkv + kvh) * (size_t)N + min(key, N - 1)) * D + 8 * hf;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            kf[ks] = *reinterpret_cast<const bf16x8 *>(p.f.k + g + 16 * ks);
-            vf[ks] = *reinterpret_cast<const bf16x8 *>(p.f.v + g + 16 * ks);
-        }
-    }
-    f32x16 dkacc[DB], dvacc[DB];
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            dkacc[db][e] = 0.f;
-            dvacc[db][e] = 0.f;
-        }
-
-    // Row blocks (32 rows) with a row that sees one of the workgroup's keys: the band blocks, then
-    // -- if a key is a sink, or there are generated rows -- the rest.  For a sink key tile the
-    // rest is cut into segments of seg_tiles 64-row tiles, and the main workgroup keeps the band.
-    const int last_block = (N - 1) / 32;
-    const int first = k0 / 32;
-    int band_hi = min(N - 1, k1 + W - 1) / 32;
-    int x0 = last_block + 1, x1 = last_block;  // second range
-    if (sink_kt) {
-        band_hi = min(band_hi | 1, last_block);  // (the segments start at a whole tile)
-        if (seg >= 0) {
-            x0 = band_hi + 1 + 2 * seg * p.seg_tiles;
-            x1 = min(last_block, x0 + 2 * p.seg_tiles - 1);
-        }
-    } else if (P < N) {
-        x0 = max(band_hi + 1, P / 32);
-    }
-    const int n_band = seg >= 0 ? 0 : band_hi - first + 1;
-    const int n_blocks = n_band + max(0, x1 - x0 + 1);  // per query head
-    const int all_blocks = G * n_blocks, from = dkv_piece_start(p, item, all_blocks, 0), total = dkv_piece_start(p, item, all_blocks, 1) - from;
-    auto block_of = [&](int i) { return i < n_band ? first + i : x0 + (i - n_band); };
-
-    const float c2 = p.f.scale_log2;
-    // A block's rows into LDS: one instruction of 8 rows x 128 bytes per wave for Q and for dO, and one of
-    // 32 lse and 32 delta by the part's first wave (all of them counted together by vmcnt).  Blocks are
-    // asked for two steps ahead, in the order of the list; `at` is the next one's place in it.
-    const int lrow = 8 * kq + (lane >> 3);
-    const uint32_t lchk = (uint32_t)(((lane & 7) ^ ((((lrow >> 1) & 1) << 2) | ((lrow >> 2) & 3))) << 4);
-    int at_head = kvh * G, at = from + part, at_entry = part, at_buf = 0;
-    auto request_next = [&]() {  // its row block, or -1 behind the end of the list
-        if (at_entry >= total) return -1;
-        while (at >= n_blocks) {
-            at -= n_blocks;
-            ++at_head;
-        }
-        const int block = block_of(at);
-        const size_t base = ((size_t)b * p.Hq + at_head) * (size_t)N;
-        const size_t row = base + min(block * 32 + lrow, N - 1);
-        const char *gq = reinterpret_cast<const char *>(p.f.q + row * D) + lchk;
-        const char *gd = reinterpret_cast<const char *>(p.dout + row * D) + lchk;
-        const uint32_t lds = (uint32_t)(at_buf * M::kBufferBytes + part * M::kPartBytes);
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gq), "s"(lds + (uint32_t)(kq * 1024)) : "memory");
-        asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gd), "s"(lds + (uint32_t)(M::kBlockBytes + kq * 1024)) : "memory");
-        if (kq == 0) {
-            const float *gl = (hf ? p.delta : p.f.lse) + base + min(block * 32 + l32, N - 1);
-            asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(gl), "s"(lds + (uint32_t)(2 * M::kBlockBytes)) : "memory");
-        }
-        at += kDkvParts;
-        at_entry += kDkvParts;
-        at_buf = at_buf == M::kBuffers - 1 ? 0 : at_buf + 1;
-        return block;
-    };
-    // The copies of all but the newest block (none, if that was not asked for) have landed: this wave's,
-    // then everybody's.
-    auto step_end = [&](bool newest) {
-        if (!newest)
-            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        else if (kq == 0)
-            __builtin_amdgcn_s_waitcnt(0x0F73);  // vmcnt(3)
-        else
-            __builtin_amdgcn_s_waitcnt(0x0F72);  // vmcnt(2)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    };
-
-    // per-lane fragment addresses inside a block (swizzle folded in)
-    //  * row fragment, k-step ks: row l32, logical chunk 2 ks + hf:  row_lane ^ (ks << 5)
-    //  * transposed fragment, 16-row step st, head-dimension block db: rows 16 st + 4 hf + j16 / 4 (lo) and
-    //    8 further (hi), logical chunk 4 db + 2 (grp & 1) + (j16 & 3) / 2:  col_lane ^ (db << 6), + rows
-    const uint32_t row_lane = (uint32_t)(l32 * M::kRowBytes + ((hf ^ ((((l32 >> 1) & 1) << 2) | ((l32 >> 2) & 3))) << 4));
-    const int grp = lane >> 4, j16 = lane & 15;
-    const int rr = 4 * hf + (j16 >> 2);
-    const int cl = 2 * (grp & 1) + ((j16 & 3) >> 1);
-    const uint32_t col_lo = (uint32_t)(rr * M::kRowBytes + ((((j16 >> 3) << 2) | (cl ^ hf)) << 4) + 8 * (j16 & 1));
-    const uint32_t col_hi = (uint32_t)((rr + 8) * M::kRowBytes + ((((j16 >> 3) << 2) | (cl ^ (hf + 2))) << 4) + 8 * (j16 & 1));
-    auto row_frag_at = [&](uint32_t tile, int ks) { return lds16(tile + (row_lane ^ (uint32_t)(ks << 5))); };
-    auto col_frag_at = [&](uint32_t tile, int st, int db) {
-        const uint32_t off = tile + (uint32_t)(16 * st * M::kRowBytes);
-        const s16x4 lo = lds8_tr(off + (col_lo ^ (uint32_t)(db << 6)));
-        const s16x4 hi = lds8_tr(off + (col_hi ^ (uint32_t)(db << 6)));
-        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-    };
-
-    const int steps = (total + kDkvParts - 1) / kDkvParts;
-    if (part == 0)
-        __builtin_amdgcn_s_setprio(2);
-    else if (part == 1)
-        __builtin_amdgcn_s_setprio(1);
-    int block = request_next(), next = request_next(), buf = 0;
-    step_end(next >= 0);  // (K and V of the wave are older than both)
-
-    for (int step = 0; step < steps; ++step) {
-        // (the buffer of the block after next was last read a step ago, in front of that step's barrier)
-        const int after = request_next();
-
-        const uint32_t Qs = (uint32_t)(buf * M::kBufferBytes + part * M::kPartBytes);
-        const uint32_t dOs = Qs + (uint32_t)M::kBlockBytes, Ls = dOs + (uint32_t)M::kBlockBytes;
-        const int i0 = block * 32, i1 = i0 + 31;
-        // can any of the rows see any key of this wave?
-        const bool sees = block >= 0 && (i1 >= kw0) && ((i0 < kw1 + W) || (kw0 < S) || (i1 >= P));
-        if (wave_active && sees) {
-            // all 32 x 32 pairs visible: rows at or below the keys' diagonal, inside every row's window
-            // (or the keys are sinks, or the rows are generated tokens), and no row past the end
-            const bool unmasked = (kw1 <= i0) && (i1 < N) && ((i1 - kw0 < W) || (kw1 < S) || (i0 >= P));
-
-            // S = Q K^T and dP = dO V^T : [32 queries] x [32 keys]
-            f32x16 sacc, dpacc;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                sacc[e] = 0.f;
-                dpacc[e] = 0.f;
-            }
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag_at(Qs, ks), kf[ks], sacc, 0, 0, 0);
-                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag_at(dOs, ks), vf[ks], dpacc, 0, 0, 0);
-                if (ks % 2) __builtin_amdgcn_sched_barrier(0);  // (four operand reads in flight: more do not fit)
-            }
-
-            // P and dS in the accumulator layout (row 8 (e/4) + 4 hf + e%4, column = this lane's key); a
-            // score that must not be seen becomes -inf, its P an exact 0
-            // (A row whose lse is not a number, or -inf, must not reach keys that it does not see, and exp2(-inf - NaN) is
-            // NaN: with an lse of -1e38 in its place, P is 0 there and infinite where the row does see the key.  A
-            // copy of the wave's own takes it.)
-            uint32_t lse_at = Ls;
-            if (!unmasked) {
-                lse_at = (uint32_t)(M::kLse + wave * 128);
-                const uint32_t bits = *(const uint32_t __attribute__((address_space(3))) *)(uintptr_t)(Ls + 4 * l32);
-                const bool sound = (bits & 0x7fffffffu) <= 0x7f800000u && bits != 0xff800000u;
-                *(uint32_t __attribute__((address_space(3))) *)(uintptr_t)(lse_at + 4 * l32) = sound ? bits : 0xfe967699u;
-                asm volatile("" ::: "memory");
-#pragma unroll
-                for (int e = 0; e < 16; ++e)
-                    sacc[e] = visible_in_range(i0 + 8 * (e / 4) + 4 * hf + e % 4, key, N, W, S, P) ? sacc[e] : -INFINITY;
-            }
-            bf16x8 pf[2], dsf[2];  // [16-row step]
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                const int r4 = 8 * e4 + 4 * hf;
-                typedef float f32x4 __attribute__((ext_vector_type(4)));
-                const f32x4 lv = *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)(lse_at + r4 * 4);
-                const f32x4 dv4 = *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)(Ls + 128 + r4 * 4);
-#pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const int e = 4 * e4 + x;
-                    const float pe = __builtin_amdgcn_exp2f(fmaf(sacc[e], c2, -kLog2e * lv[x]));
-                    pf[e / 8][e % 8] = (__bf16)pe;
-                    dsf[e / 8][e % 8] = (__bf16)(pe * (dpacc[e] - dv4[x]));
-                }
-            }
-
-            // dV^T += dO^T P,  dK^T += Q^T dS
-#pragma unroll
-            for (int st = 0; st < 2; ++st)
-#pragma unroll
-                for (int db = 0; db < DB; ++db) {
-                    dvacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag_at(dOs, st, db), pf[st], dvacc[db], 0, 0, 0);
-                    dkacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag_at(Qs, st, db), dsf[st], dkacc[db], 0, 0, 0);
-                }
-        }
-        step_end(after >= 0);
-        block = next;
-        next = after;
-        buf = buf == M::kBuffers - 1 ? 0 : buf + 1;
-    }
-
-    // ---- add the parts: the waves of part 1, 2, .. hand their sums to part 0 through LDS ----
-    float *xbuf = reinterpret_cast<float *>(smem);  // [4 key blocks][D][32 key columns]
-#pragma unroll 1
-    for (int from = 1; from < kDkvParts; ++from) {
-#pragma unroll
-        for (int which = 0; which < 2; ++which) {
-            if (part == from) {
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int d = 32 * db + 8 * (e / 4) + 4 * hf + (e % 4);
-                        xbuf[(kq * D + d) * 32 + l32] = which == 0 ? dkacc[db][e] : dvacc[db][e];
-                    }
-            }
-            __syncthreads();
-            if (part == 0) {
-#pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int d = 32 * db + 8 * (e / 4) + 4 * hf + (e % 4);
-                        const float other = xbuf[(kq * D + d) * 32 + l32];
-                        if (which == 0)
-                            dkacc[db][e] += other;
-                        else
-                            dvacc[db][e] += other;
-                    }
-            }
-            __syncthreads();
-        }
-    }
-    if (part != 0) return;
-
-    if (p.parts(kt) > 0) {
-        // fp32 partial sums of all 128 key columns (columns past the end hold zeros)
-        float *slot = p.partial + (size_t)(p.first_part(pair, kt) + (seg >= 0 ? p.n_split + seg : item.piece)) * (2 * 128 * D);
-        float *pk = slot + (size_t)(32 * kq + l32) * D, *pv = pk + 128 * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                const float4 k4 = {dkacc[db][4 * e4], dkacc[db][4 * e4 + 1], dkacc[db][4 * e4 + 2], dkacc[db][4 * e4 + 3]};
-                const float4 v4 = {dvacc[db][4 * e4], dvacc[db][4 * e4 + 1], dvacc[db][4 * e4 + 2], dvacc[db][4 * e4 + 3]};
-                *reinterpret_cast<float4 *>(pk + 32 * db + 8 * e4 + 4 * hf) = k4;
-                *reinterpret_cast<float4 *>(pv + 32 * db + 8 * e4 + 4 * hf) = v4;
-            }
-    } else if (key < N) {
-        const size_t row = (((size_t)b * p.Hkv + kvh) * (size_t)N + key) * D;
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int e4 = 0; e4 < 4; ++e4) {
-                bf16x4 k4, v4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    k4[e] = (__bf16)(dkacc[db][4 * e4 + e] * p.f.scale);
-                    v4[e] = (__bf16)dvacc[db][4 * e4 + e];
-                }
-                *reinterpret_cast<bf16x4 *>(p.dk + row + 32 * db + 8 * e4 + 4 * hf) = k4;
-                *reinterpret_cast<bf16x4 *>(p.dv + row + 32 * db + 8 * e4 + 4 * hf) = v4;
-            }
-    }
-}
-
 }  // namespace
 }  // namespace swaa
 
 #include "swaa_bwd_dkv_d128.h"        // dK, dV, head dimension 128
 #include "swaa_bwd_dkv_d128_short.h"  // ... of few query tiles per key tile
+#include "swaa_bwd_dkv_d64.h"         // dK, dV, head dimension 64
 
 namespace swaa {
 namespace {
@@ -737,7 +437,7 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
                                           hipFuncAttributeMaxDynamicSharedMemorySize, dkv128short::kBytes);
         } else {
             err = hipFuncSetAttribute(reinterpret_cast<const void *>(&swaa_bwd_dkv_kernel<D>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, DkvSmem<D>::kBytes);
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, dkv64::kBytes);
         }
         if (err != hipSuccess) return err;
         configured.fetch_or(bit, std::memory_order_release);
@@ -752,7 +452,7 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
         else
             hipLaunchKernelGGL(swaa_bwd_dkv_dma_kernel, dkv_grid, dim3(dkv128::kThreads), dkv128::kBytes, stream, p);
     } else
-        hipLaunchKernelGGL(swaa_bwd_dkv_kernel<D>, dkv_grid, dim3(256 * kDkvParts), DkvSmem<D>::kBytes, stream, p);
+        hipLaunchKernelGGL(swaa_bwd_dkv_kernel<D>, dkv_grid, dim3(dkv64::kThreads), dkv64::kBytes, stream, p);
     err = hipGetLastError();
     if (err != hipSuccess || (p.n_sink_kt == 0 && p.n_split == 1)) return err;
     const long long threads = pairs * (p.n_split > 1 ? n_kt : p.n_sink_kt) * (128LL * D / 4);

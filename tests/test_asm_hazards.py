@@ -227,3 +227,35 @@ def test_dkv_kernel_of_head_dimension_128_keeps_the_wait_states_and_its_accumula
             wait_states += int(pops[0]) + 1 if pop == "s_nop" else 1
     late = result_hazards(insts, labels)
     assert not late, late[:5]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
+                    reason="hipcc not available")
+def test_dkv_kernel_of_head_dimension_64_keeps_the_wait_states(tmp_path):
+    """The two rules above for swaa_bwd_dkv_kernel<64>, whose file holds kernels of compiler builtins as well."""
+    out = tmp_path / "b.s"
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    cmd = [build.hipcc_path(), *flags, "--cuda-device-only", "-S", "-o", str(out), os.path.join(build.CSRC, "swaa_bwd.hip")]
+    subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    lines = open(out).read().splitlines()
+    first = next(i for i, ln in enumerate(lines) if re.match(r"_Z\S*bwd_dkv_kernelILi64\S*:", ln))
+    insts, labels = [], {}
+    for ln in lines[first:next(i for i in range(first, len(lines)) if lines[i].startswith(".Lfunc_end"))]:
+        m = re.match(r"^(\.LBB\d+_\d+):", ln)
+        if m:
+            labels[m.group(1)] = len(insts)
+        p = parse(ln)
+        if p:
+            insts.append(p)
+    mfmas = [i for i, (op, _) in enumerate(insts) if op.startswith("v_mfma")]
+    assert len(mfmas) == 48  # the first block's scores, two sub-steps, the last block's sums
+    for i in mfmas:
+        srcs = set().union(*[reg_set(t) for t in insts[i][1][1:]])
+        wait_states = 0
+        for pop, pops in reversed(insts[max(0, i - 3):i]):
+            if wait_states >= 2:
+                break
+            assert not (is_valu_write(pop) and pops and reg_set(pops[0]) & srcs), ((pop, pops), insts[i])
+            wait_states += int(pops[0]) + 1 if pop == "s_nop" else 1
+    late = result_hazards(insts, labels)
+    assert not late, late[:5]
