@@ -528,6 +528,8 @@ int plan_pieces(BwdParams &p, int D) {
 
 void plan_bwd(BwdParams &p, int D, bool pieces) {
     p.die_shift = die_shift((long long)p.B * p.Hkv);
+    // (one workgroup of dQ to a compute unit: in the order of their lengths; two sequences of 2048 tokens 275 us folded, 262)
+    if (D == 128) p.f.fold = 0x7fffffff;
     p.n_split = pieces ? plan_pieces(p, D) : 1;
     plan_sink_segments(p);
 }

@@ -84,7 +84,8 @@ struct FwdParams {
     FastDiv div_tiles_per_pair, div_hkv, div_nt_h4;  // for the work-list decode of every workgroup
     FastDiv div_page;  // page_size (paged caches)
     int tiles_per_pair;
-    int die_shift, die_items;  // which items a die takes (plan_work)
+    int die_shift, die_pairs, die_items, fold;  // which items a die takes, and in which order (plan_work)
+    FastDiv div_die_pairs;
     long long total_items;
     long long chunk;  // work items per XCD
     // Packed batches whose total number of query rows the caller has stated: the work list holds
@@ -243,19 +244,25 @@ __device__ __forceinline__ bool decode_work_packed(const FwdParams &p, WorkItem 
 
 // Workgroups reach the 8 XCDs round-robin; XCD x takes the x-th contiguous
 // chunk of the work list, so the position tiles of one KV head, whose K/V
-// bands overlap, run behind the same L2.  Inside a pair, long rows go first; where several XCDs
-// share a pair whose tiles differ in length, they take them in turn (plan_work).
-__device__ __forceinline__ bool decode_work(const FwdParams &p, WorkItem &w) {
-    if (p.packed_compact) return decode_work_packed(p, w);
+// bands overlap, run behind the same L2.  Inside a pair, long rows go first; what changes where rows differ
+// in length is decided in plan_work.  Workgroup bid's pair and place in that pair's list of tiles:
+__host__ __device__ __forceinline__ bool work_place(const FwdParams &p, unsigned bid, unsigned &pair, unsigned &r) {
     // (the entry points refuse work lists of 2^31 items or more: 32-bit arithmetic, whose
     // divisions cost a fraction of the 64-bit ones -- every wave of every workgroup pays them)
-    const unsigned bid = blockIdx.x;
     const unsigned xcd = bid % kXcds, sub = xcd & ((1u << p.die_shift) - 1u);
-    const unsigned off = ((bid / kXcds) << p.die_shift) + sub, item = (xcd >> p.die_shift) * (unsigned)p.die_items + off;
-    if (off >= (unsigned)p.die_items || item >= (unsigned)p.total_items) return false;
-    const unsigned tpp = (unsigned)p.tiles_per_pair, hkv = (unsigned)p.Hkv;
-    const unsigned pair = fastdiv(item, p.div_tiles_per_pair);
-    unsigned r = item - pair * tpp;
+    const unsigned slot = bid / kXcds, place = slot >= (unsigned)p.fold ? (unsigned)p.chunk - 1u - (slot - (unsigned)p.fold) : slot;
+    const unsigned off = (place << p.die_shift) + sub, of_pair = fastdiv(off, p.div_die_pairs);
+    const unsigned item = ((xcd >> p.die_shift) * (unsigned)p.die_pairs + (off - of_pair * (unsigned)p.die_pairs)) * (unsigned)p.die_items + of_pair;
+    if (of_pair >= (unsigned)p.die_items || item >= (unsigned)p.total_items) return false;
+    pair = fastdiv(item, p.div_tiles_per_pair);
+    r = item - pair * (unsigned)p.tiles_per_pair;
+    return true;
+}
+__device__ __forceinline__ bool decode_work(const FwdParams &p, WorkItem &w) {
+    if (p.packed_compact) return decode_work_packed(p, w);
+    unsigned pair, r;
+    if (!work_place(p, blockIdx.x, pair, r)) return false;
+    const unsigned hkv = (unsigned)p.Hkv;
     w.b = (int)fastdiv(pair, p.div_hkv);
     w.kvh = (int)(pair - (unsigned)w.b * hkv);
     const unsigned nt4 = (unsigned)p.nt_h4, nt2 = (unsigned)p.nt_h2;
@@ -285,10 +292,17 @@ inline int die_shift(long long pairs) { return pairs == 1 ? 3 : pairs == 2 ? 2 :
 
 // Fills the work-decomposition fields (everything from wg_rows on) for sequences of
 // `rows` query rows; needs B, Hkv, G, Nk, W and P.  False if the work list does not fit 31 bits.
-// Dies that share a pair take its tiles in turn if the rows differ much in length (a window of half the keys and more, or
-// generated rows behind a prompt): with a contiguous part each, one has the long rows and the others are done
-// early (16 heads on 4, full attention, 8192 tokens 281 us, in turn 254; window 8192 of 16384 776, 716).  Rows of one length stay
-// in contiguous parts, whose bands one L2 holds (4 heads on 1, window 2048, 65536 tokens 250 us, in turn 305).
+// Where the rows differ much in length (a window of half the keys and more, or generated rows behind a prompt):
+//   * dies that share a pair take its tiles in turn: with a contiguous part each, one has the long rows and the others are done
+//     early (16 heads on 4, full attention, 8192 tokens 281 us, in turn 254; window 8192 of 16384 776, 716);
+//   * a die with several pairs takes the long rows of all of them first, not pair after pair (four sequences of 2048 tokens,
+//     32 heads on 8: 139 -> 134, head dimension 64 101 -> 86; four of 4096, 40 heads on 8: 639 -> 617; its backward
+//     2277 -> 2215).  Not with more than 192 tiles to a pair, whose keys no longer share the L2 (two of 8192: 934, 951);
+//   * where a die's list is one round of two workgroups to a compute unit, its second half is turned round, so that the longest
+//     is not beside the longest of the rest but beside the shortest (2048 tokens 44.8 -> 41.7; four sequences of 500 21.2 ->
+//     18.1, two of 4000, 8 heads on 8, 90.8 -> 74.2; with the line above).
+// Rows of one length stay in contiguous parts, whose bands one L2 holds (4 heads on 1, window 2048, 65536 tokens
+// 250 us, in turn 305).
 inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     p.wg_rows = wg_rows;
     p.n4 = p.G / 4;
@@ -307,7 +321,11 @@ inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     p.chunk = (p.total_items + kXcds - 1) / kXcds;
     const int shift = die_shift((long long)p.B * p.Hkv);
     p.die_shift = rows_differ ? shift : 0;
-    p.die_items = p.die_shift ? p.tiles_per_pair : (int)p.chunk;  // (ceil(die_items / dies) is chunk)
+    const long long pairs = (long long)p.B * p.Hkv;
+    p.die_pairs = rows_differ && pairs % kXcds == 0 && p.tiles_per_pair <= 192 ? (int)(pairs / kXcds) : 1;
+    p.div_die_pairs = make_fastdiv((unsigned)p.die_pairs);
+    p.die_items = p.die_shift || p.die_pairs > 1 ? p.tiles_per_pair : (int)p.chunk;  // (times die_pairs, shared by the dies: chunk)
+    p.fold = p.chunk <= 64 && rows_differ && p.n4 + p.has2 + p.has1 == 1 ? 32 : 0x7fffffff;
     return p.chunk * kXcds <= 0x7fffffffLL;
 }
 
