@@ -153,8 +153,35 @@ def swaa_visible_pairs_fa_decode(N: int, window: int, n_sink: int, n_prompt: int
 
 # What surrounds a launch costs more than the smallest kernels run for: a prompt of 64 tokens took 15 us
 # a call, all of it host time.  Switching to the device that is current already and building a stream
-# object only to read its handle were 5 of them.
+# object only to read its handle were 5 of them.  Of the 9.8 left, the library's call takes 3.7 and the results' memory 2.5;
+# checks that build no shape and device objects, no context for the device that is current, and one call
+# instead of four on the way to the library took the rest from 6.0 to 4.5 with the memory (decode 6.3 to 4.4).
 _SAME_DEVICE = contextlib.nullcontext()
+
+
+def _torch():
+    """torch, imported with the first call that has tensors."""
+    global torch
+    import torch
+    return torch
+
+
+torch = None
+
+
+def _contiguous_bf16(torch, q, k, v):
+    """Raises what is wrong with the q, k, v of a call that takes contiguous bf16 [B, H, N, D] GPU tensors, if anything is."""
+    bf16 = torch.bfloat16
+    if (q.dtype is bf16 and k.dtype is bf16 and v.dtype is bf16 and q.is_cuda and k.is_cuda and v.is_cuda
+            and q.is_contiguous() and k.is_contiguous() and v.is_contiguous() and q.dim() == k.dim() == v.dim() == 4):
+        return
+    for name, t in (("q", q), ("k", k), ("v", v)):
+        if t.dtype != bf16:
+            raise TypeError(f"{name} must be bfloat16")
+        if not t.is_cuda:
+            raise ValueError(f"{name} must live on the GPU")
+        if not t.is_contiguous() or t.dim() != 4:
+            raise ValueError(f"{name} must be a contiguous [B, H, N, D] tensor")
 
 
 def _on_device_of(t):
@@ -232,42 +259,45 @@ def swaa_attn_fwd_fa_decode(q, k, v, window: int, n_sink: int, n_prompt: int, sc
 
 
 def _fwd(q, k, v, window, n_sink, n_prompt, scale, out, lse, stream):
-    import torch
-
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != torch.bfloat16:
-            raise TypeError(f"{name} must be bfloat16")
-        if not t.is_cuda:
-            raise ValueError(f"{name} must live on the GPU")
-        if not t.is_contiguous() or t.dim() != 4:
-            raise ValueError(f"{name} must be a contiguous [B, H, N, D] tensor")
+    tc = torch or _torch()
+    _contiguous_bf16(tc, q, k, v)
     B, Hq, N, D = q.shape
-    if k.shape != v.shape or k.shape[0] != B or k.shape[2] != N or k.shape[3] != D:
+    Bk, Hkv, Nk, Dk = k_shape = k.shape
+    if k_shape != v.shape or Bk != B or Nk != N or Dk != D:
         raise ValueError("k and v must be [B, Hkv, N, D] with q's B, N, D")
-    if k.device != q.device or v.device != q.device:
+    dev = q.get_device()
+    if k.get_device() != dev or v.get_device() != dev:
         raise ValueError("q, k, v must be on the same device")
-    Hkv = k.shape[1]
     if scale is None:
         scale = 1.0 / math.sqrt(D)
+    if stream is None and tc._C._cuda_getDevice() == dev:
+        return _fwd_here(tc, q, k, v, out, lse, B, Hq, Hkv, N, D, window, n_sink, n_prompt, scale, None)
     caller = None if stream is None else _stream_handle(None, q)
     with _on_device_of(q) if stream is None else _launching_on(stream, q):
-        if out is None:
-            out = torch.empty_like(q)
-        elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
-            raise ValueError("out must be a contiguous bf16 tensor shaped like q")
-        if lse is None:
-            lse = torch.empty((B, Hq, N), dtype=torch.float32, device=q.device)
-        elif lse.shape != (B, Hq, N) or lse.dtype != torch.float32 or not lse.is_contiguous():
-            raise ValueError("lse must be a contiguous fp32 [B, Hq, N] tensor")
-        sptr = _stream_handle(stream, q)
-        ptrs = (q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr())
-        if n_prompt is None:
-            rc = swaa_attn_fwd_raw(*ptrs, B, Hq, Hkv, N, D, int(window), int(n_sink), float(scale), sptr)
-        else:
-            rc = swaa_attn_fwd_fa_decode_raw(*ptrs, B, Hq, Hkv, N, D, int(window), int(n_sink), n_prompt,
-                                             float(scale), sptr)
+        out, lse = _fwd_here(tc, q, k, v, out, lse, B, Hq, Hkv, N, D, window, n_sink, n_prompt, scale, stream)
         if stream is not None:
             _returned_to(caller, out, lse)
+    return out, lse
+
+
+def _fwd_here(tc, q, k, v, out, lse, B, Hq, Hkv, N, D, window, n_sink, n_prompt, scale, stream):
+    """The forward on q's device and `stream`, which are current."""
+    if out is None:
+        out = tc.empty_like(q)
+    elif out.shape != q.shape or out.dtype != tc.bfloat16 or not out.is_contiguous():
+        raise ValueError("out must be a contiguous bf16 tensor shaped like q")
+    if lse is None:
+        lse = tc.empty_strided((B, Hq, N), (Hq * N, N, 1), dtype=tc.float32, device=q.device)
+    elif lse.shape != (B, Hq, N) or lse.dtype != tc.float32 or not lse.is_contiguous():
+        raise ValueError("lse must be a contiguous fp32 [B, Hq, N] tensor")
+    sptr = tc._C._cuda_getCurrentRawStream(q.get_device()) if stream is None else _stream_handle(stream, q)
+    lib = _lib or load_library()
+    if n_prompt is None:
+        rc = lib.swaa_attn_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
+                               B, Hq, Hkv, N, D, int(window), int(n_sink), float(scale), sptr)
+    else:
+        rc = lib.swaa_attn_fwd_fa_decode(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
+                                         B, Hq, Hkv, N, D, int(window), int(n_sink), n_prompt, float(scale), sptr)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return out, lse
@@ -299,45 +329,50 @@ def swaa_attn_decode(q, k, v, window: int, n_sink: int, scale: float | None = No
     uint8 tensor of at least swaa_attn_decode_workspace_bytes(...) bytes (allocated
     here with torch when None).  Returns (out bf16 [B, Hq, Nq, D], lse fp32 [B, Hq, Nq]).
     """
-    import torch
-
-    for name, t in (("q", q), ("k", k), ("v", v)):
-        if t.dtype != torch.bfloat16:
-            raise TypeError(f"{name} must be bfloat16")
-        if not t.is_cuda:
-            raise ValueError(f"{name} must live on the GPU")
-        if not t.is_contiguous() or t.dim() != 4:
-            raise ValueError(f"{name} must be a contiguous [B, H, N, D] tensor")
+    tc = torch or _torch()
+    _contiguous_bf16(tc, q, k, v)
     B, Hq, Nq, D = q.shape
-    if k.shape != v.shape or k.shape[0] != B or k.shape[3] != D:
+    Bk, Hkv, Nk, Dk = k_shape = k.shape
+    if k_shape != v.shape or Bk != B or Dk != D:
         raise ValueError("k and v must be [B, Hkv, Nk, D] with q's B and D")
-    if k.device != q.device or v.device != q.device:
+    dev = q.get_device()
+    if k.get_device() != dev or v.get_device() != dev:
         raise ValueError("q, k, v must be on the same device")
-    Hkv, Nk = k.shape[1], k.shape[2]
     if scale is None:
         scale = 1.0 / math.sqrt(D)
-    if workspace is None or q.numel() == 0 or k.numel() == 0:  # (an empty tensor is refused for its shape)
+    need = 0
+    if workspace is None or not B * Hq * Nq * D * Hkv * Nk:  # (an empty tensor is refused for its shape)
         need = swaa_attn_decode_workspace_bytes(B, Hq, Hkv, Nq, Nk, D, window, n_sink)
+    shape = (B, Hq, Hkv, Nq, Nk, D, window, n_sink, scale)
+    if stream is None and tc._C._cuda_getDevice() == dev:
+        return _decode_here(tc, q, k, v, out, lse, workspace, need, shape, None)
     caller = None if stream is None else _stream_handle(None, q)
     with _on_device_of(q) if stream is None else _launching_on(stream, q):
-        if out is None:
-            out = torch.empty_like(q)
-        elif out.shape != q.shape or out.dtype != torch.bfloat16 or not out.is_contiguous():
-            raise ValueError("out must be a contiguous bf16 tensor shaped like q")
-        if lse is None:
-            lse = torch.empty((B, Hq, Nq), dtype=torch.float32, device=q.device)
-        elif lse.shape != (B, Hq, Nq) or lse.dtype != torch.float32 or not lse.is_contiguous():
-            raise ValueError("lse must be a contiguous fp32 [B, Hq, Nq] tensor")
-        if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-        elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
-            raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
-        sptr = _stream_handle(stream, q)
-        rc = swaa_attn_decode_raw(q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(),
-                                  B, Hq, Hkv, Nq, Nk, D, int(window), int(n_sink), float(scale),
-                                  workspace.data_ptr(), workspace.numel(), sptr)
+        out, lse = _decode_here(tc, q, k, v, out, lse, workspace, need, shape, stream)
         if stream is not None:
             _returned_to(caller, out, lse)
+    return out, lse
+
+
+def _decode_here(tc, q, k, v, out, lse, workspace, need, shape, stream):
+    """swaa_attn_decode on q's device and `stream`, which are current."""
+    B, Hq, Hkv, Nq, Nk, D, window, n_sink, scale = shape
+    if out is None:
+        out = tc.empty_like(q)
+    elif out.shape != q.shape or out.dtype != tc.bfloat16 or not out.is_contiguous():
+        raise ValueError("out must be a contiguous bf16 tensor shaped like q")
+    if lse is None:
+        lse = tc.empty_strided((B, Hq, Nq), (Hq * Nq, Nq, 1), dtype=tc.float32, device=q.device)
+    elif lse.shape != (B, Hq, Nq) or lse.dtype != tc.float32 or not lse.is_contiguous():
+        raise ValueError("lse must be a contiguous fp32 [B, Hq, Nq] tensor")
+    if workspace is None:
+        workspace = tc.empty(need, dtype=tc.uint8, device=q.device)
+    elif workspace.dtype is not tc.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
+        raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
+    sptr = tc._C._cuda_getCurrentRawStream(q.get_device()) if stream is None else _stream_handle(stream, q)
+    rc = (_lib or load_library()).swaa_attn_decode(
+        q.data_ptr(), k.data_ptr(), v.data_ptr(), out.data_ptr(), lse.data_ptr(), B, Hq, Hkv, Nq, Nk, D, int(window), int(n_sink),
+        float(scale), workspace.data_ptr(), workspace.numel(), sptr)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
     return out, lse
