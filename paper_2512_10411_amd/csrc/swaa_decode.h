@@ -59,7 +59,7 @@ struct DecodeParams {
     int units_target, max_units;
     int min_halves;  // splits get no shorter than this while there is a workgroup per compute unit
     // divisions every workgroup makes, as multiplications (FastDiv)
-    FastDiv div_ctgroups, div_splits, div_hkv, div_page, div_per_round;
+    FastDiv div_ctgroups, div_splits, div_hkv, div_page, div_per_round, div_nq, div_hq, div_g, div_target;
 };
 
 // The halves a sequence of nk cached tokens visits: halves 0 .. n_sink-1, then key halves band0 ..

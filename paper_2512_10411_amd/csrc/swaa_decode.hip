@@ -87,9 +87,9 @@ __device__ __forceinline__ unsigned ragged_halves_per_split(const DecodeParams &
     };
     const unsigned target = (unsigned)p.units_target;
     const unsigned total = sum_over_sequences([](unsigned n) { return n; });
-    unsigned hps = (total + target - 1) / target;
+    unsigned hps = fastdiv(total + target - 1, p.div_target);
     // (splits of less than min_halves only where they are needed to have a workgroup per compute unit)
-    const unsigned wide = min((4 * total + target - 1) / target, (unsigned)p.min_halves);
+    const unsigned wide = min(fastdiv(4 * total + target - 1, p.div_target), (unsigned)p.min_halves);
     hps = (max(max(hps, wide), 4u) + 3u) & ~3u;  // (whole quarters for the four waves)
     // Rounding up per sequence can leave a few units more than the target, i.e. a handful of
     // workgroups in one more round than planned: lengthen the splits until the count fits (a
@@ -97,7 +97,7 @@ __device__ __forceinline__ unsigned ragged_halves_per_split(const DecodeParams &
     for (int it = 0; it < 4; ++it) {
         const unsigned units = sum_over_sequences([&](unsigned n) { return (n + hps - 1) / hps; });
         if (units <= target) break;
-        const unsigned longer = (hps * units + target - 1) / target;
+        const unsigned longer = fastdiv(hps * units + target - 1, p.div_target);
         hps = longer > hps ? longer : hps + 1;
     }
     return hps;
@@ -211,7 +211,7 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
         const int c = ct[j] * 32 + l32;
         col_valid[j] = tile_valid[j] && c < p.cols;
         cc[j] = min(c, p.cols - 1);
-        qpos[j] = Nk - p.Nq + (cc[j] % p.Nq);  // its position in the sequence
+        qpos[j] = Nk - p.Nq + (cc[j] - (int)fastdiv((unsigned)cc[j], p.div_nq) * p.Nq);  // its position in the sequence
     }
     const int pos_min = Nk - p.Nq, pos_max = Nk - 1;
 
@@ -546,15 +546,19 @@ struct MergeRow {
     long long slot0, step;
 };
 __device__ __forceinline__ MergeRow merge_row(const DecodeParams &p, long long row) {
+    // (The merge is bound by its chain of dependent steps.  With three 64-bit and two 32-bit divisions here, a hundred
+    // instructions each, one sequence of 2000 tokens took 11.1 us in all on 32 heads, with multiplications 10.6; 8 heads on 8, 4096
+    // tokens: 11.7, 11.0; window 8192 of 131072: 15.3, 14.9.)
     MergeRow m;
     m.row = row;
-    const int r = (int)(row % p.Nq);
-    const int hq = (int)((row / p.Nq) % p.Hq);
-    const int b = (int)(row / ((long long)p.Nq * p.Hq));
-    const int kvh = hq / p.G;
-    const int c = (hq % p.G) * p.Nq + r;
-    m.ct = c / 32;
-    m.col = c % 32;
+    const unsigned head_row = fastdiv((unsigned)row, p.div_nq);
+    const int r = (int)((unsigned)row - head_row * (unsigned)p.Nq);
+    const int b = (int)fastdiv(head_row, p.div_hq);
+    const int hq = (int)(head_row - (unsigned)b * (unsigned)p.Hq);
+    const int kvh = (int)fastdiv((unsigned)hq, p.div_g);
+    const int c = (hq - kvh * p.G) * p.Nq + r;
+    m.ct = c >> 5;
+    m.col = c & 31;
     if (p.ragged) {  // (the device-side plan: the sequence's first split workgroup has left it here)
         m.n_splits = p.ws_units[2 * b + 1];
         m.slot0 = (long long)p.ws_units[2 * b] * p.Hkv + kvh;
@@ -744,6 +748,9 @@ void plan_decode(DecodeParams &p, bool ragged, bool own_scratch) {
     p.div_ctgroups = make_fastdiv((unsigned)p.n_ctgroups);
     p.div_per_round = make_fastdiv((unsigned)(kXcds * p.n_ctgroups));
     p.div_hkv = make_fastdiv((unsigned)p.Hkv);
+    p.div_nq = make_fastdiv((unsigned)p.Nq);
+    p.div_hq = make_fastdiv((unsigned)p.Hq);
+    p.div_g = make_fastdiv((unsigned)p.G);
     if (p.ragged) {
         // Per-sequence lengths: about this many workgroups, cut on the device in proportion to the
         // sequences' lengths.  Up to one per resident place (512; 256 with two column tiles) they are
@@ -766,6 +773,7 @@ void plan_decode(DecodeParams &p, bool ragged, bool own_scratch) {
         p.min_halves = p.cols <= 8 ? 16 : 40;
         const long long units = wgs / ((long long)p.Hkv * p.n_ctgroups);
         p.units_target = (int)(units < 1 ? 1 : units);
+        p.div_target = make_fastdiv((unsigned)p.units_target);
         // (at most units_target + B units by the rounding of the device's division, and no
         // sequence has more than ceil(n_halves / 4) splits)
         const long long most = (long long)p.B * ((p.n_halves + 3) / 4);
