@@ -59,9 +59,11 @@ struct BwdParams {
         return (long long)pair * (n_sink_kt * (n_split + n_seg) + (n_kt - n_sink_kt) * rest) + sinks * (n_split + n_seg) + (kt - sinks) * rest;
     }
     float *partial;  // workspace, after delta
+    // divisions the dK/dV workgroups make, as multiplications
+    FastDiv div_kt, div_pairs, div_hkv, div_split, div_seg, div_sink_kt;
 };
 
-// Fills die_shift, n_sink_kt, n_seg, seg_tiles and n_split from the shape and mask fields.  pieces: key tiles may be cut into
+// Fills die_shift, n_sink_kt, n_seg, seg_tiles, n_split and the reciprocals from the shape and mask fields.  pieces: key tiles may be cut into
 // pieces (their partial sums take workspace).
 void plan_bwd(BwdParams &p, int D, bool pieces);
 // Floats of workspace the plan needs (delta + partial sums).

@@ -97,14 +97,14 @@ __global__ __launch_bounds__(512, 4) void swaa_bwd_dq_kernel(const BwdParams p) 
     WorkItem wi;
     if (!decode_work(p.f, wi)) return;
     const int hpb = wi.hpb;
-    const int rows_per_wg = kWgRows / hpb;
+    const int rows_per_wg = kWgRows >> (hpb >> 1);  // (hpb is 1, 2 or 4: shifts, no divisions)
     const int N = p.N, W = p.f.W, S = p.f.S, P = p.f.P;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
 
-    const int head = wi.kvh * p.f.G + wi.h0 + (wave % hpb);
+    const int head = wi.kvh * p.f.G + wi.h0 + (wave & (hpb - 1));
     const int wg_p0 = wi.pt * rows_per_wg;
     const int wg_p1 = min(N, wg_p0 + rows_per_wg) - 1;
-    const int p0 = wg_p0 + (wave / hpb) * 32;
+    const int p0 = wg_p0 + (wave >> (hpb >> 1)) * 32;
     const bool wave_active = p0 < N;
     const int plast = min(p0 + 32, N) - 1;
     const int qpos = p0 + l32;
@@ -285,29 +285,30 @@ __device__ __forceinline__ bool dkv_item(const BwdParams &p, DkvItem &w) {
     const unsigned bid = blockIdx.x;
     w.piece = 0;
     if ((int)bid < n_extra) {
-        w.seg = bid % p.n_seg;
-        w.kt = (bid / p.n_seg) % p.n_sink_kt;
-        w.pair = bid / (p.n_seg * p.n_sink_kt);
+        const unsigned tile = fastdiv(bid, p.div_seg);
+        w.seg = (int)(bid - tile * (unsigned)p.n_seg);
+        w.pair = (int)fastdiv(tile, p.div_sink_kt);
+        w.kt = (int)tile - w.pair * p.n_sink_kt;
         return true;
     }
     w.seg = -1;
     if (p.n_split > 1) {
-        const unsigned pairs = (unsigned)(p.B * p.Hkv), id = bid - (unsigned)n_extra;
-        w.pair = (int)(id % pairs);
-        w.piece = (int)(id / pairs % (unsigned)p.n_split);
-        w.kt = (int)(id / pairs / (unsigned)p.n_split);
+        const unsigned id = bid - (unsigned)n_extra, of_pair = fastdiv(id, p.div_pairs);
+        w.pair = (int)(id - of_pair * (unsigned)(p.B * p.Hkv));
+        w.kt = (int)fastdiv(of_pair, p.div_split);
+        w.piece = (int)of_pair - w.kt * p.n_split;
         return w.kt < n_kt;
     }
     const int id = dkv_main_item(p, bid, n_extra, n_kt);
     if (id >= p.B * p.Hkv * n_kt) return false;  // (the grid is rounded up to a multiple of eight)
-    w.kt = id % n_kt;
-    w.pair = id / n_kt;
+    w.pair = (int)fastdiv((unsigned)id, p.div_kt);
+    w.kt = id - w.pair * n_kt;
     return true;
 }
 
-// A piece's share [from, to) of its key tile's steps.
+// A piece's share [from, to) of its key tile's steps (their product is small: few key tiles have pieces, see plan_pieces).
 __device__ __forceinline__ int dkv_piece_start(const BwdParams &p, const DkvItem &w, int total, int next) {
-    return w.seg >= 0 ? next * total : (int)((long long)total * (w.piece + next) / p.n_split);
+    return w.seg >= 0 || p.n_split == 1 ? next * total : (int)fastdiv((unsigned)total * (unsigned)(w.piece + next), p.div_split);
 }
 
 // Its tiles of kBq query rows (head dimension 128): the band, then -- if a key is a sink, or there are generated rows --
@@ -532,6 +533,12 @@ void plan_bwd(BwdParams &p, int D, bool pieces) {
     if (D == 128) p.f.fold = 0x7fffffff;
     p.n_split = pieces ? plan_pieces(p, D) : 1;
     plan_sink_segments(p);
+    p.div_kt = make_fastdiv((unsigned)((p.N + 127) / 128));
+    p.div_pairs = make_fastdiv((unsigned)(p.B * p.Hkv));
+    p.div_hkv = make_fastdiv((unsigned)p.Hkv);
+    p.div_split = make_fastdiv((unsigned)p.n_split);
+    p.div_seg = make_fastdiv((unsigned)p.n_seg);
+    p.div_sink_kt = make_fastdiv((unsigned)p.n_sink_kt);
 }
 
 long long bwd_workspace_floats(const BwdParams &p, int D) {

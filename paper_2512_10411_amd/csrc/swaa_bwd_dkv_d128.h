@@ -139,25 +139,26 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
     const unsigned bid = blockIdx.x;
     int kt, pair, seg, piece = 0;  // seg: -1 for a key tile's main workgroups
     if ((int)bid < n_extra) {
-        seg = bid % p.n_seg;
-        kt = (bid / p.n_seg) % p.n_sink_kt;
-        pair = bid / (p.n_seg * p.n_sink_kt);
+        const unsigned tile = fastdiv(bid, p.div_seg);
+        seg = (int)(bid - tile * (unsigned)p.n_seg);
+        pair = (int)fastdiv(tile, p.div_sink_kt);
+        kt = (int)tile - pair * p.n_sink_kt;
     } else if (p.n_split > 1) {
-        const unsigned pairs = (unsigned)(p.B * p.Hkv), id = bid - (unsigned)n_extra;
+        const unsigned id = bid - (unsigned)n_extra, of_pair = fastdiv(id, p.div_pairs);
         seg = -1;
-        pair = (int)(id % pairs);
-        piece = (int)(id / pairs % (unsigned)p.n_split);
-        kt = (int)(id / pairs / (unsigned)p.n_split);
+        pair = (int)(id - of_pair * (unsigned)(p.B * p.Hkv));
+        kt = (int)fastdiv(of_pair, p.div_split);
+        piece = (int)of_pair - kt * p.n_split;
         if (kt >= n_kt) return;
     } else {
         const int id = dkv_main_item(p, bid, n_extra, n_kt);
         if (id >= p.B * p.Hkv * n_kt) return;  // (the grid is rounded up to a multiple of eight)
         seg = -1;
-        kt = id % n_kt;
-        pair = id / n_kt;
+        pair = (int)fastdiv((unsigned)id, p.div_kt);
+        kt = id - pair * n_kt;
     }
     const bool sink_kt = kt < p.n_sink_kt;
-    const int b = pair / p.Hkv, kvh = pair % p.Hkv;
+    const int b = (int)fastdiv((unsigned)pair, p.div_hkv), kvh = pair - b * p.Hkv;
     const int k0 = kt * 128, k1 = min(k0 + 127, N - 1);  // the workgroup's keys
     const int kw0 = k0 + 64 * kq;                         // this wave's first key
     const size_t kv_base = ((size_t)b * p.Hkv + kvh) * (size_t)N * kD;
@@ -181,8 +182,8 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
     const int n_tiles = n_band + max(0, tq_x_end - tq_x + 1);
     int total = G * n_tiles, from = 0;  // (head, tile) steps, head-major
     if (p.n_split > 1 && seg < 0) {  // (dkv_piece_start)
-        from = (int)((long long)total * piece / p.n_split);
-        total = (int)((long long)total * (piece + 1) / p.n_split) - from;
+        from = (int)fastdiv((unsigned)total * (unsigned)piece, p.div_split);
+        total = (int)fastdiv((unsigned)total * (unsigned)(piece + 1), p.div_split) - from;
     }
     auto first_row = [&](int n) { return (n < n_band ? tq_lo + n : tq_x + (n - n_band)) * kRows; };
 
@@ -202,8 +203,8 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
         };
         // The next tile to ask for: its place in its head's list, its first row, its head's rows, where it
         // begins.  Behind the end of the list the last one is asked for again, into buffers that nobody reads any more.
-        int rq_left = total, rq_n = from % n_tiles, rq_row = first_row(rq_n);
-        size_t rq_base = ((size_t)b * p.Hq + kvh * G + from / n_tiles) * (size_t)N;
+        int rq_left = total, rq_head = from ? from / n_tiles : 0, rq_n = from - rq_head * n_tiles, rq_row = first_row(rq_n);
+        size_t rq_base = ((size_t)b * p.Hq + kvh * G + rq_head) * (size_t)N;
         const __bf16 *rq_q = p.f.q + (rq_base + rq_row) * kD, *rq_do = p.dout + (rq_base + rq_row) * kD;
         float lreg = 0.f, dlreg = 0.f;
         uint32_t rq_off = 0;

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
     DkvItem item;
     if (!dkv_item(p, item)) return;
     const int kt = item.kt, pair = item.pair, seg = item.seg;
-    const int b = pair / p.Hkv, kvh = pair % p.Hkv;
+    const int b = (int)fastdiv((unsigned)pair, p.div_hkv), kvh = pair - b * p.Hkv;
     const int k0 = kt * 128;                             // the workgroup's first key
     const int kw0 = k0 + 32 * kq, kw1 = kw0 + 31;         // this wave's keys
     const int key = kw0 + l32;                            // this lane's key column
@@ -91,10 +91,15 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
 
     const float c2 = p.f.scale_log2;
     float lreg = 0.f, dlreg = 0.f;
-    // step `st` = (head, query tile): its Q and dO rows into buffer `buf`, its lse and delta into registers
-    auto request_tile = [&](int st, int buf) {
-        const int head = kvh * G + (from + st) / n_tiles, tq = tiles.at((from + st) % n_tiles);
-        const size_t base = ((size_t)b * p.Hq + head) * (size_t)N;
+    // the next step = (head, query tile) to ask for, its head's rows, and the step being computed.  (Counted
+    // on: with a division and a remainder for both in every step the backward of four sequences of 2048 tokens on a window of
+    // 128, 16 heads on 4, took 149 us, 146 now; 32 heads on 8, 4001 tokens, 144 and 141.)
+    const int first_head = from ? from / n_tiles : 0;
+    int rq_n = from - first_head * n_tiles, at_n = rq_n;
+    size_t base = ((size_t)b * p.Hq + kvh * G + first_head) * (size_t)N;
+    // its Q and dO rows into buffer `buf`, its lse and delta into registers
+    auto request_tile = [&](int buf) {
+        const int tq = tiles.at(rq_n);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             copy_rows(p.f.q + base * D, tq * kBq, 2 * wave + i, (uint32_t)(kQ + buf * kQTileBytes));
@@ -106,6 +111,10 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
             const int row = min(tq * kBq + tid, N - 1);
             lreg = p.f.lse[base + row];
             dlreg = p.delta[base + row];
+        }
+        if (++rq_n == n_tiles) {
+            rq_n = 0;
+            base += N;
         }
     };
     auto publish_rows = [&](int buf) {
@@ -137,7 +146,7 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
     };
 
     if (total > 0) {
-        request_tile(0, 0);
+        request_tile(0);
         publish_rows(0);
     }
     __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): this wave's copies have landed
@@ -149,10 +158,11 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
         const int buf = step & 1;
         const bool has_next = step + 1 < total;
         // the other buffers were last read one step ago, before the barrier that ended it
-        if (has_next) request_tile(step + 1, buf ^ 1);
+        if (has_next) request_tile(buf ^ 1);
 
         const uint32_t Qs = (uint32_t)(kQ + buf * kQTileBytes), dOs = (uint32_t)(kDO + buf * kQTileBytes);
-        const int tq = tiles.at((from + step) % n_tiles);
+        const int tq = tiles.at(at_n);
+        if (++at_n == n_tiles) at_n = 0;
         const int i0 = tq * kBq + 32 * qb, i1 = i0 + 31;  // this wave's rows of the tile
         // can any of them see any key of this wave?
         const bool sees = (i0 < N) && (i1 >= kw0) && ((i0 < kw1 + W) || (kw0 < S) || (i1 >= P));

@@ -66,7 +66,7 @@ __global__ __launch_bounds__(dkv64::kThreads, 2) void swaa_bwd_dkv_kernel(const 
     DkvItem item;
     if (!dkv_item(p, item)) return;
     const int kt = item.kt, pair = item.pair, seg = item.seg;
-    const int b = pair / p.Hkv, kvh = pair % p.Hkv;
+    const int b = (int)fastdiv((unsigned)pair, p.div_hkv), kvh = pair - b * p.Hkv;
     const int k0 = kt * 128, k1 = min(k0 + 127, N - 1);  // the workgroup's keys
     const int kw0 = k0 + 32 * kq, kw1 = kw0 + 31;         // this wave's keys
     const int key = kw0 + l32;                            // this lane's key column

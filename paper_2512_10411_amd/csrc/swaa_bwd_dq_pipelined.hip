@@ -165,16 +165,16 @@ __global__ __launch_bounds__(kQThreads, 2) void swaa_bwd_dq_pipelined_kernel(con
     WorkItem wi;
     if (!decode_work(p.f, wi)) return;
     const int hpb = wi.hpb;
-    const int rows_per_wg = kWgRows / hpb;
+    const int rows_per_wg = kWgRows >> (hpb >> 1);  // (hpb is 1, 2 or 4: shifts, no divisions)
     const int N = p.N, S = p.f.S, P = p.f.P;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, l32 = lane & 31, hf = lane >> 5;
 
-    const int head = wi.kvh * p.f.G + wi.h0 + (wave % hpb);
+    const int head = wi.kvh * p.f.G + wi.h0 + (wave & (hpb - 1));
     const int wg_p0 = wi.pt * rows_per_wg;             // first row (= position) of the workgroup
     const int wg_p1 = min(N, wg_p0 + rows_per_wg) - 1;  // last valid one
-    const int p0 = wg_p0 + (wave / hpb) * kQRows;       // first row of this wave
+    const int p0 = wg_p0 + (wave >> (hpb >> 1)) * kQRows;       // first row of this wave
     const int qpos = p0 + l32;                          // this lane's query column
     // this lane's window: a generated token (position >= P) sees its whole prefix
     const int W = (qpos >= P) ? N : p.f.W;

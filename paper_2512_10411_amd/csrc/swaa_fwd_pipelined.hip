@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
         si.n = max(si.n, 1);
     }
     const int hpb = wi.hpb;
-    const int rows_per_wg = kPWgRows / hpb;
+    const int rows_per_wg = kPWgRows >> (hpb >> 1);  // (hpb is 1, 2 or 4: shifts, no divisions)
     const int wg_r0 = wi.pt * rows_per_wg;  // first query row of the workgroup
     if (wg_r0 >= sg.nq) return;             // a shorter sequence of a packed batch
     const int Nq = sg.nq, Nk = sg.nk, S = p.S;
@@ -278,8 +278,8 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
     const int l32 = lane & 31;
     const int hf = lane >> 5;
 
-    const int head = wi.kvh * p.G + wi.h0 + (wave % hpb);
-    const int r0 = wg_r0 + (wave / hpb) * kPRows;  // first query row of this wave
+    const int head = wi.kvh * p.G + wi.h0 + (wave & (hpb - 1));
+    const int r0 = wg_r0 + (wave >> (hpb >> 1)) * kPRows;  // first query row of this wave
     const int wg_p0 = pos_off + wg_r0;             // positions of the workgroup's first ...
     const int wg_p1 = pos_off + min(Nq, wg_r0 + rows_per_wg) - 1;  // ... and last valid row
     const int p0 = pos_off + r0;                   // first position of this wave
