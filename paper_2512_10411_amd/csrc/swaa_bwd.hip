@@ -26,8 +26,8 @@
 // consumes them (as in the forward kernels); operands that a product needs
 // transposed are read from row-major LDS tiles with ds_read_b64_tr_b16.
 // P and dS are rounded to bf16 before the second products, sums are fp32.
-// dQ for head dimension 64, in this file, stages tiles through registers and leaves instruction scheduling to the compiler,
-// as does dK/dV for head dimension 128 where a key tile is seen by few query tiles (swaa_bwd_dkv_d128_short.h, LDS DMA);
+// dQ for head dimension 64, in this file, leaves instruction scheduling to the compiler,
+// as does dK/dV for head dimension 128 where a key tile is seen by few query tiles (swaa_bwd_dkv_d128_short.h);
 // otherwise dQ (swaa_bwd_dq_pipelined.hip) and dK/dV (swaa_bwd_dkv_d128.h) of head dimension 128 and dK/dV of 64
 // (swaa_bwd_dkv_d64.h) are pipelined by hand.  Waves per SIMD: two (dQ, short dK/dV) or one (dK/dV) for head
 // dimension 128, four (dQ) and two (dK/dV) for 64.
@@ -43,32 +43,11 @@ namespace {
 
 constexpr int kBq = 64;  // query rows per tile of the dK/dV kernel
 
-template <int D>
-struct BTile {
-    static constexpr int kChunksPerRow = D / 8;
-    static constexpr int kStride = D + 8;  // bf16 elements per LDS row
-    static constexpr int kElems = kBk * kStride;
-};
-
-// A operand "rows of the tile x 16 of the head dimension": row 32*rb + lane%32, elements 16*ks + 8*(lane/32) ..
-template <int D>
-__device__ __forceinline__ bf16x8 row_frag(const __bf16 *tile, int rb, int ks, int l32, int hf) {
-    return *reinterpret_cast<const bf16x8 *>(&tile[(32 * rb + l32) * BTile<D>::kStride + 16 * ks + 8 * hf]);
+__device__ __forceinline__ bf16x8 lds16(uint32_t addr) {
+    return *(const bf16x8 __attribute__((address_space(3))) *)(uintptr_t)addr;
 }
-
-// A operand "32 of the head dimension x 16 tile rows" (the tile transposed): head-dimension block db,
-// tile rows 32*rb + 16*st + 4*(lane/32) + {0..3, 8..11} -- the order in which a 32x32 accumulator hands
-// its rows to the next product as a B operand.
-template <int D>
-__device__ __forceinline__ bf16x8 col_frag(const __bf16 *tile, int rb, int st, int db, int lane) {
-    const int hf = lane >> 5, grp = lane >> 4, j16 = lane & 15;
-    const int row = 32 * rb + 16 * st + 4 * hf + (j16 >> 2);
-    const int col = 32 * db + 16 * (grp & 1) + 4 * (j16 & 3);
-    const __bf16 *a0 = &tile[row * BTile<D>::kStride + col];
-    const __bf16 *a1 = a0 + 8 * BTile<D>::kStride;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(a0));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(a1));
-    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+__device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
+    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(uintptr_t)addr);
 }
 
 // Does row i see key j?  Without short-circuit evaluation, for code that must stay free of branches:
@@ -83,17 +62,21 @@ __device__ __forceinline__ bool visible_in_range(int i, int j, int N, int W, int
 // a compute unit and one wave's exponentials run under the others' matrix instructions.  (With a
 // whole 64-key tile's scores in registers a wave took 208, a compute unit one workgroup, and every
 // element of every tile its own mask branches: 95 us for two sequences of 4001 tokens, 16 heads on
-// 4, window 1000; now 62.)  A tile's two halves of 32 keys are worked through one after the other;
+// 4, window 1000; in halves 62.)  A tile is two halves of 32 keys, worked through one after the other;
 // a wave skips the halves that its rows do not see and masks those on an edge.
-template <int D>
-__global__ __launch_bounds__(512, 4) void swaa_bwd_dq_kernel(const BwdParams p) {
-    using T = BTile<D>;
-    constexpr int KS = D / 16, DB = D / 32;
-    constexpr int TH = 512;                            // threads per workgroup
-    constexpr int kCPT = kBk * T::kChunksPerRow / TH;  // 16-byte chunks of a tile per thread
-    __shared__ __attribute__((aligned(16))) __bf16 Ks[T::kElems];
-    __shared__ __attribute__((aligned(16))) __bf16 Vs[T::kElems];
+// Tiles are copied from memory to LDS without a stop in registers, one ahead, into two buffers with one barrier per tile.  (Through
+// registers into one buffer of padded rows, two barriers per tile, the backward of 2048 tokens, 32 heads on 8, full attention
+// took 117.8 us, now 109.9; two of 4001 on a window of 1000, 16 heads on 4, 161.0 and 157.8; 16384 on 128 251 and 253.  Three
+// buffers, two tiles ahead: 0.3 % slower.  The halves in a loop, operands four at a time: 1.2 % slower.)
+namespace dq64 {
+constexpr int kD = 64, kKS = kD / 16, kDB = kD / 32;
+constexpr int kThreads = 512;
+constexpr int kRowB = kD * 2, kHalfB = 32 * kRowB, kTileB = 4 * kHalfB;  // K half 0, K half 1, V half 0, V half 1
+constexpr int kBytes = 2 * kTileB;
+}  // namespace dq64
 
+__global__ __launch_bounds__(dq64::kThreads, 4) void swaa_bwd_dq_kernel(const BwdParams p) {
+    using namespace dq64;
     WorkItem wi;
     if (!decode_work(p.f, wi)) return;
     const int hpb = wi.hpb;
@@ -109,86 +92,99 @@ __global__ __launch_bounds__(512, 4) void swaa_bwd_dq_kernel(const BwdParams p) 
     const int plast = min(p0 + 32, N) - 1;
     const int qpos = p0 + l32;
 
+    // the schedule (as in the forward): sink halves, then the band's; an odd count is padded with a half past the last
+    // row, which no row can see
     const int band_lo = (wg_p1 >= P) ? 0 : max(0, wg_p0 - W + 1);
-    const int t_band_lo = band_lo / kBk;
-    const int t_hi = wg_p1 / kBk;
-    const int n_sink_tiles = min((min(S, band_lo) + kBk - 1) / kBk, t_band_lo);
+    const int hb_lo = band_lo >> 5, hb_hi = wg_p1 >> 5;
+    const int n_sink_h = min((min(S, band_lo) + 31) >> 5, hb_lo);
+    const int J = (n_sink_h + (hb_hi - hb_lo + 1) + 1) >> 1;  // tiles
+    auto half_of = [&](int i) { return i < n_sink_h ? i : i - n_sink_h + hb_lo; };
     const int wbound = window_bound(p0, 32, W, P);
 
-    const size_t kv_base = ((size_t)wi.b * p.Hkv + wi.kvh) * (size_t)N * D;
-    const __bf16 *kg = p.f.k + kv_base;
-    const __bf16 *vg = p.f.v + kv_base;
-    const size_t q_base = ((size_t)wi.b * p.Hq + head) * (size_t)N * D;
-    const size_t r_base = ((size_t)wi.b * p.Hq + head) * (size_t)N;
+    // ---- HBM -> LDS: waves 0..3 copy a tile's K, 4..7 its V; the first two of the four its first half, an instruction
+    // 8 rows of 128 bytes.  The swizzle of the reads is applied on the global side.  Rows past the sequence's last one
+    // (and the padding half) repeat it. ----
+    const size_t kv_base = ((size_t)wi.b * p.Hkv + wi.kvh) * (size_t)N * kD;
+    const char *src = reinterpret_cast<const char *>((wave < 4 ? p.f.k : p.f.v) + kv_base);
+    const int crow = 16 * (wave & 1) + (lane >> 3);  // row of the half that instruction 0 moves in this lane; 1: + 8
+    uint32_t cchk[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = crow + 8 * i;
+        cchk[i] = (uint32_t)((lane & 7) ^ ((((r >> 1) & 1) << 2) | ((r >> 2) & 3))) << 4;
+    }
+    const uint32_t lds_copy = (uint32_t)((wave >> 1) * kHalfB + (wave & 1) * (kHalfB / 2));
+    auto issue_tile = [&](int j) {
+        const int g = min(half_of(2 * j + ((wave >> 1) & 1)), hb_hi);
+        const uint32_t lds = lds_copy + (uint32_t)((j & 1) * kTileB);
+        const char *base = src + (size_t)(32 * g) * kRowB;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t row = (uint32_t)min(crow + 8 * i, N - 1 - 32 * g);
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(row * kRowB + cchk[i]), "s"(base),
+                         "s"(lds + (uint32_t)(1024 * i))
+                         : "memory");
+        }
+    };
 
+    const size_t q_base = ((size_t)wi.b * p.Hq + head) * (size_t)N * kD;
+    const size_t r_base = ((size_t)wi.b * p.Hq + head) * (size_t)N;
     // this wave's Q and dO rows as B operands, its rows' lse (log2 units) and delta
-    bf16x8 qf[KS], dof[KS];
+    bf16x8 qf[kKS], dof[kKS];
     float lse2, dl;
     {
         const int row = min(qpos, N - 1);
-        const __bf16 *qs = p.f.q + q_base + (size_t)row * D + 8 * hf;
-        const __bf16 *ds = p.dout + q_base + (size_t)row * D + 8 * hf;
+        const __bf16 *qs = p.f.q + q_base + (size_t)row * kD + 8 * hf;
+        const __bf16 *ds = p.dout + q_base + (size_t)row * kD + 8 * hf;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
+        for (int ks = 0; ks < kKS; ++ks) {
             qf[ks] = *reinterpret_cast<const bf16x8 *>(qs + 16 * ks);
             dof[ks] = *reinterpret_cast<const bf16x8 *>(ds + 16 * ks);
         }
-        lse2 = p.f.lse[r_base + row] * 1.44269504088896340736f;
-        dl = row_delta<KS>(p.out + q_base + (size_t)row * D + 8 * hf, dof);
+        lse2 = p.f.lse[r_base + row];
+        issue_tile(0);  // (behind the loads that the first waits are for)
+        dl = row_delta<kKS>(p.out + q_base + (size_t)row * kD + 8 * hf, dof);
+        lse2 *= 1.44269504088896340736f;
         if (qpos < N && hf == 0) p.delta[r_base + row] = dl;  // for the dK/dV kernel
     }
 
-    f32x16 dqacc[DB];
+    // per-lane fragment addresses inside a half (swizzle folded in)
+    //  * row fragment, k-step ks: row l32, logical chunk 2 ks + hf:  row_lane ^ (ks << 5)
+    //  * transposed fragment, 16-key step st, head-dimension block db: rows 16 st + 4 hf + j16 / 4 (lo) and 8
+    //    further (hi), logical chunk 4 db + 2 (grp & 1) + (j16 & 3) / 2:  col_lane ^ (db << 6), + rows
+    const uint32_t row_lane = (uint32_t)(l32 * kRowB + ((hf ^ ((((l32 >> 1) & 1) << 2) | ((l32 >> 2) & 3))) << 4));
+    const int grp = lane >> 4, j16 = lane & 15;
+    const int rr = 4 * hf + (j16 >> 2);
+    const int cl = 2 * (grp & 1) + ((j16 & 3) >> 1);
+    const uint32_t col_lo = (uint32_t)(rr * kRowB + ((((j16 >> 3) << 2) | (cl ^ hf)) << 4) + 8 * (j16 & 1));
+    const uint32_t col_hi = (uint32_t)((rr + 8) * kRowB + ((((j16 >> 3) << 2) | (cl ^ (hf + 2))) << 4) + 8 * (j16 & 1));
+
+    f32x16 dqacc[kDB];
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < kDB; ++db)
 #pragma unroll
         for (int e = 0; e < 16; ++e) dqacc[db][e] = 0.f;
-
-    u32x4 kreg[kCPT], vreg[kCPT];
-    auto load_tile = [&](int t) {
-#pragma unroll
-        for (int c = 0; c < kCPT; ++c) {
-            const int id = c * TH + tid;
-            const int row = min(t * kBk + id / T::kChunksPerRow, N - 1);
-            const int col = (id % T::kChunksPerRow) * 8;
-            kreg[c] = *reinterpret_cast<const u32x4 *>(kg + (size_t)row * D + col);
-            vreg[c] = *reinterpret_cast<const u32x4 *>(vg + (size_t)row * D + col);
-        }
-    };
-    auto store_tile = [&]() {
-#pragma unroll
-        for (int c = 0; c < kCPT; ++c) {
-            const int id = c * TH + tid;
-            const int row = id / T::kChunksPerRow;
-            const int col = (id % T::kChunksPerRow) * 8;
-            *reinterpret_cast<u32x4 *>(&Ks[row * T::kStride + col]) = kreg[c];
-            *reinterpret_cast<u32x4 *>(&Vs[row * T::kStride + col]) = vreg[c];
-        }
-    };
-    auto next_tile = [&](int t) {
-        int n = t + 1;
-        if (n == n_sink_tiles && n < t_band_lo) n = t_band_lo;
-        return n;
-    };
-
-    int t = (n_sink_tiles > 0) ? 0 : t_band_lo;
-    load_tile(t);
-    store_tile();
-    __syncthreads();
     const float c2 = p.f.scale_log2;
 
-    while (true) {
-        const int tn = next_tile(t);
-        const bool has_next = tn <= t_hi;
-        if (has_next) load_tile(tn);
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) asm volatile("" : "+v"(qf[ks]), "+v"(dof[ks]));  // (waits for the loads here)
+    asm volatile("" : "+v"(lse2), "+v"(dl));
 
-#pragma unroll 1
+    for (int j = 0; j < J; ++j) {
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of tile j has landed
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();        // everybody's; and everybody is done with tile j - 1
+        asm volatile("" ::: "memory");
+        if (j + 1 < J) issue_tile(j + 1);
+
+#pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
-            const int k0 = t * kBk + 32 * kb, k_last = k0 + 31;
+            const int k0 = 32 * half_of(2 * j + kb), k_last = k0 + 31;
             const bool in_future = k0 > plast;
             const bool before_band = (plast < P) && (k_last < p0 - W + 1) && (k0 >= S);
             if (!wave_active || in_future || before_band) continue;  // (uniform)
             const bool unmasked = (k_last <= p0) && ((k0 > wbound) || (k_last < S));
+            const uint32_t kt = (uint32_t)((j & 1) * kTileB + kb * kHalfB), vt = kt + 2 * kHalfB;
 
             // S^T = K Q^T and dP^T = V dO^T : [32 keys] x [32 queries]
             f32x16 sacc, dpacc;
@@ -198,10 +194,9 @@ __global__ __launch_bounds__(512, 4) void swaa_bwd_dq_kernel(const BwdParams p) 
                 dpacc[e] = 0.f;
             }
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(Ks, kb, ks, l32, hf), qf[ks], sacc, 0, 0, 0);
-                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row_frag<D>(Vs, kb, ks, l32, hf), dof[ks], dpacc, 0, 0, 0);
-                if (ks % 2) __builtin_amdgcn_sched_barrier(0);  // (four operand reads in flight: more do not fit)
+            for (int ks = 0; ks < kKS; ++ks) {
+                sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds16(kt + (row_lane ^ (uint32_t)(ks << 5))), qf[ks], sacc, 0, 0, 0);
+                dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds16(vt + (row_lane ^ (uint32_t)(ks << 5))), dof[ks], dpacc, 0, 0, 0);
             }
 
             // dS^T = P^T (dP^T - delta) with P^T = exp2(s c2 - lse2), packed to bf16; a score that must not
@@ -224,21 +219,20 @@ __global__ __launch_bounds__(512, 4) void swaa_bwd_dq_kernel(const BwdParams p) 
 #pragma unroll
             for (int st = 0; st < 2; ++st)
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
-                    dqacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(col_frag<D>(Ks, kb, st, db, lane), dsf[st], dqacc[db], 0, 0, 0);
+                for (int db = 0; db < kDB; ++db) {
+                    const uint32_t off = kt + (uint32_t)(16 * st * kRowB);
+                    const s16x4 lo = lds8_tr(off + (col_lo ^ (uint32_t)(db << 6)));
+                    const s16x4 hi = lds8_tr(off + (col_hi ^ (uint32_t)(db << 6)));
+                    const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                    dqacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, dsf[st], dqacc[db], 0, 0, 0);
+                }
         }
-
-        if (!has_next) break;
-        __syncthreads();
-        store_tile();
-        __syncthreads();
-        t = tn;
     }
 
     if (qpos >= N) return;
-    __bf16 *orow = p.dq + q_base + (size_t)qpos * D;
+    __bf16 *orow = p.dq + q_base + (size_t)qpos * kD;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int db = 0; db < kDB; ++db)
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
             bf16x4 o4;
@@ -338,13 +332,6 @@ __device__ __forceinline__ DkvTiles dkv_tiles(const BwdParams &p, const DkvItem 
     return t;
 }
 
-__device__ __forceinline__ bf16x8 lds16(uint32_t addr) {
-    return *(const bf16x8 __attribute__((address_space(3))) *)(uintptr_t)addr;
-}
-__device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(uintptr_t)addr);
-}
-
 }  // namespace
 }  // namespace swaa
 
@@ -424,7 +411,7 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     if constexpr (D == 128)
         err = launch_bwd_dq_pipelined_d128(p, stream);  // swaa_bwd_dq_pipelined.hip
     else
-        hipLaunchKernelGGL(swaa_bwd_dq_kernel<D>, dim3((unsigned)(p.f.chunk * kXcds)), dim3(512), 0, stream, p);
+        hipLaunchKernelGGL(swaa_bwd_dq_kernel, dim3((unsigned)(p.f.chunk * kXcds)), dim3(dq64::kThreads), dq64::kBytes, stream, p);
     if (err == hipSuccess) err = hipGetLastError();
     if (err != hipSuccess) return err;
     const long long n_kt = (p.N + 127) / 128;

@@ -129,6 +129,19 @@ def test_row_blocks_of_head_dimension_64(N, W, S, P, G):
 
 
 @pytest.mark.parametrize("N,W,S,P,G", [
+    (32, 32, 0, None, 1),     # one half of a tile, the other a padding half
+    (33, 33, 0, None, 4),     # one key in the second half
+    (97, 97, 0, None, 2),     # odd number of halves: padding half behind the end
+    (300, 64, 33, None, 1),   # two halves with sinks, then the band's, odd and even counts
+    (300, 40, 32, None, 5),   # sinks end with a half; windows that begin inside one
+    (600, 33, 4, None, 8),    # many halves that a wave leaves out
+    (515, 70, 40, 400, 4),    # generated rows see all halves, the others of their workgroup do not
+])
+def test_half_tiles_of_dq_head_dimension_64(N, W, S, P, G):
+    check(1, 2 * G, 2, N, 64, W, S, P, seed=7400 + N + W)
+
+
+@pytest.mark.parametrize("N,W,S,P,G", [
     (33, 33, 0, None, 1),      # one tile, its second row half one row long
     (193, 31, 0, None, 2),     # a window inside a 32-key unit, a key tile of 65 keys
     (259, 97, 0, None, 3),     # three tiles of query rows in a band, the last key tile has three keys
