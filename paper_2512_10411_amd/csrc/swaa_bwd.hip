@@ -311,9 +311,9 @@ struct DkvTiles {
     int lo, n_band;  // the band's first tile, and how many
     int x;           // the first tile of the rest
     int n;           // all of them
-    __device__ __forceinline__ int at(int i) const { return i < n_band ? lo + i : x + (i - n_band); }
+    __host__ __device__ __forceinline__ int at(int i) const { return i < n_band ? lo + i : x + (i - n_band); }
 };
-__device__ __forceinline__ DkvTiles dkv_tiles(const BwdParams &p, const DkvItem &w) {
+__host__ __device__ __forceinline__ DkvTiles dkv_tiles(const BwdParams &p, const DkvItem &w) {
     const int N = p.N, k0 = w.kt * 128, k1 = min(k0 + 127, N - 1);
     const int last = (N - 1) / kBq, band_hi = min(N - 1, k1 + p.f.W - 1) / kBq;
     DkvTiles t{k0 / kBq, 0, last + 1, 0};
@@ -449,7 +449,8 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// The segments of the sink key tiles, about as long as an ordinary key tile's band or a piece of it, but at most 512 of them in all.
+// The segments of the sink key tiles, about as long as an ordinary key tile's band or a piece of it, but at most 512 of them in
+// all, or one to a tile where there are more tiles than that.
 void plan_sink_segments(BwdParams &p) {
     const int N = p.N, W = p.f.W, S = p.f.S;
     p.n_sink_kt = 0;
@@ -463,7 +464,7 @@ void plan_sink_segments(BwdParams &p) {
     const int range = tq_last - first_beyond + 1;
     long long seg = ((W + 127) / kBq + p.n_split) / p.n_split;
     const long long groups = (long long)p.B * p.Hkv * p.n_sink_kt;
-    while ((range + seg - 1) / seg * groups > 512) seg *= 2;
+    while (seg < range && (range + seg - 1) / seg * groups > 512) seg *= 2;
     p.seg_tiles = (int)seg;
     p.n_seg = (int)((range + seg - 1) / seg);
 }

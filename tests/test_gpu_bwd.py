@@ -128,6 +128,15 @@ def test_row_blocks_of_head_dimension_64(N, W, S, P, G):
     check(1, 2 * G, 2, N, 64, W, S, P, seed=9600 + N)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hkv,N,W,S,P", [
+    (65, 8, 300, 64, 4, None),   # 520 key tiles with sinks: one segment each, of all rows beyond the band
+    (33, 8, 500, 100, 200, 450),  # two to a pair, generated rows
+])
+def test_more_sink_key_tiles_than_there_are_segments(B, Hkv, N, W, S, P, D):
+    check(B, Hkv, Hkv, N, D, W, S, P, seed=9650 + N + D)
+
+
 @pytest.mark.parametrize("N,W,S,P,G", [
     (32, 32, 0, None, 1),     # one half of a tile, the other a padding half
     (33, 33, 0, None, 4),     # one key in the second half
