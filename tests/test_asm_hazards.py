@@ -259,3 +259,26 @@ def test_dkv_kernel_of_head_dimension_64_keeps_the_wait_states(tmp_path):
             wait_states += int(pops[0]) + 1 if pop == "s_nop" else 1
     late = result_hazards(insts, labels)
     assert not late, late[:5]
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
+                    reason="hipcc not available")
+@pytest.mark.parametrize("src,kernel", [("swaa_bwd.hip", "bwd_dq_kernel")])
+def test_tile_buffers_are_reused_behind_a_wait_for_their_reads(tmp_path, src, kernel):
+    """Two buffers, one barrier per tile: behind it the buffer of the tile before is copied into.  A wave's copies must have
+    landed in front of that barrier (vmcnt), and so must its reads of that buffer (lgkmcnt): their MFMAs are compiler builtins,
+    which the barrier does not hold back."""
+    out = tmp_path / "k.s"
+    flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
+    cmd = [build.hipcc_path(), *flags, "--cuda-device-only", "-S", "-o", str(out), os.path.join(build.CSRC, src)]
+    subprocess.run(cmd, check=True, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+    lines = open(out).read().splitlines()
+    starts = [i for i, ln in enumerate(lines) if re.match(r"_Z\S*" + kernel + r"\S*:", ln)]
+    assert starts
+    for first in starts:
+        insts = [parse(ln) for ln in lines[first:next(i for i in range(first, len(lines)) if lines[i].startswith(".Lfunc_end"))]]
+        insts = [(op, " ".join(ops)) for op, ops in filter(None, insts)]
+        barriers = [i for i, (op, _) in enumerate(insts) if op == "s_barrier"]
+        assert len(barriers) == 1  # the one at the top of the loop over the tiles
+        op, counters = insts[barriers[0] - 1]
+        assert op == "s_waitcnt" and "vmcnt(0)" in counters and "lgkmcnt(0)" in counters, (op, counters)
