@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kThreads, 4) void swaa_fwd_d64_kernel(const FwdPara
     for (int ks = 0; ks < kKs; ++ks) asm volatile("" : "+v"(qf[ks]));  // (waits for the loads here)
 
     for (int j = 0; j < J; ++j) {
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of tile j has landed
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0) lgkmcnt(0): this wave's share of tile j has landed, and it has read tile j - 1
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();        // everybody's; and everybody is done with tile j - 1
         asm volatile("" ::: "memory");

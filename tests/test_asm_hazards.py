@@ -263,7 +263,7 @@ def test_dkv_kernel_of_head_dimension_64_keeps_the_wait_states(tmp_path):
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
                     reason="hipcc not available")
-@pytest.mark.parametrize("src,kernel", [("swaa_bwd.hip", "bwd_dq_kernel")])
+@pytest.mark.parametrize("src,kernel", [("swaa_bwd.hip", "bwd_dq_kernel"), ("swaa_fwd_d64.hip", "fwd_d64_kernel")])
 def test_tile_buffers_are_reused_behind_a_wait_for_their_reads(tmp_path, src, kernel):
     """Two buffers, one barrier per tile: behind it the buffer of the tile before is copied into.  A wave's copies must have
     landed in front of that barrier (vmcnt), and so must its reads of that buffer (lgkmcnt): their MFMAs are compiler builtins,
