@@ -253,12 +253,21 @@ __global__ __launch_bounds__(dq64::kThreads, 4) void swaa_bwd_dq_kernel(const Bw
 // attempt that gave them to one die lost more to the imbalance than the cache gave back.
 // The launch rounds the number of main workgroups up to a multiple of the die count; ids
 // past the list belong to workgroups that return at once.
-// Dies that share a pair take its key tiles in turn: causal key tiles differ in length, the first ones being seen by the most
-// rows (16 heads on 4, 16384 tokens, window 8192: the backward 3780 us with contiguous parts, 2790 in turn; 8192 tokens on
-// a window of 2048, 652 and 499; 16384 on 1024, 652 and 654).
-__device__ __forceinline__ int dkv_main_item(const BwdParams &p, unsigned bid, int n_extra, int n_kt) {
+// Dies that share a pair take its key tiles in turn where the window is a sixteenth of the sequence or more (plan_bwd): the
+// causal key tiles of the last window are shorter than the rest, and with contiguous parts one die has them all.  With
+// narrower windows that is little, and neighbours in one L2 save more.  The backward, contiguous parts / in turn (us):
+//    window, of the tokens                       1/64           1/32           1/16           1/8            1/2
+//    4 heads on 1   65536 tokens             645 / 652     1102 / 1113    2032 / 1875    3943 / 3363
+//                  131072                   1979 / 2090    3811 / 3816    7278 / 6880   14361 / 13297
+//      D = 64       65536                    347 / 351      615 / 618     1152 / 1035    2266 / 1910
+//    8 on 2         16384                    182 / 181      250 / 252      380 / 383      648 / 543
+//                   65536                   1185 / 1226    1948 / 1986    3790 / 3687    7329 / 6741
+//    16 on 4        16384                    307 / 307      416 / 417      625 / 634     1058 / 970     3780 / 2790
+//                   65536                   2291 / 2309    3772 / 3777    7037 / 6937   13808 / 12982
+// (n_main: their number, as the launch rounds it up.)
+__host__ __device__ __forceinline__ int dkv_main_item(const BwdParams &p, unsigned bid, int n_extra, unsigned n_main, int n_kt) {
     const unsigned xcd = bid % kXcds, slot = (bid - (unsigned)n_extra) / kXcds, dies = 1u << p.die_shift;
-    const unsigned per_die = dies > 1 ? (unsigned)n_kt : (gridDim.x - (unsigned)n_extra) / kXcds;
+    const unsigned per_die = dies > 1 ? (unsigned)n_kt : n_main / kXcds;
     const unsigned off = slot * dies + (xcd & (dies - 1));
     return off < per_die ? (int)((xcd >> p.die_shift) * per_die + off) : 0x7fffffff;
 }
@@ -293,7 +302,7 @@ __device__ __forceinline__ bool dkv_item(const BwdParams &p, DkvItem &w) {
         w.piece = (int)of_pair - w.kt * p.n_split;
         return w.kt < n_kt;
     }
-    const int id = dkv_main_item(p, bid, n_extra, n_kt);
+    const int id = dkv_main_item(p, bid, n_extra, gridDim.x - (unsigned)n_extra, n_kt);
     if (id >= p.B * p.Hkv * n_kt) return false;  // (the grid is rounded up to a multiple of eight)
     w.pair = (int)fastdiv((unsigned)id, p.div_kt);
     w.kt = id - w.pair * n_kt;
@@ -516,7 +525,7 @@ int plan_pieces(BwdParams &p, int D) {
 }  // namespace
 
 void plan_bwd(BwdParams &p, int D, bool pieces) {
-    p.die_shift = die_shift((long long)p.B * p.Hkv);
+    p.die_shift = 16LL * p.f.W >= p.N ? die_shift((long long)p.B * p.Hkv) : 0;  // (dkv_main_item has both sides of the line)
     // (one workgroup of dQ to a compute unit: in the order of their lengths; two sequences of 2048 tokens 275 us folded, 262)
     if (D == 128) p.f.fold = 0x7fffffff;
     p.n_split = pieces ? plan_pieces(p, D) : 1;

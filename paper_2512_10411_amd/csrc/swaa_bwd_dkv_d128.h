@@ -151,7 +151,7 @@ __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(c
         piece = (int)of_pair - kt * p.n_split;
         if (kt >= n_kt) return;
     } else {
-        const int id = dkv_main_item(p, bid, n_extra, n_kt);
+        const int id = dkv_main_item(p, bid, n_extra, gridDim.x - (unsigned)n_extra, n_kt);
         if (id >= p.B * p.Hkv * n_kt) return;  // (the grid is rounded up to a multiple of eight)
         seg = -1;
         pair = (int)fastdiv((unsigned)id, p.div_kt);

@@ -1,6 +1,6 @@
 // Host-side check of the backward's plan (swaa::plan_bwd) and of the tiles its workgroups take (swaa::dkv_tiles): every row that
-// sees a key of a key tile lies in exactly one query tile of one of that key tile's workgroups, and the partial sums fit the
-// workspace asked for.  Built and run by tests/test_host_bwd_plan.py; needs no GPU.
+// sees a key of a key tile lies in exactly one query tile of one of that key tile's workgroups, the partial sums fit the
+// workspace asked for, and the workgroups of whole key tiles (swaa::dkv_main_item) have each of them once.  Built and run by tests/test_host_bwd_plan.py; needs no GPU.
 #include <cstdio>
 #include <vector>
 
@@ -52,6 +52,16 @@ int main() {
                                         }
                                         sound = sound && p.first_part(1, 0) == parts &&
                                                 swaa::bwd_workspace_floats(p, D) >= (long long)B * Hkv * (G * (long long)N + parts * 2 * 128 * D);
+                                        if (p.n_split == 1) {
+                                            const int pairs = B * Hkv, n_extra = pairs * p.n_sink_kt * p.n_seg;
+                                            const unsigned n_main = (unsigned)(pairs * n_kt + 7) / 8 * 8;
+                                            std::vector<int> dealt(pairs * n_kt, 0);
+                                            for (unsigned i = 0; i < n_main; ++i) {
+                                                const int id = swaa::dkv_main_item(p, (unsigned)n_extra + i, n_extra, n_main, n_kt);
+                                                if (id >= 0 && id < pairs * n_kt) ++dealt[id];
+                                            }
+                                            for (int n : dealt) sound = sound && n == 1;
+                                        }
                                         ++checked;
                                         if (sound) continue;
                                         if (bad++ < 10)
