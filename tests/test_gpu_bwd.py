@@ -65,8 +65,14 @@ def assert_grad(name, got, ref, tag):
     assert err.mean() <= MEAN_REL * rmean + MEAN_ABS, (tag, name, err.mean(), rmean)
 
 
-def check(B, Hq, Hkv, N, D, W, S, P, seed):
-    tag = f"bwd B{B} Hq{Hq} Hkv{Hkv} N{N} D{D} W{W} S{S} P{P}"
+def whole_key_tiles(B, Hq, Hkv, N, D, W, S, P):
+    """A workspace one byte too small for a plan that cuts the key tiles' steps into pieces: the call runs without."""
+    need = binding.swaa_attn_bwd_workspace_bytes(B, Hq, Hkv, N, D, W, S, P)
+    return torch.empty(need - 1, dtype=torch.uint8, device="cuda")
+
+
+def check(B, Hq, Hkv, N, D, W, S, P, seed, whole=False):
+    tag = f"bwd B{B} Hq{Hq} Hkv{Hkv} N{N} D{D} W{W} S{S} P{P}" + (" whole key tiles" if whole else "")
     print(f"[case] {tag} seed {seed}", flush=True)
     scale = 1 / math.sqrt(D)
     q, k, v = make_qkv(B, Hq, Hkv, N, D, seed)
@@ -74,7 +80,8 @@ def check(B, Hq, Hkv, N, D, W, S, P, seed):
     qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(dout)
     n_prompt = N if P is None else P
     out, lse = binding.swaa_attn_fwd_fa_decode(qd, kd, vd, W, S, n_prompt, scale)
-    dq, dk, dv = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, S, n_prompt, scale)
+    ws = whole_key_tiles(B, Hq, Hkv, N, D, W, S, n_prompt) if whole else None
+    dq, dk, dv = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, S, n_prompt, scale, workspace=ws)
     torch.cuda.synchronize()
     rq, rk, rv = swaa_attn_bwd_oracle(q, k, v, dout, W, S, scale, n_prompt=n_prompt)
     assert_grad("dq", dq, rq, tag)
@@ -150,69 +157,95 @@ def test_half_tiles_of_dq_head_dimension_64(N, W, S, P, G):
     check(1, 2 * G, 2, N, 64, W, S, P, seed=7400 + N + W)
 
 
-@pytest.mark.parametrize("N,W,S,P,G", [
-    (33, 33, 0, None, 1),      # one tile, its second row half one row long
-    (193, 31, 0, None, 2),     # a window inside a 32-key unit, a key tile of 65 keys
-    (259, 97, 0, None, 3),     # three tiles of query rows in a band, the last key tile has three keys
-    (1029, 64, 33, None, 1),   # sinks that end inside the second unit: segments, one of them short
-    (1029, 160, 130, 901, 4),  # two sink key tiles, generated rows that start inside a tile
-    (545, 545, 0, 511, 5),     # no window; the row before a tile is generated
-    # (more query tiles per key tile than the short sequences' dK/dV kernel takes, as the last two)
-    (449, 449, 0, None, 4),    # a key tile of 65 keys
-    (515, 515, 4, None, 4),    # the last key tile has three keys
-    (1029, 150, 33, None, 2),  # sinks that end inside the second unit, a window that ends inside a unit
-    (1029, 135, 4, 700, 3),    # the same with generated rows
-    (929, 139, 1, None, 8),    # a window two rows longer than a whole number of units, a key tile of 33 keys
-])
-def test_units_and_tiles_of_head_dimension_128(N, W, S, P, G):
-    check(1, 2 * G, 2, N, 128, W, S, P, seed=9800 + N)
+# Head dimension 128 has two dK/dV kernels, of eight waves ("8") and of one wave per SIMD ("1"); which one runs depends on the
+# shape and on whether the key tiles' steps are cut into pieces.  The last entry: the kernel in pieces, then that of whole key
+# tiles (a workspace too small for pieces), which is run too; one letter where the plan has no pieces.
+# tests/test_host_bwd_plan.py checks the letters.
+UNITS = [
+    (1, 2, 1, 33, 33, 0, None, "8"),       # one tile, its second row half one row long
+    (1, 2, 2, 193, 31, 0, None, "8"),      # a window inside a 32-key unit, a key tile of 65 keys
+    (1, 2, 3, 259, 97, 0, None, "8"),      # three tiles of query rows in a band, the last key tile has three keys
+    (1, 2, 1, 1029, 64, 33, None, "8"),    # sinks that end inside the second unit: segments, one of them short
+    (1, 2, 4, 1029, 160, 130, 901, "81"),  # two sink key tiles, generated rows that start inside a tile
+    (1, 2, 5, 545, 545, 0, 511, "81"),     # no window; the row before a tile is generated
+    (1, 2, 4, 449, 449, 0, None, "81"),    # a key tile of 65 keys
+    (1, 2, 4, 515, 515, 4, None, "81"),    # the last key tile has three keys
+    (1, 2, 2, 1029, 150, 33, None, "81"),  # sinks that end inside the second unit, a window that ends inside a unit
+    (1, 2, 3, 1029, 135, 4, 700, "81"),    # the same with generated rows
+    (1, 2, 8, 929, 139, 1, None, "81"),    # a window two rows longer than a whole number of units, a key tile of 33 keys
+    (1, 1, 2, 2049, 1500, 140, 1849, "11"),  # pieces and segments of one wave per SIMD, a key tile of one key, generated rows
+    (1, 4, 5, 1281, 1281, 4, None, "11"),  # pieces that begin inside a head's list
+]
+LINE = [
+    (1, 2, 4, 384, 384, 0, None, "88"), (1, 2, 4, 385, 385, 0, None, "81"),        # few workgroups, on both sides of the rule
+    (1, 2, 4, 1024, 192, 4, None, "81"), (1, 2, 4, 1024, 193, 4, None, "81"),
+    (1, 2, 4, 1024, 128, 4, None, "88"), (1, 2, 4, 1024, 129, 4, None, "81"),      # with segments of sinks
+    (1, 2, 1, 768, 768, 0, None, "88"), (1, 2, 1, 769, 769, 0, None, "81"),        # one head per KV head
+    (8, 16, 4, 256, 256, 0, None, "8"),                                            # a full chip
+    (1, 2, 4, 640, 64, 0, 256, "8"), (1, 2, 4, 640, 64, 0, 200, "8"),              # generated rows count half
+    (1, 2, 4, 640, 64, 0, 129, "8"), (1, 2, 4, 640, 64, 0, 128, "1"),
+    (1, 1, 4, 1536, 1536, 0, None, "81"), (1, 1, 4, 1537, 1537, 0, None, "11"),    # eight pieces
+    (1, 8, 4, 896, 896, 4, None, "81"), (1, 8, 4, 897, 897, 4, None, "11"),        # five and four
+    (1, 8, 1, 1536, 1536, 0, None, "81"), (1, 8, 1, 1537, 1537, 0, None, "11"),    # one head per KV head: three and two
+]
 
 
-@pytest.mark.parametrize("B,Hkv,G,N,W,S,P", [
-    (1, 2, 4, 384, 384, 0, None), (1, 2, 4, 385, 385, 0, None),      # few workgroups, on both sides of the rule
-    (1, 2, 4, 1024, 192, 4, None), (1, 2, 4, 1024, 193, 4, None),    # with segments of sinks: six tiles run on the other kernel
-    (1, 2, 1, 768, 768, 0, None), (1, 2, 1, 769, 769, 0, None),      # one head per KV head
-    (8, 16, 4, 256, 256, 0, None),                                   # a full chip
-    (1, 2, 4, 640, 64, 0, 256), (1, 2, 4, 640, 64, 0, 200),          # generated rows count half
-])
-def test_both_kernels_of_head_dimension_128_at_the_line_between_them(B, Hkv, G, N, W, S, P):
-    check(B, Hkv * G, Hkv, N, 128, W, S, P, seed=9900 + N + W)
+def runs(cases):
+    return [(*c[:7], whole) for c in cases for whole in range(len(c[7]))]
 
 
-@pytest.mark.parametrize("W", [90, 140])  # eight waves, and one wave per SIMD
-def test_an_upstream_row_without_a_number_stays_in_its_blocks(W):
-    # head dimension 128: 32 rows x 32 keys are computed together, so NaN in one row of dO may reach the keys of
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P,whole", runs(UNITS))
+def test_units_and_tiles_of_head_dimension_128(B, Hkv, G, N, W, S, P, whole):
+    check(B, Hkv * G, Hkv, N, 128, W, S, P, seed=9800 + N, whole=whole)
+
+
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P,whole", runs(LINE))
+def test_both_kernels_of_head_dimension_128_at_the_line_between_them(B, Hkv, G, N, W, S, P, whole):
+    check(B, Hkv * G, Hkv, N, 128, W, S, P, seed=9900 + N + W, whole=whole)
+
+
+# of the tests of NaN below, as UNITS; then (head dimension, window, whole key tiles?)
+NAN_LINE = [(1, 1, 4, 700, 90, 4, None, "88"), (1, 1, 4, 700, 140, 4, None, "81"), (1, 1, 4, 700, 400, 4, None, "81")]
+NAN_RUNS = [(64, 90, 0), (64, 90, 1)] + [(128, c[4], whole) for c in NAN_LINE for whole in (0, 1)]
+
+
+@pytest.mark.parametrize("what", ["dout", "q"])
+@pytest.mark.parametrize("D,W,whole", NAN_RUNS)
+def test_an_upstream_row_without_a_number_stays_in_its_blocks(D, W, whole, what):
+    # 32 rows x 32 keys are computed together, so NaN in one row of dO (or Q) may reach the keys of
     # those blocks in which some row of its 32 sees some key, and no others
     N, row = 700, 333
-    q, k, v = make_qkv(1, 4, 1, N, 128, seed=9710)
+    q, k, v = make_qkv(1, 4, 1, N, D, seed=9710)
     qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(make_dout(q.shape, 9711))
     out, lse = binding.swaa_attn_fwd(qd, kd, vd, W, 4)
-    want = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
-    dd[:, :, row] = float("nan")
-    got = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
+    ws = whole_key_tiles(1, 4, 1, N, D, W, 4, None) if whole else None
+    want = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4, workspace=ws)
+    (dd if what == "dout" else qd)[:, :, row] = float("nan")
+    got = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4, workspace=ws)
     torch.cuda.synchronize()
     first = row // 32 * 32
     reached = torch.zeros(N, dtype=torch.bool, device="cuda")
-    reached[:32], reached[(first - W + 1) // 32 * 32:first + 32] = True, True
+    reached[:32], reached[max(0, first - W + 1) // 32 * 32:first + 32] = True, True
     rows = torch.arange(N, device="cuda") != row
     assert torch.equal(got[0][:, :, rows], want[0][:, :, rows])
     for x, y in zip(got[1:], want[1:]):  # dK, dV
         assert torch.equal(x[:, :, ~reached], y[:, :, ~reached])
 
 
-@pytest.mark.parametrize("D,W", [(64, 90), (128, 90), (128, 140)])
-def test_a_row_without_a_number_reaches_only_the_keys_it_sees(D, W):
+@pytest.mark.parametrize("D,W,whole", NAN_RUNS)
+def test_a_row_without_a_number_reaches_only_the_keys_it_sees(D, W, whole):
     # NaN in one row's log-sum-exp: P = 0 where the row does not see the key, whatever the row holds
     N, row = 700, 333
     q, k, v = make_qkv(1, 4, 1, N, D, seed=9700)
     qd, kd, vd, dd = to_device(q), to_device(k), to_device(v), to_device(make_dout(q.shape, 9701))
     out, lse = binding.swaa_attn_fwd(qd, kd, vd, W, 4)
-    want = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
+    ws = whole_key_tiles(1, 4, 1, N, D, W, 4, None) if whole else None
+    want = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4, workspace=ws)
     lse[:, :, row] = float("nan")
-    got = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4)
+    got = binding.swaa_attn_bwd(qd, kd, vd, out, lse, dd, W, 4, workspace=ws)
     torch.cuda.synchronize()
     seen = torch.zeros(N, dtype=torch.bool, device="cuda")
-    seen[:4], seen[row - W + 1:row + 1] = True, True
+    seen[:4], seen[max(0, row - W + 1):row + 1] = True, True
     rows = torch.arange(N, device="cuda") != row
     assert torch.equal(got[0][:, :, rows], want[0][:, :, rows])
     for x, y in zip(got[1:], want[1:]):  # dK, dV
