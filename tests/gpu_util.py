@@ -2,6 +2,8 @@
 import numpy as np
 import torch
 
+from paper_2512_10411_amd import binding
+
 # acceptance tolerances: bf16 output against the unrounded fp64 oracle
 O_MAX_ABS = 2e-2
 O_MEAN_ABS = 2e-3
@@ -12,6 +14,18 @@ def to_device(bits: np.ndarray, fmt: str = "bf16") -> torch.Tensor:
     """uint16 bf16 (or binary16) bit patterns -> tensor of that type on cuda:0 (bit-exact)."""
     dtype = torch.bfloat16 if fmt == "bf16" else torch.float16
     return torch.from_numpy(np.ascontiguousarray(bits).view(np.int16)).view(dtype).cuda()
+
+
+def forward_packed(q, k, v, W, S, scale, P=None, fmt="bf16"):
+    """The forward of a [B, H, N, D] batch (bit patterns) as a packed one.  Head dimension 128: prompts of one length and few rows
+    run on the short prompts' kernel, packed ones on row tiles whatever their length."""
+    B, _, N, D = q.shape
+    flat = lambda x: to_device(x.transpose(1, 0, 2, 3).reshape(x.shape[1], B * N, D), fmt)
+    cu = torch.arange(0, (B + 1) * N, N, dtype=torch.int32, device="cuda")
+    out, lse = binding.swaa_attn_fwd_ex(flat(q), flat(k), flat(v), W, S, P, scale, cu_seqlens_q=cu, cu_seqlens_k=cu,
+                                        max_seqlen_q=N, max_seqlen_k=N)
+    torch.cuda.synchronize()
+    return out.view(-1, B, N, D).transpose(0, 1).contiguous(), lse.view(-1, B, N).transpose(0, 1).contiguous()
 
 
 def errors(out_gpu: torch.Tensor, lse_gpu: torch.Tensor, out_ref: np.ndarray, lse_ref: np.ndarray, rows=None):

@@ -12,23 +12,25 @@ from oracle import swaa_attn_oracle
 from paper_2512_10411_amd import binding
 from paper_2512_10411_amd.inputs import (WORKLOADS, bf16_bits_to_f32, f32_to_bf16_bits, make_qkv,
                                          make_workload, sample_rows)
-from gpu_util import assert_parity, to_device
+from gpu_util import assert_parity, forward_packed, to_device
 
 pytestmark = pytest.mark.gpu
 
 
-def run_gpu(q, k, v, W, S, P, scale):
+def run_gpu(q, k, v, W, S, P, scale, packed=False):
+    if packed:  # (head dimension 128: on row tiles, where this call may run on the short prompts' kernel)
+        return forward_packed(q, k, v, W, S, scale, P)
     out, lse = binding.swaa_attn_fwd_fa_decode(to_device(q), to_device(k), to_device(v), W, S, P, scale)
     torch.cuda.synchronize()
     return out, lse
 
 
-def check(B, Hq, Hkv, N, D, W, S, P, seed, rows=None):
+def check(B, Hq, Hkv, N, D, W, S, P, seed, rows=None, packed=False):
     scale = 1.0 / math.sqrt(D)
-    tag = f"B{B} Hq{Hq} Hkv{Hkv} N{N} D{D} W{W} S{S} P{P}"
+    tag = f"B{B} Hq{Hq} Hkv{Hkv} N{N} D{D} W{W} S{S} P{P}" + (" packed" if packed else "")
     print(f"[case] {tag} seed {seed}", flush=True)
     q, k, v = make_qkv(B, Hq, Hkv, N, D, seed)
-    out, lse = run_gpu(q, k, v, W, S, P, scale)
+    out, lse = run_gpu(q, k, v, W, S, P, scale, packed)
     ro, rl = swaa_attn_oracle(q, k, v, W, S, scale, rows=rows, n_prompt=P)
     assert_parity(out, lse, ro, rl, rows=rows, tag=tag)
 
@@ -41,11 +43,14 @@ def test_small_shapes_sweep_prompt_length(N, D):
     for W, S in ((1, 0), (7, 4), (64, 0), (200, 70)):
         for P in sorted({0, 1, 31, 32, 33, 64, 100, N // 2, N - 1, N, N + 5}):
             check(1, 4, 1, N, D, W, S, P, seed)
+            if D == 128 and N > 64:
+                check(1, 4, 1, N, D, W, S, P, seed, packed=True)
 
 
 @pytest.mark.parametrize("G", [1, 2, 3, 5, 7, 8])
 def test_gqa_group_sizes(G):
     check(2, 2 * G, 2, 333, 128, 100, 3, 250, seed=5200 + G)
+    check(2, 2 * G, 2, 333, 128, 100, 3, 250, seed=5200 + G, packed=True)
     check(1, G, 1, 515, 64, 65, 10, 300, seed=5300 + G)
 
 
@@ -66,7 +71,8 @@ def test_prompt_length_at_or_past_n_equals_the_prefill_call_bit_for_bit():
         binding.swaa_attn_fwd_fa_decode(qd, kd, vd, 300, 4, -1)
 
 
-def test_generated_rows_see_a_score_spike_deep_in_the_prompt():
+@pytest.mark.parametrize("packed", [False, True])
+def test_generated_rows_see_a_score_spike_deep_in_the_prompt(packed):
     # the generated rows' reference comes from the first keys; a key far above it, outside
     # every prompt row's reach, must still come out right (and must not touch prompt rows)
     B, Hq, Hkv, N, D, W, S, P = 1, 4, 1, 3100, 128, 256, 4, 3000
@@ -77,7 +83,7 @@ def test_generated_rows_see_a_score_spike_deep_in_the_prompt():
     kf[:, :, 1500, 0] = 160.0
     q, k = f32_to_bf16_bits(qf), f32_to_bf16_bits(kf)
     scale = 1 / math.sqrt(D)
-    out, lse = run_gpu(q, k, v, W, S, P, scale)
+    out, lse = run_gpu(q, k, v, W, S, P, scale, packed)
     ro, rl = swaa_attn_oracle(q, k, v, W, S, scale, n_prompt=P)
     assert_parity(out, lse, ro, rl, tag="spike seen by generated rows")
 

@@ -11,9 +11,20 @@ import torch
 from oracle import input_format, swaa_attn_oracle, swaa_decode_oracle
 from paper_2512_10411_amd import binding
 from paper_2512_10411_amd.inputs import make_qkv, sample_rows
-from gpu_util import assert_parity, to_device
+from gpu_util import assert_parity, forward_packed, to_device
 
 pytestmark = pytest.mark.gpu
+
+# (prompts of one length and few rows run on the short prompts' kernel, packed ones on row tiles)
+on_both_kernels = pytest.mark.parametrize("packed", [False, True])
+
+
+def run_gpu(q, k, v, W, S, scale, packed):
+    if packed:
+        return forward_packed(q, k, v, W, S, scale, fmt="fp16")
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q, "fp16"), to_device(k, "fp16"), to_device(v, "fp16"), W, S, None, scale)
+    torch.cuda.synchronize()
+    return out, lse
 
 
 def check(B, Hq, Hkv, Nq, Nk, D, W, S, P, seed, rows=None):
@@ -41,20 +52,21 @@ def test_small_shapes(D):
     check(1, 4, 2, 100, 777, D, 64, 4, None, seed=9710 + D)     # a chunk of a longer prefill
 
 
-def test_sink_heavy_scores_keep_probabilities_in_range():
+@on_both_kernels
+def test_sink_heavy_scores_keep_probabilities_in_range(packed):
     # scores tens of nats apart (k scaled by 4): later keys outgrow the reference taken from the
     # first half tile by more than binary16 holds in places, which must end in the max-based pass
     B, Hq, Hkv, N, D = 1, 4, 1, 2000, 128
     q, k, v = make_qkv(B, Hq, Hkv, N, D, seed=9720, k_mult=4.0, fmt="fp16")
-    out, lse = binding.swaa_attn_fwd_ex(to_device(q, "fp16"), to_device(k, "fp16"), to_device(v, "fp16"), 512, 4)
-    torch.cuda.synchronize()
+    out, lse = run_gpu(q, k, v, 512, 4, 1 / math.sqrt(D), packed)
     with input_format("fp16"):
         ro, rl = swaa_attn_oracle(q, k, v, 512, 4, 1 / math.sqrt(D))
     assert_parity(out, lse, ro, rl, tag="fp16 peaked softmax")
 
 
+@on_both_kernels
 @pytest.mark.parametrize("spike", [0.0, 24.0, 40.0, 160.0])
-def test_late_score_spike_against_the_binary16_range(spike):
+def test_late_score_spike_against_the_binary16_range(spike, packed):
     # one key deep inside the windows scores 3 * spike / sqrt(D) nats above the rest: 6 nats stay
     # inside binary16 with the fixed reference (P up to 2^13), 10 nats and more overflow a P and
     # must be caught; a very negative key and small values ride along
@@ -69,14 +81,14 @@ def test_late_score_spike_against_the_binary16_range(spike):
     q = qf.astype(np.float16).view(np.uint16)
     k = kf.astype(np.float16).view(np.uint16)
     scale = 1 / math.sqrt(D)
-    out, lse = binding.swaa_attn_fwd_ex(to_device(q, "fp16"), to_device(k, "fp16"), to_device(v, "fp16"), W, S, None, scale)
-    torch.cuda.synchronize()
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     with input_format("fp16"):
         ro, rl = swaa_attn_oracle(q, k, v, W, S, scale)
     assert_parity(out, lse, ro, rl, tag=f"fp16 late spike {spike}")
 
 
-def test_all_scores_far_below_the_reference():
+@on_both_kernels
+def test_all_scores_far_below_the_reference(packed):
     # rows whose first visited half tile is invisible to them start from reference 0; with every
     # score near -30 nats their binary16 probabilities vanish altogether and the kernel has to
     # notice (the sum of the rounded P is zero although the fp32 sum is in range)
@@ -90,8 +102,7 @@ def test_all_scores_far_below_the_reference():
     kf[..., 0] = -a
     q = qf.astype(np.float16).view(np.uint16)
     k = kf.astype(np.float16).view(np.uint16)
-    out, lse = binding.swaa_attn_fwd_ex(to_device(q, "fp16"), to_device(k, "fp16"), to_device(v, "fp16"), W, S, None, scale)
-    torch.cuda.synchronize()
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     with input_format("fp16"):
         ro, rl = swaa_attn_oracle(q, k, v, W, S, scale)
     assert float(rl.max()) < -15.0

@@ -13,23 +13,30 @@ from oracle import swaa_attn_oracle, swaa_decode_oracle
 from paper_2512_10411_amd import binding
 from paper_2512_10411_amd.inputs import (WORKLOADS, bf16_bits_to_f32, f32_to_bf16_bits, make_qkv, paged_cache,
                                          make_workload, sample_rows)
-from gpu_util import assert_parity, errors as errors_of, to_device
+from gpu_util import assert_parity, errors as errors_of, forward_packed, to_device
 
 pytestmark = pytest.mark.gpu
 
 
-def run_gpu(q, k, v, W, S, scale):
+# Head dimension 128: prompts of one length and few rows run on the short prompts' kernel (csrc/swaa_fwd_short.hip), packed
+# ones on row tiles (csrc/swaa_fwd_pipelined.hip).
+on_both_kernels = pytest.mark.parametrize("packed", [False, True])
+
+
+def run_gpu(q, k, v, W, S, scale, packed=False):
+    if packed:
+        return forward_packed(q, k, v, W, S, scale)
     out, lse = binding.swaa_attn_fwd(to_device(q), to_device(k), to_device(v), W, S, scale)
     torch.cuda.synchronize()
     return out, lse
 
 
-def check(B, Hq, Hkv, N, D, W, S, seed, scale=None, k_mult=1.0, rows=None, tag=None):
+def check(B, Hq, Hkv, N, D, W, S, seed, scale=None, k_mult=1.0, rows=None, tag=None, packed=False):
     scale = 1.0 / math.sqrt(D) if scale is None else scale
-    tag = tag or f"B{B} Hq{Hq} Hkv{Hkv} N{N} D{D} W{W} S{S}"
+    tag = tag or f"B{B} Hq{Hq} Hkv{Hkv} N{N} D{D} W{W} S{S}" + (" packed" if packed else "")
     print(f"[case] {tag} seed {seed}", flush=True)
     q, k, v = make_qkv(B, Hq, Hkv, N, D, seed, k_mult)
-    out, lse = run_gpu(q, k, v, W, S, scale)
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     ro, rl = swaa_attn_oracle(q, k, v, W, S, scale, rows=rows)
     assert_parity(out, lse, ro, rl, rows=rows, tag=tag)
 
@@ -42,6 +49,13 @@ def test_small_shapes_sweep_window_and_sinks(N, D):
     for W in sorted({1, 2, 7, 63, 64, 65, 200, N, N + 5}):
         for S in (0, 1, 4, 70):
             check(1, 4, 1, N, D, W, S, seed)
+
+
+@pytest.mark.parametrize("N", [65, 130, 257, 700])
+def test_small_packed_shapes_sweep_window_and_sinks(N):
+    for W in sorted({1, 2, 7, 63, 64, 65, 200, N, N + 5}):
+        for S in (0, 1, 4, 70):
+            check(1, 4, 1, N, 128, W, S, 1000 + N + 128, packed=True)
 
 
 @pytest.mark.parametrize("D", [32, 96, 160, 192, 224, 256])
@@ -60,6 +74,7 @@ def test_gqa_group_sizes(G):
     # every decomposition of a GQA group into 4-, 2- and 1-head workgroups
     check(2, 2 * G, 2, 333, 128, 100, 3, seed=2000 + G)
     check(1, G, 1, 515, 64, 65, 10, seed=2100 + G)
+    check(2, 2 * G, 2, 333, 128, 100, 3, seed=2000 + G, packed=True)
 
 
 @pytest.mark.parametrize("W,S", [(2000, 0), (2000, 10), (2048, 100), (127, 1000), (3000, 1000), (1, 0), (4096, 0)])
@@ -100,7 +115,8 @@ def test_window_of_one_returns_the_value_rows_bit_for_bit(D, scale):
     assert float((lse_dec - lse[:, :, -3:]).abs().max()) <= 1e-5
 
 
-def test_rows_dominated_by_one_key_outside_the_first_tile_with_large_values():
+@on_both_kernels
+def test_rows_dominated_by_one_key_outside_the_first_tile_with_large_values(packed):
     # Every key at a multiple of 97 is aligned with the queries' common component, and the
     # window holds at most one of them: a row that sees one gives it nearly all its weight.
     # For most such rows the key is not in the first half tile they visit, so its score differs
@@ -116,7 +132,7 @@ def test_rows_dominated_by_one_key_outside_the_first_tile_with_large_values():
     vf[:, :, ::97, :] *= 1.75
     q, k, v = f32_to_bf16_bits(qf), f32_to_bf16_bits(kf), f32_to_bf16_bits(vf)
     scale = 1 / math.sqrt(D)
-    out, lse = run_gpu(q, k, v, W, S, scale)
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     ro, rl = swaa_attn_oracle(q, k, v, W, S, scale)
     assert float(np.abs(ro).max()) > 4.5  # the case is what it claims to be
     assert_parity(out, lse, ro, rl, tag="dominant far key, large values")
@@ -131,7 +147,8 @@ def test_run_to_run_determinism():
     assert torch.equal(o1, o2) and torch.equal(l1, l2)
 
 
-def test_sink_heavy_scores_stress_rescaling():
+@on_both_kernels
+def test_sink_heavy_scores_stress_rescaling(packed):
     # sink keys aligned with the mean query direction: the attention-sink
     # pattern of Sec. 3.2.1; the running maximum is set by tile 0 for far rows
     B, Hq, Hkv, N, D, W, S = 1, 4, 1, 3000, 128, 256, 4
@@ -144,14 +161,15 @@ def test_sink_heavy_scores_stress_rescaling():
     kf[:, :, 2500, 0] = 20.0
     q, k = f32_to_bf16_bits(qf), f32_to_bf16_bits(kf)
     scale = 1 / math.sqrt(D)
-    out, lse = run_gpu(q, k, v, W, S, scale)
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     ro, rl = swaa_attn_oracle(q, k, v, W, S, scale)
     assert_parity(out, lse, ro, rl, tag="sink heavy")
 
 
+@on_both_kernels
 @pytest.mark.parametrize("spike", [40.0, 160.0, 216.0, 304.0, 1024.0])
-def test_late_score_spike_far_above_the_first_keys(spike):
-    # interior tiles do not search for the row maximum; a key whose score
+def test_late_score_spike_far_above_the_first_keys(spike, packed):
+    # row tiles do not search for the row maximum; a key whose score
     # exceeds everything seen before by tens of nats must still come out right
     B, Hq, Hkv, N, D, W, S = 1, 4, 1, 3100, 128, 1024, 4
     q, k, v = make_qkv(B, Hq, Hkv, N, D, seed=45)
@@ -162,12 +180,13 @@ def test_late_score_spike_far_above_the_first_keys(spike):
     kf[:, :, 2700, 0] = -spike    # and a very negative one
     q, k = f32_to_bf16_bits(qf), f32_to_bf16_bits(kf)
     scale = 1 / math.sqrt(D)
-    out, lse = run_gpu(q, k, v, W, S, scale)
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     ro, rl = swaa_attn_oracle(q, k, v, W, S, scale)
     assert_parity(out, lse, ro, rl, tag=f"late spike {spike}")
 
 
-def test_non_finite_key_rows_reach_only_the_rows_that_see_them():
+@on_both_kernels
+def test_non_finite_key_rows_reach_only_the_rows_that_see_them(packed):
     # Locality of the mask on the GPU (the oracle's own locality is pinned on the CPU): NaN and
     # infinity in a few key rows.  A row that does not see such a key -- it lies in the row's
     # future, or behind its window and outside the sinks -- must come out exactly as the oracle
@@ -179,7 +198,7 @@ def test_non_finite_key_rows_reach_only_the_rows_that_see_them():
     for j, bits in poisoned.items():
         k[:, :, j, 5::7] = np.uint16(bits)
     scale = 1 / math.sqrt(D)
-    out, lse = run_gpu(q, k, v, W, S, scale)
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     touched = set()
     for j in poisoned:
         touched.update(range(j, min(N, j + W)))
@@ -190,12 +209,13 @@ def test_non_finite_key_rows_reach_only_the_rows_that_see_them():
     assert_parity(out, lse, ro, rl, rows=rows, tag="non-finite invisible keys")
 
 
+@on_both_kernels
 @pytest.mark.parametrize("level", [-40.0, -200.0, -3000.0])
-def test_all_scores_far_below_zero(level):
+def test_all_scores_far_below_zero(level, packed):
     # q and k anti-aligned along one component: every scaled score is about `level` nats.  Rows
-    # whose first visited half tile is invisible to them start from reference 0; their
+    # whose first visited half tile is invisible to them start from reference 0 on row tiles; their
     # exponentials underflow (to nothing at all for the lower levels) and the kernel has to
-    # notice and fall back to the maximum-based routine.  MHA, so that a workgroup holds 256
+    # notice and fall back to the maximum-based routine.  MHA, so that a workgroup holds 128
     # consecutive rows and most of its waves are such rows.
     B, H, N, D, W, S = 1, 2, 900, 128, 70, 0
     scale = 1 / math.sqrt(D)
@@ -205,7 +225,7 @@ def test_all_scores_far_below_zero(level):
     qf[..., 0] = a
     kf[..., 0] = -a
     q, k = f32_to_bf16_bits(qf), f32_to_bf16_bits(kf)
-    out, lse = run_gpu(q, k, v, W, S, scale)
+    out, lse = run_gpu(q, k, v, W, S, scale, packed)
     ro, rl = swaa_attn_oracle(q, k, v, W, S, scale)
     assert float(rl.max()) < 0.5 * level
     mx, mean, _ = errors_of(out, lse, ro, rl)
@@ -283,6 +303,8 @@ def test_random_shapes_and_masks():
         S = int(rng.choice([0, 1, 3, 4, 31, 32, 33, 64, 65, 130, N, N + 3]))
         D = int(rng.choice([64, 128, 128, 128]))
         check(B, Hkv * G, Hkv, N, D, max(W, 1), S, seed=4600 + case)
+        if D == 128 and N > 64:
+            check(B, Hkv * G, Hkv, N, D, max(W, 1), S, seed=4600 + case, packed=True)
 
 
 @pytest.mark.parametrize("S", [64, 128, 1000, 1024])
@@ -294,7 +316,7 @@ def test_many_sink_tiles(S):
 
 def test_batched_uneven_gqa_groups_at_scale():
     # G = 7 = 4 + 2 + 1: all three workgroup shapes in one launch, several batch entries
-    check(3, 14, 2, 1111, 128, 300, 4, seed=4800)
+    check(3, 14, 2, 1111, 128, 300, 4, seed=4800)  # (1470 units of 32 rows: row tiles)
 
 
 def test_million_token_context_with_offsets_beyond_32_bits():
