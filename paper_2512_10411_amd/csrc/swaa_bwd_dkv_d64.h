@@ -43,10 +43,10 @@ constexpr int kBufBytes = kLseAt + 2 * 32 * 4;
 constexpr int kBufs = 6;
 constexpr int kPartBytes = kBufs * kBufBytes;
 constexpr int kZero = kParts * kPartBytes;          // a block of zeros, Q and dO
-constexpr int kSumBytes = 4 * 32 * kD * 4;          // the area doubles as the buffer of the final sums
+constexpr int kSumBytes = 4 * 32 * kD * 4;          // of the final sums, for dK and for dV, in the rings' place
 constexpr int kBytes = kZero + 2 * kBlockBytes;
 constexpr int kAhead = 3;                           // MFMAs between an LDS operand read and its use
-static_assert(kBytes >= kSumBytes && kBytes <= 160 * 1024, "one workgroup's LDS");
+static_assert(kBytes >= 2 * kSumBytes && kBytes <= 160 * 1024, "one workgroup's LDS");
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ f32x4 lds_f4(uint32_t addr) { return *(const f32x4 __attribute__((address_space(3))) *)(uintptr_t)addr; }
