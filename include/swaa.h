@@ -362,7 +362,7 @@ int swaa_attn_decode_static(const void *q, const void *k, const void *v, void *o
  *   D                   64 or 128; window, n_sink, n_prompt, scale, stream as in the forward call
  *   workspace           device scratch memory owned by the caller, 16-byte aligned, at
  *                       least swaa_attn_bwd_workspace_bytes(same shape and mask arguments)
- *                       bytes; calls that may overlap on the device need separate workspaces
+ *                       bytes, or, for a slower call, what is said there; calls that may overlap on the device need separate workspaces
  *
  * bf16 tensors 16-byte aligned; P and dS are rounded to bf16 before the second
  * products, all sums are fp32.  Deterministic (no atomics).  The library
@@ -374,11 +374,13 @@ int swaa_attn_bwd(const void *q, const void *k, const void *v, const void *out, 
                   float scale, void *workspace, long long workspace_bytes, void *stream);
 
 /*
- * Bytes of workspace swaa_attn_bwd uses (one float per query row, plus partial
- * sums for the key tiles that hold sink keys, or, of short sequences whose key tiles
- * are shared out over several workgroups each, for all of them: 128 MiB at most), or a
- * negative swaa_status.  With less, down to what key tiles that are not shared out need, the
- * call runs without sharing them out.
+ * Bytes of workspace swaa_attn_bwd uses, or a negative swaa_status: one float per query row (in
+ * all rounded up to 16 bytes) and 1024 D bytes per partial sum of a tile of 128 keys.  With T = B Hkv
+ * ceil(min(n_sink, N) / 128) tiles that hold sink keys there are none if T = 0, else at most
+ * T + max(512, T); for short sequences, whose tiles are shared out over several workgroups each, all tiles have
+ * some, at most 1536 (192 MiB of head dimension 128).  A call with less runs without sharing tiles out,
+ * as long as it has what that takes: the rows' floats and (T + max(512, T)) * 1024 D bytes (T = 0: the
+ * floats) are always enough.
  */
 long long swaa_attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int D, int window, int n_sink, int n_prompt);
 

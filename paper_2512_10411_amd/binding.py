@@ -540,7 +540,8 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
 
 
 def swaa_attn_bwd_workspace_bytes(B, Hq, Hkv, N, D, window, n_sink, n_prompt=None) -> int:
-    """Bytes of device scratch swaa_attn_bwd needs for this shape and mask."""
+    """Bytes of device scratch swaa_attn_bwd uses for this shape and mask.  Short sequences run with less, too, on fewer
+    workgroups: include/swaa.h says how much is always enough."""
     r = int(load_library().swaa_attn_bwd_workspace_bytes(
         int(B), int(Hq), int(Hkv), int(N), int(D), int(window), int(n_sink),
         2**31 - 1 if n_prompt is None else int(n_prompt)))
@@ -561,7 +562,8 @@ def swaa_attn_bwd(q, k, v, out, lse, dout, window: int, n_sink: int, n_prompt: i
     """Gradients (dq, dk, dv) of the forward call with the same mask arguments.
 
     q, out, dout: bf16 [B, Hq, N, D]; k, v: bf16 [B, Hkv, N, D]; lse: fp32 [B, Hq, N]; all
-    contiguous GPU tensors (out and lse as the forward call returned them).
+    contiguous GPU tensors (out and lse as the forward call returned them).  workspace: a uint8 tensor of
+    swaa_attn_bwd_workspace_bytes(...) bytes (allocated here with torch when None), or a smaller one as described there.
     """
     import torch
 

@@ -1,6 +1,8 @@
 // Host-side check of the backward's plan (swaa::plan_bwd) and of the tiles its workgroups take (swaa::dkv_tiles): every row that
 // sees a key of a key tile lies in exactly one query tile of one of that key tile's workgroups, the partial sums fit the
-// workspace asked for, and the workgroups of whole key tiles (swaa::dkv_main_item) have each of them once.  Built and run by tests/test_host_bwd_plan.py; needs no GPU.
+// workspace asked for, that is no more than include/swaa.h states, and the workgroups of whole key tiles (swaa::dkv_main_item) have
+// each of them once.  Built and run by tests/test_host_bwd_plan.py; needs no GPU.
+#include <algorithm>
 #include <cstdio>
 #include <vector>
 
@@ -52,6 +54,9 @@ int main() {
                                         }
                                         sound = sound && p.first_part(1, 0) == parts &&
                                                 swaa::bwd_workspace_floats(p, D) >= (long long)B * Hkv * (G * (long long)N + parts * 2 * 128 * D);
+                                        const long long T = (long long)B * Hkv * ((p.f.S + 127) / 128), few = T ? T + std::max(512LL, T) : 0;
+                                        sound = sound && 4 * swaa::bwd_workspace_floats(p, D) <=
+                                                             ((long long)B * Hkv * G * N + 3) / 4 * 16 + (pieces ? std::max(few, 1536LL) : few) * 1024 * D;
                                         if (p.n_split == 1) {
                                             const int pairs = B * Hkv, n_extra = pairs * p.n_sink_kt * p.n_seg;
                                             const unsigned n_main = (unsigned)(pairs * n_kt + 7) / 8 * 8;
