@@ -62,6 +62,12 @@ typedef enum swaa_status {
  *   scale   finite and > 0 (callers normally pass 1/sqrt(D))
  *   stream  a hipStream_t, or NULL for the default stream
  *
+ * A call repeated gives the same bits.  A prompt's bits may differ between calls of different
+ * form, here and in the two calls below: at D = 128 prompts of one length of 65 to 4096 tokens, with at most 512 tiles of
+ * 32 rows of one head in all (B Hq ceil(N / 32)), are computed by another kernel than in larger,
+ * packed and paged calls.  The results are equally exact (their distance is one rounding of
+ * the probabilities to 16 bits).
+ *
  * Returns SWAA_OK or a negative swaa_status.
  */
 int swaa_attn_fwd(const void *q, const void *k, const void *v, void *out, float *lse,

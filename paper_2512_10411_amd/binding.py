@@ -247,7 +247,8 @@ def swaa_attn_fwd(q, k, v, window: int, n_sink: int, scale: float | None = None,
     tensors on one device.  Returns (out bf16 [B, Hq, N, D], lse fp32 [B, Hq, N]).
     The call is asynchronous on `stream` (a torch stream or a HIP handle; default: torch's current stream),
     here and in all calls below; results allocated for the caller may be used on torch's current stream once that
-    has waited for `stream`.
+    has waited for `stream`.  A short prompt's bits may differ between calls of different form (batch size, packed, paged):
+    include/swaa.h says which calls run on which kernel.
     """
     return _fwd(q, k, v, window, n_sink, None, scale, out, lse, stream)
 

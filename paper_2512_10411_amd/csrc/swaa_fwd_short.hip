@@ -230,7 +230,9 @@ __global__ __launch_bounds__(kSThreads, 2) void swaa_fwd_short_kernel(const FwdS
 //    40 heads on 8    9.0 / 6.9                                 11.7 / 9.8 (400)   15.2 / 16.6
 //    4 x 32 on 8                                                8.9 / 8.8 (128 tokens: the chains are short either way)
 // Up to 64 keys there is nothing to share out (32 heads on 8 6.8 / 6.7, 8 on 8 6.3 / 6.4).  Chunks on longer caches are left to
-// the plan of split keys (plan_fwd_split), and to the pipelined kernel without a workspace: one result however they are called.
+// the plan of split keys (plan_fwd_split), and to the pipelined kernel without a workspace: one result however they are called.  A
+// whole prompt's bits depend on this rule: every wave here has a softmax reference of its own, so P is rounded elsewhere than in row
+// tiles (relative error against 64 bits, mean over 24 calls: bfloat16 0.00196, row tiles 0.00202; binary16 0.000245, 0.000253).
 bool plan_fwd_short(const FwdParams &p, FwdShortParams &sp) {
     const long long tiles = (p.Nq + kSRows - 1) / kSRows;
     if (p.cu_q || p.block_table || p.Nq != p.Nk || p.Nk <= 64 || p.Nk > 4096 || (long long)p.B * p.Hq * tiles > 512) return false;

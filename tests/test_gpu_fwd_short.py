@@ -1,7 +1,7 @@
 """GPU parity of the short prompts' forward (head dimension 128, csrc/swaa_fwd_short.hip) against the fp64 CPU oracle,
 where it can go wrong: halves that do not divide over four waves, ragged last rows and keys, sinks beside the band,
-generated rows, both formats, strided tensors, the two ends of its range.  Packed prompts stay on the pipelined kernel,
-whose second pass the last test takes at the sizes that fixed-length calls no longer run there."""
+generated rows, both formats, strided tensors, the two ends of its range.  Packed prompts stay on the pipelined kernel
+(row tiles), whose second pass the last test takes, as do the tests of other files that run packed."""
 import math
 
 import pytest
@@ -45,6 +45,31 @@ def test_strided_tensors_give_the_same_bits():
     o1, l1 = binding.swaa_attn_fwd_ex(qt, kv[:, :, 0].permute(0, 2, 1, 3), kv[:, :, 1].permute(0, 2, 1, 3), W, S)
     torch.cuda.synchronize()
     assert torch.equal(o0, o1.contiguous()) and torch.equal(l0, l1)
+
+
+def test_bits_of_a_prompt_by_the_form_of_the_call():
+    # Row tiles give a prompt the same bits packed, paged and in a batch of more than 512 units; alone it runs on the short
+    # prompts' kernel.  Each of two results is off by its rounding of P and of O, u / sqrt 3 relative each (u = 2^-9, errors spread
+    # evenly over [-u, u]); their distance is 2 u / sqrt 3 of the norm, and the bar twice that.
+    Hq, Hkv, N, W, S, page = 8, 2, 500, 200, 4, 16
+    B = 512 // (Hq * ((N + 31) // 32)) + 1
+    q, k, v = (to_device(x) for x in make_qkv(B, Hq, Hkv, N, 128, seed=97700))
+    batch, lse_batch = binding.swaa_attn_fwd(q, k, v, W, S)
+    cu = torch.tensor([0, N], dtype=torch.int32).cuda()
+    packed, lse_packed = binding.swaa_attn_fwd_ex(q[0], k[0], v[0], W, S, cu_seqlens_q=cu, cu_seqlens_k=cu, max_seqlen_q=N, max_seqlen_k=N)
+    pages = (N + page - 1) // page
+    cache = [torch.zeros(Hkv, pages * page, 128, dtype=x.dtype, device="cuda") for x in (k, v)]
+    for c, x in zip(cache, (k, v)):
+        c[:, :N] = x[0]
+    cache = [c.view(Hkv, pages, page, 128).transpose(0, 1).contiguous() for c in cache]
+    table = torch.arange(pages, dtype=torch.int32, device="cuda")[None]
+    paged, lse_paged = binding.swaa_attn_fwd_ex(q[:1], *cache, W, S, block_table=table, max_seqlen_k=N)
+    alone, lse_alone = binding.swaa_attn_fwd(q[:1].contiguous(), k[:1].contiguous(), v[:1].contiguous(), W, S)
+    torch.cuda.synchronize()
+    assert torch.equal(batch[0], packed) and torch.equal(batch[:1], paged)
+    assert torch.equal(lse_batch[0], lse_packed) and torch.equal(lse_batch[:1], lse_paged)
+    assert (alone.float() - paged.float()).norm() <= 4 * 2.0**-9 / math.sqrt(3) * paged.float().norm()
+    assert (lse_alone - lse_paged).abs().max() <= 1e-5
 
 
 @pytest.mark.parametrize("factor", [1.0, 60.0])  # 60: scores far above the first keys', the second pass
