@@ -238,7 +238,7 @@ __device__ __forceinline__ void softmax_half(f32x16 &s, int k0h, int qpos, int W
     const float m_new = fmaxf(mc_old, mx * c2 - (float)kBelow);
     const bool move = m_new > mc_old + kRefSlack;  // -inf never moves to -inf
     st.mc = move ? m_new : mc_old;
-    const float mc_use = (kMask && st.mc == -INFINITY) ? 0.f : st.mc;
+    const float mc_use = st.mc == -INFINITY ? 0.f : st.mc;  // (no key yet that is visible and scores more than -infinity)
     alpha = move ? __builtin_amdgcn_exp2f(mc_old - mc_use) : 1.f;
     float rs = 0.f, rb = 0.f;
 #pragma unroll

@@ -47,6 +47,27 @@ def test_strided_tensors_give_the_same_bits():
     assert torch.equal(o0, o1.contiguous()) and torch.equal(l0, l1)
 
 
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+@pytest.mark.parametrize("Nq,N,W,S,dead", [
+    (500, 500, 500, 0, (128, 256)),     # all the keys of one wave
+    (1000, 1000, 700, 4, (300, 900)),   # of several, behind the sinks; row 899's own key among them
+    (1, 4000, 4000, 4, (0, 1500)),      # few rows on a longer cache: the same routine
+    (4, 3000, 1000, 4, (64, 2500)),
+])
+def test_keys_that_score_minus_infinity_weigh_nothing(Nq, N, W, S, dead, fmt):
+    # a mask carried by a component of its own: 1 in every query, 0 or -infinity in the keys.  A wave whose first halves hold
+    # such keys alone has no reference yet.
+    q, k, v = make_qkv(1, 8, 2, N, 128, seed=97800 + N, n_query=None if Nq == N else Nq, fmt=fmt)
+    one, minus_inf = (0x3F80, 0xFF80) if fmt == "bf16" else (0x3C00, 0xFC00)
+    q[..., 5], k[..., 5] = one, 0
+    k[:, :, dead[0]:dead[1], 5] = minus_inf
+    out, lse = binding.swaa_attn_fwd_ex(to_device(q, fmt), to_device(k, fmt), to_device(v, fmt), W, S)
+    torch.cuda.synchronize()
+    with input_format(fmt):
+        ro, rl = swaa_decode_oracle(q, k, v, W, S, 1 / math.sqrt(128))
+    assert_parity(out, lse, ro, rl, tag=f"keys {dead} of {N} at -infinity {fmt}")
+
+
 def test_bits_of_a_prompt_by_the_form_of_the_call():
     # Row tiles give a prompt the same bits packed, paged and in a batch of more than 512 units; alone it runs on the short
     # prompts' kernel.  Each of two results is off by its rounding of P and of O, u / sqrt 3 relative each (u = 2^-9, errors spread
