@@ -294,7 +294,16 @@ inline int die_shift(long long pairs) { return pairs == 1 ? 3 : pairs == 2 ? 2 :
 // `rows` query rows; needs B, Hkv, G, Nk, W and P.  False if the work list does not fit 31 bits.
 // Where the rows differ much in length (a window of half the keys and more, or generated rows behind a prompt):
 //   * dies that share a pair take its tiles in turn: with a contiguous part each, one has the long rows and the others are done
-//     early (16 heads on 4, full attention, 8192 tokens 281 us, in turn 254; window 8192 of 16384 776, 716);
+//     early (16 heads on 4, full attention, 8192 tokens 281 us, in turn 254; window 8192 of 16384 776, 716).  With generated rows,
+//     or prompt lengths of their own, behind narrower windows the few long rows are the time in either order, and if there are
+//     none the neighbours' common bands count (prompt lengths that leave no generated row, contiguous / in turn, us:
+//        window, of the tokens           1/32          1/16          1/8            1/6            1/4            1/3
+//        4 heads on 1   16384 tokens  28.9 / 31.2   41.4 / 47.2   72.2 / 75.4    93.3 / 92.6     131 / 127      173 / 166
+//                       65536          269 / 305                   970 / 1024   1277 / 1298     1878 / 1836    2503 / 2283
+//        8 on 2         16384         46.5 / 50.3   79.9 / 83.3    134 / 133     175 / 170       251 / 237      326 / 289
+//                       65536          513 / 521                  1929 / 1837   2569 / 2370     3825 / 3344    4962 / 4263
+//        16 on 4        65536         1007 / 1012                 3743 / 3585   4966 / 4676     7265 / 6610    9463 / 8385
+//     32 generated rows, 65536 tokens, window 1/32: 912 / 935, 1020 / 1013 and 1245 / 1251);
 //   * a die with several pairs takes the long rows of all of them first, not pair after pair (four sequences of 2048 tokens,
 //     32 heads on 8: 139 -> 134, head dimension 64 101 -> 86; four of 4096, 40 heads on 8: 639 -> 617; its backward
 //     2277 -> 2215).  Not with more than 192 tiles to a pair, whose keys no longer share the L2 (two of 8192: 934, 951);
@@ -315,13 +324,13 @@ inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     p.packed_compact = 0;
     p.total_items = (long long)p.B * p.Hkv * p.tiles_per_pair;
     const bool rows_differ = 2LL * p.W >= p.Nk || p.P < p.Nk || p.n_prompts;
+    const long long pairs = (long long)p.B * p.Hkv;
+    const bool in_turn = 2LL * p.W >= p.Nk || (rows_differ && (pairs == 1 ? 4LL : 8LL) * p.W >= p.Nk);
     p.div_tiles_per_pair = make_fastdiv((unsigned)p.tiles_per_pair);
     p.div_hkv = make_fastdiv((unsigned)p.Hkv);
     p.div_nt_h4 = make_fastdiv((unsigned)p.nt_h4);
     p.chunk = (p.total_items + kXcds - 1) / kXcds;
-    const int shift = die_shift((long long)p.B * p.Hkv);
-    p.die_shift = rows_differ ? shift : 0;
-    const long long pairs = (long long)p.B * p.Hkv;
+    p.die_shift = in_turn ? die_shift(pairs) : 0;
     p.die_pairs = rows_differ && pairs % kXcds == 0 && p.tiles_per_pair <= 192 ? (int)(pairs / kXcds) : 1;
     p.div_die_pairs = make_fastdiv((unsigned)p.die_pairs);
     p.die_items = p.die_shift || p.die_pairs > 1 ? p.tiles_per_pair : (int)p.chunk;  // (times die_pairs, shared by the dies: chunk)

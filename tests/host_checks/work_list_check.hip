@@ -1,5 +1,5 @@
 // Host-side check of the work list's order (swaa::work_place): whatever the plan, every row tile of every pair is one
-// workgroup's and no workgroup has two.  Built and run by tests/test_host_work_list.py; needs no GPU.
+// workgroup's and no workgroup has two; and dies take a pair's tiles in turn only behind windows that make rows differ.  Built and run by tests/test_host_work_list.py; needs no GPU.
 #include <cstdio>
 #include <vector>
 
@@ -11,7 +11,7 @@ int main() {
         for (int Hkv : {1, 2, 3, 4, 8, 12})
             for (int G : {1, 2, 4, 5, 7, 8})
                 for (int rows : {1, 33, 128, 500, 1000, 2048, 2049, 6200, 9000})
-                    for (int W : {64, rows / 2, rows})
+                    for (int W : {64, rows / 9, rows / 6, rows / 2, rows})
                         for (int P : {rows, rows - 1})
                             for (int wg_rows : {128, 256})
                                 for (bool fold : {true, false}) {
@@ -21,7 +21,7 @@ int main() {
                                     if (!fold) p.fold = 0x7fffffff;
                                     std::vector<int> seen((size_t)p.total_items, 0);
                                     long items = 0;
-                                    bool sound = true;
+                                    bool sound = p.die_shift == 0 || (B * Hkv == 1 ? 4 : 8) * p.W >= rows;
                                     for (unsigned bid = 0; bid < (unsigned)(p.chunk * swaa::kXcds); ++bid) {
                                         unsigned pair, r;
                                         if (!swaa::work_place(p, bid, pair, r)) continue;
