@@ -374,8 +374,8 @@ def main():
         roofline = {"bound": "mfma", "achieved": achieved, "peak": BF16_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": achieved / BF16_MFMA_PEAK_TFLOPS, "traffic": traffic, "traffic_source": traffic_source,
                     "kernel": (("swaa_bwd_dkv_dma_kernel + swaa_bwd_dq_pipelined_kernel" if w.D == 128 else
-                                f"swaa_bwd_dkv_kernel<{w.D}> + swaa_bwd_dq_kernel<{w.D}>") if w.backward
-                               else "swaa_fwd_pipelined_kernel" if w.D == 128
+                                f"swaa_bwd_dkv_kernel<{w.D}> + swaa_bwd_dq_kernel") if w.backward
+                               else "swaa_fwd_pipelined_kernel" if w.D == 128 else "swaa_fwd_d64_kernel" if w.D == 64
                                else f"swaa_fwd_kernel<{w.D}>"),
                     "kernel_avg_ms": kern_avg_ms}
 

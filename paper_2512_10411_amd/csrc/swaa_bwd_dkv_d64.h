@@ -11,9 +11,10 @@
 // S, dP of block n + 1 and of dV^T += dO^T P, dK^T += Q^T dS of block n - 1, and in their shadow the vector work of block n,
 // fixed by hand with scheduling fences; LDS operands are asked for kAhead MFMAs ahead.
 // Two sequences of 4001 tokens, 16 heads on 4, window 1000: 126 us with twelve waves, three per SIMD, that took products, vector
-// work and products in turn, all in the same phase (matrix pipe busy 37 % of the cycles, vector ALU 48 %, the waves
-// waiting 47 % of theirs); now 96.  16384 tokens, 32 heads on 8, window 8192: 1970 -> 1660 (matrix 47 %, vector 46 %).  No one thing bounds
-// it: without the exponentials, the copies, the barrier or a third of the LDS reads it takes 0 to 5 % less.  (Also tried: one wave per
+// work and products in turn, all in the same phase; now 96.  16384 tokens, 32 heads on 8, window 8192: 1970 -> 1660.  There the matrix
+// pipe is busy 47 % of the time, the vector ALU 46 %, LDS 35 %; on the first shape, whose 280 workgroups leave the
+// compute units empty for 29 % of it, 30, 33 and 23 % (profiles/swaa_train_d64_sq_counters.txt).  No one thing bounds
+// the loop: without the exponentials, the copies, the barrier or a third of the LDS reads it takes 0 to 5 % less.  (Also tried: one wave per
 // SIMD on 64 keys, as for head dimension 128: no faster than the twelve waves.)
 //
 // Blocks travel HBM -> LDS by global_load_lds_dwordx4 into a ring of six buffers per half of the list, two blocks and one
