@@ -306,7 +306,11 @@ inline int die_shift(long long pairs) { return pairs == 1 ? 3 : pairs == 2 ? 2 :
 //     32 generated rows, 65536 tokens, window 1/32: 912 / 935, 1020 / 1013 and 1245 / 1251);
 //   * a die with several pairs takes the long rows of all of them first, not pair after pair (four sequences of 2048 tokens,
 //     32 heads on 8: 139 -> 134, head dimension 64 101 -> 86; four of 4096, 40 heads on 8: 639 -> 617; its backward
-//     2277 -> 2215).  Not with more than 192 tiles to a pair, whose keys no longer share the L2 (two of 8192: 934, 951);
+//     2277 -> 2215).  Not with more than 192 tiles to a pair, whose keys no longer share the L2 (two of 8192: 934, 951).
+//     Where the heads of a pair make tiles of several kinds, the long rows of one kind stand behind the short ones of another,
+//     and a list of 45 to 63 tiles, which is not folded, puts them beside the longest (pair after pair / long rows of all first,
+//     24 heads on 8: two of 1150 tokens, 54 tiles, 30.3 / 33.8, four of 584, 60 tiles, 21.9 / 24.6; 48 on 8, two of 503, 48 tiles, 19.1 / 20.0):
+//     pair after pair there.  Shorter lists have few seconds (40 on 8, two of 430, 36 tiles, 20.6 / 17.0 on half the keys), longer ones more rounds;
 //   * where a die's list is one round of two workgroups to a compute unit, its second half is turned round, so that the longest
 //     is not beside the longest of the rest but beside the shortest (2048 tokens 44.8 -> 41.7; four sequences of 500 21.2 ->
 //     18.1, two of 4000, 8 heads on 8, 90.8 -> 74.2; with the line above).
@@ -331,7 +335,9 @@ inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     p.div_nt_h4 = make_fastdiv((unsigned)p.nt_h4);
     p.chunk = (p.total_items + kXcds - 1) / kXcds;
     p.die_shift = in_turn ? die_shift(pairs) : 0;
-    p.die_pairs = rows_differ && pairs % kXcds == 0 && p.tiles_per_pair <= 192 ? (int)(pairs / kXcds) : 1;
+    const int kinds = (p.n4 > 0) + p.has2 + p.has1;  // of tiles: of four, two and one head
+    const bool beside_long = kinds > 1 && p.chunk > 44 && p.chunk < 64;
+    p.die_pairs = rows_differ && pairs % kXcds == 0 && p.tiles_per_pair <= 192 && !beside_long ? (int)(pairs / kXcds) : 1;
     p.div_die_pairs = make_fastdiv((unsigned)p.die_pairs);
     p.die_items = p.die_shift || p.die_pairs > 1 ? p.tiles_per_pair : (int)p.chunk;  // (times die_pairs, shared by the dies: chunk)
     p.fold = p.chunk <= 64 && rows_differ && p.n4 + p.has2 + p.has1 == 1 ? 32 : 0x7fffffff;

@@ -1,5 +1,6 @@
 // Host-side check of the work list's order (swaa::work_place): whatever the plan, every row tile of every pair is one
-// workgroup's and no workgroup has two; and dies take a pair's tiles in turn only behind windows that make rows differ.  Built and run by tests/test_host_work_list.py; needs no GPU.
+// workgroup's and no workgroup has two; dies take a pair's tiles in turn only behind windows that
+// make rows differ, and lists of one round with tiles of several kinds go pair after pair.  Built and run by tests/test_host_work_list.py; needs no GPU.
 #include <cstdio>
 #include <vector>
 
@@ -21,7 +22,9 @@ int main() {
                                     if (!fold) p.fold = 0x7fffffff;
                                     std::vector<int> seen((size_t)p.total_items, 0);
                                     long items = 0;
-                                    bool sound = p.die_shift == 0 || (B * Hkv == 1 ? 4 : 8) * p.W >= rows;
+                                    const bool mixed = (G > 3) + (G % 4 > 1) + G % 2 > 1;
+                                    bool sound = (!mixed || p.chunk <= 44 || p.chunk >= 64 || p.die_pairs == 1) &&
+                                                 (p.die_shift == 0 || (B * Hkv == 1 ? 4 : 8) * p.W >= rows);
                                     for (unsigned bid = 0; bid < (unsigned)(p.chunk * swaa::kXcds); ++bid) {
                                         unsigned pair, r;
                                         if (!swaa::work_place(p, bid, pair, r)) continue;
