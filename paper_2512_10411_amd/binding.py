@@ -585,7 +585,14 @@ def swaa_attn_bwd(q, k, v, out, lse, dout, window: int, n_sink: int, n_prompt: i
     with _on_device_of(q) if stream is None else _launching_on(stream, q):
         dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
         if workspace is None:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            try:
+                workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            except torch.cuda.OutOfMemoryError:  # (what is always enough, include/swaa.h: slower, not refused)
+                tiles = B * Hkv * ((min(int(n_sink), N) + 127) // 128)
+                least = (B * Hq * N + 3) // 4 * 16 + (tiles + max(512, tiles) if tiles else 0) * 1024 * D
+                if least >= need:
+                    raise
+                workspace = torch.empty(least, dtype=torch.uint8, device=q.device)
         elif workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
             raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
         sptr = _stream_handle(stream, q)

@@ -348,3 +348,25 @@ def test_key_tiles_in_pieces(B, Hkv, G, N, W, S, P, D):
     assert all(torch.equal(x, y) for x, y in zip(runs[0], runs[1]))
     for x, y in zip(runs[0], runs[2]):  # fp32 sums in another order, then one rounding each to bf16
         assert (x.float() - y.float()).norm() <= 2.0 ** -8 * x.float().norm()
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,Hkv,G,N,W,S", [(1, 2, 4, 1000, 1000, 0), (16, 2, 16, 1000, 512, 500)])  # delta alone; segments too
+def test_no_memory_for_pieces(B, Hkv, G, N, W, S, D, monkeypatch):
+    # where the partial sums of pieces find no memory the call runs on whole key tiles, as with a workspace too small for pieces
+    q, k, v, dd = (to_device(x) for x in (*make_qkv(B, G * Hkv, Hkv, N, D, seed=9900 + D), make_dout((B, G * Hkv, N, D), 9901 + D)))
+    out, lse = binding.swaa_attn_fwd(q, k, v, W, S)
+    want = binding.swaa_attn_bwd(q, k, v, out, lse, dd, W, S, workspace=whole_key_tiles(B, G * Hkv, Hkv, N, D, W, S, None))
+    need = binding.swaa_attn_bwd_workspace_bytes(B, G * Hkv, Hkv, N, D, W, S)
+    empty = torch.empty
+
+    def little(*args, **kwargs):
+        if kwargs.get("dtype") == torch.uint8 and args[0] >= need:
+            raise torch.cuda.OutOfMemoryError("no memory")
+        return empty(*args, **kwargs)
+
+    monkeypatch.setattr(torch, "empty", little)
+    got = binding.swaa_attn_bwd(q, k, v, out, lse, dd, W, S)
+    torch.cuda.synchronize()
+    monkeypatch.undo()
+    assert all(torch.equal(x, y) for x, y in zip(got, want))
