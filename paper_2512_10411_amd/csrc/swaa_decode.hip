@@ -55,26 +55,30 @@ constexpr int kDWaves = 4;
 constexpr int kDThreads = 64 * kDWaves;
 // LDS of a workgroup: every wave's ring, then the waves' references and row sums at the end
 constexpr int decode_wave_bytes(int tiles) { return decode_stages(tiles) * kDStageBytes; }
-constexpr int decode_smem_bytes(int tiles) { return kDWaves * (decode_wave_bytes(tiles) + tiles * 256); }
+constexpr int decode_smem_bytes(int tiles) { return kDWaves * (decode_wave_bytes(tiles) + tiles * 512); }
 constexpr int kCopiesPerHalf = 16;                    // wave instructions per stage: 8 for K, 8 for V
-constexpr int kMergeThreads = 1024;
+constexpr int kMergeThreads = 256;
 constexpr long long kDResident = 512;                 // workgroups of one column tile that run at once
 constexpr long long kDResidentPairs = 256;            // ... of two
 
 // ---- the split plan of a batch with per-sequence lengths, worked out by every workgroup of the
 // split kernel (DecodeParams::ragged has the rules) ----
-// Lane l keeps the halves that sequences l, 64 + l, ... visit (0 beyond the batch).
+// Lane l keeps the lengths of sequences l, 64 + l, ... and the halves they visit (0 beyond the batch).
 constexpr int kRaggedLaneRounds = kRaggedMaxBatch / 64;
 struct RaggedHalves {
+    int nk[kRaggedLaneRounds];
     unsigned n[kRaggedLaneRounds];
 };
 __device__ __forceinline__ RaggedHalves ragged_halves(const DecodeParams &p, int lane) {
     RaggedHalves h;
 #pragma unroll
+    for (int r = 0; r < kRaggedLaneRounds; ++r) h.nk[r] = p.seq_lens[min(64 * r + lane, p.B - 1)];
+    static_assert(kRaggedLaneRounds == 4, "");
+    asm volatile("" : "+v"(h.nk[0]), "+v"(h.nk[1]), "+v"(h.nk[2]), "+v"(h.nk[3]));  // (all asked for at once, not one behind the other's branch)
+#pragma unroll
     for (int r = 0; r < kRaggedLaneRounds; ++r) {
-        const int b = 64 * r + lane;
-        const int nk = max(min(p.seq_lens[min(b, p.B - 1)], p.Nk), p.Nq);
-        h.n[r] = b < p.B ? (unsigned)visited_halves(nk, p.Nq, p.W, p.S).n : 0u;
+        h.nk[r] = max(min(h.nk[r], p.Nk), p.Nq);
+        h.n[r] = 64 * r + lane < p.B ? (unsigned)visited_halves(h.nk[r], p.Nq, p.W, p.S).n : 0u;
     }
     return h;
 }
@@ -103,8 +107,8 @@ __device__ __forceinline__ unsigned ragged_halves_per_split(const DecodeParams &
     return hps;
 }
 // The sequence and the split of unit `unit` of the list (sequence 0's splits, then sequence 1's, ...)
-// and how many splits that sequence has; false beyond the list's end.
-__device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps, unsigned unit, int &b, int &split, int &n_splits) {
+// and how many splits and keys that sequence has; false beyond the list's end.
+__device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps, unsigned unit, int &b, int &split, int &n_splits, int &nk) {
     unsigned before = 0;
 #pragma unroll
     for (int r = 0; r < kRaggedLaneRounds; ++r) {
@@ -120,6 +124,7 @@ __device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps,
             b = __builtin_amdgcn_readfirstlane(64 * r + n);
             split = __builtin_amdgcn_readfirstlane((int)(rel - base));
             n_splits = (int)wave_read_lane(mine, n);
+            nk = (int)wave_read_lane((unsigned)h.nk[r], n);
             return true;
         }
         before += in_round;
@@ -132,6 +137,7 @@ __device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps,
 // query rows: two tiles in two workgroups read every key twice, which only some sizes make up for, see plan_decode).
 template <bool kF16, bool kPaged, int kTiles>
 __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_decode_split_kernel(const DecodeParams p) {
+    fetch_args<DecodeParams>();
     // Workgroups reach the eight dies round-robin; the list has fewer than 2^31 items: 32-bit
     // arithmetic, divisions as multiplications.  Sequences of one length: die x takes the x-th
     // contiguous chunk of the item list (a die streams neighbouring memory: 3 % faster on one
@@ -157,13 +163,14 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
     const unsigned item_ct = fastdiv(witem, p.div_ctgroups);      // witem / n_ctgroups
     const int ctg = (int)(witem - item_ct * (unsigned)p.n_ctgroups);
     int b, kvh, split, halves_per_split, n_splits;
+    int Nk;  // this sequence's cache length (at least the query rows themselves)
     size_t slot0;  // workspace slot of the item's column tile 0
     if (p.ragged) {
         const unsigned unit = fastdiv(item_ct, p.div_hkv);        // (sequence, split) units, KV head innermost
         kvh = (int)(item_ct - unit * (unsigned)p.Hkv);
         const RaggedHalves rh = ragged_halves(p, lane);
         halves_per_split = __builtin_amdgcn_readfirstlane((int)ragged_halves_per_split(p, rh));
-        if (!ragged_find(rh, (unsigned)halves_per_split, unit, b, split, n_splits)) return;  // beyond the true list
+        if (!ragged_find(rh, (unsigned)halves_per_split, unit, b, split, n_splits, Nk)) return;  // beyond the true list
         slot0 = (size_t)item_ct * p.n_coltiles;
         // the sequence's first workgroup tells the merge kernel where its splits are (all lanes
         // store the same two words: a branch on the lane id here would make the compiler treat
@@ -180,6 +187,9 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
         halves_per_split = p.halves_per_split;
         n_splits = p.n_splits;
         slot0 = ((size_t)upair * p.n_splits + split) * p.n_coltiles;
+        // (read as constant memory -- nothing writes the lengths while the kernel runs -- so that it is a scalar load)
+        typedef const int __attribute__((address_space(4))) *ConstInts;
+        Nk = p.seq_lens ? max(min(((ConstInts)p.seq_lens)[b], p.Nk), p.Nq) : p.Nk;
     }
     // this workgroup's column tiles and the workspace slots of their partial results
     int ct[kTiles];
@@ -194,11 +204,6 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
 
     const int l32 = lane & 31;
     const int hf = lane >> 5;
-    // this sequence's cache length (at least the query rows themselves) and its visited halves
-    // (read as constant memory -- nothing writes the lengths while the kernel runs -- so that it is
-    // a scalar load whatever the kernel has stored before it)
-    typedef const int __attribute__((address_space(4))) *ConstInts;
-    const int Nk = p.seq_lens ? max(min(((ConstInts)p.seq_lens)[b], p.Nk), p.Nq) : p.Nk;
     const int W = p.W, S = p.S;
     const VisitedHalves vh = visited_halves(Nk, p.Nq, W, S);
 
@@ -248,9 +253,38 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
     const TablePtr bt = paged ? (TablePtr)(p.block_table + (size_t)b * p.bt_stride) : nullptr;
 
     // ---- HBM -> LDS copies of one half: instruction i moves rows 4i .. 4i+3, 16 lanes
-    // per row; the XOR swizzle of the operand reads is applied on the global side.  Rows
-    // past the end of the cache repeat its last row (they are masked later). ----
+    // per row; the XOR swizzle of the operand reads is applied on the global side (K's has a period of four
+    // instructions, V's of one).  Rows past the end of the cache repeat its last row (they are masked later).
+    // A half with all its rows takes its lanes' offsets from the registers below, and the instruction's row
+    // enters through the scalar base: a row's clamp and product per copy were 300 cycles in front of every half. ----
     const int lrow = lane >> 4, lchk = lane & 15;
+    uint32_t k_lane[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) k_lane[i] = (uint32_t)lrow * k_rsb + (uint32_t)((lchk ^ (((4 * (i & 1) + lrow) << 1) | (i >> 1))) << 4);
+    const uint32_t v_lane = (uint32_t)lrow * v_rsb + (uint32_t)((lchk ^ (lrow << 2)) << 4);
+    auto copy_row4 = [](uint32_t lds, uint32_t off, const char *base) __attribute__((always_inline)) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+    };
+    // The half whose row 0 is at kb[0], vb[0] and whose row 16 is 16 rows behind kb[1], vb[1]; `last` is its last row inside the cache.
+    auto copy_half = [&](uint32_t lds, const char *const(&kb)[2], const char *const(&vb)[2], int last) __attribute__((always_inline)) {
+        if (last >= 31) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) copy_row4(lds + (uint32_t)(i * 1024), k_lane[i & 3], kb[i / 4] + (size_t)(4 * i) * k_rsb);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) copy_row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane, vb[i / 4] + (size_t)(4 * i) * v_rsb);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {  // (the swizzle goes by the row's place in the half, the address by the row that is there)
+            const int back = max(4 * i + lrow - last, 0);
+            copy_row4(lds + (uint32_t)(i * 1024), k_lane[i & 3] + (uint32_t)(4 * i - back) * k_rsb, kb[i / 4]);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int back = max(4 * i + lrow - last, 0);
+            copy_row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane + (uint32_t)(4 * i - back) * v_rsb, vb[i / 4]);
+        }
+    };
     // Paged cache: the block-table entries one half needs -- one if a page holds a multiple of 32
     // tokens, two for a multiple of 16, else none here (looked up per copy instruction).  They
     // are scalar loads with a long way to go, asked for one loop iteration before the copy.
@@ -272,6 +306,7 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
     auto issue_half = [&](int t, int stage, const Pages pg) __attribute__((always_inline)) {
         const int k0 = first_key(t);
         const uint32_t lds = (uint32_t)(wave * decode_wave_bytes(kTiles) + stage * kDStageBytes);
+        const char *kb[2], *vb[2];
         if constexpr (paged) {
             if (pages_per_half == 0) {
                 // page_size is a multiple of 4 only: the four rows of one instruction share a
@@ -282,18 +317,11 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
                     const unsigned pi = fastdiv((unsigned)key4, p.div_page);
                     const int page = min(max(bt[pi], 0), p.num_pages - 1);  // inside the cache whatever the table says
                     const int in_page = key4 - (int)pi * p.page_size;
-                    const char *kb = kg + ((long long)page * p.k_sb + (long long)in_page * p.k_sn) * 2;
-                    const char *vb = vg + ((long long)page * p.v_sb + (long long)in_page * p.v_sn) * 2;
-                    const int row = min(key4 + lrow, Nk - 1) - key4;
-                    const int fk = ((4 * (i & 1) + lrow) << 1) | ((i >> 1) & 1);
-                    const uint32_t koff = (uint32_t)row * k_rsb + (uint32_t)((lchk ^ fk) << 4);
-                    const uint32_t voff = (uint32_t)row * v_rsb + (uint32_t)((lchk ^ (lrow << 2)) << 4);
-                    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(koff), "s"(kb),
-                                 "s"(lds + (uint32_t)(i * 1024))
-                                 : "memory");
-                    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(vb),
-                                 "s"(lds + (uint32_t)(kHalfBytes + i * 1024))
-                                 : "memory");
+                    const int back = max(key4 + lrow - (Nk - 1), 0);
+                    copy_row4(lds + (uint32_t)(i * 1024), k_lane[i & 3] - (uint32_t)back * k_rsb,
+                              kg + ((long long)page * p.k_sb + (long long)in_page * p.k_sn) * 2);
+                    copy_row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane - (uint32_t)back * v_rsb,
+                              vg + ((long long)page * p.v_sb + (long long)in_page * p.v_sn) * 2);
                 }
                 return;
             }
@@ -310,7 +338,6 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
             };
             const int in_a = k0 - (int)fastdiv((unsigned)k0, p.div_page) * p.page_size;
             const int page_a = min(max(pg.a, 0), p.num_pages - 1);
-            const char *kb[2], *vb[2];
             kb[0] = kb[1] = base_of(kg, p.k_sb, p.k_sn, page_a, in_a);
             vb[0] = vb[1] = base_of(vg, p.v_sb, p.v_sn, page_a, in_a);
             if (pages_per_half == 2 && k0 + 16 <= Nk - 1) {
@@ -319,44 +346,11 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
                 kb[1] = base_of(kg, p.k_sb, p.k_sn, page_b, in_b - 16);
                 vb[1] = base_of(vg, p.v_sb, p.v_sn, page_b, in_b - 16);
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int row = min(4 * i + lrow, Nk - 1 - k0);
-                const int fk = ((4 * (i & 1) + lrow) << 1) | ((i >> 1) & 1);
-                const uint32_t off = (uint32_t)row * k_rsb + (uint32_t)((lchk ^ fk) << 4);
-                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(kb[i / 4]),
-                             "s"(lds + (uint32_t)(i * 1024))
-                             : "memory");
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int row = min(4 * i + lrow, Nk - 1 - k0);
-                const uint32_t off = (uint32_t)row * v_rsb + (uint32_t)((lchk ^ (lrow << 2)) << 4);
-                asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(vb[i / 4]),
-                             "s"(lds + (uint32_t)(kHalfBytes + i * 1024))
-                             : "memory");
-            }
-            return;
+        } else {
+            kb[0] = kb[1] = kg + (size_t)k0 * k_rsb;  // uniform
+            vb[0] = vb[1] = vg + (size_t)k0 * v_rsb;
         }
-        const char *kb = kg + (size_t)k0 * k_rsb;  // uniform
-        const char *vb = vg + (size_t)k0 * v_rsb;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = min(4 * i + lrow, Nk - 1 - k0);
-            const int fk = ((4 * (i & 1) + lrow) << 1) | ((i >> 1) & 1);
-            const uint32_t off = (uint32_t)row * k_rsb + (uint32_t)((lchk ^ fk) << 4);
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(kb),
-                         "s"(lds + (uint32_t)(i * 1024))
-                         : "memory");
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int row = min(4 * i + lrow, Nk - 1 - k0);
-            const uint32_t off = (uint32_t)row * v_rsb + (uint32_t)((lchk ^ (lrow << 2)) << 4);
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(vb),
-                         "s"(lds + (uint32_t)(kHalfBytes + i * 1024))
-                         : "memory");
-        }
+        copy_half(lds, kb, vb, Nk - 1 - k0);
     };
     const LaneAddr la = make_lane_addr(lane, 0);
 
@@ -456,80 +450,70 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
         stage = (stage + 1 == kDStages) ? 0 : stage + 1;
     }
 
-    // ---- the four waves' results are added up through LDS (each wave's O in its own ring, which
-    // only it has used, in accumulator order: conflict-free and without padding), then leave as
-    // the split's partial result -- or, with one split, as the output itself.
-    // The merge divides by the fp32 sums it combines; a wave's O is the sum over the rounded P,
-    // so it enters scaled by l / (sum of the rounded P). ----
-    typedef float __attribute__((address_space(3))) *LdsFloats;
+    // ---- the four waves' results are added up through LDS: each wave's O goes to its own ring, which only it has
+    // used, one row of 512 bytes per valid column (16-byte chunk q of column c at q ^ c: neither the writes, a column
+    // per lane, nor the reads, a column per 32 lanes, meet on a bank), and next to the rings what a column's share is
+    // weighted with.  Behind one barrier, 32 threads take a column.  The sum leaves as the split's partial
+    // result -- or, with one split, as the output itself.  The merge divides by the fp32 sums it combines; a wave's
+    // O is the sum over the rounded P, so it enters scaled by l / (sum of the rounded P). ----
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef f32x4 __attribute__((address_space(3))) *LdsQuads;
-    constexpr uint32_t kMl = (uint32_t)(kDWaves * decode_wave_bytes(kTiles));  // [tile][wave][2][32]
-    float fix[kTiles];
+    constexpr uint32_t kMl = (uint32_t)(kDWaves * decode_wave_bytes(kTiles));  // [tile][wave][32] of reference, l, l / sum of rounded, 0
 #pragma unroll
     for (int j = 0; j < kTiles; ++j) {
         float l_row, lb_row;
         row_sums(rs[j], l_row, lb_row);
-        fix[j] = lb_row > 0.f ? l_row / lb_row : 0.f;  // a column that saw no key: O = 0, l = 0
-        ((LdsFloats)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + wave) * 256)))[lane] = hf ? l_row : rs[j].mc;
-    }
-    __syncthreads();
-    float m[kTiles], l[kTiles];
-#pragma unroll
-    for (int j = 0; j < kTiles; ++j) {
-        float mcs[kDWaves];
-        m[j] = -INFINITY;
-#pragma unroll
-        for (int x = 0; x < kDWaves; ++x) {
-            mcs[x] = ((LdsFloats)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + x) * 256)))[l32];
-            m[j] = fmaxf(m[j], mcs[x]);
-        }
-        const float m_use = m[j] == -INFINITY ? 0.f : m[j];
-        l[j] = 0.f;
-#pragma unroll
-        for (int x = 0; x < kDWaves; ++x)
-            l[j] += __builtin_amdgcn_exp2f(mcs[x] - m_use) * ((LdsFloats)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + x) * 256)))[32 + l32];
-        fix[j] *= __builtin_amdgcn_exp2f(rs[j].mc - m_use);
         if (col_valid[j]) {
+            const f32x4 ml = {rs[j].mc, l_row, lb_row > 0.f ? l_row / lb_row : 0.f, 0.f};  // a column that saw no key: O = 0, l = 0
+            if (hf == 0) *(LdsQuads)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + wave) * 512 + l32 * 16)) = ml;
+            const uint32_t at = (uint32_t)(wave * decode_wave_bytes(kTiles) + j * kDStageBytes + l32 * 512 + ((hf ^ l32) << 4));
 #pragma unroll
             for (int c = 0; c < 16; ++c) {
                 f32x4 o4;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) o4[e] = oacc[j][c / 4][4 * (c % 4) + e] * fix[j];
-                *(LdsQuads)(uintptr_t)(wave * decode_wave_bytes(kTiles) + j * kDStageBytes + c * 1024 + lane * 16) = o4;
+                for (int e = 0; e < 4; ++e) o4[e] = oacc[j][c / 4][4 * (c % 4) + e];
+                *(LdsQuads)(uintptr_t)(at ^ (uint32_t)(c << 5)) = o4;  // head-dimension elements 8 c + 4 hf ..
             }
         }
     }
     __syncthreads();
+    const size_t row0 = ((size_t)b * p.Hq + (size_t)kvh * p.G) * p.Nq;
 #pragma unroll
     for (int j = 0; j < kTiles; ++j) {
-        if (!col_valid[j]) continue;
-        const size_t row = ((size_t)b * p.Hq + (size_t)kvh * p.G) * p.Nq + cc[j];
-        const float inv_l = 1.f / l[j];
+        const int n_chunks = tile_valid[j] ? 32 * min(32, p.cols - 32 * ct[j]) : 0;
+        for (int i = (int)threadIdx.x; i < n_chunks; i += kDThreads) {
+            const int c = i >> 5, q = i & 31;  // column of the tile; its head-dimension elements 4 q ..
+            f32x4 ml[kDWaves], ox[kDWaves];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c = 4 * wave + i;  // this wave's share: head-dimension block `wave`
+            for (int x = 0; x < kDWaves; ++x) {
+                ml[x] = *(LdsQuads)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + x) * 512 + c * 16));
+                ox[x] = *(LdsQuads)(uintptr_t)(uint32_t)(x * decode_wave_bytes(kTiles) + j * kDStageBytes + c * 512 + ((q ^ c) << 4));
+            }
+            const float m = fmaxf(fmaxf(ml[0][0], ml[1][0]), fmaxf(ml[2][0], ml[3][0]));
+            const float m_use = m == -INFINITY ? 0.f : m;
+            float l = 0.f;
             f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int x = 0; x < kDWaves; ++x)
-                o4 += *(LdsQuads)(uintptr_t)(x * decode_wave_bytes(kTiles) + j * kDStageBytes + c * 1024 + lane * 16);
-            const int d = 8 * c + 4 * hf;  // 32 (c / 4) + 8 (c % 4)
-            if (n_splits == 1) {
-                o4 *= inv_l;
-                const bf16x2 lo = pack_pair<kF16>(o4[0], o4[1]), hi = pack_pair<kF16>(o4[2], o4[3]);
-                *reinterpret_cast<bf16x4 *>(p.out + row * kD + d) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
-            } else {
-                *reinterpret_cast<f32x4 *>(p.ws_o + (item[j] * p.col_stride + l32) * kD + d) = o4;
+            for (int x = 0; x < kDWaves; ++x) {
+                const float w = __builtin_amdgcn_exp2f(ml[x][0] - m_use), wo = w * ml[x][2];
+                l += w * ml[x][1];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o4[e] += ox[x][e] * wo;
             }
-        }
-        if (wave == 0 && hf == 0) {
             if (n_splits == 1) {
-                p.lse[row] = (m[j] + __builtin_amdgcn_logf(l[j])) * 0.69314718055994530942f;
+                const size_t row = row0 + (size_t)(32 * ct[j] + c);
+                o4 *= 1.f / l;
+                const bf16x2 lo = pack_pair<kF16>(o4[0], o4[1]), hi = pack_pair<kF16>(o4[2], o4[3]);
+                *reinterpret_cast<bf16x4 *>(p.out + row * kD + 4 * q) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+                if (q == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
             } else {
-                // (a sum that is not a number travels with a finite reference: -inf, the largest score of a column that
-                // sees NaN only, would mark the split as empty, and the merge would leave it out)
-                p.ws_ml[item[j] * 64 + l32] = non_finite(l[j]) ? 0.f : m[j];
-                p.ws_ml[item[j] * 64 + 32 + l32] = l[j];
+                *reinterpret_cast<f32x4 *>(p.ws_o + (item[j] * p.col_stride + c) * kD + 4 * q) = o4;
+                if (q == 0) {
+                    // (a sum that is not a number travels with a finite reference: -inf, the largest score of a column that
+                    // sees NaN only, would mark the split as empty, and the merge would leave it out)
+                    p.ws_ml[item[j] * 64 + c] = non_finite(l) ? 0.f : m;
+                    p.ws_ml[item[j] * 64 + 32 + c] = l;
+                }
             }
         }
     }
@@ -537,169 +521,200 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
 
 // ---- merging the splits: out = sum_s 2^(mc_s - m) O_s / sum_s 2^(mc_s - m) l_s with m = max_s mc_s;
 // lse = (m + log2 of the denominator) ln 2 ----
-// One output row (b, hq, r) and where its partial results are: n_splits items, `step` workspace
-// slots apart (times the column tiles), the first at slot0.
-struct MergeRow {
-    long long row;
-    int ct, col;
-    int n_splits;
-    long long slot0, step;
+// What the merge needs to know, two lines of arguments instead of the split kernel's six.
+struct MergeParams {
+    const float *ws_o, *ws_ml;
+    const int *ws_units;
+    __bf16 *out;
+    float *lse;
+    FastDiv div_nq, div_hq, div_g;
+    int Nq, Hq, Hkv, G, n_splits, n_coltiles, col_stride, B;
+    int ragged, fp16;
+    unsigned rows, n_small;  // B * Hq * Nq; workgroups of the ragged launch that take kMergeRows rows each
 };
-__device__ __forceinline__ MergeRow merge_row(const DecodeParams &p, long long row) {
+// One output row (b, hq, r) and where its partial results are: n_splits items, item_step workspace
+// slots apart, the first at item0.
+struct MergeRow {
+    unsigned row;
+    int col;
+    int n_splits;
+    long long item0, item_step;
+};
+__device__ __forceinline__ MergeRow merge_row(const MergeParams &p, unsigned row) {
     // (The merge is bound by its chain of dependent steps.  With three 64-bit and two 32-bit divisions here, a hundred
     // instructions each, one sequence of 2000 tokens took 11.1 us in all on 32 heads, with multiplications 10.6; 8 heads on 8, 4096
     // tokens: 11.7, 11.0; window 8192 of 131072: 15.3, 14.9.)
     MergeRow m;
     m.row = row;
-    const unsigned head_row = fastdiv((unsigned)row, p.div_nq);
-    const int r = (int)((unsigned)row - head_row * (unsigned)p.Nq);
+    const unsigned head_row = fastdiv(row, p.div_nq);
+    const int r = (int)(row - head_row * (unsigned)p.Nq);
     const int b = (int)fastdiv(head_row, p.div_hq);
     const int hq = (int)(head_row - (unsigned)b * (unsigned)p.Hq);
     const int kvh = (int)fastdiv((unsigned)hq, p.div_g);
     const int c = (hq - kvh * p.G) * p.Nq + r;
-    m.ct = c >> 5;
-    m.col = c & 31;
+    long long slot0, step;
     if (p.ragged) {  // (the device-side plan: the sequence's first split workgroup has left it here)
         m.n_splits = p.ws_units[2 * b + 1];
-        m.slot0 = (long long)p.ws_units[2 * b] * p.Hkv + kvh;
-        m.step = p.Hkv;
+        slot0 = (long long)p.ws_units[2 * b] * p.Hkv + kvh;
+        step = p.Hkv;
     } else {
         m.n_splits = p.n_splits;
-        m.slot0 = ((long long)b * p.Hkv + kvh) * p.n_splits;
-        m.step = 1;
+        slot0 = ((long long)b * p.Hkv + kvh) * p.n_splits;
+        step = 1;
     }
+    m.col = c & 31;
+    m.item0 = slot0 * p.n_coltiles + (c >> 5);
+    m.item_step = step * p.n_coltiles;
     return m;
 }
-__device__ __forceinline__ void merge_store(const DecodeParams &p, long long row, int d, float o, float l, float m) {
-    if (p.fp16)
-        reinterpret_cast<_Float16 *>(p.out)[(size_t)row * kD + d] = (_Float16)(o / l);
-    else
-        p.out[(size_t)row * kD + d] = (__bf16)(o / l);
-    if (d == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
+typedef float merge_f32x4 __attribute__((ext_vector_type(4)));
+// Elements 4 q .. 4 q + 3 of a row.
+__device__ __forceinline__ void merge_store(const MergeParams &p, unsigned row, int q, merge_f32x4 o, float l, float m) {
+    o /= l;
+    const bf16x2 lo = p.fp16 ? pack_pair<true>(o[0], o[1]) : pack_pair<false>(o[0], o[1]);
+    const bf16x2 hi = p.fp16 ? pack_pair<true>(o[2], o[3]) : pack_pair<false>(o[2], o[3]);
+    *reinterpret_cast<bf16x4 *>(p.out + (size_t)row * kD + 4 * q) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+    if (q == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
+}
+// Largest value and sum over the 64 lanes of a wave, all of them active (shift steps as in wave_inclusive_scan).
+template <typename F>
+__device__ __forceinline__ float wave_reduce(float x, float none, F f) {
+    const int id = __float_as_int(none);
+    auto step = [&](auto ctrl, auto rows) {
+        x = f(x, __int_as_float(__builtin_amdgcn_update_dpp(id, __float_as_int(x), decltype(ctrl)::value, decltype(rows)::value, 0xf, false)));
+    };
+    using std::integral_constant;
+    step(integral_constant<int, 0x111>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x112>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x114>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x118>{}, integral_constant<int, 0xf>{});
+    step(integral_constant<int, 0x142>{}, integral_constant<int, 0xa>{});
+    step(integral_constant<int, 0x143>{}, integral_constant<int, 0xc>{});
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 63));
 }
 
-// A whole workgroup of kMergeThreads on one row (many splits): red and lsum are its LDS.
-__device__ __forceinline__ void merge_row_by_workgroup(const DecodeParams &p, const MergeRow &mr, float *red, float *lsum) {
-    const int tid = threadIdx.x;
-    const int n_splits = mr.n_splits, col = mr.col;
-    auto item_of = [&](int s) { return (mr.slot0 + s * mr.step) * p.n_coltiles + mr.ct; };
-
-    // largest reference over the splits: wave maxima by lane exchange, then one LDS round
-    float m = -INFINITY;
-    for (int s = tid; s < n_splits; s += kMergeThreads) m = fmaxf(m, p.ws_ml[item_of(s) * 64 + col]);
+// A whole workgroup on one row (many splits): 32 threads to a split, four elements each, eight splits side by side.
+// Every wave finds the largest reference and the sum of the l by itself, a split per lane, from loads that go out
+// together with the first O's: one trip to memory and one barrier.
+__device__ __forceinline__ void merge_row_by_workgroup(const MergeParams &p, const MergeRow &mr, merge_f32x4 *red) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int q = tid % 32, g = tid / 32;
+    constexpr int kGroups = kMergeThreads / 32, kBatch = 4;
+    const int n = mr.n_splits;
+    auto ml_of = [&](int s) { return p.ws_ml + (mr.item0 + s * mr.item_step) * 64 + mr.col; };
+    // A split that saw no visible key has reference -inf and may not have written its O: it is loaded all the same
+    // (the workspace is there) and left out of the sums by selection, not by a branch; so is what lies beyond the last split.
+    float mcs[kBatch];
+    merge_f32x4 os[kBatch];
+    auto load = [&](int s0) {
 #pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) m = fmaxf(m, __shfl_xor(m, sh));
-    if ((tid & 63) == 0) red[tid >> 6] = m;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < kMergeThreads / 64; ++w) m = fmaxf(m, red[w]);  // finite: every row sees at least its own key
-    __syncthreads();
-
-    // Four splits per round, their loads issued together.  A split that saw no visible
-    // key has reference -inf and may not have written its O: it is loaded all the same
-    // (the workspace is there) and left out of the sums by selection, not by a branch.
-    const int d = tid % kD, g = tid / kD;
-    constexpr int kGroups = kMergeThreads / kD;
-    float acc = 0.f, l = 0.f;
-    for (int s0 = g; s0 < n_splits; s0 += 4 * kGroups) {
-        float mcs[4], ls[4], os[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int s = s0 + u * kGroups;
-            const bool there = s < n_splits;
-            const long long it = item_of(there ? s : s0);
-            mcs[u] = p.ws_ml[it * 64 + col];
-            ls[u] = p.ws_ml[it * 64 + 32 + col];
-            os[u] = p.ws_o[(it * p.col_stride + col) * kD + d];
-            if (!there) mcs[u] = -INFINITY;
+        for (int u = 0; u < kBatch; ++u) {
+            const int s = s0 + u * kGroups, at = min(s, n - 1);
+            mcs[u] = *ml_of(at);
+            os[u] = *reinterpret_cast<const merge_f32x4 *>(p.ws_o + ((mr.item0 + at * mr.item_step) * p.col_stride + mr.col) * kD + 4 * q);
+            if (s >= n) mcs[u] = -INFINITY;
         }
+    };
+    float mc = *ml_of(min(lane, n - 1)), l = *(ml_of(min(lane, n - 1)) + 32);
+    load(g);
+    if (lane >= n) mc = -INFINITY;
+    float m = mc;
+    for (int s = lane + 64; s < n; s += 64) m = fmaxf(m, *ml_of(s));
+    m = wave_reduce(m, -INFINITY, [](float a, float b) { return fmaxf(a, b); });  // finite: every row sees at least its own key
+    l = mc == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mc - m) * l;
+    for (int s = lane + 64; s < n; s += 64) {
+        const float mcx = *ml_of(s), w = __builtin_amdgcn_exp2f(mcx - m) * *(ml_of(s) + 32);
+        l += mcx == -INFINITY ? 0.f : w;
+    }
+    l = wave_reduce(l, 0.f, [](float a, float b) { return a + b; });
+    merge_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = g;;) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < kBatch; ++u) {
             const bool empty = mcs[u] == -INFINITY;
             const float w = __builtin_amdgcn_exp2f(mcs[u] - m);
-            l += empty ? 0.f : w * ls[u];
-            acc += empty ? 0.f : w * os[u];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] += empty ? 0.f : w * os[u][e];
         }
+        s0 += kBatch * kGroups;
+        if (s0 - g >= n) break;  // (the same in all groups)
+        load(s0);
     }
     red[tid] = acc;
-    if (d == 0) lsum[g] = l;
     __syncthreads();
     if (g == 0) {
-        float o = 0.f, lt = 0.f;
 #pragma unroll
-        for (int gg = 0; gg < kMergeThreads / kD; ++gg) {
-            o += red[gg * kD + d];
-            lt += lsum[gg];
-        }
-        merge_store(p, mr.row, d, o, lt, m);
+        for (int gg = 1; gg < kGroups; ++gg) acc += red[gg * 32 + q];
+        merge_store(p, mr.row, q, acc, l, m);
     }
 }
 
-// 128 threads (one per head dimension element) on one row of at most kMergeRowSplits splits: every
+// 32 threads (four head dimension elements each) on one row of at most kMergeRowSplits splits: every
 // thread adds up the row's splits by itself -- no exchange between threads.
 constexpr int kMergeRowSplits = 8;
-__device__ __forceinline__ void merge_row_by_group(const DecodeParams &p, const MergeRow &mr, int d) {
-    const long long item0 = mr.slot0 * p.n_coltiles + mr.ct, item_step = mr.step * p.n_coltiles;
-    float mcs[kMergeRowSplits], ls[kMergeRowSplits], os[kMergeRowSplits];
+__device__ __forceinline__ void merge_row_by_group(const MergeParams &p, const MergeRow &mr, int q) {
+    float mcs[kMergeRowSplits], ls[kMergeRowSplits];
+    merge_f32x4 os[kMergeRowSplits];
     // (a split that saw no visible key has reference -inf and may not have written its O: loaded all
-    // the same and left out by selection; splits beyond the row's repeat split 0 and count as empty)
+    // the same and left out by selection; splits beyond the row's repeat the last one and count as empty)
 #pragma unroll
     for (int s = 0; s < kMergeRowSplits; ++s) {
         const bool there = s < mr.n_splits;
-        const long long it = item0 + (there ? s : 0) * item_step;
+        const long long it = mr.item0 + (there ? s : 0) * mr.item_step;
         mcs[s] = p.ws_ml[it * 64 + mr.col];
         ls[s] = p.ws_ml[it * 64 + 32 + mr.col];
-        os[s] = p.ws_o[(it * p.col_stride + mr.col) * kD + d];
+        os[s] = *reinterpret_cast<const merge_f32x4 *>(p.ws_o + (it * p.col_stride + mr.col) * kD + 4 * q);
         if (!there) mcs[s] = -INFINITY;
     }
     float m = mcs[0];
 #pragma unroll
     for (int s = 1; s < kMergeRowSplits; ++s) m = fmaxf(m, mcs[s]);  // finite: every row sees at least its own key
-    float acc = 0.f, l = 0.f;
+    float l = 0.f;
+    merge_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < kMergeRowSplits; ++s) {
         const bool empty = mcs[s] == -INFINITY;
         const float w = __builtin_amdgcn_exp2f(mcs[s] - m);
         l += empty ? 0.f : w * ls[s];
-        acc += empty ? 0.f : w * os[s];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[e] += empty ? 0.f : w * os[s][e];
     }
-    merge_store(p, mr.row, d, acc, l, m);
+    merge_store(p, mr.row, q, acc, l, m);
 }
 
 // Sequences of one length, more than kMergeRowSplits splits per pair: one workgroup per output row.
-__global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_kernel(const DecodeParams p) {
-    __shared__ float red[kMergeThreads];
-    __shared__ float lsum[kMergeThreads / kD];
-    merge_row_by_workgroup(p, merge_row(p, blockIdx.x), red, lsum);
+__global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_kernel(const MergeParams p) {
+    __shared__ merge_f32x4 red[kMergeThreads];
+    merge_row_by_workgroup(p, merge_row(p, blockIdx.x), red);
 }
 
-// Sequences of one length, at most kMergeRowSplits splits per pair: kMergeThreads / 128 output rows
+// Sequences of one length, at most kMergeRowSplits splits per pair: kMergeRows output rows
 // per workgroup.  A batch of many sequences has thousands of rows of two or three splits each;
 // one workgroup of 1024 threads per row spent most of the merge waiting for workgroup slots (64
 // sequences x 8 new tokens: the call took 275 us, 70 of them here).
-__global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_rows_kernel(const DecodeParams p) {
-    const long long row = (long long)blockIdx.x * (kMergeThreads / kD) + threadIdx.x / kD;
-    if (row >= (long long)p.B * p.Hq * p.Nq) return;
-    merge_row_by_group(p, merge_row(p, row), threadIdx.x % kD);
+constexpr int kMergeRows = kMergeThreads / 32;
+__global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_rows_kernel(const MergeParams p) {
+    const unsigned row = blockIdx.x * kMergeRows + threadIdx.x / 32;
+    if (row >= p.rows) return;
+    merge_row_by_group(p, merge_row(p, row), threadIdx.x % 32);
 }
 
-// Per-sequence lengths: both at once.  The first n_small workgroups take kMergeThreads / 128 rows
-// each and merge those of at most kMergeRowSplits splits, 128 threads per row.  The rows of the
+// Per-sequence lengths: both at once.  The first n_small workgroups take kMergeRows rows
+// each and merge those of at most kMergeRowSplits splits, 32 threads per row.  The rows of the
 // sequences with more splits -- there are at most (units_target + B) / (kMergeRowSplits + 1) such
 // sequences -- are left to the workgroups behind them, one row each: workgroup n_small + k looks
 // for the (k / (Hq Nq))-th such sequence in the plan the split kernel has left (a prefix sum of
 // flags over the lanes, every wave for itself) and goes home if there is none.
-__global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_ragged_kernel(const DecodeParams p, unsigned n_small) {
-    __shared__ float red[kMergeThreads];
-    __shared__ float lsum[kMergeThreads / kD];
-    if (blockIdx.x < n_small) {
-        const long long row = (long long)blockIdx.x * (kMergeThreads / kD) + threadIdx.x / kD;
-        if (row >= (long long)p.B * p.Hq * p.Nq) return;
+__global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_ragged_kernel(const MergeParams p) {
+    __shared__ merge_f32x4 red[kMergeThreads];
+    if (blockIdx.x < p.n_small) {
+        const unsigned row = blockIdx.x * kMergeRows + threadIdx.x / 32;
+        if (row >= p.rows) return;
         const MergeRow mr = merge_row(p, row);
-        if (mr.n_splits > 1 && mr.n_splits <= kMergeRowSplits) merge_row_by_group(p, mr, threadIdx.x % kD);
+        if (mr.n_splits > 1 && mr.n_splits <= kMergeRowSplits) merge_row_by_group(p, mr, threadIdx.x % 32);
         return;
     }
-    const unsigned k = blockIdx.x - n_small, rows_per_seq = (unsigned)(p.Hq * p.Nq);
+    const unsigned k = blockIdx.x - p.n_small, rows_per_seq = (unsigned)(p.Hq * p.Nq);
     const unsigned want = k / rows_per_seq;  // the want-th sequence with many splits (from 0)
     const int lane = threadIdx.x & 63;
     unsigned before = 0;
@@ -715,7 +730,7 @@ __global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_ragged_kernel
         before += in_round;
     }
     if (b < 0) return;  // (the same in every wave of the workgroup)
-    merge_row_by_workgroup(p, merge_row(p, (long long)b * rows_per_seq + (k - want * rows_per_seq)), red, lsum);
+    merge_row_by_workgroup(p, merge_row(p, (unsigned)b * rows_per_seq + (k - want * rows_per_seq)), red);
 }
 
 }  // namespace
@@ -937,18 +952,20 @@ hipError_t launch_decode(const DecodeParams &p, hipStream_t stream) {
     if (err == hipSuccess) err = hipGetLastError();
     if (err != hipSuccess || (!p.ragged && p.n_splits == 1)) return err;
     const long long rows = (long long)p.B * p.Hq * p.Nq;
-    constexpr int kRowsPerWg = kMergeThreads / kD;
-    const unsigned n_small = (unsigned)((rows + kRowsPerWg - 1) / kRowsPerWg);
+    const unsigned n_small = (unsigned)((rows + kMergeRows - 1) / kMergeRows);
+    const MergeParams mp{p.ws_o, p.ws_ml, p.ws_units, p.out, p.lse, p.div_nq, p.div_hq, p.div_g,
+                         p.Nq, p.Hq, p.Hkv, p.G, p.n_splits, p.n_coltiles, p.col_stride, p.B,
+                         p.ragged, p.fp16, (unsigned)rows, n_small};
     if (p.ragged) {
         long long many = ((long long)p.units_target + p.B) / (kMergeRowSplits + 1);  // sequences that can have more splits
         many = many < p.B ? many : p.B;
         if (n_small + many * p.Hq * p.Nq > 0x7fffffffLL) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(swaa_decode_merge_ragged_kernel, dim3(n_small + (unsigned)(many * p.Hq * p.Nq)), dim3(kMergeThreads),
-                           0, stream, p, n_small);
+        hipLaunchKernelGGL(swaa_decode_merge_ragged_kernel, dim3(n_small + (unsigned)(many * p.Hq * p.Nq)), dim3(kMergeThreads), 0,
+                           stream, mp);
     } else if (p.n_splits <= kMergeRowSplits) {
-        hipLaunchKernelGGL(swaa_decode_merge_rows_kernel, dim3(n_small), dim3(kMergeThreads), 0, stream, p);
+        hipLaunchKernelGGL(swaa_decode_merge_rows_kernel, dim3(n_small), dim3(kMergeThreads), 0, stream, mp);
     } else {
-        hipLaunchKernelGGL(swaa_decode_merge_kernel, dim3((unsigned)rows), dim3(kMergeThreads), 0, stream, p);
+        hipLaunchKernelGGL(swaa_decode_merge_kernel, dim3((unsigned)rows), dim3(kMergeThreads), 0, stream, mp);
     }
     return hipGetLastError();
 }
