@@ -76,7 +76,6 @@ constexpr int kBytes = 2 * kTileB;
 }  // namespace dq64
 
 __global__ __launch_bounds__(dq64::kThreads, 4) void swaa_bwd_dq_kernel(const BwdParams p) {
-    fetch_args<BwdParams>();
     using namespace dq64;
     WorkItem wi;
     if (!decode_work(p.f, wi)) return;
@@ -355,7 +354,6 @@ namespace {
 // dK, dV of the key tiles that have partial sums (all of them, or those with sinks): pieces, then segments, in this order.
 template <int D>
 __global__ __launch_bounds__(kThreads) void swaa_bwd_part_sum_kernel(const BwdParams p) {
-    fetch_args<BwdParams>();
     // one thread per 4 consecutive head-dimension elements of one key
     const int n_kt = p.n_split > 1 ? (p.N + 127) / 128 : p.n_sink_kt;
     const long long per_kt = 128LL * D / 4;

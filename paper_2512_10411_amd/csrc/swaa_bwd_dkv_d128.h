@@ -128,7 +128,6 @@ __device__ constexpr int rest_slot(int k) { return 3 * k / 2 + 3; }
 }  // namespace dkv128
 
 __global__ __launch_bounds__(dkv128::kThreads, 1) void swaa_bwd_dkv_dma_kernel(const BwdParams p) {
-    fetch_args<BwdParams>();
     using namespace dkv128;
     const int N = p.N, W = p.f.W, S = p.f.S, P = p.f.P, G = p.f.G;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l32 = lane & 31, hf = lane >> 5;

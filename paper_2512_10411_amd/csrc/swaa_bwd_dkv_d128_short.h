@@ -38,7 +38,6 @@ static_assert(2 * kKeyTileBytes >= 4 * 32 * kD * 4, "the K/V area doubles as the
 }  // namespace dkv128short
 
 __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_short_kernel(const BwdParams p) {
-    fetch_args<BwdParams>();
     using namespace dkv128short;
     constexpr int D = kD, KS = kKS, DB = kDB;
 

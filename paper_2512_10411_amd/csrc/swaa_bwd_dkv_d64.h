@@ -58,7 +58,6 @@ __device__ constexpr int first_elem(int c) { return c >= 14 ? 16 : c * 16 / 14; 
 
 template <int D>
 __global__ __launch_bounds__(dkv64::kThreads, 2) void swaa_bwd_dkv_kernel(const BwdParams p) {
-    fetch_args<BwdParams>();
     using namespace dkv64;
     static_assert(D == dkv64::kD, "the layout below is for rows of 128 bytes");
 

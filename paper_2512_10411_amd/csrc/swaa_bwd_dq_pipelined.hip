@@ -162,7 +162,6 @@ __device__ __forceinline__ void dq_substep(const DqLane &la, const DqHalves &h, 
 }
 
 __global__ __launch_bounds__(kQThreads, 2) void swaa_bwd_dq_pipelined_kernel(const BwdParams p) {
-    fetch_args<BwdParams>();
     WorkItem wi;
     if (!decode_work(p.f, wi)) return;
     const int hpb = wi.hpb;

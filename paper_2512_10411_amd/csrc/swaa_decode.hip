@@ -17,6 +17,11 @@
 //     workgroup, two to a CU: 128 KiB of copies in flight per CU, 32 MiB over the chip): the
 //     registers are the second stage.  Workgroups that compute two column tiles take a two-stage
 //     ring, one to a CU.
+//   * Short calls are chains of latencies (decode of 682 tokens: 9.5 us as a graph, 1.9 of them each launch's own):
+//     arguments in one trip (fetch_args), copies without a product or a clamp per row, one barrier and the valid
+//     columns only where the waves' results meet, and a merge that asks for everything it needs at once.  By timestamps
+//     in the kernel, us: arguments and plan 1.0 -> 0.4, first copies and Q 1.0 -> 0.7, meeting of the waves
+//     1.8 -> 1.0; the kernel 6.4 -> 4.9, the merge 4.2 -> 3.2 (window 8192 of 128k tokens 13.0 -> 10.0 in all).
 //   * At the end the four waves' results are added up through LDS; a sequence with one split
 //     then writes its output from here, and the merge kernel is not needed.  (Single-wave
 //     workgroups, whose every result went through the workspace: 64 sequences x 2k tokens 101 us,
@@ -60,6 +65,28 @@ constexpr int kCopiesPerHalf = 16;                    // wave instructions per s
 constexpr int kMergeThreads = 256;
 constexpr long long kDResident = 512;                 // workgroups of one column tile that run at once
 constexpr long long kDResidentPairs = 256;            // ... of two
+
+// First statement of the split kernel: brings its argument block into the scalar cache
+// in one round trip.  The compiler loads arguments where they are first used, a line of 64 bytes at a time, and a line
+// that the caches have lost since the last launch is 350 ns away: three to five such waits stood in front of a kernel's first
+// request to memory (one new token on a window of 8192 12.9 -> 12.3 us;
+// kernels that read less of a long cache gain nothing).
+// Workgroups behind the first round find the lines in the cache.
+__device__ __forceinline__ void fetch_args() {
+    static_assert(sizeof(DecodeParams) % 4 == 0, "");
+    if (blockIdx.x >= kDResident) return;
+    const auto args = (const int __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+    int word;  // (waited for in the same block: the register is free again behind it)
+    asm volatile(".set swaa_line, 0\n\t"
+                 ".rept %c2\n\t"
+                 "s_load_dword %0, %1, swaa_line\n\t"
+                 ".set swaa_line, swaa_line + 64\n\t"
+                 ".endr\n\t"
+                 "s_load_dword %0, %1, %c3\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(word)
+                 : "s"(args), "n"((sizeof(DecodeParams) + 63) / 64), "n"(sizeof(DecodeParams) - 4));
+}
 
 // ---- the split plan of a batch with per-sequence lengths, worked out by every workgroup of the
 // split kernel (DecodeParams::ragged has the rules) ----
@@ -137,7 +164,7 @@ __device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps,
 // query rows: two tiles in two workgroups read every key twice, which only some sizes make up for, see plan_decode).
 template <bool kF16, bool kPaged, int kTiles>
 __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_decode_split_kernel(const DecodeParams p) {
-    fetch_args<DecodeParams>();
+    fetch_args();
     // Workgroups reach the eight dies round-robin; the list has fewer than 2^31 items: 32-bit
     // arithmetic, divisions as multiplications.  Sequences of one length: die x takes the x-th
     // contiguous chunk of the item list (a die streams neighbouring memory: 3 % faster on one
@@ -354,12 +381,17 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
     };
     const LaneAddr la = make_lane_addr(lane, 0);
 
-    // ---- start-up: this lane's Q fragments (B operand of S^T = K Q^T: query row l32, 16 bytes at
-    // 32 ks + 16 hf) straight from HBM with ordinary loads, then the first halves into the
-    // stages.  The compiler places the wait for the Q loads in front of their first use,
-    // and that wait covers the copies issued behind them as well (it cannot see them): a short
-    // item has all its keys in flight at once and starts when they are there; a long one gives
-    // away the head start of its first two steps, once. ----
+    // ---- start-up: the first halves into the stages and this lane's Q fragments (B operand of S^T = K Q^T: query
+    // row l32, 16 bytes at 32 ks + 16 hf) straight from HBM with ordinary loads.  The compiler waits for all of
+    // them, the copies included, before it parks the first fragment.  The copies go first (Q's addresses and requests in
+    // front of them are 0.1 us) unless they have a page to look up: Q is asked for while the table entry is on its way
+    // (four sequences of 0.4-10k tokens 10.0 us, behind the copies 10.25). ----
+    const Pages pg_first = n_mine >= 1 ? lookup(0) : Pages{0, 0};
+    auto copy_first = [&]() __attribute__((always_inline)) {
+        if (n_mine >= 1) issue_half(0, 0, pg_first);
+        if (kDStages >= 2 && n_mine >= 2) issue_half(1, 1, lookup(1));
+    };
+    if constexpr (!paged) copy_first();
     bf16x8 qf[kTiles][kKS];
 #pragma unroll
     for (int j = 0; j < kTiles; ++j) {
@@ -368,8 +400,7 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
 #pragma unroll
         for (int ks = 0; ks < kKS; ++ks) qf[j][ks] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * ks);
     }
-    if (n_mine >= 1) issue_half(0, 0, lookup(0));
-    if (kDStages >= 2 && n_mine >= 2) issue_half(1, 1, lookup(1));
+    if constexpr (paged) copy_first();
     // (the idle cycles keep the loads two wait states away from the first MFMA that reads them)
 #pragma unroll
     for (int j = 0; j < kTiles; ++j)

@@ -249,7 +249,6 @@ __device__ __forceinline__ void pipelined_substep(const LaneAddr &la, const Half
 // instantiation of its own too.
 template <bool kF16, bool kPaged, bool kSplit>
 __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const FwdParams p) {
-    fetch_args<FwdParams>();
     WorkItem wi;
     SplitItem si{1, 0, 0u};
     if constexpr (kSplit) {
@@ -800,7 +799,6 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
 // contiguous bytes per 32 threads).  Which tile follows from the split counts that the splits left.
 template <bool kF16>
 __global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) {
-    fetch_args<FwdParams>();
     const int tid = threadIdx.x, lane = tid & 63, l32 = tid & 31, q = tid >> 5;
     const unsigned wave = blockIdx.x & 3u, rank = blockIdx.x >> 2;  // rank: tile among those of split sequences
     const unsigned n_mine = (unsigned)p.ws_n[lane];

@@ -26,7 +26,6 @@ constexpr int kSBytes = kSWaves * (int)kSRing;
 
 template <bool kF16>
 __global__ __launch_bounds__(kSThreads, 2) void swaa_fwd_short_kernel(const FwdShortParams sp) {
-    fetch_args<FwdShortParams>();
     const FwdParams &p = sp.f;
     constexpr int kBelow = kF16 ? 4 : 0;  // as the row tiles' reference: terms keep full precision down to 2^-18 of it
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;

@@ -83,7 +83,6 @@ constexpr int kSmallD = 96;
 constexpr int min_blocks(int D) { return D <= 64 ? 4 : D <= kSmallD ? 3 : D <= 160 ? 2 : 1; }
 template <int D, typename E, int QB>
 __global__ __launch_bounds__(kThreads, min_blocks(D)) void swaa_fwd_kernel(const FwdParams p) {
-    fetch_args<FwdParams>();
     using T = Tile<D>;
     using X = Elem<E>;
     using x8 = typename X::x8;

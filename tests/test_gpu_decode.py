@@ -390,3 +390,22 @@ def test_decode_workloads_with_sequence_lengths_full_size(name):
         ro, rl = swaa_decode_oracle(q[b:b + 1], k[:, :, t:t + n], v[:, :, t:t + n], w.window, w.n_sink, w.scale)
         assert_parity(out[b:b + 1], lse[b:b + 1], ro, rl, tag=f"{name} seq {b} ({n} tokens)")
         t += n
+
+
+@pytest.mark.parametrize("Hkv,G,Nq,lens", [(1, 1, 1, (60000, 100)),    # more splits than a wave has lanes, one row
+                                           (1, 31, 1, (9000, 33)), (2, 8, 4, (700, 5000, 40)),  # columns of a tile: all but one, all
+                                           (1, 11, 3, (3000, 2500)), (1, 8, 8, (31, 2900))])  # one more than a tile, two tiles
+def test_waves_meet_and_splits_merge_at_the_edges(Hkv, G, Nq, lens):
+    B, D, Nk, W, S = len(lens), 128, max(lens), max(lens), 0
+    q, k, v = make_qkv(B, Hkv * G, Hkv, Nk, D, seed=7500 + G, n_query=Nq)
+    print(f"[case] Hkv{Hkv} G{G} Nq{Nq} lens {lens}", flush=True)
+    seq_lens = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    ragged = binding.swaa_attn_decode_ex(to_device(q), to_device(k), to_device(v), W, S, seq_lens=seq_lens)
+    torch.cuda.synchronize()
+    for b, n in enumerate(lens):
+        one = [np.ascontiguousarray(t[b:b + 1]) for t in (q, k[:, :, :n], v[:, :, :n])]
+        ro, rl = swaa_decode_oracle(*one, min(W, n), S, 1 / math.sqrt(D))
+        assert_parity(ragged[0][b:b + 1], ragged[1][b:b + 1], ro, rl, tag=f"ragged {lens} sequence {b}")
+        alone = binding.swaa_attn_decode(*[to_device(t) for t in one], n, S)
+        torch.cuda.synchronize()
+        assert_parity(alone[0], alone[1], ro, rl, tag=f"alone, {n} tokens")
