@@ -1,4 +1,4 @@
-"""ctypes binding of libswaa.so: argument marshalling only.
+"""Binding of libswaa.so: argument marshalling only, by ctypes, and for calls in plain form by native code (_host_calls.so).
 
 Every step of the attention forward runs inside the HIP kernels; torch is
 used for device memory and the stream handle.  There is no fallback: if the
@@ -14,6 +14,7 @@ import os
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libswaa.so")
+HOST_CALLS_PATH = os.path.join(_PKG, "_host_calls.so")
 
 SWAA_OK = 0
 SWAA_ERR_NULL = -1
@@ -151,22 +152,40 @@ def swaa_visible_pairs_fa_decode(N: int, window: int, n_sink: int, n_prompt: int
     return r
 
 
-# What surrounds a launch costs more than the smallest kernels run for: a prompt of 64 tokens took 15 us
-# a call, all of it host time.  Switching to the device that is current already and building a stream
-# object only to read its handle were 5 of them.  Of the 9.8 left, the library's call takes 3.7 and the results' memory 2.5;
-# checks that build no shape and device objects, no context for the device that is current, and one call
-# instead of four on the way to the library took the rest from 6.0 to 4.5 with the memory (decode 6.3 to 4.4).
+# What surrounds a launch costs more than the smallest kernels run for: a prompt of 64 tokens took 8.9 us a call, 6.1 of
+# them on the GPU, a short decode step 12.6 and 7.4.  A call in plain form (csrc/host_calls.cpp says which) therefore goes
+# through native code: checks, results and launch take 6.3 us (decode, two launches: 8.9; swaa_attn_fwd_ex 11 where it was 21).
+# That code answers None for any other call, and what follows here in Python takes it: the general path, which says what is
+# wrong with a call's arguments, if anything is.
 _SAME_DEVICE = contextlib.nullcontext()
 
 
 def _torch():
-    """torch, imported with the first call that has tensors."""
-    global torch
-    import torch
+    """torch, imported with the first call that has tensors, and with it the native part of this binding."""
+    global torch, _host
+    import torch as imported
+    if not os.path.exists(HOST_CALLS_PATH):
+        raise RuntimeError(f"{HOST_CALLS_PATH} is missing: build it with `python -m paper_2512_10411_amd.build`")
+    from . import _host_calls
+    lib = load_library()
+    _host_calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+        lib.swaa_attn_fwd, lib.swaa_attn_fwd_fa_decode, lib.swaa_attn_decode, lib.swaa_attn_decode_workspace_bytes,
+        lib.swaa_attn_decode_ex, lib.swaa_attn_decode_ex_workspace_bytes)),
+        imported._C._cuda_getDevice, imported._C._cuda_getCurrentRawStream)
+    _host = _host_calls
+    torch = imported  # (last: who sees it finds the native part bound)
     return torch
 
 
 torch = None
+_host = None
+
+
+def _results(r):
+    """(out, lse) of a native call; raises the status it ended with otherwise."""
+    if r.__class__ is tuple:
+        return r
+    raise SwaaError(r, swaa_status_string(r))
 
 
 def _contiguous_bf16(torch, q, k, v):
@@ -261,6 +280,10 @@ def swaa_attn_fwd_fa_decode(q, k, v, window: int, n_sink: int, n_prompt: int, sc
 
 def _fwd(q, k, v, window, n_sink, n_prompt, scale, out, lse, stream):
     tc = torch or _torch()
+    if out is None and lse is None and stream is None:
+        r = _host.fwd(q, k, v, window, n_sink, n_prompt, scale)
+        if r is not None:
+            return _results(r)
     _contiguous_bf16(tc, q, k, v)
     B, Hq, N, D = q.shape
     Bk, Hkv, Nk, Dk = k_shape = k.shape
@@ -331,6 +354,10 @@ def swaa_attn_decode(q, k, v, window: int, n_sink: int, scale: float | None = No
     here with torch when None).  Returns (out bf16 [B, Hq, Nq, D], lse fp32 [B, Hq, Nq]).
     """
     tc = torch or _torch()
+    if out is None and lse is None and stream is None:
+        r = _host.decode(q, k, v, window, n_sink, scale, workspace)
+        if r is not None:
+            return _results(r)
     _contiguous_bf16(tc, q, k, v)
     B, Hq, Nq, D = q.shape
     Bk, Hkv, Nk, Dk = k_shape = k.shape
@@ -445,7 +472,14 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
     one type).  out defaults to a new tensor with q's shape in q's memory order;
     lse is fp32 [B, Hq, Nq] ([Hq, Tq] when packed).  Returns (out, lse).
     """
-    import torch
+    tc = torch or _torch()
+    if out is None and lse is None and stream is None:
+        a = SwaaFwdArgs()
+        r = _host.fill_fwd_ex(a, q, k, v, window, n_sink, n_prompt, scale, cu_seqlens_q, cu_seqlens_k, max_seqlen_q, max_seqlen_k,
+                              block_table, total_rows_q, n_prompts)
+        if r is not None:
+            _launch_fwd_ex(a, workspace, q.device)
+            return r
 
     packed = cu_seqlens_q is not None or cu_seqlens_k is not None
     nd = 3 if packed else 4
@@ -520,24 +554,29 @@ def swaa_attn_fwd_ex(q, k, v, window: int, n_sink: int, n_prompt: int | None = N
                     or n_prompts.shape != (B,):
                 raise ValueError("n_prompts must be a contiguous int32 [B] GPU tensor")
             a.n_prompts = n_prompts.data_ptr()
-        lib = load_library()
-        need = lib.swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(a))
-        if need > 0 and workspace is None:
-            try:
-                workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-            except torch.cuda.OutOfMemoryError:
-                need = 0  # (the call itself needs no scratch: whole keys are slower, not refused)
-        if need > 0:
-            if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
-                raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
-            rc = int(lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), workspace.data_ptr(), workspace.numel()))
-        else:
-            rc = swaa_attn_fwd_ex_raw(a)  # (keys stay whole, or an argument error to be reported)
+        _launch_fwd_ex(a, workspace, q.device)
         if stream is not None:
             _returned_to(caller, out, lse)
+    return out, lse
+
+
+def _launch_fwd_ex(a, workspace, device):
+    """Launches the filled argument block on its stream, with a workspace on `device`, which is current, if it has use for one."""
+    lib = _lib or load_library()
+    need = lib.swaa_attn_fwd_ex_workspace_bytes(ctypes.byref(a))
+    if need > 0 and workspace is None:
+        try:
+            workspace = torch.empty(need, dtype=torch.uint8, device=device)
+        except torch.cuda.OutOfMemoryError:
+            need = 0  # (the call itself needs no scratch: whole keys are slower, not refused)
+    if need > 0:
+        if workspace.dtype != torch.uint8 or not workspace.is_cuda or not workspace.is_contiguous():
+            raise ValueError("workspace must be a contiguous uint8 tensor on the GPU")
+        rc = int(lib.swaa_attn_fwd_ex_ws(ctypes.byref(a), workspace.data_ptr(), workspace.numel()))
+    else:
+        rc = int(lib.swaa_attn_fwd_ex(ctypes.byref(a)))  # (keys stay whole, or an argument error to be reported)
     if rc != SWAA_OK:
         raise SwaaError(rc, swaa_status_string(rc))
-    return out, lse
 
 
 def swaa_attn_bwd_workspace_bytes(B, Hq, Hkv, N, D, window, n_sink, n_prompt=None) -> int:
@@ -634,7 +673,11 @@ def swaa_attn_decode_ex(q, k, v, window: int, n_sink: int, scale: float | None =
     lengths (the Nq newest tokens included) or None; max_seqlen_k: the largest of them (required
     with a paged cache).  Returns (out, lse).
     """
-    import torch
+    tc = torch or _torch()
+    if out is None and lse is None and stream is None:
+        r = _host.decode_ex(q, k, v, window, n_sink, scale, seq_lens, block_table, max_seqlen_k, workspace)
+        if r is not None:
+            return _results(r)
 
     if q.dtype not in (torch.bfloat16, torch.float16) or not q.is_cuda or not q.is_contiguous() or q.dim() != 4:
         raise ValueError("q must be a contiguous bf16 or fp16 [B, Hq, Nq, D] GPU tensor")

@@ -1,4 +1,4 @@
-"""Builds libswaa.so (HIP, gfx950 only) in-tree with hipcc.
+"""Builds libswaa.so (HIP, gfx950 only) with hipcc and _host_calls.so (the binding's native part) with g++, in-tree.
 
     python -m paper_2512_10411_amd.build
 """
@@ -53,5 +53,32 @@ def build_library(verbose: bool = False, extra_flags=(), out: str = LIB) -> str:
     return out
 
 
+HOST_CALLS = os.path.join(PKG, "_host_calls.so")
+
+
+def build_host_calls(verbose: bool = False, out: str = HOST_CALLS) -> str:
+    """Compile csrc/host_calls.cpp against the installed torch into paper_2512_10411_amd/_host_calls.so (or `out`)."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+
+    tmp = out + ".tmp.%d" % os.getpid()
+    lib = cpp_extension.library_paths()[0]
+    cmd = [shutil.which("g++") or "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+           *[f for d in cpp_extension.include_paths() for f in ("-isystem", d)],
+           os.path.join(CSRC, "host_calls.cpp"), "-o", tmp, "-L", lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd))
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + res.stdout)
+    os.replace(tmp, out)
+    return out
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True))
+    print(build_host_calls(verbose=True))
