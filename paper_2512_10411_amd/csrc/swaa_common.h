@@ -44,6 +44,28 @@ __host__ __device__ __forceinline__ unsigned fastdiv(unsigned n, const FastDiv f
     return f.sh < 0 ? n : (unsigned)(((unsigned long long)n * f.m) >> 32) >> f.sh;  // (the upper half of one 32 x 32 bit product)
 }
 
+// First statement of a kernel of short calls: brings its argument block (a struct Args, the kernel's first argument) into the
+// scalar cache in one round trip.  The compiler loads arguments where they are first used, a line of 64 bytes at a time, and a
+// line that the caches have lost since the last launch is 350 ns away: three to five such waits stood in front of the decode
+// kernel's first request to memory (one new token on a window of 8192 12.9 -> 12.3 us; where a call reads less of a long
+// cache there is nothing to gain, nor in kernels of whole prompts).  Workgroups behind the first round find the lines there.
+template <typename Args>
+__device__ __forceinline__ void fetch_args() {
+    static_assert(sizeof(Args) % 4 == 0, "");
+    if (blockIdx.x >= 512) return;
+    const auto args = (const int __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+    int word;  // (waited for in the same block: the register is free again behind it)
+    asm volatile(".set swaa_line, 0\n\t"
+                 ".rept %c2\n\t"
+                 "s_load_dword %0, %1, swaa_line\n\t"
+                 ".set swaa_line, swaa_line + 64\n\t"
+                 ".endr\n\t"
+                 "s_load_dword %0, %1, %c3\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(word)
+                 : "s"(args), "n"((sizeof(Args) + 63) / 64), "n"(sizeof(Args) - 4));
+}
+
 struct FwdParams {
     const __bf16 *q;
     const __bf16 *k;

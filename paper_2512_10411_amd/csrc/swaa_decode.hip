@@ -66,28 +66,6 @@ constexpr int kMergeThreads = 256;
 constexpr long long kDResident = 512;                 // workgroups of one column tile that run at once
 constexpr long long kDResidentPairs = 256;            // ... of two
 
-// First statement of the split kernel: brings its argument block into the scalar cache
-// in one round trip.  The compiler loads arguments where they are first used, a line of 64 bytes at a time, and a line
-// that the caches have lost since the last launch is 350 ns away: three to five such waits stood in front of a kernel's first
-// request to memory (one new token on a window of 8192 12.9 -> 12.3 us;
-// kernels that read less of a long cache gain nothing).
-// Workgroups behind the first round find the lines in the cache.
-__device__ __forceinline__ void fetch_args() {
-    static_assert(sizeof(DecodeParams) % 4 == 0, "");
-    if (blockIdx.x >= kDResident) return;
-    const auto args = (const int __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
-    int word;  // (waited for in the same block: the register is free again behind it)
-    asm volatile(".set swaa_line, 0\n\t"
-                 ".rept %c2\n\t"
-                 "s_load_dword %0, %1, swaa_line\n\t"
-                 ".set swaa_line, swaa_line + 64\n\t"
-                 ".endr\n\t"
-                 "s_load_dword %0, %1, %c3\n\t"
-                 "s_waitcnt lgkmcnt(0)"
-                 : "=&s"(word)
-                 : "s"(args), "n"((sizeof(DecodeParams) + 63) / 64), "n"(sizeof(DecodeParams) - 4));
-}
-
 // ---- the split plan of a batch with per-sequence lengths, worked out by every workgroup of the
 // split kernel (DecodeParams::ragged has the rules) ----
 // Lane l keeps the lengths of sequences l, 64 + l, ... and the halves they visit (0 beyond the batch).
@@ -164,7 +142,7 @@ __device__ __forceinline__ bool ragged_find(const RaggedHalves &h, unsigned hps,
 // query rows: two tiles in two workgroups read every key twice, which only some sizes make up for, see plan_decode).
 template <bool kF16, bool kPaged, int kTiles>
 __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_decode_split_kernel(const DecodeParams p) {
-    fetch_args();
+    fetch_args<DecodeParams>();
     // Workgroups reach the eight dies round-robin; the list has fewer than 2^31 items: 32-bit
     // arithmetic, divisions as multiplications.  Sequences of one length: die x takes the x-th
     // contiguous chunk of the item list (a die streams neighbouring memory: 3 % faster on one
@@ -279,39 +257,8 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
     typedef const int __attribute__((address_space(4))) *TablePtr;
     const TablePtr bt = paged ? (TablePtr)(p.block_table + (size_t)b * p.bt_stride) : nullptr;
 
-    // ---- HBM -> LDS copies of one half: instruction i moves rows 4i .. 4i+3, 16 lanes
-    // per row; the XOR swizzle of the operand reads is applied on the global side (K's has a period of four
-    // instructions, V's of one).  Rows past the end of the cache repeat its last row (they are masked later).
-    // A half with all its rows takes its lanes' offsets from the registers below, and the instruction's row
-    // enters through the scalar base: a row's clamp and product per copy were 300 cycles in front of every half. ----
-    const int lrow = lane >> 4, lchk = lane & 15;
-    uint32_t k_lane[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) k_lane[i] = (uint32_t)lrow * k_rsb + (uint32_t)((lchk ^ (((4 * (i & 1) + lrow) << 1) | (i >> 1))) << 4);
-    const uint32_t v_lane = (uint32_t)lrow * v_rsb + (uint32_t)((lchk ^ (lrow << 2)) << 4);
-    auto copy_row4 = [](uint32_t lds, uint32_t off, const char *base) __attribute__((always_inline)) {
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
-    };
-    // The half whose row 0 is at kb[0], vb[0] and whose row 16 is 16 rows behind kb[1], vb[1]; `last` is its last row inside the cache.
-    auto copy_half = [&](uint32_t lds, const char *const(&kb)[2], const char *const(&vb)[2], int last) __attribute__((always_inline)) {
-        if (last >= 31) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) copy_row4(lds + (uint32_t)(i * 1024), k_lane[i & 3], kb[i / 4] + (size_t)(4 * i) * k_rsb);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) copy_row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane, vb[i / 4] + (size_t)(4 * i) * v_rsb);
-            return;
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {  // (the swizzle goes by the row's place in the half, the address by the row that is there)
-            const int back = max(4 * i + lrow - last, 0);
-            copy_row4(lds + (uint32_t)(i * 1024), k_lane[i & 3] + (uint32_t)(4 * i - back) * k_rsb, kb[i / 4]);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int back = max(4 * i + lrow - last, 0);
-            copy_row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane + (uint32_t)(4 * i - back) * v_rsb, vb[i / 4]);
-        }
-    };
+    const HalfCopy half_copy(lane, k_rsb, v_rsb);
+    const int lrow = lane >> 4;
     // Paged cache: the block-table entries one half needs -- one if a page holds a multiple of 32
     // tokens, two for a multiple of 16, else none here (looked up per copy instruction).  They
     // are scalar loads with a long way to go, asked for one loop iteration before the copy.
@@ -345,10 +292,10 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
                     const int page = min(max(bt[pi], 0), p.num_pages - 1);  // inside the cache whatever the table says
                     const int in_page = key4 - (int)pi * p.page_size;
                     const int back = max(key4 + lrow - (Nk - 1), 0);
-                    copy_row4(lds + (uint32_t)(i * 1024), k_lane[i & 3] - (uint32_t)back * k_rsb,
-                              kg + ((long long)page * p.k_sb + (long long)in_page * p.k_sn) * 2);
-                    copy_row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane - (uint32_t)back * v_rsb,
-                              vg + ((long long)page * p.v_sb + (long long)in_page * p.v_sn) * 2);
+                    HalfCopy::row4(lds + (uint32_t)(i * 1024), half_copy.k_lane[i & 3] - (uint32_t)back * k_rsb,
+                                   kg + ((long long)page * p.k_sb + (long long)in_page * p.k_sn) * 2);
+                    HalfCopy::row4(lds + (uint32_t)(kHalfBytes + i * 1024), half_copy.v_lane - (uint32_t)back * v_rsb,
+                                   vg + ((long long)page * p.v_sb + (long long)in_page * p.v_sn) * 2);
                 }
                 return;
             }
@@ -377,7 +324,7 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
             kb[0] = kb[1] = kg + (size_t)k0 * k_rsb;  // uniform
             vb[0] = vb[1] = vg + (size_t)k0 * v_rsb;
         }
-        copy_half(lds, kb, vb, Nk - 1 - k0);
+        half_copy.half(lds, kb, vb, Nk - 1 - k0);
     };
     const LaneAddr la = make_lane_addr(lane, 0);
 
@@ -481,32 +428,13 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
         stage = (stage + 1 == kDStages) ? 0 : stage + 1;
     }
 
-    // ---- the four waves' results are added up through LDS: each wave's O goes to its own ring, which only it has
-    // used, one row of 512 bytes per valid column (16-byte chunk q of column c at q ^ c: neither the writes, a column
-    // per lane, nor the reads, a column per 32 lanes, meet on a bank), and next to the rings what a column's share is
-    // weighted with.  Behind one barrier, 32 threads take a column.  The sum leaves as the split's partial
-    // result -- or, with one split, as the output itself.  The merge divides by the fp32 sums it combines; a wave's
-    // O is the sum over the rounded P, so it enters scaled by l / (sum of the rounded P). ----
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    typedef f32x4 __attribute__((address_space(3))) *LdsQuads;
-    constexpr uint32_t kMl = (uint32_t)(kDWaves * decode_wave_bytes(kTiles));  // [tile][wave][32] of reference, l, l / sum of rounded, 0
+    // ---- the four waves' results are added up through LDS (leave_result) and leave as the split's partial
+    // result -- or, with one split, as the output itself ----
+    constexpr uint32_t kMl = (uint32_t)(kDWaves * decode_wave_bytes(kTiles));
 #pragma unroll
-    for (int j = 0; j < kTiles; ++j) {
-        float l_row, lb_row;
-        row_sums(rs[j], l_row, lb_row);
-        if (col_valid[j]) {
-            const f32x4 ml = {rs[j].mc, l_row, lb_row > 0.f ? l_row / lb_row : 0.f, 0.f};  // a column that saw no key: O = 0, l = 0
-            if (hf == 0) *(LdsQuads)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + wave) * 512 + l32 * 16)) = ml;
-            const uint32_t at = (uint32_t)(wave * decode_wave_bytes(kTiles) + j * kDStageBytes + l32 * 512 + ((hf ^ l32) << 4));
-#pragma unroll
-            for (int c = 0; c < 16; ++c) {
-                f32x4 o4;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o4[e] = oacc[j][c / 4][4 * (c % 4) + e];
-                *(LdsQuads)(uintptr_t)(at ^ (uint32_t)(c << 5)) = o4;  // head-dimension elements 8 c + 4 hf ..
-            }
-        }
-    }
+    for (int j = 0; j < kTiles; ++j)
+        leave_result((uint32_t)(wave * decode_wave_bytes(kTiles) + j * kDStageBytes), kMl + (uint32_t)((j * kDWaves + wave) * 512), l32, hf,
+                     col_valid[j], oacc[j], rs[j]);
     __syncthreads();
     const size_t row0 = ((size_t)b * p.Hq + (size_t)kvh * p.G) * p.Nq;
 #pragma unroll
@@ -514,23 +442,8 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
         const int n_chunks = tile_valid[j] ? 32 * min(32, p.cols - 32 * ct[j]) : 0;
         for (int i = (int)threadIdx.x; i < n_chunks; i += kDThreads) {
             const int c = i >> 5, q = i & 31;  // column of the tile; its head-dimension elements 4 q ..
-            f32x4 ml[kDWaves], ox[kDWaves];
-#pragma unroll
-            for (int x = 0; x < kDWaves; ++x) {
-                ml[x] = *(LdsQuads)(uintptr_t)(kMl + (uint32_t)((j * kDWaves + x) * 512 + c * 16));
-                ox[x] = *(LdsQuads)(uintptr_t)(uint32_t)(x * decode_wave_bytes(kTiles) + j * kDStageBytes + c * 512 + ((q ^ c) << 4));
-            }
-            const float m = fmaxf(fmaxf(ml[0][0], ml[1][0]), fmaxf(ml[2][0], ml[3][0]));
-            const float m_use = m == -INFINITY ? 0.f : m;
-            float l = 0.f;
-            f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int x = 0; x < kDWaves; ++x) {
-                const float w = __builtin_amdgcn_exp2f(ml[x][0] - m_use), wo = w * ml[x][2];
-                l += w * ml[x][1];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o4[e] += ox[x][e] * wo;
-            }
+            float m, l;
+            f32x4_t o4 = add_results((uint32_t)(j * kDStageBytes), (uint32_t)decode_wave_bytes(kTiles), kMl + (uint32_t)(j * kDWaves * 512), c, q, m, l);
             if (n_splits == 1) {
                 const size_t row = row0 + (size_t)(32 * ct[j] + c);
                 o4 *= 1.f / l;
@@ -538,7 +451,7 @@ __global__ __launch_bounds__(kDThreads, decode_wgs_per_cu(kTiles)) void swaa_dec
                 *reinterpret_cast<bf16x4 *>(p.out + row * kD + 4 * q) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
                 if (q == 0) p.lse[row] = (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
             } else {
-                *reinterpret_cast<f32x4 *>(p.ws_o + (item[j] * p.col_stride + c) * kD + 4 * q) = o4;
+                *reinterpret_cast<f32x4_t *>(p.ws_o + (item[j] * p.col_stride + c) * kD + 4 * q) = o4;
                 if (q == 0) {
                     // (a sum that is not a number travels with a finite reference: -inf, the largest score of a column that
                     // sees NaN only, would mark the split as empty, and the merge would leave it out)
@@ -598,9 +511,8 @@ __device__ __forceinline__ MergeRow merge_row(const MergeParams &p, unsigned row
     m.item_step = step * p.n_coltiles;
     return m;
 }
-typedef float merge_f32x4 __attribute__((ext_vector_type(4)));
 // Elements 4 q .. 4 q + 3 of a row.
-__device__ __forceinline__ void merge_store(const MergeParams &p, unsigned row, int q, merge_f32x4 o, float l, float m) {
+__device__ __forceinline__ void merge_store(const MergeParams &p, unsigned row, int q, f32x4_t o, float l, float m) {
     o /= l;
     const bf16x2 lo = p.fp16 ? pack_pair<true>(o[0], o[1]) : pack_pair<false>(o[0], o[1]);
     const bf16x2 hi = p.fp16 ? pack_pair<true>(o[2], o[3]) : pack_pair<false>(o[2], o[3]);
@@ -627,7 +539,7 @@ __device__ __forceinline__ float wave_reduce(float x, float none, F f) {
 // A whole workgroup on one row (many splits): 32 threads to a split, four elements each, eight splits side by side.
 // Every wave finds the largest reference and the sum of the l by itself, a split per lane, from loads that go out
 // together with the first O's: one trip to memory and one barrier.
-__device__ __forceinline__ void merge_row_by_workgroup(const MergeParams &p, const MergeRow &mr, merge_f32x4 *red) {
+__device__ __forceinline__ void merge_row_by_workgroup(const MergeParams &p, const MergeRow &mr, f32x4_t *red) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int q = tid % 32, g = tid / 32;
     constexpr int kGroups = kMergeThreads / 32, kBatch = 4;
@@ -636,13 +548,13 @@ __device__ __forceinline__ void merge_row_by_workgroup(const MergeParams &p, con
     // A split that saw no visible key has reference -inf and may not have written its O: it is loaded all the same
     // (the workspace is there) and left out of the sums by selection, not by a branch; so is what lies beyond the last split.
     float mcs[kBatch];
-    merge_f32x4 os[kBatch];
+    f32x4_t os[kBatch];
     auto load = [&](int s0) {
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             const int s = s0 + u * kGroups, at = min(s, n - 1);
             mcs[u] = *ml_of(at);
-            os[u] = *reinterpret_cast<const merge_f32x4 *>(p.ws_o + ((mr.item0 + at * mr.item_step) * p.col_stride + mr.col) * kD + 4 * q);
+            os[u] = *reinterpret_cast<const f32x4_t *>(p.ws_o + ((mr.item0 + at * mr.item_step) * p.col_stride + mr.col) * kD + 4 * q);
             if (s >= n) mcs[u] = -INFINITY;
         }
     };
@@ -658,7 +570,7 @@ __device__ __forceinline__ void merge_row_by_workgroup(const MergeParams &p, con
         l += mcx == -INFINITY ? 0.f : w;
     }
     l = wave_reduce(l, 0.f, [](float a, float b) { return a + b; });
-    merge_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
     for (int s0 = g;;) {
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
@@ -685,7 +597,7 @@ __device__ __forceinline__ void merge_row_by_workgroup(const MergeParams &p, con
 constexpr int kMergeRowSplits = 8;
 __device__ __forceinline__ void merge_row_by_group(const MergeParams &p, const MergeRow &mr, int q) {
     float mcs[kMergeRowSplits], ls[kMergeRowSplits];
-    merge_f32x4 os[kMergeRowSplits];
+    f32x4_t os[kMergeRowSplits];
     // (a split that saw no visible key has reference -inf and may not have written its O: loaded all
     // the same and left out by selection; splits beyond the row's repeat the last one and count as empty)
 #pragma unroll
@@ -694,14 +606,14 @@ __device__ __forceinline__ void merge_row_by_group(const MergeParams &p, const M
         const long long it = mr.item0 + (there ? s : 0) * mr.item_step;
         mcs[s] = p.ws_ml[it * 64 + mr.col];
         ls[s] = p.ws_ml[it * 64 + 32 + mr.col];
-        os[s] = *reinterpret_cast<const merge_f32x4 *>(p.ws_o + (it * p.col_stride + mr.col) * kD + 4 * q);
+        os[s] = *reinterpret_cast<const f32x4_t *>(p.ws_o + (it * p.col_stride + mr.col) * kD + 4 * q);
         if (!there) mcs[s] = -INFINITY;
     }
     float m = mcs[0];
 #pragma unroll
     for (int s = 1; s < kMergeRowSplits; ++s) m = fmaxf(m, mcs[s]);  // finite: every row sees at least its own key
     float l = 0.f;
-    merge_f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < kMergeRowSplits; ++s) {
         const bool empty = mcs[s] == -INFINITY;
@@ -715,7 +627,7 @@ __device__ __forceinline__ void merge_row_by_group(const MergeParams &p, const M
 
 // Sequences of one length, more than kMergeRowSplits splits per pair: one workgroup per output row.
 __global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_kernel(const MergeParams p) {
-    __shared__ merge_f32x4 red[kMergeThreads];
+    __shared__ f32x4_t red[kMergeThreads];
     merge_row_by_workgroup(p, merge_row(p, blockIdx.x), red);
 }
 
@@ -737,7 +649,7 @@ __global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_rows_kernel(c
 // for the (k / (Hq Nq))-th such sequence in the plan the split kernel has left (a prefix sum of
 // flags over the lanes, every wave for itself) and goes home if there is none.
 __global__ __launch_bounds__(kMergeThreads) void swaa_decode_merge_ragged_kernel(const MergeParams p) {
-    __shared__ merge_f32x4 red[kMergeThreads];
+    __shared__ f32x4_t red[kMergeThreads];
     if (blockIdx.x < p.n_small) {
         const unsigned row = blockIdx.x * kMergeRows + threadIdx.x / 32;
         if (row >= p.rows) return;

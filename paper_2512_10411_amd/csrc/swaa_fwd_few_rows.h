@@ -9,7 +9,7 @@
 // loop, and their results are added up through LDS.  What bounds it is reading: every key once (466 MB fetched, 470
 // by count), at 4.1 TB/s beside a chunk and 5.0 alone of 6.4 for large reads; asking for a half's K before its V is read
 // changed nothing.  The softmax is max-based, so there is
-// no second pass.  The registers (two workgroups per CU) and the 64 KiB of LDS are those of the forward.
+// no second pass.  The registers (two workgroups per CU) are those of the forward.
 // Measured, row tiles -> this (binary16, pages of 16 tokens): 23 tokens on 1-12k keys beside a chunk of 999 rows on a
 // window of 2k, 32 heads on 8, 141 -> 123 us (470 MB: 74 us at the rate of large reads); 31 tokens on 3-28k keys
 // beside 500 rows, 40 heads on 8 (five heads were two tiles, each reading the keys) 362 -> 268, 32 heads on 8 266 -> 247;
@@ -25,7 +25,10 @@
 
 namespace swaa {
 
-// One workgroup of four waves on split si of the few-row sequence of wi.  LDS: 64 KiB from address 0.
+// LDS of such a workgroup: the four rings, then what the waves' results are weighted with.
+constexpr int kFewSmemBytes = 4 * (2 * kHalfBytes + 512);
+
+// One workgroup of four waves on split si of the few-row sequence of wi.  LDS: kFewSmemBytes from address 0.
 template <bool kF16, bool kPaged>
 __device__ __forceinline__ void few_rows_item(const FwdParams &p, const WorkItem &wi, const SplitItem &si, const SeqGeom &sg) {
     constexpr uint32_t kRing = 2 * kHalfBytes;  // a wave's: K half, then V half
@@ -64,12 +67,10 @@ __device__ __forceinline__ void few_rows_item(const FwdParams &p, const WorkItem
         return 32 * (h < n_sink ? h : h - n_sink + hb_lo);
     };
 
-    // ---- HBM -> LDS copies of one half: instruction i moves rows 4 i .. 4 i + 3, swizzled on the global side as in
-    // the row tiles.  Rows past the sequence's last key repeat it (they are masked later). ----
     const uint32_t k_rsb = (uint32_t)(p.k_sn * 2), v_rsb = (uint32_t)(p.v_sn * 2);
     const char *kg = reinterpret_cast<const char *>(p.k + sg.k_batch * p.k_sb + (long long)wi.kvh * p.k_sh + sg.k_row0 * p.k_sn);
     const char *vg = reinterpret_cast<const char *>(p.v + sg.k_batch * p.v_sb + (long long)wi.kvh * p.v_sh + sg.k_row0 * p.v_sn);
-    const int lrow = lane >> 4, lchk = lane & 15;
+    const HalfCopy half_copy(lane, k_rsb, v_rsb);
     const uint32_t ring = (uint32_t)wave * kRing;
     typedef const int __attribute__((address_space(4))) *TablePtr;  // (constant memory: scalar loads)
     const TablePtr bt = kPaged ? (TablePtr)(p.block_table + (size_t)wi.b * p.bt_stride) : nullptr;
@@ -107,27 +108,14 @@ __device__ __forceinline__ void few_rows_item(const FwdParams &p, const WorkItem
             kb[0] = kb[1] = kg + (size_t)k0 * k_rsb;
             vb[0] = vb[1] = vg + (size_t)k0 * v_rsb;
         }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = min(4 * i + lrow, Nk - 1 - k0);
-            const int fk = ((4 * (i & 1) + lrow) << 1) | ((i >> 1) & 1);
-            const uint32_t off = (uint32_t)r * k_rsb + (uint32_t)((lchk ^ fk) << 4);
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(kb[i / 4]),
-                         "s"(ring + (uint32_t)(i * 1024))
-                         : "memory");
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int r = min(4 * i + lrow, Nk - 1 - k0);
-            const uint32_t off = (uint32_t)r * v_rsb + (uint32_t)((lchk ^ (lrow << 2)) << 4);
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(vb[i / 4]),
-                         "s"(ring + (uint32_t)(kHalfBytes + i * 1024))
-                         : "memory");
-        }
+        half_copy.half(ring, kb, vb, Nk - 1 - k0);
     };
     const LaneAddr la = make_lane_addr(lane, 0);
 
-    // ---- this lane's Q fragments (ordinary loads: the compiler's wait covers the copies behind them as well) ----
+    // ---- the first half and this lane's Q fragments (ordinary loads, asked for while a page of the half is looked up;
+    // the compiler's wait covers the copies as well) ----
+    const Pages pg_first = n_mine >= 1 ? lookup(0) : Pages{0, 0};
+    if (!kPaged && n_mine >= 1) issue_half(0, pg_first);
     bf16x8 qf[kKS];
     {
         const char *qrow = reinterpret_cast<const char *>(p.q + sg.q_batch * p.q_sb + (long long)head * p.q_sh +
@@ -135,7 +123,7 @@ __device__ __forceinline__ void few_rows_item(const FwdParams &p, const WorkItem
 #pragma unroll
         for (int ks = 0; ks < kKS; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qrow + 32 * ks);
     }
-    if (n_mine >= 1) issue_half(0, lookup(0));
+    if (kPaged && n_mine >= 1) issue_half(0, pg_first);
     asm volatile("s_nop 1"
                  : "+a"(qf[0]), "+a"(qf[1]), "+a"(qf[2]), "+a"(qf[3]), "+a"(qf[4]), "+a"(qf[5]), "+a"(qf[6]), "+a"(qf[7]));
     Pages pg_next = n_mine > 1 ? lookup(1) : Pages{0, 0};
@@ -191,64 +179,29 @@ __device__ __forceinline__ void few_rows_item(const FwdParams &p, const WorkItem
             }
     }
 
-    // ---- the four waves' results through LDS (references and sums first, at the start of each wave's own ring, then O
-    // in accumulator order); O enters scaled by l / (sum of the rounded P), as the merge divides by the fp32 sums ----
-    typedef float __attribute__((address_space(3))) *LdsFloats;
-    typedef float f32x4 __attribute__((ext_vector_type(4)));
-    typedef f32x4 __attribute__((address_space(3))) *LdsQuads;
-    float l_row, lb_row;
-    row_sums(rs, l_row, lb_row);
-    float fix = lb_row > 0.f ? l_row / lb_row : 0.f;  // a column that saw no key: O = 0, l = 0
-    ((LdsFloats)(uintptr_t)ring)[lane] = hf ? l_row : rs.mc;
+    // ---- the four waves' results through LDS (leave_result) ----
+    constexpr uint32_t kMl = 4 * kRing;
+    leave_result(ring, kMl + (uint32_t)(wave * 512), l32, hf, col_valid, oacc, rs);
     __syncthreads();
-    float mcs[4], ls[4], m = -INFINITY, l = 0.f;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-        mcs[x] = ((LdsFloats)(uintptr_t)((uint32_t)x * kRing))[l32];
-        ls[x] = ((LdsFloats)(uintptr_t)((uint32_t)x * kRing))[32 + l32];
-        m = fmaxf(m, mcs[x]);
-    }
-    __syncthreads();
-    const float m_use = m == -INFINITY ? 0.f : m;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) l += __builtin_amdgcn_exp2f(mcs[x] - m_use) * ls[x];
-    fix *= __builtin_amdgcn_exp2f(rs.mc - m_use);
-    if (col_valid) {
-#pragma unroll
-        for (int c = 0; c < 16; ++c) {
-            f32x4 o4;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o4[e] = oacc[c / 4][4 * (c % 4) + e] * fix;
-            *(LdsQuads)(uintptr_t)(ring + (uint32_t)(c * 1024 + lane * 16)) = o4;
-        }
-    }
-    __syncthreads();
-    if (!col_valid) return;
-    const float inv_l = 1.f / l;
-    __bf16 *orow = p.out + sg.q_batch * p.o_sb + (long long)head * p.o_sh + (sg.q_row0 + row) * p.o_sn;
-    float *wo = p.ws_o + (size_t)(si.slot * 4u) * (16 * 64 * 4) + lane * 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = 4 * wave + i;  // this wave's share: head-dimension block `wave`
-        f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int x = 0; x < 4; ++x) o4 += *(LdsQuads)(uintptr_t)((uint32_t)x * kRing + (uint32_t)(c * 1024 + lane * 16));
+    for (int i = (int)threadIdx.x; i < 32 * cols; i += 256) {
+        const int c = i >> 5, q = i & 31;  // column; its head-dimension elements 4 q ..
+        float m, l;
+        f32x4_t o4 = add_results(0u, kRing, kMl, c, q, m, l);
         if (si.n == 1) {
-            o4 *= inv_l;
+            const int h = (int)(((unsigned)c * inv_nq) >> 16);
+            const long long r = sg.q_row0 + c - h * nq, hq = wi.kvh * p.G + h;
+            o4 *= 1.f / l;
             const bf16x2 lo = pack_pair<kF16>(o4[0], o4[1]), hi = pack_pair<kF16>(o4[2], o4[3]);
-            *reinterpret_cast<bf16x4 *>(orow + 8 * c + 4 * hf) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+            *reinterpret_cast<bf16x4 *>(p.out + sg.q_batch * p.o_sb + hq * p.o_sh + r * p.o_sn + 4 * q) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3);
+            if (q == 0) p.lse[sg.q_batch * p.lse_sb + hq * p.lse_sh + r] = (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
         } else {
-            *reinterpret_cast<f32x4 *>(wo + c * 256) = o4;  // (the layout of a row tile's first wave)
-        }
-    }
-    if (wave == 0) {
-        if (si.n == 1) {
-            if (hf == 0)
-                p.lse[sg.q_batch * p.lse_sb + (long long)head * p.lse_sh + sg.q_row0 + row] =
-                    (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
-        } else {
-            // (a sum that is not a number travels with a finite reference: -inf would mark the split as empty)
-            p.ws_ml[(size_t)(si.slot * 4u) * 64 + lane] = hf ? l : non_finite(l) ? 0.f : m;
+            // (the layout of a row tile's first wave: accumulator order)
+            *reinterpret_cast<f32x4_t *>(p.ws_o + (size_t)(si.slot * 4u) * (16 * 64 * 4) + (q >> 1) * 256 + (q & 1) * 128 + c * 4) = o4;
+            if (q == 0) {
+                // (a sum that is not a number travels with a finite reference: -inf would mark the split as empty)
+                p.ws_ml[(size_t)(si.slot * 4u) * 64 + c] = non_finite(l) ? 0.f : m;
+                p.ws_ml[(size_t)(si.slot * 4u) * 64 + 32 + c] = l;
+            }
         }
     }
 }

@@ -37,6 +37,7 @@
 //
 // This kernel declares no static LDS: its dynamic LDS starts at address 0 and
 // all LDS accesses below use plain byte addresses.
+#include <atomic>
 #include <type_traits>
 
 #include "swaa_fwd_few_rows.h"
@@ -55,6 +56,7 @@ constexpr int kStages = 2;                            // tiles per ring
 constexpr int kTileBytes = kBk * kD * 2;              // 16 KiB
 constexpr int kVRing = kStages * kTileBytes;          // V ring follows the K ring
 constexpr int kSmemBytes = 2 * kStages * kTileBytes;  // 64 KiB: two workgroups per compute unit
+constexpr int kSplitSmemBytes = kSmemBytes > kFewSmemBytes ? kSmemBytes : kFewSmemBytes;  // (with split keys)
 constexpr int kStageBytes = kPRows * kD * 2;          // 8 KiB: a wave's 32 O rows on the way out (inside the K ring)
 constexpr float kSumLimit = 1.2089258e24f;  // 2^80: a row sum that sends the workgroup back to the max-based path
 constexpr float kSumFloor = 7.8886091e-31f;  // 2^-100: so does one this small (every score far below the reference)
@@ -251,13 +253,13 @@ template <bool kF16, bool kPaged, bool kSplit>
 __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const FwdParams p) {
     WorkItem wi;
     SplitItem si{1, 0, 0u};
-    if constexpr (kSplit) {
-        if (!decode_work_split(p, 0u, wi, si)) return;
-    } else {
-        if (!decode_work(p, wi)) return;
-    }
     SeqGeom sg;
-    if (!seq_geom(p, wi.b, sg)) return;
+    if constexpr (kSplit) {
+        fetch_args<FwdParams>();
+        if (!decode_work_split(p, 0u, wi, si, sg)) return;
+    } else {
+        if (!decode_work(p, wi) || !seq_geom(p, wi.b, sg)) return;
+    }
     if constexpr (kSplit) {
         if (few_rows(p, sg.nq) && si.n > 0) {
             few_rows_item<kF16, kPaged>(p, wi, si, sg);
@@ -799,13 +801,13 @@ __global__ __launch_bounds__(kPThreads, 2) void swaa_fwd_pipelined_kernel(const 
 // contiguous bytes per 32 threads).  Which tile follows from the split counts that the splits left.
 template <bool kF16>
 __global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) {
+    fetch_args<FwdParams>();
     const int tid = threadIdx.x, lane = tid & 63, l32 = tid & 31, q = tid >> 5;
     const unsigned wave = blockIdx.x & 3u, rank = blockIdx.x >> 2;  // rank: tile among those of split sequences
     const unsigned n_mine = (unsigned)p.ws_n[lane];
+    const SplitLengths lengths = split_lengths(p, lane);
     if (!__any(n_mine > 1u)) return;  // (the plan has left everything whole)
-    int nq, nk, np;
-    split_lengths(p, lane, nq, nk, np);
-    const SplitSeq me = split_seq(p, nq, nk, np);
+    const SplitSeq me = split_seq(p, lengths.nq, lengths.nk, lengths.np);
     const unsigned items = (unsigned)(me.tiles * p.Hkv);
     const unsigned incl = wave_inclusive_scan(n_mine > 1u ? items : 0u);
     const unsigned slots = wave_inclusive_scan(n_mine > 1u ? items * n_mine : 0u);
@@ -817,9 +819,9 @@ __global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) 
     const unsigned kvh = r / tiles;
     r -= kvh * tiles;
     WorkItem w;
-    split_tile(p, (int)wave_read_lane((unsigned)nq, b), r, w);
     SeqGeom sg;
-    if (!seq_geom(p, b, sg)) return;
+    if (!split_geom(p, lengths, b, sg)) return;
+    split_tile(p, sg.nq, r, w);
     int row = w.pt * (kPWgRows / w.hpb) + ((int)wave / w.hpb) * kPRows + l32;
     int head = (int)kvh * p.G + w.h0 + (int)wave % w.hpb;
     if (few_rows(p, sg.nq)) {  // one column tile, in the first wave's place
@@ -957,6 +959,14 @@ long long plan_fwd_split(FwdParams &p) {
         p.split_keys = 1;
         p.split_cap = room < kSplitUnits ? (int)room : kSplitUnits;
         p.chunk = (bound + p.split_cap + kXcds - 1) / kXcds + p.B;
+        // One sequence is as long as the host says, or shorter, and then has a few splits more than it needs: the plan from above,
+        // unless it has a prompt length of its own behind a window, and the device alone knows what its rows see.  (512 rows on
+        // 24k tokens: 4.4 us of plan stood in front of every workgroup's first key, without the model 2.)
+        const long long units = (long long)p.Hkv * longest.tiles * n;
+        if (p.B == 1 && n > 1 && units <= p.split_cap && (!p.n_prompts || p.W >= p.Nk)) {
+            p.split_keys = n;
+            p.chunk = (units + kXcds - 1) / kXcds;
+        }
     }
     p.total_items = p.chunk * kXcds;
     p.split_items = bound;
@@ -972,12 +982,25 @@ void place_fwd_split(FwdParams &p, void *workspace) {
 hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream) {
     if (p.wg_rows != kPWgRows) return hipErrorInvalidValue;  // the plan must be the one for this kernel's workgroups
     const unsigned grid = (unsigned)(p.chunk * kXcds);
-    // (64 KiB of dynamic LDS is what a kernel gets without asking)
-    static_assert(kSmemBytes <= 64 * 1024, "more would need hipFuncSetAttribute");
     const bool paged = p.block_table != nullptr;
+    hipError_t err = hipSuccess;
     auto launch = [&](auto f16, auto pg, auto split) {
-        hipLaunchKernelGGL((swaa_fwd_pipelined_kernel<decltype(f16)::value, decltype(pg)::value, decltype(split)::value>),
-                           dim3(grid), dim3(kPThreads), kSmemBytes, stream, p);
+        auto kernel = swaa_fwd_pipelined_kernel<decltype(f16)::value, decltype(pg)::value, decltype(split)::value>;
+        constexpr int kBytes = decltype(split)::value ? kSplitSmemBytes : kSmemBytes;
+        static_assert(kSmemBytes <= 64 * 1024, "what a kernel gets without asking");
+        if constexpr (kBytes > 64 * 1024) {  // (requested once per device)
+            static std::atomic<unsigned long long> configured{0};
+            int dev = 0;
+            err = hipGetDevice(&dev);
+            if (err != hipSuccess) return;
+            const unsigned long long bit = 1ull << (dev & 63);
+            if (!(configured.load(std::memory_order_acquire) & bit)) {
+                err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+                if (err != hipSuccess) return;
+                configured.fetch_or(bit, std::memory_order_release);
+            }
+        }
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kPThreads), kBytes, stream, p);
     };
     auto pick_split = [&](auto f16, auto pg) {
         if (p.split_keys)
@@ -995,7 +1018,7 @@ hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream) {
         pick_paged(std::true_type{});
     else
         pick_paged(std::false_type{});
-    const hipError_t err = hipGetLastError();
+    if (err == hipSuccess) err = hipGetLastError();
     if (err != hipSuccess || p.split_keys <= 0) return err;
     const unsigned merges = (unsigned)(4 * (p.split_items < p.split_cap / 2 ? p.split_items : p.split_cap / 2));
     if (p.fp16)

@@ -215,16 +215,41 @@ struct SplitItem {
     unsigned slot;  // partial result (n >= 2)
 };
 
-// Sequence b's rows, keys and prompt length (0 rows for b >= B).
-__device__ __forceinline__ void split_lengths(const FwdParams &p, int b, int &nq, int &nk, int &np) {
-    nq = nk = np = 0;
-    if (b >= p.B) return;
-    nq = p.cu_q ? p.cu_q[b + 1] - p.cu_q[b] : p.Nq;
-    nk = p.cu_k ? p.cu_k[b + 1] - p.cu_k[b] : p.Nk;
-    np = p.n_prompts ? max(p.n_prompts[b], 0) : p.P;
-    nq = max(0, min(min(nq, p.Nq), nk));
-    nk = min(nk, p.Nk);
-    nq = min(nq, nk);
+// Sequence `lane` of the batch (0 rows and keys beyond its end): rows, keys, prompt length, and first row along the row axes.
+struct SplitLengths {
+    int nq, nk, np, q0, k0;
+};
+__device__ __forceinline__ SplitLengths split_lengths(const FwdParams &p, int lane) {
+    // (a lane beyond the batch reads the last sequence's, so that all loads go out together and none waits for a branch)
+    const int b = min(lane, p.B - 1);
+    int q0 = 0, q1 = p.Nq, k0 = 0, k1 = p.Nk, np = p.P;
+    if (p.cu_q) {
+        q0 = p.cu_q[b];
+        q1 = p.cu_q[b + 1];
+    }
+    if (p.cu_k) {
+        k0 = p.cu_k[b];
+        k1 = p.cu_k[b + 1];
+    }
+    if (p.n_prompts) np = p.n_prompts[b];
+    asm volatile("" : "+v"(q0), "+v"(q1), "+v"(k0), "+v"(k1), "+v"(np));
+    SplitLengths s{q1 - q0, k1 - k0, max(np, 0), q0, k0};
+    s.nq = max(0, min(min(s.nq, p.Nq), s.nk));
+    s.nk = min(s.nk, p.Nk);
+    s.nq = min(s.nq, s.nk);
+    if (lane >= p.B) s.nq = s.nk = s.np = 0;
+    return s;
+}
+// Sequence b of them as seq_geom describes it, without a second trip to memory; false if it has no rows.
+__device__ __forceinline__ bool split_geom(const FwdParams &p, const SplitLengths &s, int b, SeqGeom &g) {
+    g.nq = (int)wave_read_lane((unsigned)s.nq, b);
+    g.nk = (int)wave_read_lane((unsigned)s.nk, b);
+    g.n_prompt = (int)wave_read_lane((unsigned)s.np, b);
+    g.q_row0 = (int)wave_read_lane((unsigned)s.q0, b);
+    g.q_batch = p.cu_q ? 0 : b;
+    g.k_row0 = p.block_table ? 0 : (int)wave_read_lane((unsigned)s.k0, b);  // (a paged cache: the offsets only give the lengths)
+    g.k_batch = p.cu_k || p.block_table ? 0 : b;
+    return g.nq > 0;
 }
 
 // Row tile `t` of a (sequence, KV head) pair with nq query rows (the order of decode_work).
@@ -275,12 +300,12 @@ __device__ __forceinline__ float wave_sum(float x) {
 // contiguous chunks, one per die (die_share); inside a sequence by KV head, then
 // split, then row tile, so that the workgroups side by side on a die read the same keys.  scratch:
 // 4 KiB of LDS of a workgroup of four waves, free again after the caller's next barrier.
-__device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t scratch, WorkItem &w, SplitItem &si) {
+__device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t scratch, WorkItem &w, SplitItem &si, SeqGeom &sg) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned xcd = blockIdx.x % kXcds, rank = blockIdx.x / kXcds;
-    int nq, nk, np;
-    split_lengths(p, lane, nq, nk, np);
-    const SplitSeq me = split_seq(p, nq, nk, np);
+    const SplitLengths lengths = split_lengths(p, lane);
+    const int nq = lengths.nq;
+    const SplitSeq me = split_seq(p, nq, lengths.nk, lengths.np);
     const int items = me.tiles * p.Hkv;
     int n = 1;
     bool few_even = true;  // few rows only, of about one length: the average is 0.8 of the longest and more
@@ -308,7 +333,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
             split_units += c > 1 ? u : 0.f;
             const float start = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(me.start), b));
             starts += u * start;
-            longest = fmaxf(longest, it ? (float)h / (float)c + start : 0.f);
+            longest = fmaxf(longest, it ? (float)h * __builtin_amdgcn_rcpf((float)c) + start : 0.f);
         }
         typedef float __attribute__((address_space(3))) *LdsFloats;
         const LdsFloats mine = (LdsFloats)(uintptr_t)(scratch + (uint32_t)(wave * 1024 + lane * 4));
@@ -333,7 +358,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
         const int Lb = __builtin_amdgcn_readlane(L, pick);
         // (no candidate fits the workspace only if candidate 0 splits as well: caches of 2^27 keys, whose halves
         // split_count can no longer tell apart)
-        if (splittable > 0 && best < 3.0e38f && !whole_batch(p, least, least_units(p, rows))) n = split_count(me.cost, Lb, 1.f / (float)Lb);
+        if (splittable > 0 && best < 3.0e38f && (least < 64 || !whole_batch(p, least, least_units(p, rows)))) n = split_count(me.cost, Lb, 1.f / (float)Lb);
         const float whole_units = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(units), 0));  // (candidate 0's)
         few_even = total >= 0.8f * (float)h_max * whole_units && !__any(!few_rows(p, nq));
         if (few_even && few_stay_whole((unsigned)whole_units)) n = 1;
@@ -367,6 +392,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     r -= (unsigned)w.kvh * per_head;
     si.s = (int)(r / tiles);
     split_tile(p, nq_b, r - (unsigned)si.s * tiles, w);
+    if (!split_geom(p, lengths, b, sg)) return false;
     if (in_rows) si.n = 0;  // (said in another field, it cost other batches 1 us: scalar registers move to vector ones)
     return true;
 }

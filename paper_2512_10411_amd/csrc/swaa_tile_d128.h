@@ -290,6 +290,93 @@ __device__ __forceinline__ LaneAddr make_lane_addr(int lane, uint32_t v_base) {
     return la;
 }
 
+// HBM -> LDS copies of one half by one wave: instruction i moves rows 4 i .. 4 i + 3 of K, then of V, 16 lanes per row;
+// the XOR swizzle of the operand reads is applied on the global side (K's has a period of four instructions, V's of one).
+// Rows past the end of the cache repeat its last row (they are masked later).  A half with all its rows takes its lanes'
+// offsets from registers, and the instruction's row enters through the scalar base: a clamp and a product per row and
+// instruction were 300 cycles in front of every half.
+struct HalfCopy {
+    uint32_t k_rsb, v_rsb;  // row strides in bytes
+    uint32_t k_lane[4], v_lane;
+    int lrow;
+    __device__ __forceinline__ HalfCopy(int lane, uint32_t k_row_bytes, uint32_t v_row_bytes) : k_rsb(k_row_bytes), v_rsb(v_row_bytes) {
+        lrow = lane >> 4;
+        const int lchk = lane & 15;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) k_lane[i] = (uint32_t)lrow * k_rsb + (uint32_t)((lchk ^ (((4 * (i & 1) + lrow) << 1) | (i >> 1))) << 4);
+        v_lane = (uint32_t)lrow * v_rsb + (uint32_t)((lchk ^ (lrow << 2)) << 4);
+    }
+    static __device__ __forceinline__ void row4(uint32_t lds, uint32_t off, const char *base) {
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds) : "memory");
+    }
+    // The half whose row 0 is at kb[0], vb[0] and whose row 16 is 16 rows behind kb[1], vb[1], to K and then V of the ring
+    // at lds; `last` (>= 0) is its last row inside the cache.
+    __device__ __forceinline__ void half(uint32_t lds, const char *const (&kb)[2], const char *const (&vb)[2], int last) const {
+        if (last >= 31) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) row4(lds + (uint32_t)(i * 1024), k_lane[i & 3], kb[i / 4] + (size_t)(4 * i) * k_rsb);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane, vb[i / 4] + (size_t)(4 * i) * v_rsb);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {  // (the swizzle goes by the row's place in the half, the address by the row that is there)
+            const int back = max(4 * i + lrow - last, 0);
+            row4(lds + (uint32_t)(i * 1024), k_lane[i & 3] + (uint32_t)(4 * i - back) * k_rsb, kb[i / 4]);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int back = max(4 * i + lrow - last, 0);
+            row4(lds + (uint32_t)(kHalfBytes + i * 1024), v_lane + (uint32_t)(4 * i - back) * v_rsb, vb[i / 4]);
+        }
+    }
+};
+
+// Where the four waves of a workgroup of few rows, each with a share of the keys, add up their results through LDS: each
+// wave's O goes to its own ring, which only it has used, one row of 512 bytes per valid column (16-byte chunk q of column c
+// at q ^ c: neither the writes, a column per lane, nor the reads, a column per 32 lanes, meet on a bank), and next to
+// the rings what a column's share is weighted with.  Behind one barrier, 32 threads take a column.  A wave's O is
+// the sum over the rounded P; it enters scaled by l / (sum of the rounded P), so that the sum divides by fp32 sums.
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef f32x4_t __attribute__((address_space(3))) *LdsQuads;
+// o: 16 KiB of LDS of this wave; ml: 512 bytes.
+__device__ __forceinline__ void leave_result(uint32_t o, uint32_t ml, int l32, int hf, bool col_valid, const f32x16 (&oacc)[kDB], const RowState &rs) {
+    float l_row, lb_row;
+    row_sums(rs, l_row, lb_row);
+    if (!col_valid) return;
+    const f32x4_t weight = {rs.mc, l_row, lb_row > 0.f ? l_row / lb_row : 0.f, 0.f};  // a column that saw no key: O = 0, l = 0
+    if (hf == 0) *(LdsQuads)(uintptr_t)(ml + (uint32_t)(l32 * 16)) = weight;
+    const uint32_t at = o + (uint32_t)(l32 * 512 + ((hf ^ l32) << 4));
+#pragma unroll
+    for (int c = 0; c < 16; ++c) {
+        f32x4_t o4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o4[e] = oacc[c / 4][4 * (c % 4) + e];
+        *(LdsQuads)(uintptr_t)(at ^ (uint32_t)(c << 5)) = o4;  // head-dimension elements 8 c + 4 hf ..
+    }
+}
+// Elements 4 q .. 4 q + 3 of column c over the four waves (o_stride bytes apart): O, its reference m and row sum l.
+__device__ __forceinline__ f32x4_t add_results(uint32_t o, uint32_t o_stride, uint32_t ml, int c, int q, float &m, float &l) {
+    f32x4_t w[4], ox[4];
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        w[x] = *(LdsQuads)(uintptr_t)(ml + (uint32_t)(x * 512 + c * 16));
+        ox[x] = *(LdsQuads)(uintptr_t)(o + (uint32_t)x * o_stride + (uint32_t)(c * 512 + ((q ^ c) << 4)));
+    }
+    m = fmaxf(fmaxf(w[0][0], w[1][0]), fmaxf(w[2][0], w[3][0]));
+    const float m_use = m == -INFINITY ? 0.f : m;
+    l = 0.f;
+    f32x4_t o4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < 4; ++x) {
+        const float e2 = __builtin_amdgcn_exp2f(w[x][0] - m_use), wo = e2 * w[x][2];
+        l += e2 * w[x][1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o4[e] += ox[x][e] * wo;
+    }
+    return o4;
+}
+
 }  // namespace swaa
 
 #endif  // SWAA_TILE_D128_H_

@@ -401,3 +401,22 @@ def test_few_rows_and_what_is_not_a_number(scratch, nk, what, fmt):
     torch.cuda.synchronize()
     assert not torch.isfinite(out[0, 4:, 2].float()).any() and not torch.isfinite(lse[0, 4:, 2]).any()
     assert torch.equal(out[0, :, :2], want[0, :, :2]) and torch.equal(lse[0, :, :2], want_l[0, :, :2])
+
+
+@pytest.mark.parametrize("nq,nk,max_q,max_k,W,prompt", [
+    (70, 4000, 70, 4000, 10**9, 3000),    # as long as the host says: its plan; generated rows
+    (70, 2100, 128, 6000, 10**9, None),   # shorter, more splits than a model of the true lengths makes
+    (5, 300, 128, 6000, 10**9, None),     # ... few rows, and fewer halves than splits
+    (40, 4000, 70, 4000, 500, 3980),      # prompt and generated rows behind a window: planned on the device, whole
+])
+def test_one_packed_sequence(scratch, nq, nk, max_q, max_k, W, prompt):
+    Hkv, G, D = 2, 4, 128
+    print(f"[case] packed alone nq {nq} nk {nk} of {max_q} {max_k} W {W}", flush=True)
+    q, k, v = make_qkv(1, Hkv * G, Hkv, nk, D, seed=9750 + nq, n_query=nq)
+    ints = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    out, lse = binding.swaa_attn_fwd_ex(*(to_device(x[0]) for x in (q, k, v)), W, 4, cu_seqlens_q=ints(0, nq), cu_seqlens_k=ints(0, nk),
+                                        max_seqlen_q=max_q, max_seqlen_k=max_k, n_prompts=None if prompt is None else ints(prompt))
+    torch.cuda.synchronize()
+    assert scratch[0] > 0
+    ro, rl = swaa_decode_oracle(q, k, v, min(W, nk), 4, 1 / math.sqrt(D), n_prompt=prompt)
+    assert_parity(out[None], lse[None], ro, rl, tag=f"packed alone {nq} of {nk}")
