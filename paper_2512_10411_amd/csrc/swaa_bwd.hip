@@ -50,13 +50,6 @@ __device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
     return __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)(uintptr_t)addr);
 }
 
-// Does row i see key j?  Without short-circuit evaluation, for code that must stay free of branches:
-// per-element branches in the softmax stages (sixteen elements, several conditions each) cost
-// more than all of the stage's arithmetic.
-__device__ __forceinline__ bool visible_in_range(int i, int j, int N, int W, int S, int P) {
-    return (i < N) & (j <= i) & ((i >= P) | (j > i - W) | (j < S));
-}
-
 // ---- dQ, head dimension 64 -------------------------------------------------------------
 // A workgroup is eight waves of 32 query rows; 128 registers per wave, so that two workgroups share
 // a compute unit and one wave's exponentials run under the others' matrix instructions.  (With a
@@ -202,11 +195,9 @@ __global__ __launch_bounds__(dq64::kThreads, 4) void swaa_bwd_dq_kernel(const Bw
             // dS^T = P^T (dP^T - delta) with P^T = exp2(s c2 - lse2), packed to bf16; a score that must not
             // be seen becomes -inf, its P an exact 0
             if (!unmasked) {
+                const uint32_t bits = qpos < N ? visible_keys(k0, qpos, qpos >= P ? N : W, S) >> (4 * hf) : 0u;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = k0 + 8 * (e / 4) + 4 * hf + (e % 4);
-                    sacc[e] = visible_in_range(qpos, key, N, W, S, P) ? sacc[e] : -INFINITY;
-                }
+                for (int e = 0; e < 16; ++e) sacc[e] = where_visible(bits, e, sacc[e]);
             }
             bf16x8 dsf[2];  // [16-key step]
 #pragma unroll

@@ -193,8 +193,12 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
 
             // P and dS in the accumulator layout (row 8 (e/4) + 4 hf + e%4, column = this lane's key)
             bf16x8 pf[2], dsf[2];  // [16-row step]
-            // (one uniform branch per tile, none per element: see visible_in_range)
+            // (one uniform branch per tile, none per element: a bit for each of the 32 rows that sees this lane's key)
             auto softmax_stage = [&](auto masked) {
+                const int i32 = tq * kBq + 32 * qb;
+                const uint32_t rows = !decltype(masked)::value ? 0u
+                                      : (keys_below(N - i32) & ~keys_below(key - i32) &
+                                         (keys_below(key < S ? 32 : key + W - i32) | ~keys_below(P - i32))) >> (4 * hf);
 #pragma unroll
                 for (int e4 = 0; e4 < 4; ++e4) {
                     const int r4 = 32 * qb + 8 * e4 + 4 * hf;
@@ -206,9 +210,9 @@ __global__ __launch_bounds__(dkv128short::kThreads, 1) void swaa_bwd_dkv_dma_sho
 #pragma unroll
                     for (int x = 0; x < 4; ++x) {
                         const int e = 4 * e4 + x;
-                        const int row = tq * kBq + r4 + x;
                         float pe = __builtin_amdgcn_exp2f(fmaf(sacc[e], c2, -lv[x]));
-                        if (decltype(masked)::value) pe = visible_in_range(row, key, N, W, S, P) ? pe : 0.f;
+                        if (decltype(masked)::value)
+                            pe = __uint_as_float((uint32_t)((int)(rows << (31 - (8 * e4 + x))) >> 31) & __float_as_uint(pe));
                         pf[e / 8][e % 8] = (__bf16)pe;
                         dsf[e / 8][e % 8] = (__bf16)(pe * (dpacc[e] - dv4[x]));
                     }

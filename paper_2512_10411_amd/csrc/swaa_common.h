@@ -390,6 +390,23 @@ __device__ __forceinline__ int window_bound(int p0, int rows, int W, int P) {
     return p0 >= P ? -(1 << 30) : min(p0 + rows - 1, P - 1) - W;
 }
 
+// The mask of 32 keys k0 .. k0 + 31 for a row at position qpos, as bits: bit j says whether it sees key k0 + j.
+// Three comparisons, two logical operations and a selection per score were 120 to 170 instructions for a half, and their
+// results, a pair of scalar registers each, spilled; from the word it is two per score (54 in all; us: four prompts of 643
+// tokens 16.2 -> 14.6, seven packed ones of 0.1-7k on a window of 1024 73.1 -> 67.7, four of 8192 on 1024 681 -> 672).
+__host__ __device__ __forceinline__ uint32_t keys_below(int n) {  // the first n keys (none below 0, all from 32 on)
+    return n >= 32 ? ~0u : (1u << ((n > 0 ? n : 0) & 31)) - 1u;
+}
+__host__ __device__ __forceinline__ uint32_t visible_keys(int k0, int qpos, int W, int S) {
+    return keys_below(qpos + 1 - k0) & (~keys_below(qpos + 1 - W - k0) | keys_below(S - k0));
+}
+// A lane's 16 scores of a 32 x 32 product belong to keys 8 (e / 4) + 4 hf + e % 4: x where element e's bit is set in
+// bits = visible_keys(...) >> 4 hf, -infinity where it is not.
+__device__ __forceinline__ float where_visible(uint32_t bits, int e, float x) {
+    const uint32_t all = (uint32_t)((int)(bits << (31 - (8 * (e / 4) + e % 4))) >> 31);
+    return __uint_as_float((all & __float_as_uint(x)) | (~all & 0xff800000u));
+}
+
 // Is x infinite or not a number?  On the bits, and behind the optimiser's back: the build does not honour NaNs
 // (-fno-honor-nans), and a comparison, or a test of the bits that the compiler recognises, would be folded.
 __device__ __forceinline__ uint32_t opaque_bits(float x) {

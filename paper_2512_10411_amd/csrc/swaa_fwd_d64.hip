@@ -202,12 +202,9 @@ __global__ __launch_bounds__(kThreads, 4) void swaa_fwd_d64_kernel(const FwdPara
 
             // ---- scores that must not be seen become -inf (edge halves only) ----
             if (!((k_last <= p0) && ((k0 > wbound) || (k_last < S)))) {
+                const uint32_t bits = visible_keys(k0, qpos, W, S) >> (4 * hf);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int key = k0 + 8 * (e / 4) + 4 * hf + (e % 4);
-                    const bool vis = (key <= qpos) & ((key > qpos - W) | (key < S));
-                    s[e] = vis ? s[e] : -INFINITY;
-                }
+                for (int e = 0; e < 16; ++e) s[e] = where_visible(bits, e, s[e]);
             }
 
             // ---- does a score exceed its row's reference by more than the slack? ----

@@ -125,12 +125,9 @@ __device__ __forceinline__ void softmax_chunk(int c, const f32x16 &s, float c2, 
 // Scores of keys a lane's query row must not see become -inf (a select: the old
 // value, whatever it is, is dropped).  k0h: first key of the half.
 __device__ __forceinline__ void mask_scores(f32x16 &s, int k0h, int qpos, int W, int S, int hf) {
+    const uint32_t bits = visible_keys(k0h, qpos, W, S) >> (4 * hf);
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int key = k0h + 8 * (e / 4) + 4 * hf + (e % 4);
-        const bool vis = (key <= qpos) && ((key > qpos - W) || (key < S));
-        s[e] = vis ? s[e] : -INFINITY;
-    }
+    for (int e = 0; e < 16; ++e) s[e] = where_visible(bits, e, s[e]);
 }
 
 // ---- the divisor of O: column sums of the rounded P^T, on the matrix pipe -------------

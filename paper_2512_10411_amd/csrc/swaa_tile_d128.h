@@ -103,12 +103,9 @@ __device__ __forceinline__ void pin_p(bf16x8 &pf) { asm volatile("" : "+v"(pf));
 __device__ __forceinline__ void qk_chain_start(f32x16 &s, const bf16x8 kfrag, const bf16x8 q_acc, bool masked, int k0h,
                                                int qpos, int W, int S, int hf) {
     if (__builtin_expect(masked, 0)) {
+        const uint32_t bits = visible_keys(k0h, qpos, W, S) >> (4 * hf);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int key = k0h + 8 * (e / 4) + 4 * hf + (e % 4);
-            const bool vis = (key <= qpos) && ((key > qpos - W) || (key < S));
-            s[e] = vis ? 0.f : -INFINITY;
-        }
+        for (int e = 0; e < 16; ++e) s[e] = where_visible(bits, e, 0.f);
         asm volatile("s_nop 1" : "+v"(s));  // two wait states between these writes and the MFMA
         mfma_s(s, kfrag, q_acc);
     } else {
@@ -223,12 +220,9 @@ template <bool kMask, bool kF16 = false, int kBelow = 0>
 __device__ __forceinline__ void softmax_half(f32x16 &s, int k0h, int qpos, int W, int S, int hf, float c2, RowState &st,
                                              bf16x8 (&pf)[2], float &alpha) {
     if (kMask) {
+        const uint32_t bits = visible_keys(k0h, qpos, W, S) >> (4 * hf);
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const int key = k0h + 8 * (e / 4) + 4 * hf + (e % 4);
-            const bool vis = (key <= qpos) && ((key > qpos - W) || (key < S));
-            s[e] = vis ? s[e] : -INFINITY;
-        }
+        for (int e = 0; e < 16; ++e) s[e] = where_visible(bits, e, s[e]);
     }
     float mx = s[0];
 #pragma unroll
