@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 
 namespace swaa {
@@ -46,9 +47,10 @@ __host__ __device__ __forceinline__ unsigned fastdiv(unsigned n, const FastDiv f
 
 // First statement of a kernel of short calls: brings its argument block (a struct Args, the kernel's first argument) into the
 // scalar cache in one round trip.  The compiler loads arguments where they are first used, a line of 64 bytes at a time, and a
-// line that the caches have lost since the last launch is 350 ns away: three to five such waits stood in front of the decode
-// kernel's first request to memory (one new token on a window of 8192 12.9 -> 12.3 us; where a call reads less of a long
-// cache there is nothing to gain, nor in kernels of whole prompts).  Workgroups behind the first round find the lines there.
+// line that no cache holds (a launch has a block of its own; a captured one is replayed from the same) is 350 ns away:
+// three to five such waits stood in front of the first request to memory.  us a call: one new token on a window of 8192
+// 12.9 -> 12.3; short prompts of 300 tokens 8.55 -> 8.35; 84 tokens, D = 64, 6.0 -> 5.4.  Kernels of longer calls gain nothing
+// (the pipelined forward loses 0.4 % on packed prompts).  Workgroups behind the first round find the lines there.
 template <typename Args>
 __device__ __forceinline__ void fetch_args() {
     static_assert(sizeof(Args) % 4 == 0, "");
@@ -424,6 +426,20 @@ __device__ __forceinline__ float half_swap_max(float x) {
 __device__ __forceinline__ float half_swap_sum(float x) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// More than 64 KiB of LDS per workgroup has to be requested once per device.
+template <auto kernel, int kBytes>
+hipError_t allow_lds() {
+    static std::atomic<unsigned long long> configured{0};
+    int dev = 0;
+    hipError_t err = hipGetDevice(&dev);
+    if (err != hipSuccess) return err;
+    const unsigned long long bit = 1ull << (dev & 63);
+    if (configured.load(std::memory_order_acquire) & bit) return hipSuccess;
+    err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
+    if (err == hipSuccess) configured.fetch_or(bit, std::memory_order_release);
+    return err;
 }
 
 // Launchers (one per kernel family); return the HIP error of the launch.

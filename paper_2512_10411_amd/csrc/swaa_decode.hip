@@ -863,19 +863,9 @@ hipError_t launch_decode(const DecodeParams &p, hipStream_t stream) {
     hipError_t err = hipSuccess;
     auto launch = [&](auto f16, auto pg, auto tiles) {
         constexpr int kT = decltype(tiles)::value;
-        auto kernel = swaa_decode_split_kernel<decltype(f16)::value, decltype(pg)::value, kT>;
-        // more than 64 KiB of LDS per workgroup has to be requested once per device
-        static std::atomic<unsigned long long> configured{0};
-        int dev = 0;
-        err = hipGetDevice(&dev);
+        constexpr auto kernel = swaa_decode_split_kernel<decltype(f16)::value, decltype(pg)::value, kT>;
+        err = allow_lds<kernel, decode_smem_bytes(kT)>();
         if (err != hipSuccess) return;
-        const unsigned long long bit = 1ull << (dev & 63);
-        if (!(configured.load(std::memory_order_acquire) & bit)) {
-            err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      decode_smem_bytes(kT));
-            if (err != hipSuccess) return;
-            configured.fetch_or(bit, std::memory_order_release);
-        }
         hipLaunchKernelGGL(kernel, grid, dim3(kDThreads), decode_smem_bytes(kT), stream, p);
     };
     auto pick_tiles = [&](auto f16, auto pg) {

@@ -69,6 +69,7 @@ __device__ __forceinline__ s16x4 lds8_tr(uint32_t addr) {
 
 template <bool kF16>
 __global__ __launch_bounds__(kThreads, 4) void swaa_fwd_d64_kernel(const FwdParams p) {
+    fetch_args<FwdParams>();
     WorkItem wi;
     if (!decode_work(p, wi)) return;
     SeqGeom sg;

@@ -37,7 +37,6 @@
 //
 // This kernel declares no static LDS: its dynamic LDS starts at address 0 and
 // all LDS accesses below use plain byte addresses.
-#include <atomic>
 #include <type_traits>
 
 #include "swaa_fwd_few_rows.h"
@@ -982,21 +981,11 @@ hipError_t launch_fwd_pipelined_d128(const FwdParams &p, hipStream_t stream) {
     const bool paged = p.block_table != nullptr;
     hipError_t err = hipSuccess;
     auto launch = [&](auto f16, auto pg, auto split) {
-        auto kernel = swaa_fwd_pipelined_kernel<decltype(f16)::value, decltype(pg)::value, decltype(split)::value>;
+        constexpr auto kernel = swaa_fwd_pipelined_kernel<decltype(f16)::value, decltype(pg)::value, decltype(split)::value>;
         constexpr int kBytes = decltype(split)::value ? kSplitSmemBytes : kSmemBytes;
         static_assert(kSmemBytes <= 64 * 1024, "what a kernel gets without asking");
-        if constexpr (kBytes > 64 * 1024) {  // (requested once per device)
-            static std::atomic<unsigned long long> configured{0};
-            int dev = 0;
-            err = hipGetDevice(&dev);
-            if (err != hipSuccess) return;
-            const unsigned long long bit = 1ull << (dev & 63);
-            if (!(configured.load(std::memory_order_acquire) & bit)) {
-                err = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kBytes);
-                if (err != hipSuccess) return;
-                configured.fetch_or(bit, std::memory_order_release);
-            }
-        }
+        if constexpr (kBytes > 64 * 1024) err = allow_lds<kernel, kBytes>();
+        if (err != hipSuccess) return;
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(kPThreads), kBytes, stream, p);
     };
     auto pick_split = [&](auto f16, auto pg) {
