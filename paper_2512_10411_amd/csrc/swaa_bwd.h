@@ -61,6 +61,7 @@ struct BwdParams {
     float *partial;  // workspace, after delta
     // divisions the dK/dV workgroups make, as multiplications
     FastDiv div_kt, div_pairs, div_hkv, div_split, div_seg, div_sink_kt;
+    FastDiv div_group;  // (and the dQ workgroups of short sequences)
 };
 
 // Fills die_shift, n_sink_kt, n_seg, seg_tiles, n_split and the reciprocals from the shape and mask fields.  pieces: key tiles may be cut into
@@ -70,7 +71,7 @@ void plan_bwd(BwdParams &p, int D, bool pieces);
 long long bwd_workspace_floats(const BwdParams &p, int D);
 
 hipError_t launch_bwd(const BwdParams &p, int D, hipStream_t stream);
-// dQ and delta, head dimension 128, software-pipelined (swaa_bwd_dq_pipelined.hip)
+// dQ and delta, head dimension 128 (swaa_bwd_dq_pipelined.hip)
 hipError_t launch_bwd_dq_pipelined_d128(const BwdParams &p, hipStream_t stream);
 
 }  // namespace swaa

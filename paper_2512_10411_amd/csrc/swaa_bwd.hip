@@ -524,6 +524,7 @@ void plan_bwd(BwdParams &p, int D, bool pieces) {
     p.div_kt = make_fastdiv((unsigned)((p.N + 127) / 128));
     p.div_pairs = make_fastdiv((unsigned)(p.B * p.Hkv));
     p.div_hkv = make_fastdiv((unsigned)p.Hkv);
+    p.div_group = make_fastdiv((unsigned)(p.Hq / p.Hkv));
     p.div_split = make_fastdiv((unsigned)p.n_split);
     p.div_seg = make_fastdiv((unsigned)p.n_seg);
     p.div_sink_kt = make_fastdiv((unsigned)p.n_sink_kt);

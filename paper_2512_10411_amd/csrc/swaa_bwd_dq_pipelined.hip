@@ -42,7 +42,7 @@ constexpr int kQVRing = kQStages * kQTileBytes;        // V ring follows the K r
 constexpr int kQSmemBytes = 2 * kQStages * kQTileBytes;  // 96 KiB
 constexpr int kQAhead = 3;                             // MFMAs between an LDS fragment read and its use
 
-// Per-lane byte offsets of the fragments inside one tile (swizzle folded in); a uniform
+// Per-lane byte offsets of the fragments inside one tile (swizzle folded in, `base` added); a uniform
 // offset (buffer, half, 16-key step) is added through the instruction's offset field.
 struct DqLane {
     uint32_t row[kKS];     // row fragment, k-step ks: row lane%32, logical chunk 2 ks + lane/32
@@ -50,13 +50,13 @@ struct DqLane {
     uint32_t col_hi[kDB];  // ... and the rows 8 further
 };
 
-__device__ __forceinline__ DqLane make_dq_lane(int lane) {
+__device__ __forceinline__ DqLane make_dq_lane(int lane, uint32_t base = 0u) {
     DqLane la;
     const int l32 = lane & 31, hf = lane >> 5;
     const int gl = ((l32 & 3) << 2) | ((l32 >> 2) & 3);
     const uint32_t row_lane = (uint32_t)(l32 * kRowBytes + ((hf ^ gl) << 4));
 #pragma unroll
-    for (int ks = 0; ks < kKS; ++ks) la.row[ks] = row_lane ^ (uint32_t)(ks << 5);
+    for (int ks = 0; ks < kKS; ++ks) la.row[ks] = base + (row_lane ^ (uint32_t)(ks << 5));
     const int grp = lane >> 4, j16 = lane & 15;
     const int rr = 4 * hf + (j16 >> 2);
     const int cl = 2 * (grp & 1) + ((j16 & 3) >> 1);
@@ -64,8 +64,8 @@ __device__ __forceinline__ DqLane make_dq_lane(int lane) {
     const uint32_t hi = (uint32_t)((rr + 8) * kRowBytes + ((((rr & 3) << 2) | (cl ^ (hf + 2))) << 4) + 8 * (j16 & 1));
 #pragma unroll
     for (int db = 0; db < kDB; ++db) {
-        la.col_lo[db] = lo ^ (uint32_t)(db << 6);
-        la.col_hi[db] = hi ^ (uint32_t)(db << 6);
+        la.col_lo[db] = base + (lo ^ (uint32_t)(db << 6));
+        la.col_hi[db] = base + (hi ^ (uint32_t)(db << 6));
     }
     // opaque: the compiler must add the buffers' constant offsets through the instructions'
     // offset fields, not precompute an address register per buffer and fragment
@@ -330,9 +330,225 @@ __global__ __launch_bounds__(kQThreads, 2) void swaa_bwd_dq_pipelined_kernel(con
         }
 }
 
+// ---- short sequences ----
+// A workgroup of the kernel above is 256 rows that walk the same keys together: 500 tokens on 32 heads are 64 of them, a
+// quarter of the compute units, and the longest walks sixteen halves one behind the other: the chain is the bound.
+// Here a workgroup is 32 rows of ONE head and its four waves take a quarter of the keys each (as the forward of
+// short prompts, swaa_fwd_short.hip: a ring of one half of their own, no barriers in the loop, max. two workgroups to a
+// compute unit), and their sums meet in LDS.  V of the next half is asked for as soon as this one's fragments are in
+// registers, K behind its transposed ones, which take the registers of the fragments that the products have used.
+constexpr int kQsWaves = 4, kQsThreads = 64 * kQsWaves;
+constexpr uint32_t kQsRing = 2 * kHalfBytes;  // a wave's: K half, then V half
+constexpr int kQsBytes = kQsWaves * (int)kQsRing;
+static_assert(kQsBytes <= 64 * 1024, "what a kernel gets without asking");
+
+__global__ __launch_bounds__(kQsThreads, 2) void swaa_bwd_dq_short_kernel(const BwdParams p) {
+    const int N = p.N, S = p.f.S, P = p.f.P;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int l32 = lane & 31, hf = lane >> 5;
+    // Long rows first; the (batch, KV head) pair innermost.
+    const unsigned pairs = (unsigned)(p.B * p.Hkv);
+    const unsigned by_pair = fastdiv(blockIdx.x, p.div_pairs), pair = blockIdx.x - by_pair * pairs;
+    const unsigned by_group = fastdiv(by_pair, p.div_group), g = by_pair - by_group * (unsigned)p.f.G;
+    const int b = (int)fastdiv(pair, p.div_hkv), kvh = (int)pair - b * p.Hkv;
+    const int head = kvh * p.f.G + (int)g;
+    const int r0 = kQRows * ((N + kQRows - 1) / kQRows - 1 - (int)by_group);  // first query row
+    const int p1 = min(r0 + kQRows, N) - 1;  // last row
+    const int row = min(r0 + l32, N - 1);             // this lane's column
+    const int W = row >= P ? N : p.f.W;
+
+    // ---- the schedule, in halves of 32 keys: sinks, then the band; a quarter of them is this wave's ----
+    const int band_lo = p1 >= P ? 0 : max(0, r0 - p.f.W + 1);
+    const int hb_lo = band_lo >> 5, hb_hi = p1 >> 5;
+    const int n_sink = min((min(S, band_lo) + 31) >> 5, hb_lo);
+    const int n_all = n_sink + (hb_hi - hb_lo + 1);
+    const int quarter = (n_all + kQsWaves - 1) / kQsWaves;
+    const int h_mine = wave * quarter;
+    const int n_mine = max(0, min(quarter, n_all - h_mine));
+    auto first_key = [&](int t) __attribute__((always_inline)) {
+        const int h = h_mine + t;
+        return 32 * (h < n_sink ? h : h - n_sink + hb_lo);
+    };
+
+    const size_t kv_base = ((size_t)b * p.Hkv + kvh) * (size_t)N * kD;
+    const char *kg = reinterpret_cast<const char *>(p.f.k + kv_base), *vg = reinterpret_cast<const char *>(p.f.v + kv_base);
+    const size_t q_base = ((size_t)b * p.Hq + head) * (size_t)N * kD;
+    const size_t r_base = ((size_t)b * p.Hq + head) * (size_t)N;
+
+    // ---- HBM -> LDS copies of one half: instruction i moves rows 4 i .. 4 i + 3 (256 bytes each, so that the instruction's
+    // offset field, 1024 i, moves the LDS address and the global address alike).  Rows past the end repeat the last one. ----
+    const int lrow = lane >> 4, lchk = lane & 15;
+    const uint32_t ring = (uint32_t)wave * kQsRing;
+    uint32_t lane_off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) lane_off[i] = (uint32_t)(lrow * kRowBytes + ((lchk ^ ((lrow << 2) | i)) << 4));  // g(r) of row 4 i + lrow
+    auto issue = [&](const char *g0, uint32_t lds, int k0) __attribute__((always_inline)) {
+        const char *base = g0 + (size_t)k0 * kRowBytes;
+        if (__builtin_expect(k0 + 32 > N, 0)) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint32_t off = lane_off[i & 3] + (uint32_t)(1024 * i) - (uint32_t)(max(k0 + 4 * i + lrow - (N - 1), 0) * kRowBytes);
+                HalfCopy::row4(lds + (uint32_t)(1024 * i), off, base);
+            }
+            return;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            asm volatile(
+                "s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+                "global_load_lds_dwordx4 %0, %4\n\t"
+                "global_load_lds_dwordx4 %1, %4 offset:1024\n\t"
+                "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
+                "global_load_lds_dwordx4 %3, %4 offset:3072" ::"v"(lane_off[0]),
+                "v"(lane_off[1]), "v"(lane_off[2]), "v"(lane_off[3]), "s"(base + 4096 * h), "s"(lds + (uint32_t)(4096 * h))
+                : "memory");
+    };
+    if (n_mine > 0) {
+        issue(kg, ring, first_key(0));
+        issue(vg, ring + (uint32_t)kHalfBytes, first_key(0));
+    }
+
+    // ---- this wave's Q and dO rows (B operands), parked in AccVGPRs; its rows' lse (log2 units) and delta ----
+    bf16x8 qf[kKS], dof[kKS];
+    float lse2, dl;
+    {
+        const __bf16 *qs = p.f.q + q_base + (size_t)row * kD + 8 * hf;
+        const __bf16 *ds = p.dout + q_base + (size_t)row * kD + 8 * hf;
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {
+            qf[ks] = *reinterpret_cast<const bf16x8 *>(qs + 16 * ks);
+            dof[ks] = *reinterpret_cast<const bf16x8 *>(ds + 16 * ks);
+        }
+        lse2 = p.f.lse[r_base + row] * 1.44269504088896340736f;
+        dl = row_delta<kKS>(p.out + q_base + (size_t)row * kD + 8 * hf, dof);
+        if (wave == 0 && r0 + l32 < N && hf == 0) p.delta[r_base + row] = dl;  // for the dK/dV kernel
+    }
+    asm volatile("s_nop 1"
+                 : "+a"(qf[0]), "+a"(qf[1]), "+a"(qf[2]), "+a"(qf[3]), "+a"(qf[4]), "+a"(qf[5]), "+a"(qf[6]), "+a"(qf[7]));
+    asm volatile("s_nop 1"
+                 : "+a"(dof[0]), "+a"(dof[1]), "+a"(dof[2]), "+a"(dof[3]), "+a"(dof[4]), "+a"(dof[5]), "+a"(dof[6]),
+                   "+a"(dof[7]));
+    f32x16 dq[kDB];
+#pragma unroll
+    for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dq[db][e] = 0.f;
+    pin_acc(dq);
+
+    const DqLane la = make_dq_lane(lane, ring);
+    const float c2 = p.f.scale_log2;
+    const int wbound = window_bound(r0, kQRows, p.f.W, P);
+    const DqHalves h = {0u, (uint32_t)kHalfBytes, 0u};
+
+    for (int t = 0; t < n_mine; ++t) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // half t has landed
+        const int k0 = first_key(t);
+        bf16x8 kf[kKS], vf[kKS], ct[2 * kDB];
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {
+            kf[ks] = load_a_slot(la, h, 2 * ks);
+            vf[ks] = load_a_slot(la, h, 2 * ks + 1);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (t + 1 < n_mine) issue(vg, ring + (uint32_t)kHalfBytes, first_key(t + 1));
+        f32x16 s, dp;
+        mfma_s_first(s, kf[0], qf[0]);
+        mfma_s_first(dp, vf[0], dof[0]);
+#pragma unroll
+        for (int ks = 1; ks < kKS - 1; ++ks) {
+            mfma_s(s, kf[ks], qf[ks]);
+            mfma_s(dp, vf[ks], dof[ks]);
+        }
+#pragma unroll
+        for (int c = 0; c < 2 * kDB; ++c) ct[c] = load_c_slot(la, h, c);
+        // the last of both chains, in one statement: the vector ALU reads both next
+        asm volatile("v_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\tv_mfma_f32_32x32x16_bf16 %1, %4, %5, %1\n\ts_nop 15\n\ts_nop 7"
+                     : "+v"(s), "+v"(dp)
+                     : "v"(kf[kKS - 1]), "a"(qf[kKS - 1]), "v"(vf[kKS - 1]), "a"(dof[kKS - 1]));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (t + 1 < n_mine) issue(kg, ring, first_key(t + 1));
+
+        if (!((k0 + 31 <= r0) && ((k0 > wbound) || (k0 + 31 < S)))) {
+            const uint32_t bits = visible_keys(k0, row, W, S) >> (4 * hf);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) s[e] = where_visible(bits, e, s[e]);
+        }
+        bf16x8 dsf[2];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float pe = __builtin_amdgcn_exp2f(fmaf(s[e], c2, -lse2));
+            dsf[e / 8][e % 8] = (__bf16)(pe * (dp[e] - dl));
+        }
+        asm volatile("s_nop 1" : "+v"(dsf[0]), "+v"(dsf[1]));  // (two wait states in front of the MFMAs)
+#pragma unroll
+        for (int c = 0; c < 2 * kDB; ++c) {
+            if (c < 2 * kDB - 1)
+                mfma_acc(dq[c % kDB], ct[c], dsf[c / kDB]);
+            else
+                mfma_acc_settled(dq[c % kDB], ct[c], dsf[c / kDB]);
+        }
+    }
+
+    // ---- the four waves' sums through LDS (16-byte chunk q of row c at q ^ c of its 512 bytes); 32 threads take a row ----
+    {
+        const uint32_t at = ring + (uint32_t)(l32 * 512 + ((hf ^ l32) << 4));
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+            f32x4_t o4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o4[e] = dq[c / 4][4 * (c % 4) + e];
+            *(LdsQuads)(uintptr_t)(at ^ (uint32_t)(c << 5)) = o4;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kQRows / 8; ++i) {
+        const int c = 8 * i + (int)(threadIdx.x >> 5), q = (int)(threadIdx.x & 31);
+        if (r0 + c >= N) break;
+        const uint32_t at = (uint32_t)(c * 512 + ((q ^ c) << 4));
+        f32x4_t o4 = *(LdsQuads)(uintptr_t)at;
+#pragma unroll
+        for (int x = 1; x < kQsWaves; ++x) o4 += *(LdsQuads)(uintptr_t)(at + (uint32_t)x * kQsRing);
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (__bf16)(o4[e] * p.f.scale);
+        *reinterpret_cast<bf16x4 *>(p.dq + q_base + (size_t)(r0 + c) * kD + 4 * q) = o;
+    }
+}
+
 }  // namespace
 
+// Which of the two?  The whole backward, rows together / a head's 32 rows (us; full attention unless a window is stated):
+//    units (of 32 rows)      512           768           1024          1280          1536          2048
+//    32 heads on 8       68.8 / 54.8   85.7 / 73.9    107 / 92.9    127 / 118     156 / 147     210 / 209
+//      window 1024                                                  129 / 121     141 / 139     180 / 191
+//    8 heads on 8         137 / 89.1    207 / 152     288 / 227     365 / 306     444 / 388     651 / 612   (3072: 1298 / 1330)
+//      window 1024        111 / 78.0    128 / 104     138 / 124     169 / 163     178 / 178     229 / 236
+//    40 heads on 8       65.5 / 57.4   77.8 / 69.9   95.2 / 88.2                  142 / 139     192 / 197
+//    8 x 32 on 8, 128 tokens                         48.4 / 50.0   (4 x, 512 units: 48.0 / 41.4; 4 x, 256 tokens, 1024: 58.8 / 57.2)
+//    3 x 32 on 8, 500 tokens                                                     81.4 / 85.1
+// One round of workgroups and two gain, unless the sequences are short and many.  Beyond, the chip is full either way, and
+// rows that walk their keys together read less, but a chain that is nearly twice what every compute unit has to do is still
+// the time, above all generated rows behind a prompt: the longest row's halves against the halves of 256-row workgroups
+// that a compute unit gets on average (a quotient; 512 generated rows):
+//    8 on 8, 10374 tokens, window 2048, 2.8: 818 / 628     16384, 16 on 4, window 1024, 2.6: 1312 / 1177
+//    16 on 4, 8704, window 2048, 1.6: 800 / 774            32 on 8, 3000, window 1024, 1.4: 356 / 364     16384, window 2048, 0.8: 2720 / 2969
+bool dq_short(const BwdParams &p) {
+    const long long heads = (long long)p.B * p.Hq, N = p.N;
+    const long long units = heads * ((N + kQRows - 1) / kQRows);
+    if (units <= 512 || (units <= 1024 && N >= 256)) return true;
+    const long long prompt = p.f.P < N ? p.f.P : N, w = p.f.W < prompt ? p.f.W : prompt;
+    const long long pairs = w * (w + 1) / 2 + (prompt - w) * w + (N * (N + 1) - prompt * (prompt + 1)) / 2;
+    const long long longest = (prompt < N ? N : w) / 32;  // halves
+    return longest >= 72 && (double)longest * (256.0 * 256 * 32) >= 1.85 * (double)pairs * (double)heads;
+}
+
 hipError_t launch_bwd_dq_pipelined_d128(const BwdParams &p, hipStream_t stream) {
+    if (dq_short(p)) {
+        const unsigned units = (unsigned)(p.B * p.Hq * ((p.N + kQRows - 1) / kQRows));
+        hipLaunchKernelGGL(swaa_bwd_dq_short_kernel, dim3(units), dim3(kQsThreads), kQsBytes, stream, p);
+        return hipGetLastError();
+    }
     // more than 64 KiB of LDS per workgroup has to be requested once per device
     static std::atomic<unsigned long long> configured{0};
     int dev = 0;

@@ -370,3 +370,15 @@ def test_no_memory_for_pieces(B, Hkv, G, N, W, S, D, monkeypatch):
     torch.cuda.synchronize()
     monkeypatch.undo()
     assert all(torch.equal(x, y) for x, y in zip(got, want))
+
+
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P", [
+    (16, 2, 8, 130, 50, 3, 100),      # more than a round of 32-row units of short sequences: rows together, edges of 64 and 256 rows
+    (16, 2, 5, 230, 230, 0, None),    # ... groups of four heads and one
+    (20, 1, 3, 601, 65, 70, 333),     # ... of two and one, sinks next to the band, generated rows
+    (4, 2, 4, 1000, 300, 4, None),    # 1024 units: a head's 32 rows
+    (1, 4, 4, 2500, 300, 4, 2400),    # 1264, few generated rows are the time: a head's 32 rows, quarters that differ
+    (1, 4, 4, 2500, 300, 4, None),    # ... none: rows together
+])
+def test_both_dq_kernels_of_head_dimension_128(B, Hkv, G, N, W, S, P):
+    check(B, Hkv * G, Hkv, N, 128, W, S, P, seed=9900 + N + G)
