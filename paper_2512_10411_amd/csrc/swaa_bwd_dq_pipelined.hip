@@ -537,10 +537,8 @@ bool dq_short(const BwdParams &p) {
     const long long heads = (long long)p.B * p.Hq, N = p.N;
     const long long units = heads * ((N + kQRows - 1) / kQRows);
     if (units <= 512 || (units <= 1024 && N >= 256)) return true;
-    const long long prompt = p.f.P < N ? p.f.P : N, w = p.f.W < prompt ? p.f.W : prompt;
-    const long long pairs = w * (w + 1) / 2 + (prompt - w) * w + (N * (N + 1) - prompt * (prompt + 1)) / 2;
-    const long long longest = (prompt < N ? N : w) / 32;  // halves
-    return longest >= 72 && (double)longest * (256.0 * 256 * 32) >= 1.85 * (double)pairs * (double)heads;
+    const long long longest = longest_row(p.f) / 32;  // halves
+    return longest >= 72 && (double)longest * (256.0 * 256 * 32) >= 1.85 * pairs_of_rows(p.f, p.f.P < N ? p.f.P : N) * (double)heads;
 }
 
 hipError_t launch_bwd_dq_pipelined_d128(const BwdParams &p, hipStream_t stream) {

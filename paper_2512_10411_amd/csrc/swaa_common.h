@@ -368,6 +368,13 @@ inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     return p.chunk * kXcds <= 0x7fffffffLL;
 }
 
+// Keys that the longest row of a whole prompt sees (sinks beside its window left out), and the pairs of all rows of a head.
+inline long long longest_row(const FwdParams &p) { return p.P < p.Nk ? p.Nk : p.W; }
+inline double pairs_of_rows(const FwdParams &p, long long prompt) {
+    const double n = (double)prompt, w = (double)(p.W < prompt ? p.W : prompt), all = (double)p.Nk;
+    return w * (w + 1) / 2 + (n - w) * w + (all * (all + 1) - n * (n + 1)) / 2;
+}
+
 // The plan of a packed batch of B sequences with total_rows query rows in all (each at most
 // `rows` long): the compact work list of decode_work_packed, bounded from above -- a sequence
 // adds at most one partly filled tile per head group to total_rows / tile rows, and at most one

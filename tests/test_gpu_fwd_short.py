@@ -106,3 +106,17 @@ def test_packed_prompts_on_the_pipelined_kernel(factor):
     torch.cuda.synchronize()
     ro, rl = swaa_attn_oracle(q, k, v, W, S, 1 / math.sqrt(128))
     assert_parity(out[None], lse[None], ro, rl, tag=f"packed, factor {factor}")
+
+
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P", [
+    (1, 2, 1, 5003, 300, 4, 4800),    # longer than the kernel's own prompts, few generated rows: their chain is the call
+    (9, 2, 1, 2500, 100, 70, 2490),   # more than a round of units, sinks, a tile with both kinds of rows
+    (1, 1, 4, 6000, 300, 4, 5990),    # four heads to a row tile
+])
+def test_long_rows_among_short_ones(B, Hkv, G, N, W, S, P):
+    q, k, v = make_qkv(B, Hkv * G, Hkv, N, 128, seed=97900 + N)
+    print(f"[case] long rows B{B} Hkv{Hkv} G{G} N{N} W{W} S{S} P{P}", flush=True)
+    qd, kd, vd = to_device(q), to_device(k), to_device(v)
+    out, lse = binding.swaa_attn_fwd_fa_decode(qd, kd, vd, W, S, P)
+    ro, rl = swaa_decode_oracle(q, k, v, W, S, 1 / math.sqrt(128), n_prompt=P)
+    assert_parity(out, lse, ro, rl, tag=f"long rows of {N}")
