@@ -233,6 +233,189 @@ __global__ __launch_bounds__(dq64::kThreads, 4) void swaa_bwd_dq_kernel(const Bw
         }
 }
 
+// Short sequences: 32 rows of ONE head per workgroup, whose four waves take a quarter of the keys each with a ring of one half
+// of their own and no barriers in the loop (as swaa_bwd_dq_short_kernel of head dimension 128); their sums meet in LDS.
+namespace dq64s {
+constexpr int kWaves = 4, kThreads = 64 * kWaves, kRows = 32;
+constexpr uint32_t kRing = 2 * dq64::kHalfB;  // a wave's: K half, then V half; its dQ at the end
+constexpr int kBytes = kWaves * (int)kRing;
+static_assert(kRows * dq64::kD * 4 == kRing, "");
+}  // namespace dq64s
+
+__global__ __launch_bounds__(dq64s::kThreads, 3) void swaa_bwd_dq64_short_kernel(const BwdParams p) {
+    using dq64::kD, dq64::kKS, dq64::kDB, dq64::kRowB, dq64::kHalfB;
+    using dq64s::kWaves, dq64s::kRows, dq64s::kRing;
+    const int N = p.N, S = p.f.S, P = p.f.P;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, l32 = lane & 31, hf = lane >> 5;
+    // Long rows first; the (batch, KV head) pair innermost.
+    const unsigned by_pair = fastdiv(blockIdx.x, p.div_pairs), pair = blockIdx.x - by_pair * (unsigned)(p.B * p.Hkv);
+    const unsigned by_group = fastdiv(by_pair, p.div_group), g = by_pair - by_group * (unsigned)p.f.G;
+    const int b = (int)fastdiv(pair, p.div_hkv), kvh = (int)pair - b * p.Hkv;
+    const int head = kvh * p.f.G + (int)g;
+    const int r0 = kRows * ((N + kRows - 1) / kRows - 1 - (int)by_group);  // first query row
+    const int p1 = min(r0 + kRows, N) - 1;  // last row
+    const int row = min(r0 + l32, N - 1);   // this lane's column
+    const int W = row >= P ? N : p.f.W;
+
+    // the schedule, in halves of 32 keys: sinks, then the band; a quarter of them is this wave's
+    const int band_lo = p1 >= P ? 0 : max(0, r0 - p.f.W + 1);
+    const int hb_lo = band_lo >> 5, hb_hi = p1 >> 5;
+    const int n_sink = min((min(S, band_lo) + 31) >> 5, hb_lo);
+    const int n_all = n_sink + (hb_hi - hb_lo + 1);
+    const int quarter = (n_all + kWaves - 1) / kWaves;
+    const int h_mine = wave * quarter;
+    const int n_mine = max(0, min(quarter, n_all - h_mine));
+    auto first_key = [&](int t) __attribute__((always_inline)) {
+        const int h = h_mine + t;
+        return 32 * (h < n_sink ? h : h - n_sink + hb_lo);
+    };
+
+    // HBM -> LDS copies of one half: instruction i moves rows 8 i .. 8 i + 7.  Rows past the end repeat the last one.
+    const size_t kv_base = ((size_t)b * p.Hkv + kvh) * (size_t)N * kD;
+    const char *kg = reinterpret_cast<const char *>(p.f.k + kv_base), *vg = reinterpret_cast<const char *>(p.f.v + kv_base);
+    const size_t q_base = ((size_t)b * p.Hq + head) * (size_t)N * kD, r_base = ((size_t)b * p.Hq + head) * (size_t)N;
+    const uint32_t ring = (uint32_t)wave * kRing;
+    const int lr = lane >> 3;
+    uint32_t cchk[2];  // (the swizzle of row 8 i + lr depends on i & 1)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) cchk[i] = (uint32_t)((lane & 7) ^ ((((lr >> 1) & 1) << 2) | ((2 * i + (lr >> 2)) & 3))) << 4;
+    auto issue = [&](const char *g0, uint32_t lds, int k0) __attribute__((always_inline)) {
+        const char *base = g0 + (size_t)k0 * kRowB;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t off = (uint32_t)min(8 * i + lr, N - 1 - k0) * kRowB + cchk[i & 1];
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds + (uint32_t)(1024 * i))
+                         : "memory");
+        }
+    };
+    if (n_mine > 0) {
+        issue(kg, ring, first_key(0));
+        issue(vg, ring + kHalfB, first_key(0));
+    }
+    // this wave's Q and dO rows as B operands, its rows' lse (log2 units) and delta
+    bf16x8 qf[kKS], dof[kKS];
+    const __bf16 *qs = p.f.q + q_base + (size_t)row * kD + 8 * hf, *ds = p.dout + q_base + (size_t)row * kD + 8 * hf;
+#pragma unroll
+    for (int ks = 0; ks < kKS; ++ks) {
+        qf[ks] = *reinterpret_cast<const bf16x8 *>(qs + 16 * ks);
+        dof[ks] = *reinterpret_cast<const bf16x8 *>(ds + 16 * ks);
+    }
+    const float lse2 = p.f.lse[r_base + row] * 1.44269504088896340736f;
+    const float dl = row_delta<kKS>(p.out + q_base + (size_t)row * kD + 8 * hf, dof);
+    if (wave == 0 && r0 + l32 < N && hf == 0) p.delta[r_base + row] = dl;  // for the dK/dV kernel
+
+    // per-lane fragment addresses in this wave's ring (as in swaa_bwd_dq_kernel)
+    const uint32_t row_lane = ring + (uint32_t)(l32 * kRowB + ((hf ^ ((((l32 >> 1) & 1) << 2) | ((l32 >> 2) & 3))) << 4));
+    const int grp = lane >> 4, j16 = lane & 15;
+    const int rr = 4 * hf + (j16 >> 2);
+    const int cl = 2 * (grp & 1) + ((j16 & 3) >> 1);
+    const uint32_t col_lo = ring + (uint32_t)(rr * kRowB + ((((j16 >> 3) << 2) | (cl ^ hf)) << 4) + 8 * (j16 & 1));
+    const uint32_t col_hi = ring + (uint32_t)((rr + 8) * kRowB + ((((j16 >> 3) << 2) | (cl ^ (hf + 2))) << 4) + 8 * (j16 & 1));
+
+    f32x16 dqacc[kDB];
+#pragma unroll
+    for (int db = 0; db < kDB; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) dqacc[db][e] = 0.f;
+    const float c2 = p.f.scale_log2;
+    const int wbound = window_bound(r0, kRows, p.f.W, P);
+
+    for (int t = 0; t < n_mine; ++t) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // half t has landed
+        const int k0 = first_key(t);
+        // all fragments to registers, then the next half's copies into the same ring, then the arithmetic
+        bf16x8 kf[kKS], vf[kKS], ct[2][kDB];
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {
+            kf[ks] = lds16(row_lane ^ (uint32_t)(ks << 5));
+            vf[ks] = lds16((row_lane ^ (uint32_t)(ks << 5)) + kHalfB);
+        }
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int db = 0; db < kDB; ++db) {
+                const s16x4 lo = lds8_tr((col_lo ^ (uint32_t)(db << 6)) + (uint32_t)(16 * st * kRowB));
+                const s16x4 hi = lds8_tr((col_hi ^ (uint32_t)(db << 6)) + (uint32_t)(16 * st * kRowB));
+                ct[st][db] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (t + 1 < n_mine) {
+            issue(kg, ring, first_key(t + 1));
+            issue(vg, ring + kHalfB, first_key(t + 1));
+        }
+        f32x16 sacc, dpacc;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            sacc[e] = 0.f;
+            dpacc[e] = 0.f;
+        }
+#pragma unroll
+        for (int ks = 0; ks < kKS; ++ks) {
+            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[ks], sacc, 0, 0, 0);
+            dpacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks], dof[ks], dpacc, 0, 0, 0);
+        }
+        if (!((k0 + 31 <= r0) && ((k0 > wbound) || (k0 + 31 < S)))) {
+            const uint32_t bits = visible_keys(k0, row, W, S) >> (4 * hf);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sacc[e] = where_visible(bits, e, sacc[e]);
+        }
+        bf16x8 dsf[2];  // [16-key step]
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float pe = __builtin_amdgcn_exp2f(fmaf(sacc[e], c2, -lse2));
+            dsf[e / 8][e % 8] = (__bf16)(pe * (dpacc[e] - dl));
+        }
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int db = 0; db < kDB; ++db) dqacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ct[st][db], dsf[st], dqacc[db], 0, 0, 0);
+    }
+
+    // the four waves' sums: rows of 256 bytes, 16-byte chunk q of row c at q ^ (c & 15); 16 threads take a row
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    typedef f32x4 __attribute__((address_space(3))) *Quads;
+    const uint32_t at = ring + (uint32_t)(l32 * 256 + ((hf ^ (l32 & 15)) << 4));
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        f32x4 o4;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o4[e] = dqacc[c / 4][4 * (c % 4) + e];
+        *(Quads)(uintptr_t)(at ^ (uint32_t)(c << 5)) = o4;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int c = 16 * i + (int)(threadIdx.x >> 4), q = (int)(threadIdx.x & 15);
+        if (r0 + c >= N) break;
+        const uint32_t from = (uint32_t)(c * 256 + ((q ^ (c & 15)) << 4));
+        f32x4 o4 = *(Quads)(uintptr_t)from;
+#pragma unroll
+        for (int x = 1; x < kWaves; ++x) o4 += *(Quads)(uintptr_t)(from + (uint32_t)x * kRing);
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (__bf16)(o4[e] * p.f.scale);
+        *reinterpret_cast<bf16x4 *>(p.dq + q_base + (size_t)(r0 + c) * kD + 4 * q) = o;
+    }
+}
+
+// Which of the two?  The whole training step, 256 rows together / a head's 32 rows (us; full attention unless a window is stated):
+//    units (of 32 rows)     512           1024          1536          2048          3072
+//    8 heads on 8       92.7 / 60.3    180 / 131     286 / 226     424 / 369     829 / 798
+//      window 1024      69.5 / 48.4   86.8 / 77.9    110 / 109     136 / 140     194 / 194
+//    16 heads on 4      61.8 / 44.4    104 / 83.4    161 / 135     241 / 213     444 / 432
+//      window 1024                    83.5 / 75.5    107 / 108     122 / 127     187 / 184
+//    40 heads on 8      41.7 / 35.9   64.6 / 58.0   99.5 / 91.8    125 / 120     236 / 211
+//    window 128, 32 heads on 8, 1000 tokens, 1024 units: 47.5 / 47.8
+//    512 generated rows: 8 on 8, 6336, window 1024: 235 / 145   19000: 736 / 434   16 on 4, 8704, window 4096: 717 / 675
+// Beyond 1024 units where the longest row's chain is several times what one of the 512 resident workgroups gets on average
+// (full attention, 3072 units, 2.7; window 1024, 2048 units, 2.1; the last line's 17, 17 and 2.4).
+bool dq64_short(const BwdParams &p) {
+    const long long units = (long long)p.B * p.Hq * ((p.N + dq64s::kRows - 1) / dq64s::kRows);
+    if (units <= 512 || (units <= 1024 && longest_row(p.f) >= 256)) return true;
+    const long long longest = longest_row(p.f) / 32;
+    return longest >= 48 && (double)longest * (512.0 * 256 * 32) >= 2.35 * pairs_of_rows(p.f, p.f.P < p.N ? p.f.P : p.N) * (double)p.B * p.Hq;
+}
+
 // ---- dK, dV --------------------------------------------------------------------------
 // Which key tile's main workgroup is block `bid` (the blocks before n_extra are sink
 // segments)?  Workgroups are dealt to the eight dies round-robin, and each die has its own
@@ -410,6 +593,9 @@ hipError_t launch_bwd_d(const BwdParams &p, hipStream_t stream) {
     const bool first_time = !(configured.load(std::memory_order_acquire) & bit);
     if constexpr (D == 128)
         err = launch_bwd_dq_pipelined_d128(p, stream);  // swaa_bwd_dq_pipelined.hip
+    else if (dq64_short(p))
+        hipLaunchKernelGGL(swaa_bwd_dq64_short_kernel, dim3((unsigned)(p.B * p.Hq * ((p.N + dq64s::kRows - 1) / dq64s::kRows))),
+                           dim3(dq64s::kThreads), dq64s::kBytes, stream, p);
     else
         hipLaunchKernelGGL(swaa_bwd_dq_kernel, dim3((unsigned)(p.f.chunk * kXcds)), dim3(dq64::kThreads), dq64::kBytes, stream, p);
     if (err == hipSuccess) err = hipGetLastError();

@@ -23,7 +23,10 @@
 // | ((r >> 2) & 3), applied on the global side of the copy: 16 consecutive rows reading one logical chunk
 // (K fragments) and 4 consecutive rows reading the same 64 bytes (transposed V fragments) are free of
 // bank conflicts.  This kernel declares no static LDS: its dynamic LDS starts at address 0.
-#include "swaa_common.h"
+#include <type_traits>
+
+#include "swaa_fwd_short.h"
+#include "swaa_tile_d128.h"  // (softmax_half and its row state)
 
 namespace swaa {
 namespace {
@@ -276,10 +279,228 @@ __global__ __launch_bounds__(kThreads, 4) void swaa_fwd_d64_kernel(const FwdPara
             (mc + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
 }
 
+// ---- short prompts ----
+// The kernel above walks a head's 32 rows, or 32 rows of four heads, along their keys in one wave: 765 tokens on 8 heads are 48
+// workgroups, and the longest walks 24 halves one behind the other: the chain is the bound.  As at 128 (swaa_fwd_short.hip), a
+// workgroup here is 32 rows of ONE head and its four waves take a quarter of the keys each, with a ring of one half of their
+// own, no barriers in the loop and a max-based softmax; their results meet in LDS.  (Relative error of O against 64 bits over 12
+// calls: 0.00196 where the kernel above has 0.00205, each wave's reference being its own keys' largest score.)
+constexpr int kS64Waves = 4, kS64Threads = 64 * kS64Waves, kS64Rows = 32;
+constexpr uint32_t kS64Ring = 2 * kHalfB;             // a wave's: K half, then V half; its O at the end
+constexpr uint32_t kS64Ml = kS64Waves * kS64Ring;     // [wave][32] of reference, l, l / sum of the rounded P, 0
+constexpr int kS64Bytes = kS64Waves * ((int)kS64Ring + 512);
+static_assert(kS64Rows * kD64 * 4 == kS64Ring && kS64Bytes <= 64 * 1024, "");
+
+template <bool kF16>
+__global__ __launch_bounds__(kS64Threads, 4) void swaa_fwd_d64_short_kernel(const FwdShortParams sp) {
+    fetch_args<FwdShortParams>();
+    const FwdParams &p = sp.f;
+    constexpr int kBelow = kF16 ? 4 : 0;  // terms keep full precision down to 2^-18 of the reference
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int l32 = lane & 31, hf = lane >> 5;
+    // Long rows first; the (batch, KV head) pair innermost.
+    const unsigned by_pair = fastdiv(blockIdx.x, sp.div_pairs), pair = blockIdx.x - by_pair * (unsigned)sp.pairs;
+    const unsigned by_group = fastdiv(by_pair, sp.div_group), g = by_pair - by_group * (unsigned)p.G;
+    const int b = (int)fastdiv(pair, p.div_hkv), kvh = (int)pair - b * p.Hkv;
+    const int head = kvh * p.G + (int)g;
+    const int r0 = kS64Rows * (sp.tiles - 1 - (int)by_group);  // first query row
+    const int N = p.Nq, S = p.S;  // (whole prompts: as many keys)
+    const int n_prompt = p.n_prompts ? max(p.n_prompts[b], 0) : p.P;
+    const int p1 = min(r0 + kS64Rows, N) - 1;  // last row
+    const int row = min(r0 + l32, N - 1);      // this lane's column
+    const int W = row >= n_prompt ? N : p.W;
+
+    // ---- the schedule, in halves of 32 keys: sinks, then the band; a quarter of them is this wave's ----
+    const int band_lo = p1 >= n_prompt ? 0 : max(0, r0 - p.W + 1);
+    const int hb_lo = band_lo >> 5, hb_hi = p1 >> 5;
+    const int n_sink = min((min(S, band_lo) + 31) >> 5, hb_lo);
+    const int n_all = n_sink + (hb_hi - hb_lo + 1);
+    const int quarter = (n_all + kS64Waves - 1) / kS64Waves;
+    const int h_mine = wave * quarter;
+    const int n_mine = max(0, min(quarter, n_all - h_mine));
+    auto first_key = [&](int t) __attribute__((always_inline)) {
+        const int h = h_mine + t;
+        return 32 * (h < n_sink ? h : h - n_sink + hb_lo);
+    };
+
+    // ---- HBM -> LDS copies of one half: instruction i moves rows 8 i .. 8 i + 7.  Rows past the end repeat the last one. ----
+    const uint32_t k_rsb = (uint32_t)(p.k_sn * 2), v_rsb = (uint32_t)(p.v_sn * 2);
+    const char *kg = reinterpret_cast<const char *>(p.k + b * p.k_sb + kvh * p.k_sh);
+    const char *vg = reinterpret_cast<const char *>(p.v + b * p.v_sb + kvh * p.v_sh);
+    const uint32_t ring = (uint32_t)wave * kS64Ring;
+    const int lr = lane >> 3;
+    uint32_t cchk[2];  // (the swizzle f(r) of row 8 i + lr depends on i & 1)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) cchk[i] = (uint32_t)((lane & 7) ^ ((((lr >> 1) & 1) << 2) | ((2 * i + (lr >> 2)) & 3))) << 4;
+    auto issue = [&](const char *g0, uint32_t rsb, uint32_t lds, int k0) __attribute__((always_inline)) {
+        const char *base = g0 + (size_t)k0 * rsb;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t off = (uint32_t)min(8 * i + lr, N - 1 - k0) * rsb + cchk[i & 1];
+            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "s"(lds + (uint32_t)(1024 * i))
+                         : "memory");
+        }
+    };
+    if (n_mine > 0) {
+        issue(kg, k_rsb, ring, first_key(0));
+        issue(vg, v_rsb, ring + kHalfB, first_key(0));
+    }
+    bf16x8 qf[kKs];
+    {
+        const __bf16 *qrow = p.q + b * p.q_sb + (long long)head * p.q_sh + (long long)row * p.q_sn + 8 * hf;
+#pragma unroll
+        for (int ks = 0; ks < kKs; ++ks) qf[ks] = *reinterpret_cast<const bf16x8 *>(qrow + 16 * ks);
+    }
+
+    // per-lane fragment addresses in this wave's ring (as above)
+    const uint32_t k_lane = ring + (uint32_t)(l32 * kRowB + ((hf ^ ((((l32 >> 1) & 1) << 2) | ((l32 >> 2) & 3))) << 4));
+    const int grp = lane >> 4, j16 = lane & 15;
+    const int rr = 4 * hf + (j16 >> 2);
+    const int cl = 2 * (grp & 1) + ((j16 & 3) >> 1);
+    const uint32_t v_lo = (uint32_t)(rr * kRowB + ((((j16 >> 3) << 2) | (cl ^ hf)) << 4) + 8 * (j16 & 1));
+    const uint32_t v_hi = (uint32_t)((rr + 8) * kRowB + ((((j16 >> 3) << 2) | (cl ^ (hf + 2))) << 4) + 8 * (j16 & 1));
+
+    f32x16 oacc[kDb];
+#pragma unroll
+    for (int db = 0; db < kDb; ++db)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
+    RowState rs;
+    rs.mc = -INFINITY;
+    rs.l = 0.f;
+    rs.lb = 0.f;
+    const float c2 = p.scale_log2;
+    const int wbound = window_bound(r0, kS64Rows, p.W, n_prompt);
+#pragma unroll
+    for (int ks = 0; ks < kKs; ++ks) asm volatile("" : "+v"(qf[ks]));  // (waits for the loads here)
+
+    for (int t = 0; t < n_mine; ++t) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // half t has landed
+        const int k0 = first_key(t);
+        // all fragments to registers, then the next half's copy into the same ring, then the arithmetic
+        bf16x8 kf[kKs], vf[2][kDb];
+#pragma unroll
+        for (int ks = 0; ks < kKs; ++ks) kf[ks] = lds16(k_lane ^ (uint32_t)(ks << 5));
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int db = 0; db < kDb; ++db) {
+                const uint32_t off = ring + (uint32_t)(kHalfB + 16 * st * kRowB);
+                const s16x4 lo = lds8_tr(off + (v_lo ^ (uint32_t)(db << 6)));
+                const s16x4 hi = lds8_tr(off + (v_hi ^ (uint32_t)(db << 6)));
+                vf[st][db] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if (t + 1 < n_mine) {
+            issue(kg, k_rsb, ring, first_key(t + 1));
+            issue(vg, v_rsb, ring + kHalfB, first_key(t + 1));
+        }
+        f32x16 s;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < kKs; ++ks) s = mfma32<kF16>(kf[ks], qf[ks], s);
+        bf16x8 pf[2];
+        float alpha;
+        if (!((k0 + 31 <= r0) && ((k0 > wbound) || (k0 + 31 < S))))
+            softmax_half<true, kF16, kBelow>(s, k0, row, W, S, hf, c2, rs, pf, alpha);
+        else
+            softmax_half<false, kF16, kBelow>(s, k0, row, W, S, hf, c2, rs, pf, alpha);
+        if (__any(alpha != 1.f)) {
+#pragma unroll
+            for (int db = 0; db < kDb; ++db)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+        }
+#pragma unroll
+        for (int st = 0; st < 2; ++st)
+#pragma unroll
+            for (int db = 0; db < kDb; ++db) oacc[db] = mfma32<kF16>(vf[st][db], pf[st], oacc[db]);
+    }
+
+    // ---- the four waves' results through LDS: rows of 256 bytes, 16-byte chunk q of row c at q ^ (c & 15); 16 threads take a row.
+    // A wave's O is the sum over the rounded P: it enters scaled by l / (sum of the rounded P). ----
+    {
+        float l_row, lb_row;
+        row_sums(rs, l_row, lb_row);
+        const f32x4_t weight = {rs.mc, l_row, lb_row > 0.f ? l_row / lb_row : 0.f, 0.f};  // a row that saw no key: O = 0, l = 0
+        if (hf == 0) *(LdsQuads)(uintptr_t)(kS64Ml + (uint32_t)(wave * 512 + l32 * 16)) = weight;
+        const uint32_t at = ring + (uint32_t)(l32 * 256 + ((hf ^ (l32 & 15)) << 4));
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            f32x4_t o4;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o4[e] = oacc[c / 4][4 * (c % 4) + e];
+            *(LdsQuads)(uintptr_t)(at ^ (uint32_t)(c << 5)) = o4;  // head-dimension elements 8 c + 4 hf ..
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int c = 16 * i + (int)(threadIdx.x >> 4), q = (int)(threadIdx.x & 15);
+        if (r0 + c >= N) break;
+        f32x4_t w[kS64Waves], ox[kS64Waves];
+#pragma unroll
+        for (int x = 0; x < kS64Waves; ++x) {
+            w[x] = *(LdsQuads)(uintptr_t)(kS64Ml + (uint32_t)(x * 512 + c * 16));
+            ox[x] = *(LdsQuads)(uintptr_t)((uint32_t)x * kS64Ring + (uint32_t)(c * 256 + ((q ^ (c & 15)) << 4)));
+        }
+        const float m = fmaxf(fmaxf(w[0][0], w[1][0]), fmaxf(w[2][0], w[3][0])), m_use = m == -INFINITY ? 0.f : m;
+        float l = 0.f;
+        f32x4_t o4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < kS64Waves; ++x) {
+            const float e2 = __builtin_amdgcn_exp2f(w[x][0] - m_use), wo = e2 * w[x][2];
+            l += e2 * w[x][1];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o4[e] += ox[x][e] * wo;
+        }
+        o4 *= 1.f / l;
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = round16<kF16>(o4[e]);
+        *reinterpret_cast<bf16x4 *>(p.out + b * p.o_sb + (long long)head * p.o_sh + (long long)(r0 + c) * p.o_sn + 4 * q) = o;
+        if (q == 0) p.lse[b * p.lse_sb + (long long)head * p.lse_sh + r0 + c] = (m + __builtin_amdgcn_logf(l)) * 0.69314718055994530942f;
+    }
+}
+
+// Which of the two?  Four heads in a workgroup's waves, or one head in four parts of its keys (us, bfloat16; full attention
+// unless a window is stated):
+//    units (of 32 rows)      256           512           1024          1536          2048
+//    8 heads on 8        18.6 / 8.4    33.8 / 13.7   63.6 / 31.7   94.1 / 61.2   125 / 105
+//      window 1024                     22.1 / 10.8   22.3 / 18.4   29.1 / 25.8   30.0 / 33.3
+//    16 heads on 4       11.3 / 5.9    19.1 / 8.8    34.2 / 18.8   49.9 / 34.0   65.3 / 55.6
+//      window 1024                                   20.8 / 16.1   28.3 / 23.3   29.0 / 30.3
+//    40 heads on 8       6.9 / 4.9     10.0 / 6.7    16.4 / 11.9   29.1 / 18.6   35.8 / 28.1
+//    window 128, 32 heads on 8, 1000 tokens, 1024 units: 7.7 / 8.1     32 tokens, 8 on 8: 3.7 / 3.9 (one half: nothing to share out)
+// Beyond 1536 units where the longest row's chain is three times what a resident workgroup gets on average (2048 units above,
+// full attention: 4.0; window 1024: 2.1 to 2.9).
+bool plan_fwd_d64_short(const FwdParams &p, FwdShortParams &sp) {
+    const long long units = (long long)p.B * p.Hq * ((p.Nq + kS64Rows - 1) / kS64Rows);
+    if (p.cu_q || p.Nq != p.Nk || p.Nk <= 32 || units > 0x7fffffffLL) return false;
+    if (units > 512 && (units > 1536 || longest_row(p) < 256)) {
+        if (p.n_prompts) return false;  // (what its rows see is known on the device only)
+        const long long longest = longest_row(p) / 32;
+        if (longest < 48 || (double)longest * (1024.0 * 128 * 32) < 3.0 * pairs_of_rows(p, p.P < p.Nk ? p.P : p.Nk) * (double)p.B * p.Hq)
+            return false;
+    }
+    fill_fwd_short(p, sp);
+    return true;
+}
+
 }  // namespace
 
 hipError_t launch_fwd_d64(const FwdParams &p, hipStream_t stream) {
     if (p.wg_rows != kFwdWgRows) return hipErrorInvalidValue;  // the plan must be the one for this kernel's workgroups
+    FwdShortParams sp;
+    if (plan_fwd_d64_short(p, sp)) {
+        const dim3 units((unsigned)(sp.pairs * p.G * sp.tiles));
+        if (p.fp16)
+            hipLaunchKernelGGL(swaa_fwd_d64_short_kernel<true>, units, dim3(kS64Threads), kS64Bytes, stream, sp);
+        else
+            hipLaunchKernelGGL(swaa_fwd_d64_short_kernel<false>, units, dim3(kS64Threads), kS64Bytes, stream, sp);
+        return hipGetLastError();
+    }
     const dim3 grid((unsigned)(p.chunk * kXcds));
     if (p.fp16)
         hipLaunchKernelGGL(swaa_fwd_d64_kernel<true>, grid, dim3(kThreads), kSmem64, stream, p);

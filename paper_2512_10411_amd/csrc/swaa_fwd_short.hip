@@ -221,11 +221,8 @@ bool plan_fwd_short(const FwdParams &p, FwdShortParams &sp) {
         const long long prompt = p.P < p.Nk ? p.P : p.Nk, longest = longest_row(p) / 32;
         if (longest < 72 || (double)longest * (512.0 * 128 * 32) < 3.6 * pairs_of_rows(p, prompt) * (double)p.B * p.Hq) return false;
     }
-    sp.f = p;
-    sp.pairs = p.B * p.Hkv;
-    sp.tiles = (int)tiles;
-    sp.div_pairs = make_fastdiv((unsigned)sp.pairs);
-    sp.div_group = make_fastdiv((unsigned)p.G);
+    static_assert(kSRows == 32, "fill_fwd_short's units");
+    fill_fwd_short(p, sp);
     return true;
 }
 

@@ -382,3 +382,15 @@ def test_no_memory_for_pieces(B, Hkv, G, N, W, S, D, monkeypatch):
 ])
 def test_both_dq_kernels_of_head_dimension_128(B, Hkv, G, N, W, S, P):
     check(B, Hkv * G, Hkv, N, 128, W, S, P, seed=9900 + N + G)
+
+
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P", [
+    (16, 2, 8, 130, 50, 3, 100),      # more than 1024 units of 32 rows: 256 rows together
+    (16, 2, 5, 230, 230, 0, None),    # ... groups of four heads and one; the forward too (1280 and 1536 units)
+    (20, 1, 3, 865, 65, 70, 333),     # ... of two and one, sinks next to the band, generated rows
+    (4, 2, 4, 1000, 300, 4, None),    # 1024 units: a head's 32 rows
+    (1, 4, 4, 2500, 300, 4, 2400),    # 1264, few generated rows are the time: a head's 32 rows
+    (1, 4, 4, 2500, 300, 4, None),    # ... none: together
+])
+def test_both_dq_kernels_of_head_dimension_64(B, Hkv, G, N, W, S, P):
+    check(B, Hkv * G, Hkv, N, 64, W, S, P, seed=9950 + N + G)

@@ -68,3 +68,48 @@ def test_non_finite_key_rows_reach_only_the_rows_that_see_them(fmt):
     assert_parity(out, lse, ro, rl, rows=rows, tag=f"d64 non-finite invisible keys {fmt}")
     for j in (500, 1290):  # and the rows that see a NaN show it
         assert not torch.isfinite(out[:, :, j:j + W].float()).any() and not torch.isfinite(lse[:, :, j:j + W]).any()
+
+
+@pytest.mark.parametrize("what", ["spike", "nan"])
+@pytest.mark.parametrize("fmt", ["bf16", "fp16"])
+def test_packed_prompts_keep_to_the_row_tiles(what, fmt):
+    # (prompts of one length run on another kernel up to a size; packed ones never do)
+    Hq, Hkv, N, W, S = 8, 2, 900, 100, 4
+    q, k, v = make_qkv(1, Hq, Hkv, N, 64, seed=4970, fmt=fmt)
+    if what == "spike":  # far above the slack, behind the first halves
+        one, high = (0x4000, 0x4396) if fmt == "bf16" else (0x4000, 0x5CB0)  # 2 and 300
+        q[..., 0], k[..., 0] = one, 0
+        k[:, :, 600, 0] = high
+        sees = np.zeros(N, bool)
+    else:
+        k[:, :, 600, 5::7] = 0x7FC0 if fmt == "bf16" else 0x7E00
+        sees = (np.arange(N) >= 600) & (np.arange(N) < 600 + W)
+    cu = torch.tensor([0, N], dtype=torch.int32, device="cuda")
+    out, lse = binding.swaa_attn_fwd_ex(*(to_device(t[0], fmt) for t in (q, k, v)), W, S, cu_seqlens_q=cu, cu_seqlens_k=cu,
+                                        max_seqlen_q=N, max_seqlen_k=N)
+    torch.cuda.synchronize()
+    k[:, :, 600, 5::7] = k[:, :, 600, 5::7] if what == "spike" else 0
+    with input_format(fmt):
+        ro, rl = swaa_decode_oracle(q, k, v, W, S, 1 / math.sqrt(64))
+    keep = torch.from_numpy(~sees)
+    assert_parity(out[None][:, :, keep.cuda()], lse[None][:, :, keep.cuda()], ro[:, :, ~sees], rl[:, :, ~sees], tag=f"packed d64 {what} {fmt}")
+    assert what == "spike" or torch.isnan(lse[:, torch.from_numpy(sees).cuda()]).all()
+
+
+@pytest.mark.parametrize("B,Hkv,G,N,W,S,P,fmt", [
+    (1, 1, 1, 32, 32, 0, None, "bf16"),     # one half: rows of four heads together
+    (1, 1, 1, 33, 33, 0, None, "bf16"),     # two, a wave each, two waves without any
+    (2, 1, 3, 161, 40, 70, 100, "fp16"),    # sinks beside the band, generated rows
+    (3, 4, 4, 1000, 260, 4, None, "bf16"),  # 1536 units
+    (3, 4, 4, 1030, 260, 4, None, "bf16"),  # 1584: row tiles
+    (3, 4, 4, 1030, 40, 4, None, "fp16"),   # ... on a short window
+    (4, 4, 4, 1700, 100, 4, 1690, "bf16"),  # 3456, few generated rows are the time
+])
+def test_both_kernels_at_the_lines_between_them(B, Hkv, G, N, W, S, P, fmt):
+    print(f"[case] d64 line B{B} Hkv{Hkv} G{G} N{N} W{W} S{S} P{P} {fmt}", flush=True)
+    q, k, v = make_qkv(B, Hkv * G, Hkv, N, 64, seed=96500 + N, fmt=fmt)
+    out, lse = binding.swaa_attn_fwd_ex(*(to_device(t, fmt) for t in (q, k, v)), W, S, P)
+    torch.cuda.synchronize()
+    with input_format(fmt):
+        ro, rl = swaa_decode_oracle(q, k, v, W, S, 1 / math.sqrt(64), n_prompt=P)
+    assert_parity(out, lse, ro, rl, tag=f"d64 line N{N} W{W}")
