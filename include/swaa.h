@@ -64,10 +64,11 @@ typedef enum swaa_status {
  *
  * A call repeated gives the same bits.  A prompt's bits may differ between calls of different
  * form, here and in the two calls below: at D = 128 prompts of one length of 65 to 4096 tokens, with at most 512 tiles of
- * 32 rows of one head in all (B Hq ceil(N / 32)), at D = 64 of 33 tokens and more with at most 1536 of them, and longer or more ones whose longest row (a generated row, or the last
- * under full attention) sees several times the keys that rows see on average, are computed by another kernel than in
- * larger, packed and paged calls.  The results are equally exact (their distance is one rounding of
- * the probabilities to 16 bits).
+ * 32 rows of one head in all (B Hq ceil(N / 32)), and at D = 64 of 33 tokens and more with at most 1536 of them, are
+ * computed by another kernel than in larger, packed and paged calls.  So are longer or more ones whose longest row (a
+ * generated row, or the last under full attention) sees several times the keys that rows see on average, at D = 128 in
+ * this call and the next only, not in the general form.  The results are equally exact (their distance is one rounding
+ * of the probabilities to 16 bits).
  *
  * Returns SWAA_OK or a negative swaa_status.
  */

@@ -140,7 +140,7 @@ int fwd_setup(const swaa_fwd_args *a, bool allow_split, FwdParams &p, long long 
     return SWAA_OK;
 }
 
-int fwd_call(const swaa_fwd_args *a, void *workspace, long long workspace_bytes) {
+int fwd_call(const swaa_fwd_args *a, void *workspace, long long workspace_bytes, bool general = true) {
     FwdParams p{};
     long long need = 0;
     const int rc = fwd_setup(a, workspace != nullptr, p, need);
@@ -156,8 +156,8 @@ int fwd_call(const swaa_fwd_args *a, void *workspace, long long workspace_bytes)
     }
     hipStream_t s = static_cast<hipStream_t>(a->stream);
     swaa::FwdShortParams sp;
-    const hipError_t err = a->D == 128  ? (swaa::plan_fwd_short(p, sp) ? swaa::launch_fwd_short_d128(sp, s)
-                                                                       : swaa::launch_fwd_pipelined_d128(p, s))
+    const hipError_t err = a->D == 128  ? (swaa::plan_fwd_short(p, general, sp) ? swaa::launch_fwd_short_d128(sp, s)
+                                                                                : swaa::launch_fwd_pipelined_d128(p, s))
                            : a->D == 64 ? swaa::launch_fwd_d64(p, s)
                                         : swaa::launch_fwd_simple(p, a->D, s);
     return err == hipSuccess ? SWAA_OK : SWAA_ERR_LAUNCH;
@@ -203,7 +203,7 @@ int swaa_attn_fwd_fa_decode(const void *q, const void *k, const void *v, void *o
     a.dtype = SWAA_BF16;
     a.block_table = nullptr;
     a.block_table_stride = a.page_size = a.num_pages = 0;
-    return swaa_attn_fwd_ex(&a);
+    return fwd_call(&a, nullptr, 0, false);
 }
 
 int swaa_attn_fwd(const void *q, const void *k, const void *v, void *out, float *lse,

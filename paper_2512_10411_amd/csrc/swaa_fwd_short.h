@@ -21,8 +21,8 @@ inline void fill_fwd_short(const FwdParams &p, FwdShortParams &sp) {
     sp.div_group = make_fastdiv((unsigned)p.G);
 }
 
-// Does the call (planned, keys whole) run on the short prompts' kernel?  Fills sp if so.
-bool plan_fwd_short(const FwdParams &p, FwdShortParams &sp);
+// Does the call (planned, keys whole) run on the short prompts' kernel?  Fills sp if so.  general: a call of the general form.
+bool plan_fwd_short(const FwdParams &p, bool general, FwdShortParams &sp);
 hipError_t launch_fwd_short_d128(const FwdShortParams &sp, hipStream_t stream);
 
 }  // namespace swaa

@@ -213,11 +213,13 @@ __global__ __launch_bounds__(kSThreads, 2) void swaa_fwd_short_kernel(const FwdS
 //    4 on 1, 8000, full attention, none, 4.1: 108 / 95.3   8 on 8, 4096, full, none, 4.0: 59.4 / 54.7
 //    16 on 4, 3000, window 1024, 3.6:        52.2 / 52.8   2 x 8 on 8, 9000, 2.9: 189 / 180   16 on 4, 16384, 2.8: 273 / 322
 //    8 on 8, 3000, window 1024, none, 3.3:   23.8 / 27.9   16 on 4, 2500, full, none, 3.3: 41.1 / 48.6
-bool plan_fwd_short(const FwdParams &p, FwdShortParams &sp) {
+// Calls of the general form stay on row tiles there: above 4096 tokens, or with more than one round of units, they give a
+// contiguous cache the bits of the same call on a paged one.
+bool plan_fwd_short(const FwdParams &p, bool general, FwdShortParams &sp) {
     const long long tiles = (p.Nq + kSRows - 1) / kSRows;
     if (p.cu_q || p.block_table || p.Nq != p.Nk || p.Nk <= 64) return false;
     if (p.Nk > 4096 || (long long)p.B * p.Hq * tiles > 512) {
-        if (p.n_prompts || (long long)p.B * p.Hq * tiles > 0x7fffffffLL) return false;  // (what its rows see is known on the device only)
+        if (general || (long long)p.B * p.Hq * tiles > 0x7fffffffLL) return false;
         const long long prompt = p.P < p.Nk ? p.P : p.Nk, longest = longest_row(p) / 32;
         if (longest < 72 || (double)longest * (512.0 * 128 * 32) < 3.6 * pairs_of_rows(p, prompt) * (double)p.B * p.Hq) return false;
     }
