@@ -14,3 +14,6 @@ def pytest_configure(config):
     if not os.path.exists(binding.LIB_PATH):
         from paper_2512_10411_amd.build import build_library
         build_library()
+    if not os.path.exists(binding.HOST_CALLS_PATH):
+        from paper_2512_10411_amd.build import build_host_calls
+        build_host_calls()
