@@ -125,6 +125,9 @@ struct FwdParams {
     // (fixed-length batches of few rows, swaa_fwd_few_rows.h).
     int split_keys;
     int few_only;  // the host expects no splits: the plan is for the sake of few rows, and may be dropped
+    // One sequence whose lengths the host knows as upper bounds (split_keys 1): how many splits it gets if it is as long as they say
+    // (0: the host makes no plan), and what it then costs (SplitSeq); the device plans for any other.
+    int bound_splits, bound_cost;
     long long split_items;  // upper bound on the row tiles (times KV heads) of the batch
     int split_cap;  // partial results the workspace holds
     float *ws_o;    // [split_cap][4 waves][16][64 lanes][4]: unnormalised O in accumulator order

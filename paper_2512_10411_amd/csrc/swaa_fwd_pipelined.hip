@@ -894,7 +894,7 @@ __global__ __launch_bounds__(256) void swaa_fwd_merge_kernel(const FwdParams p) 
 }  // namespace
 
 long long plan_fwd_split(FwdParams &p) {
-    p.split_keys = p.few_only = 0;
+    p.split_keys = p.few_only = p.bound_splits = p.bound_cost = 0;
     if (p.B > kSplitMaxBatch || p.wg_rows != kPWgRows) return 0;
     const bool packed = p.cu_q != nullptr;
     // Whole prompts on themselves: their tiles are many and short enough as they are.
@@ -955,13 +955,15 @@ long long plan_fwd_split(FwdParams &p) {
         p.split_keys = 1;
         p.split_cap = room < kSplitUnits ? (int)room : kSplitUnits;
         p.chunk = (bound + p.split_cap + kXcds - 1) / kXcds + p.B;
-        // One sequence is as long as the host says, or shorter, and then has a few splits more than it needs: the plan from above,
-        // unless it has a prompt length of its own behind a window, and the device alone knows what its rows see.  (512 rows on
-        // 24k tokens: 4.4 us of plan stood in front of every workgroup's first key, without the model 2.)
-        const long long units = (long long)p.Hkv * longest.tiles * n;
-        if (p.B == 1 && n > 1 && units <= p.split_cap && (!p.n_prompts || p.W >= p.Nk)) {
-            p.split_keys = n;
-            p.chunk = (units + kXcds - 1) / kXcds;
+        // One sequence has either its row tiles or, split, as many partial results as there is room for.  If it is as long as the host
+        // says, the plan is the one from above (512 rows on 24k tokens: 4.4 us of plan stood in front of every workgroup's first key,
+        // without the model 2), unless it has a prompt length of its own behind a window: what its rows see, the device alone knows.
+        if (p.B == 1) {
+            p.chunk = ((bound > p.split_cap ? bound : p.split_cap) + kXcds - 1) / kXcds;
+            if (n > 1 && (long long)p.Hkv * longest.tiles * n <= p.split_cap && (!p.n_prompts || p.W >= p.Nk)) {
+                p.bound_splits = n;
+                p.bound_cost = longest.cost;
+            }
         }
     }
     p.total_items = p.chunk * kXcds;

@@ -209,6 +209,17 @@ __host__ __device__ inline bool few_in_row_tiles(const FwdParams &p, unsigned un
 // Up to 160 it depends on where the keys lie (144 units on 10270 keys, packed: 160 / 151).
 __host__ __device__ inline bool few_stay_whole(unsigned units) { return units > 160 && units <= 256; }
 
+// Is the only sequence of a batch as long as the host's bounds on its lengths (bound_splits), or up to a sixteenth shorter?  Bounds
+// may be far above the lengths (a captured graph is launched for the longest cache that it will meet), and the host's split count is
+// then too high, or too low where there are fewer rows than it reckons with.  The host's count / the device's plan (us;
+// binary16, 32 heads on 8, full attention; rows and keys, of their bounds where those differ):
+//    1 row on 600 keys of 32768 24.9 / 12.3   64 on 1000 of 32768 28.1 / 20.4     64 on 16384 of 32768 41.7 / 36.4
+//    64 rows of 512 on 32768 keys 114 / 57.4  64 of 512 on 131072 503 / 171       1 on 4000 of 8192 18.8 / 19.7
+//    1 on 7936 of 8192 24.1 / 26.7 (the plan's own time in front of the first key)
+__host__ __device__ inline bool as_the_bounds_say(const FwdParams &p, int nq, int cost) {
+    return p.bound_splits > 1 && nq == p.Nq && cost <= p.bound_cost && 16LL * cost >= 15LL * p.bound_cost;
+}
+
 // One workgroup's share of the keys.
 struct SplitItem {
     int n, s;       // the sequence's splits (0: none, and few rows on a row tile all the same), and which of them this is
@@ -311,6 +322,8 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     bool few_even = true;  // few rows only, of about one length: the average is 0.8 of the longest and more
     if (p.split_keys != 1) {
         n = p.split_keys;  // (-1: one)
+    } else if (as_the_bounds_say(p, (int)wave_read_lane((unsigned)nq, 0), (int)wave_read_lane((unsigned)me.cost, 0))) {
+        n = p.bound_splits;
     } else {
         // the model's terms of candidate `lane`, summed over the sequences: wave w takes every fourth
         const int splittable = me.whole ? 0 : me.cost;

@@ -405,8 +405,8 @@ def test_few_rows_and_what_is_not_a_number(scratch, nk, what, fmt):
 
 @pytest.mark.parametrize("nq,nk,max_q,max_k,W,prompt", [
     (70, 4000, 70, 4000, 10**9, 3000),    # as long as the host says: its plan; generated rows
-    (70, 2100, 128, 6000, 10**9, None),   # shorter, more splits than a model of the true lengths makes
-    (5, 300, 128, 6000, 10**9, None),     # ... few rows, and fewer halves than splits
+    (70, 2100, 128, 6000, 10**9, None),   # shorter: the device's
+    (5, 300, 128, 6000, 10**9, None),     # ... few rows, fewer halves than the host's splits
     (40, 4000, 70, 4000, 500, 3980),      # prompt and generated rows behind a window: planned on the device, whole
 ])
 def test_one_packed_sequence(scratch, nq, nk, max_q, max_k, W, prompt):
@@ -420,3 +420,39 @@ def test_one_packed_sequence(scratch, nq, nk, max_q, max_k, W, prompt):
     assert scratch[0] > 0
     ro, rl = swaa_decode_oracle(q, k, v, min(W, nk), 4, 1 / math.sqrt(D), n_prompt=prompt)
     assert_parity(out[None], lse[None], ro, rl, tag=f"packed alone {nq} of {nk}")
+
+
+@pytest.mark.parametrize("nq,nk,max_q,max_k,as_bounded", [
+    (64, 1000, 64, 32768, False),    # a cache far shorter than its bound
+    (3, 600, 3, 32768, False),       # ... few rows
+    (64, 20000, 512, 32768, False),  # fewer rows than their bound: more splits, not fewer
+    (64, 7648, 64, 8192, False),     # 239 halves of 256
+    (64, 7680, 64, 8192, True),      # 240: the host's plan
+])
+def test_one_packed_sequence_is_split_for_the_length_it_has(monkeypatch, nq, nk, max_q, max_k, as_bounded):
+    Hkv, G = 8, 4
+    lib, scratch = binding.load_library(), []
+    query = lib.swaa_attn_fwd_ex_workspace_bytes
+    monkeypatch.setattr(lib, "swaa_attn_fwd_ex_workspace_bytes", lambda a: scratch.append(int(query(a))) or scratch[-1])
+    q, k, v = (to_device(x[0]) for x in make_qkv(1, Hkv * G, Hkv, max_k, 128, seed=9800 + nk, n_query=max_q))
+    ints = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
+
+    def run(nq, nk, batch):  # the call, and the splits that its plan (the workspace's last 64 ints) gave the sequence
+        print(f"[case] nq {nq} of {max_q} nk {nk} of {max_k}, batch of {batch}", flush=True)
+        cu = lambda n: ints(0, *[n] * batch)
+        ws = torch.zeros(160 << 20, dtype=torch.uint8, device="cuda")
+        out, lse = binding.swaa_attn_fwd_ex(q[:, :nq], k[:, :nk], v[:, :nk], 10**9, 4, workspace=ws, cu_seqlens_q=cu(nq),
+                                            cu_seqlens_k=cu(nk), max_seqlen_q=max_q, max_seqlen_k=max_k)
+        torch.cuda.synchronize()
+        end = scratch.pop()
+        assert end > 0
+        return out, lse, int(ws[end - 256:end - 252].view(torch.int32)[0])
+
+    out, lse, n = run(nq, nk, 1)
+    if as_bounded:
+        assert n == run(nq, max_k, 1)[2]
+        return
+    # beside an empty sequence the device always plans for itself
+    want, want_l, n2 = run(nq, nk, 2)
+    assert n == n2
+    assert torch.equal(out, want) and torch.equal(lse, want_l)
