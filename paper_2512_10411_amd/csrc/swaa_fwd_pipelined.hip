@@ -960,7 +960,9 @@ long long plan_fwd_split(FwdParams &p) {
         // without the model 2), unless it has a prompt length of its own behind a window: what its rows see, the device alone knows.
         if (p.B == 1) {
             p.chunk = ((bound > p.split_cap ? bound : p.split_cap) + kXcds - 1) / kXcds;
-            if (n > 1 && (long long)p.Hkv * longest.tiles * n <= p.split_cap && (!p.n_prompts || p.W >= p.Nk)) {
+            // (a chunk that whole_batch leaves whole is left so by the device, too, if its rows are not stated)
+            if (n > 1 && (long long)p.Hkv * longest.tiles * n <= p.split_cap && (!p.n_prompts || p.W >= p.Nk) &&
+                !whole_batch(p, p.Nq, least_units(p, p.Nq))) {
                 p.bound_splits = n;
                 p.bound_cost = longest.cost;
             }

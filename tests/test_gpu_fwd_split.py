@@ -456,3 +456,24 @@ def test_one_packed_sequence_is_split_for_the_length_it_has(monkeypatch, nq, nk,
     want, want_l, n2 = run(nq, nk, 2)
     assert n == n2
     assert torch.equal(out, want) and torch.equal(lse, want_l)
+
+
+@pytest.mark.parametrize("Hkv,G,nq,nk,W,whole", [
+    (8, 4, 512, 4000, 1500, True),   # 128 units: whole up to windows of about 2200
+    (8, 4, 512, 4000, 2048, True),
+    (4, 4, 1000, 4000, 1250, True),
+    (8, 4, 512, 4000, 3000, False),  # split, and as many times
+    (8, 4, 64, 4000, 2048, False),
+])
+def test_one_chunk_gives_the_same_bits_whichever_list_it_runs_on(scratch, Hkv, G, nq, nk, W, whole):
+    print(f"[case] one chunk {nq} on {nk} W{W}", flush=True)
+    q, k, v = make_qkv(1, Hkv * G, Hkv, nk, 128, seed=95500 + nq + W, n_query=nq)
+    ints = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    (out, lse), (o0, l0) = (tuple(t.clone() for t in binding.swaa_attn_fwd_ex(
+        *(to_device(x[0]) for x in (q, k, v)), W, 4, total_rows_q=rows, cu_seqlens_q=ints(0, nq), cu_seqlens_k=ints(0, nk),
+        max_seqlen_q=nq, max_seqlen_k=nk)) for rows in (None, 0))
+    torch.cuda.synchronize()
+    assert (scratch[0] == 0) == whole and scratch[1] > 0
+    assert torch.equal(out, o0) and torch.equal(lse, l0)
+    ro, rl = swaa_decode_oracle(q, k, v, W, 4, 1 / math.sqrt(128))
+    assert_parity(out[None], lse[None], ro, rl, tag=f"one chunk {nq} on {nk}")
