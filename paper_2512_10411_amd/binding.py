@@ -3,7 +3,8 @@
 Every step of the attention forward runs inside the HIP kernels; torch is
 used for device memory and the stream handle.  There is no fallback: if the
 library has not been built (python -m paper_2512_10411_amd.build), the first
-call raises.
+call raises.  The native code is a shorter way to the same library and not
+needed: without it every call takes the general path.
 """
 from __future__ import annotations
 
@@ -11,6 +12,7 @@ import contextlib
 import ctypes
 import math
 import os
+import warnings
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libswaa.so")
@@ -160,19 +162,39 @@ def swaa_visible_pairs_fa_decode(N: int, window: int, n_sink: int, n_prompt: int
 _SAME_DEVICE = contextlib.nullcontext()
 
 
+class _NoHostCalls:
+    """In place of the native part: takes no call."""
+
+    @staticmethod
+    def fwd(*args):
+        return None
+
+    decode = decode_ex = fill_fwd_ex = fwd
+
+
+def _native_part(torch):
+    """The native part of this binding, bound to the library, if one is built for this torch."""
+    if not os.path.exists(HOST_CALLS_PATH) or not os.path.exists(LIB_PATH):  # (the general path says so of a missing library)
+        return _NoHostCalls
+    lib = load_library()
+    try:
+        from . import _host_calls
+        _host_calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
+            lib.swaa_attn_fwd, lib.swaa_attn_fwd_fa_decode, lib.swaa_attn_decode, lib.swaa_attn_decode_workspace_bytes,
+            lib.swaa_attn_decode_ex, lib.swaa_attn_decode_ex_workspace_bytes)),
+            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    except ImportError as e:
+        warnings.warn(f"{HOST_CALLS_PATH} is not used, calls take longer on the way to the library ({e}): "
+                      "build it with `python -m paper_2512_10411_amd.build`", RuntimeWarning, stacklevel=4)
+        return _NoHostCalls
+    return _host_calls
+
+
 def _torch():
     """torch, imported with the first call that has tensors, and with it the native part of this binding."""
     global torch, _host
     import torch as imported
-    if not os.path.exists(HOST_CALLS_PATH):
-        raise RuntimeError(f"{HOST_CALLS_PATH} is missing: build it with `python -m paper_2512_10411_amd.build`")
-    from . import _host_calls
-    lib = load_library()
-    _host_calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
-        lib.swaa_attn_fwd, lib.swaa_attn_fwd_fa_decode, lib.swaa_attn_decode, lib.swaa_attn_decode_workspace_bytes,
-        lib.swaa_attn_decode_ex, lib.swaa_attn_decode_ex_workspace_bytes)),
-        imported._C._cuda_getDevice, imported._C._cuda_getCurrentRawStream)
-    _host = _host_calls
+    _host = _native_part(imported)
     torch = imported  # (last: who sees it finds the native part bound)
     return torch
 
