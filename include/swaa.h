@@ -395,7 +395,8 @@ long long swaa_attn_bwd_workspace_bytes(int B, int Hq, int Hkv, int N, int D, in
 /* Static description of a status code; never NULL, never freed. */
 const char *swaa_status_string(int status);
 
-/* Library version: major * 10000 + minor * 100 + patch. */
+/* Version, major * 10000 + minor * 100 + patch, of this header (raised whenever a struct or a signature changes) and of the library. */
+#define SWAA_VERSION 131
 int swaa_version(void);
 
 #ifdef __cplusplus

@@ -173,7 +173,7 @@ class _NoHostCalls:
 
 
 def _native_part(torch):
-    """The native part of this binding, bound to the library, if one is built for this torch."""
+    """The native part of this binding, bound to the library, if one is built for it and this torch."""
     if not os.path.exists(HOST_CALLS_PATH) or not os.path.exists(LIB_PATH):  # (the general path says so of a missing library)
         return _NoHostCalls
     lib = load_library()
@@ -182,8 +182,9 @@ def _native_part(torch):
         _host_calls.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in (
             lib.swaa_attn_fwd, lib.swaa_attn_fwd_fa_decode, lib.swaa_attn_decode, lib.swaa_attn_decode_workspace_bytes,
             lib.swaa_attn_decode_ex, lib.swaa_attn_decode_ex_workspace_bytes)),
-            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
-    except ImportError as e:
+            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream,
+            lib.swaa_version(), ctypes.sizeof(SwaaFwdArgs), ctypes.sizeof(SwaaDecodeArgs), str(torch.__version__))
+    except (ImportError, TypeError) as e:  # (TypeError: its `bind` takes other arguments)
         warnings.warn(f"{HOST_CALLS_PATH} is not used, calls take longer on the way to the library ({e}): "
                       "build it with `python -m paper_2512_10411_amd.build`", RuntimeWarning, stacklevel=4)
         return _NoHostCalls

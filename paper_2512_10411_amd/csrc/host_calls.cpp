@@ -11,6 +11,7 @@
 #include <ATen/PythonTorchFunctionTLS.h>
 #include <c10/core/impl/LocalDispatchKeySet.h>
 #include <c10/core/impl/TorchDispatchModeTLS.h>
+#include <torch/version.h>
 
 #include <cmath>
 #include <cstring>
@@ -283,16 +284,30 @@ PyObject *fill_fwd_ex(PyObject *, PyObject *const *a, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
-// bind(addresses of the six entry points above, in their order, then current_device and current_stream)
+// bind(addresses of the six entry points above, in their order, then current_device and current_stream, the library's version, the
+// sizes of the binding's two argument blocks, torch's version).  ImportError if this file was compiled for others: a call from here
+// hands the library pointers and strides where the header it was compiled with has them.
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
     void *at[6];
-    if (n != 8) {
-        PyErr_SetString(PyExc_TypeError, "bind takes six addresses and two functions");
+    if (n != 12) {
+        PyErr_SetString(PyExc_TypeError, "bind takes six addresses, two functions, three numbers and a text");
         return nullptr;
     }
     for (int i = 0; i < 6; ++i) {
         at[i] = PyLong_AsVoidPtr(a[i]);
         if (PyErr_Occurred()) return nullptr;
+    }
+    const long long version = PyLong_AsLongLong(a[8]), fwd_bytes = PyLong_AsLongLong(a[9]), decode_bytes = PyLong_AsLongLong(a[10]);
+    const char *torch_version = PyErr_Occurred() ? nullptr : PyUnicode_AsUTF8(a[11]);
+    if (!torch_version) return nullptr;
+    if (version != SWAA_VERSION || fwd_bytes != (long long)sizeof(swaa_fwd_args) || decode_bytes != (long long)sizeof(swaa_decode_args)) {
+        PyErr_Format(PyExc_ImportError, "compiled for libswaa %d with argument blocks of %zu and %zu bytes, not %lld with %lld and %lld",
+                     SWAA_VERSION, sizeof(swaa_fwd_args), sizeof(swaa_decode_args), version, fwd_bytes, decode_bytes);
+        return nullptr;
+    }
+    if (std::strncmp(torch_version, TORCH_VERSION, std::strlen(TORCH_VERSION)) != 0) {
+        PyErr_Format(PyExc_ImportError, "compiled for torch %s, not %s", TORCH_VERSION, torch_version);
+        return nullptr;
     }
     fwd_entry = reinterpret_cast<decltype(fwd_entry)>(at[0]);
     fwd_fa_decode_entry = reinterpret_cast<decltype(fwd_fa_decode_entry)>(at[1]);

@@ -59,7 +59,7 @@ const char *swaa_status_string(int status) {
     }
 }
 
-int swaa_version(void) { return 131; }
+int swaa_version(void) { return SWAA_VERSION; }
 
 namespace {
 

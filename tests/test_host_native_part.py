@@ -1,5 +1,6 @@
 """The binding's native part (_host_calls.so) is a shorter way to the library and may be missing.  No GPU: the calls
 here are refused by the general path's own checks, which shows that it took them."""
+import ctypes
 import sys
 
 import pytest
@@ -50,3 +51,30 @@ def test_the_native_part_that_is_built_is_bound(first_call, recwarn):
     assert binding._torch() is torch
     assert binding._host.__name__ == "paper_2512_10411_amd._host_calls"
     assert not recwarn.list
+
+
+@pytest.mark.parametrize("other", ["forward arguments", "decode arguments", "library", "torch"])
+def test_a_native_part_compiled_for_another_layout_or_torch_is_left_out(first_call, monkeypatch, other):
+    for name, block in (("forward arguments", "SwaaFwdArgs"), ("decode arguments", "SwaaDecodeArgs")):
+        if other == name:  # (a field more than the native part knows of)
+            old = getattr(binding, block)
+            monkeypatch.setattr(binding, block, type(block, (ctypes.Structure,), {"_fields_": old._fields_ + [("more", ctypes.c_void_p)]}))
+    if other == "library":
+        lib = binding.load_library()
+        version = lib.swaa_version()
+        monkeypatch.setattr(lib, "swaa_version", lambda: version + 1)
+    if other == "torch":
+        monkeypatch.setattr(torch, "__version__", "1.13.1")
+    with pytest.warns(RuntimeWarning, match="compiled for"):
+        binding._torch()
+    assert binding._host is binding._NoHostCalls
+
+
+def test_an_older_native_part_is_left_out(first_call, monkeypatch):
+    def bind(*args):
+        raise TypeError("bind takes six addresses and two functions")
+    binding._torch()
+    monkeypatch.setattr(binding._host, "bind", bind)
+    monkeypatch.setattr(binding, "torch", None)
+    with pytest.warns(RuntimeWarning, match="paper_2512_10411_amd.build"):
+        refused_by_the_general_path()
