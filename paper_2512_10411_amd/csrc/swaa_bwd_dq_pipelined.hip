@@ -538,7 +538,7 @@ bool dq_short(const BwdParams &p) {
     const long long units = heads * ((N + kQRows - 1) / kQRows);
     if (units <= 512 || (units <= 1024 && N >= 256)) return true;
     const long long longest = longest_row(p.f) / 32;  // halves
-    return longest >= 72 && (double)longest * (256.0 * 256 * 32) >= 1.85 * pairs_of_rows(p.f, p.f.P < N ? p.f.P : N) * (double)heads;
+    return longest >= 72 && (double)longest * (256.0 * 256 * 32) >= 1.85 * pairs_of_rows(p.f) * (double)heads;
 }
 
 hipError_t launch_bwd_dq_pipelined_d128(const BwdParams &p, hipStream_t stream) {

@@ -371,11 +371,12 @@ inline bool plan_work(FwdParams &p, int rows, int wg_rows) {
     return p.chunk * kXcds <= 0x7fffffffLL;
 }
 
-// Keys that the longest row of a whole prompt sees (sinks beside its window left out), and the pairs of all rows of a head.
-inline long long longest_row(const FwdParams &p) { return p.P < p.Nk ? p.Nk : p.W; }
-inline double pairs_of_rows(const FwdParams &p, long long prompt) {
-    const double n = (double)prompt, w = (double)(p.W < prompt ? p.W : prompt), all = (double)p.Nk;
-    return w * (w + 1) / 2 + (n - w) * w + (all * (all + 1) - n * (n + 1)) / 2;
+// Keys that the longest row of a whole prompt sees, and the pairs of all rows of a head (as swaa_visible_pairs_fa_decode counts them).
+inline long long longest_row(const FwdParams &p) { return p.P < p.Nk || (long long)p.W + p.S > p.Nk ? p.Nk : (long long)p.W + p.S; }
+inline double pairs_of_rows(const FwdParams &p) {
+    const double n = (double)(p.P < p.Nk ? p.P : p.Nk), w = (double)p.W < n ? (double)p.W : n, all = (double)p.Nk;
+    const double more = n - w, ramp = (double)p.S < more ? (double)p.S : more;  // rows behind the first window, and those that see less than all sinks beside it
+    return w * (w + 1) / 2 + more * w + ramp * (ramp + 1) / 2 + (more - ramp) * (double)p.S + (all * (all + 1) - n * (n + 1)) / 2;
 }
 
 // The plan of a packed batch of B sequences with total_rows query rows in all (each at most

@@ -481,7 +481,7 @@ bool plan_fwd_d64_short(const FwdParams &p, FwdShortParams &sp) {
     if (units > 512 && (units > 1536 || longest_row(p) < 256)) {
         if (p.n_prompts) return false;  // (what its rows see is known on the device only)
         const long long longest = longest_row(p) / 32;
-        if (longest < 48 || (double)longest * (1024.0 * 128 * 32) < 3.0 * pairs_of_rows(p, p.P < p.Nk ? p.P : p.Nk) * (double)p.B * p.Hq)
+        if (longest < 48 || (double)longest * (1024.0 * 128 * 32) < 3.0 * pairs_of_rows(p) * (double)p.B * p.Hq)
             return false;
     }
     fill_fwd_short(p, sp);

@@ -220,8 +220,8 @@ bool plan_fwd_short(const FwdParams &p, bool general, FwdShortParams &sp) {
     if (p.cu_q || p.block_table || p.Nq != p.Nk || p.Nk <= 64) return false;
     if (p.Nk > 4096 || (long long)p.B * p.Hq * tiles > 512) {
         if (general || (long long)p.B * p.Hq * tiles > 0x7fffffffLL) return false;
-        const long long prompt = p.P < p.Nk ? p.P : p.Nk, longest = longest_row(p) / 32;
-        if (longest < 72 || (double)longest * (512.0 * 128 * 32) < 3.6 * pairs_of_rows(p, prompt) * (double)p.B * p.Hq) return false;
+        const long long longest = longest_row(p) / 32;
+        if (longest < 72 || (double)longest * (512.0 * 128 * 32) < 3.6 * pairs_of_rows(p) * (double)p.B * p.Hq) return false;
     }
     static_assert(kSRows == 32, "fill_fwd_short's units");
     fill_fwd_short(p, sp);
