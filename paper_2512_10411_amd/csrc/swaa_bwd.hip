@@ -412,8 +412,7 @@ __global__ __launch_bounds__(dq64s::kThreads, 3) void swaa_bwd_dq64_short_kernel
 bool dq64_short(const BwdParams &p) {
     const long long units = (long long)p.B * p.Hq * ((p.N + dq64s::kRows - 1) / dq64s::kRows);
     if (units <= 512 || (units <= 1024 && longest_row(p.f) >= 256)) return true;
-    const long long longest = longest_row(p.f) / 32;
-    return longest >= 48 && (double)longest * (512.0 * 256 * 32) >= 2.35 * pairs_of_rows(p.f) * (double)p.B * p.Hq;
+    return longest_row(p.f) >= 48 * 32 && chain_is_the_time(p.f, 512, 256, 2.35, 1.95);
 }
 
 // ---- dK, dV --------------------------------------------------------------------------

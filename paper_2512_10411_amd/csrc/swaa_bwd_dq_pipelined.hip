@@ -537,8 +537,7 @@ bool dq_short(const BwdParams &p) {
     const long long heads = (long long)p.B * p.Hq, N = p.N;
     const long long units = heads * ((N + kQRows - 1) / kQRows);
     if (units <= 512 || (units <= 1024 && N >= 256)) return true;
-    const long long longest = longest_row(p.f) / 32;  // halves
-    return longest >= 72 && (double)longest * (256.0 * 256 * 32) >= 1.85 * pairs_of_rows(p.f) * (double)heads;
+    return longest_row(p.f) >= 72 * 32 && chain_is_the_time(p.f, 256, 256, 1.85, 1.05);
 }
 
 hipError_t launch_bwd_dq_pipelined_d128(const BwdParams &p, hipStream_t stream) {

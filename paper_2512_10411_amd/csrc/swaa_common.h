@@ -379,6 +379,20 @@ inline double pairs_of_rows(const FwdParams &p) {
     return w * (w + 1) / 2 + more * w + ramp * (ramp + 1) / 2 + (more - ramp) * (double)p.S + (all * (all + 1) - n * (n + 1)) / 2;
 }
 
+// Is the chain of the longest row what the call takes?  Its halves against those of `group` rows that one of `resident` workgroups
+// gets on average (the quotient that the rules' tables name): at least `line`, and at least `narrow` with ten halves more for every
+// 32 rows, what a workgroup of 32 rows costs outside its loop.  Without these, narrow windows, whose workgroups are little else,
+// came out wrong (us, rows together / a head's 32 rows: 8 x 16 heads on 4, 2285 tokens, window 67, one generated row, quotient 7.2:
+// 57.9 / 120; D = 64, 8 x 32 on 8, 1600, window 123, 14 generated rows, 3.8: 43.5 / 79.4; backward, D = 64, 8 x 16 on 4, 2195,
+// window 342, one, 3.2: 154 / 198).  Of 782 to 870 calls per rule, drawn around the lines (400 to 60000 tokens, windows from 64 on, up to
+// 1000 sinks, 8 to 40 heads, 4 on 1), the kernel that it picks is slower than rows together by more than 5 % in 2 (forward, D = 128), 11
+// (D = 64), 6 and 9 (backward), by the quotient alone 21, 14, 10 and 23; on average it is 1.0 to 1.7 % behind the better one.
+inline bool chain_is_the_time(const FwdParams &p, double resident, int group, double line, double narrow) {
+    const double pairs = pairs_of_rows(p), begins = 10.0 * 32 * (double)p.Nk;
+    const double need = line * pairs > narrow * (pairs + begins) ? line * pairs : narrow * (pairs + begins);
+    return (double)(longest_row(p) / 32) * (resident * group * 32) >= need * (double)p.B * p.Hq;
+}
+
 // The plan of a packed batch of B sequences with total_rows query rows in all (each at most
 // `rows` long): the compact work list of decode_work_packed, bounded from above -- a sequence
 // adds at most one partly filled tile per head group to total_rows / tile rows, and at most one

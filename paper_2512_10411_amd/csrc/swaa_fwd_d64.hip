@@ -473,16 +473,14 @@ __global__ __launch_bounds__(kS64Threads, 4) void swaa_fwd_d64_short_kernel(cons
 //      window 1024                                   20.8 / 16.1   28.3 / 23.3   29.0 / 30.3
 //    40 heads on 8       6.9 / 4.9     10.0 / 6.7    16.4 / 11.9   29.1 / 18.6   35.8 / 28.1
 //    window 128, 32 heads on 8, 1000 tokens, 1024 units: 7.7 / 8.1     32 tokens, 8 on 8: 3.7 / 3.9 (one half: nothing to share out)
-// Beyond 1536 units where the longest row's chain is three times what a resident workgroup gets on average (2048 units above,
+// Beyond 1536 units where the longest row's chain is 2.7 times what a resident workgroup gets on average (2048 units above,
 // full attention: 4.0; window 1024: 2.1 to 2.9).
 bool plan_fwd_d64_short(const FwdParams &p, FwdShortParams &sp) {
     const long long units = (long long)p.B * p.Hq * ((p.Nq + kS64Rows - 1) / kS64Rows);
     if (p.cu_q || p.Nq != p.Nk || p.Nk <= 32 || units > 0x7fffffffLL) return false;
     if (units > 512 && (units > 1536 || longest_row(p) < 256)) {
         if (p.n_prompts) return false;  // (what its rows see is known on the device only)
-        const long long longest = longest_row(p) / 32;
-        if (longest < 48 || (double)longest * (1024.0 * 128 * 32) < 3.0 * pairs_of_rows(p) * (double)p.B * p.Hq)
-            return false;
+        if (longest_row(p) < 48 * 32 || !chain_is_the_time(p, 1024, 128, 2.7, 1.7)) return false;
     }
     fill_fwd_short(p, sp);
     return true;

@@ -207,8 +207,8 @@ __global__ __launch_bounds__(kSThreads, 2) void swaa_fwd_short_kernel(const FwdS
 // tiles (relative error against 64 bits, mean over 24 calls: bfloat16 0.00196, row tiles 0.00202; binary16 0.000245, 0.000253).
 //
 // More units, or longer ones, where the chain of the longest row is what the call takes: its halves against the halves of 128
-// rows that one of the 512 resident workgroups gets on average (a quotient), from 3.6 on.  Generated rows behind a prompt above
-// all.  Pipelined / short (us; 512 generated rows unless stated):
+// rows that one of the 512 resident workgroups gets on average (a quotient), from 3.6 on where windows are not narrow
+// (chain_is_the_time).  Generated rows behind a prompt above all.  Pipelined / short (us; 512 generated rows unless stated):
 //    8 on 8, 4000 tokens, window 1024, 6.6:  66.0 / 39.1   20000, 5.6: 386 / 200    10374, window 2048, 3.7: 208 / 164
 //    4 on 1, 8000, full attention, none, 4.1: 108 / 95.3   8 on 8, 4096, full, none, 4.0: 59.4 / 54.7
 //    16 on 4, 3000, window 1024, 3.6:        52.2 / 52.8   2 x 8 on 8, 9000, 2.9: 189 / 180   16 on 4, 16384, 2.8: 273 / 322
@@ -220,8 +220,7 @@ bool plan_fwd_short(const FwdParams &p, bool general, FwdShortParams &sp) {
     if (p.cu_q || p.block_table || p.Nq != p.Nk || p.Nk <= 64) return false;
     if (p.Nk > 4096 || (long long)p.B * p.Hq * tiles > 512) {
         if (general || (long long)p.B * p.Hq * tiles > 0x7fffffffLL) return false;
-        const long long longest = longest_row(p) / 32;
-        if (longest < 72 || (double)longest * (512.0 * 128 * 32) < 3.6 * pairs_of_rows(p) * (double)p.B * p.Hq) return false;
+        if (longest_row(p) < 72 * 32 || !chain_is_the_time(p, 512, 128, 3.6, 2.35)) return false;
     }
     static_assert(kSRows == 32, "fill_fwd_short's units");
     fill_fwd_short(p, sp);

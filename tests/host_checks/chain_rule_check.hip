@@ -36,6 +36,8 @@ int main() {
         {1, 8, 4, 8000, 512, 1000, 7999, false},     // 324 us on 32 rows of a head, 215 on row tiles
         {2, 8, 4, 16384, 128, 1000, 16320, false},   // 1162 / 695
         {1, 8, 1, 4001, 512, 4096, 4001, true},      // full attention, by its sinks
+        {8, 4, 4, 2285, 67, 4, 2284, false},         // narrow windows: 120 / 57.9
+        {8, 4, 4, 6124, 123, 4, 6119, false},        // 339 / 166
     };
     for (const Call &c : calls) {
         swaa::FwdParams p{};
