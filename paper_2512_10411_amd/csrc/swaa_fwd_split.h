@@ -217,7 +217,7 @@ __host__ __device__ inline bool few_stay_whole(unsigned units) { return units > 
 //    64 rows of 512 on 32768 keys 114 / 57.4  64 of 512 on 131072 503 / 171       1 on 4000 of 8192 18.8 / 19.7
 //    1 on 7936 of 8192 24.1 / 26.7 (the plan's own time in front of the first key)
 __host__ __device__ inline bool as_the_bounds_say(const FwdParams &p, int nq, int cost) {
-    return p.bound_splits > 1 && nq == p.Nq && cost <= p.bound_cost && 16LL * cost >= 15LL * p.bound_cost;
+    return nq == p.Nq && cost <= p.bound_cost && 16 * cost >= 15 * p.bound_cost;  // (at most 2^26 halves and one)
 }
 
 // One workgroup's share of the keys.
@@ -322,7 +322,7 @@ __device__ __forceinline__ bool decode_work_split(const FwdParams &p, uint32_t s
     bool few_even = true;  // few rows only, of about one length: the average is 0.8 of the longest and more
     if (p.split_keys != 1) {
         n = p.split_keys;  // (-1: one)
-    } else if (as_the_bounds_say(p, (int)wave_read_lane((unsigned)nq, 0), (int)wave_read_lane((unsigned)me.cost, 0))) {
+    } else if (p.bound_splits > 1 && as_the_bounds_say(p, (int)wave_read_lane((unsigned)nq, 0), (int)wave_read_lane((unsigned)me.cost, 0))) {
         n = p.bound_splits;
     } else {
         // the model's terms of candidate `lane`, summed over the sequences: wave w takes every fourth
