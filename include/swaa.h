@@ -63,12 +63,13 @@ typedef enum swaa_status {
  *   stream  a hipStream_t, or NULL for the default stream
  *
  * A call repeated gives the same bits.  A prompt's bits may differ between calls of different
- * form, here and in the two calls below: at D = 128 prompts of one length of 65 to 4096 tokens, with at most 512 tiles of
- * 32 rows of one head in all (B Hq ceil(N / 32)), and at D = 64 of 33 tokens and more with at most 1536 of them, are
- * computed by another kernel than in larger, packed and paged calls.  So are longer or more ones whose longest row (a
- * generated row, or the last under full attention) sees several times the keys that rows see on average, at D = 128 in
- * this call and the next only, not in the general form.  The results are equally exact (their distance is one rounding
- * of the probabilities to 16 bits).
+ * form, here and in the two calls below.  These are computed by another kernel than in larger, packed and paged calls (in
+ * tiles of 32 rows of one head, B Hq ceil(N / 32) of them): at D = 128 prompts of one length of 65 to 4096 tokens with at most
+ * 512 tiles; at D = 64 of 33 tokens and more with at most 512 tiles, or 1536 if a row sees 256 keys or more.  So are longer or
+ * more ones whose longest row (a generated row, or the last under full attention) sees several times the keys that rows see
+ * on average: at D = 128 in this call and the next only, not in the general form, whose contiguous and paged calls give the
+ * same bits there; at D = 64 in all three unless n_prompts is given.  The results are equally exact (their distance is one
+ * rounding of the probabilities to 16 bits).
  *
  * Returns SWAA_OK or a negative swaa_status.
  */
