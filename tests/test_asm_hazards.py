@@ -164,10 +164,13 @@ def test_no_vector_write_within_two_instructions_of_an_mfma_that_reads_it(tmp_pa
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"),
                     reason="hipcc not available")
-@pytest.mark.parametrize("src,kernels", [("swaa_bwd.hip", ("dkv_dma_kernel", "dkv_dma_short", "bwd_dkv_kernelILi64")), ("swaa_fwd_d64.hip", ("fwd_d64",))])
+@pytest.mark.parametrize("src,kernels", [
+    ("swaa_bwd.hip", ("dkv_dma_kernel", "dkv_dma_short", "bwd_dkv_kernelILi64", "bwd_dq_kernel", "bwd_dq64_short")),
+    ("swaa_fwd_d64.hip", ("fwd_d64_kernel", "fwd_d64_short")), ("swaa_bwd_dq_pipelined.hip", ("bwd_dq_pipelined", "bwd_dq_short")),
+    ("swaa_fwd_short.hip", ("fwd_short",))])
 def test_lds_dma_kernels_own_all_lds(tmp_path, src, kernels):
-    """These LDS-DMA kernels address LDS with plain byte addresses from 0, too.  (The MFMAs of all but dkv_dma_kernel, which
-    the next test looks at, go through compiler builtins: the wait-state rules above are the compiler's there.)"""
+    """These LDS-DMA kernels address LDS with plain byte addresses from 0, too.  (The MFMAs of swaa_bwd.hip but dkv_dma_kernel's, which
+    the next test looks at, and of swaa_fwd_d64.hip go through compiler builtins: the wait-state rules above are the compiler's there.)"""
     out = tmp_path / "b.s"
     flags = [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")]
     cmd = [build.hipcc_path(), *flags, "--cuda-device-only", "-S", "-o", str(out), os.path.join(build.CSRC, src)]
