@@ -419,7 +419,8 @@ __device__ __forceinline__ int window_bound(int p0, int rows, int W, int P) {
 
 // The mask of 32 keys k0 .. k0 + 31 for a row at position qpos, as bits: bit j says whether it sees key k0 + j.
 // Three comparisons, two logical operations and a selection per score were 120 to 170 instructions for a half, and their
-// results, a pair of scalar registers each, spilled; from the word it is two per score (54 in all; us: four prompts of 643
+// results, a pair of scalar registers each, spilled (forward of whole keys 88 to 110 scalar registers, now 0 to 3; split keys 164 to
+// 172, now 42 to 65); from the word it is two per score (54 in all; us: four prompts of 643
 // tokens 16.2 -> 14.6, seven packed ones of 0.1-7k on a window of 1024 73.1 -> 67.7, four of 8192 on 1024 681 -> 672).
 __host__ __device__ __forceinline__ uint32_t keys_below(int n) {  // the first n keys (none below 0, all from 32 on)
     return n >= 32 ? ~0u : (1u << ((n > 0 ? n : 0) & 31)) - 1u;
