@@ -285,3 +285,18 @@ def test_tile_buffers_are_reused_behind_a_wait_for_their_reads(tmp_path, src, ke
         assert len(barriers) == 1  # the one at the top of the loop over the tiles
         op, counters = insts[barriers[0] - 1]
         assert op == "s_waitcnt" and "vmcnt(0)" in counters and "lgkmcnt(0)" in counters, (op, counters)
+
+
+@pytest.mark.parametrize("src", sorted(f for f in os.listdir(build.CSRC) if f.endswith((".hip", ".h"))))
+def test_loads_written_in_assembly_are_waited_for_and_taken(src):
+    """A load in inline assembly writes its register whenever it arrives, and the compiler thinks it written at once: the same block has
+    to wait for it, and a statement has to take what it loads.  (Copies straight to LDS have no register to write.)"""
+    text = open(os.path.join(build.CSRC, src)).read()
+    for m in re.finditer(r"\basm\b(?: volatile)?\s*\((.*?)\);", text, re.S):
+        block = m.group(1)
+        loads = re.findall(r"\b(?:s_load|s_buffer_load|global_load|flat_load|buffer_load|scratch_load|ds_read|ds_load)_(?!lds)\w+", block)
+        if not loads:
+            continue
+        assert "s_waitcnt" in block.split(loads[-1])[-1], (src, block)
+        outputs = re.findall(r'"=&?[svagr]+"\((\w+)\)', block)
+        assert outputs and all(re.search(r'\(' + name + r'\)', text[m.end():m.end() + 400]) for name in outputs), (src, block)
